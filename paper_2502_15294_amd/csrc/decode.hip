@@ -496,7 +496,7 @@ static int decode_impl(ra_ctx* ctx, const Workspace* scratch, void* stream, cons
         f.q_len = 1;
         f.cur_len = 0;
         f.n_chunks_max = n_tiles_max;
-        f.chunk_tokens = 32;
+        f.chunk_shift = 5;
         f.has_cur = false;
         f.p_out = scores_head;
         f.s_out = scores;

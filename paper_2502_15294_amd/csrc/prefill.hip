@@ -125,7 +125,7 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
         f.has_cur = cur_len > 0 && q_len > 1;
         f.cur_len = f.has_cur ? cur_len : 0;
         f.n_chunks_max = n_tiles_max;
-        f.chunk_tokens = score_unit;
+        f.chunk_shift = few_rows ? 5 : 8;
         f.p_out = scores_head;
         f.s_out = scores;
         launch_scores_finish(f, B, reinterpret_cast<float*>(ctx->ws.base + scratch_total + tile_bytes), st);

@@ -172,274 +172,384 @@ __global__ __launch_bounds__(256) void scores_stream_kernel(ScoreArgs a) {
     }
 }
 
-// Reductions over the 64 lanes of a wavefront, every lane ends with the result: DPP inside the 16-lane rows,
-// then lane-permute swaps across the rows; no LDS traffic.
+// Reductions over every SEG consecutive lanes (16, 32 or 64) of a wavefront, every lane ends with its segment's result:
+// DPP inside the 16-lane rows, then lane-permute swaps across the rows; no LDS traffic.
+template <int SEG = 64>
 __device__ __forceinline__ float wave_max(float v) {
     v = vmax(v, dpp_mov<0xB1>(v));   // quad_perm [1,0,3,2]
     v = vmax(v, dpp_mov<0x4E>(v));   // quad_perm [2,3,0,1]
     v = vmax(v, dpp_mov<0x141>(v));  // row_half_mirror
     v = vmax(v, dpp_mov<0x140>(v));  // row_mirror
-    return xrow_max4(v);
+    if constexpr (SEG == 16) return v;
+    if constexpr (SEG == 64) return xrow_max4(v);
+    auto a = __builtin_amdgcn_permlane16_swap(as_u32(v), as_u32(v), false, false);
+    return vmax(as_f32(a[0]), as_f32(a[1]));
 }
-__device__ __forceinline__ float wave_sum(float v) { return xrow_sum4(row16_sum(v)); }
-// log-sum-exp of x[lo .. hi)
+template <int SEG = 64>
+__device__ __forceinline__ float wave_sum(float v) {
+    v = row16_sum(v);
+    if constexpr (SEG == 16) return v;
+    if constexpr (SEG == 64) return xrow_sum4(v);
+    auto a = __builtin_amdgcn_permlane16_swap(as_u32(v), as_u32(v), false, false);
+    return as_f32(a[0]) + as_f32(a[1]);
+}
+// Sum of the lanes of equal index in the wave's segments of SEG lanes.
+template <int SEG>
+__device__ __forceinline__ float sum_segments(float v) {
+    if constexpr (SEG == 16) v = xrow_sum4(v);
+    if constexpr (SEG == 32) {
+        auto a = __builtin_amdgcn_permlane32_swap(as_u32(v), as_u32(v), false, false);
+        v = as_f32(a[0]) + as_f32(a[1]);
+    }
+    return v;
+}
+// log-sum-exp of x[lo .. hi).  A round of up to four values (1024 tokens) is read in one go.
 __device__ __forceinline__ float lse_range(const float* x, int lo, int hi) {
-    float mx = -__builtin_inff();
-    for (int k = lo; k < hi; ++k) mx = fmaxf(mx, x[k]);
-    if (hi - lo <= 1 || mx == -__builtin_inff()) return mx;
+    if (hi <= lo) return -__builtin_inff();
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = x[min(lo + j, hi - 1)];
+    float mx = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+    for (int k = lo + 4; k < hi; ++k) mx = fmaxf(mx, x[k]);
+    if (hi - lo == 1 || mx == -__builtin_inff()) return mx;
     float s = 0.f;
-    for (int k = lo; k < hi; ++k) s += __expf(x[k] - mx);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s += lo + j < hi ? __expf(v[j] - mx) : 0.f;
+    for (int k = lo + 4; k < hi; ++k) s += __expf(x[k] - mx);
     return mx + __logf(s);
 }
 
-// grid (B), block 512.  Wave w finishes heads w, w + 8, ...; lane j owns rounds j, j + 64, ...
-// (KPL rounds per lane).  P goes to p_out [B][Hq][R_max] if wanted; the head mean is accumulated per
-// wave in registers and reduced over the eight waves through LDS in a fixed order.
-constexpr int kFinishWaves = 8;
-constexpr int kRowBufMax = 2048;  // chunk values a wave can stage in LDS (8 waves x 8 KB)
+// The finishing kernels.  They are latency: a few kilobytes per sequence on one compute unit, and what they cost is the
+// chain of memory and LDS round trips one behind the other and the instructions of that unit's sixteen waves.  So
+//   * a wave asks for the rows of all the heads (or query tokens) it finishes at once, before the round lengths have
+//     arrived, and finds the rounds' places by a prefix sum over its own lanes (up to 64 rounds): no barrier;
+//   * a lane owns a round, and short dialogues (up to 32, up to 16 rounds) put two or four heads into one wave, in
+//     segments of SEG lanes;
+//   * the barriers are for LDS only: they do not wait for the stores of the per-head scores.
+// With one head per wave at a time, its row asked for when its turn came, the one-token kernel took 8.4 microseconds for
+// one sequence of 12 rounds and 32 heads and 16.7 for 64 of 50 rounds and 64 heads (with the selection, which had 2 and 6
+// of them); now 4.4 and 12.8, and the head kernel of a 128-token question 13.6 -> 7.0 microseconds.
 
-template <int KPL, int W>
-__global__ __launch_bounds__(W * 64) void scores_finish_kernel(FinishArgs a, bool stage_rows) {
+// Where the values of the rounds r = (lane mod SEG) + SEG k lie in a row: [lo[k], hi[k]), empty for r >= R.  `cum` is LDS
+// for the prefix sum over more than 64 rounds.  Returns the values of all history rounds.  Called by all threads.
+template <int SEG, int KPL>
+__device__ __forceinline__ int round_places(const FinishArgs& a, int b, int& R, int* cum, int (&lo)[KPL], int (&hi)[KPL]) {
+    const int j = threadIdx.x & (SEG - 1);
+    const int round_up = (1 << a.chunk_shift) - 1;
+    if constexpr (KPL == 1) {
+        const int len = j < a.R_max ? a.seg_len[(size_t)b * a.R_max + j] : 0;  // asked for before R has arrived
+        R = min(max(a.n_rounds[b], 0), a.R_max);
+        const int nc = j < R ? (max(len, 0) + round_up) >> a.chunk_shift : 0;
+        hi[0] = wave_inclusive_sum<SEG>(nc);
+        lo[0] = hi[0] - nc;
+        return __builtin_amdgcn_readlane(hi[0], SEG - 1);
+    } else {
+        static_assert(KPL == 1 || SEG == 64, "more than 64 rounds take whole waves");
+        R = min(max(a.n_rounds[b], 0), a.R_max);
+        for (int r = threadIdx.x; r < a.R_max; r += blockDim.x) {
+            const int len = a.seg_len[(size_t)b * a.R_max + r];
+            if (r < R) cum[r] = (max(len, 0) + round_up) >> a.chunk_shift;
+        }
+        exclusive_scan_units(cum, R);
+#pragma unroll
+        for (int k = 0; k < KPL; ++k) {
+            const int r = j + 64 * k;
+            lo[k] = r < R ? cum[r] : 0;
+            hi[k] = r < R ? cum[r + 1] : 0;
+        }
+        return R > 0 ? cum[R] : 0;
+    }
+}
+
+// n consecutive floats of memory into the wave's LDS strip, 512 of them in flight at a time.
+__device__ __forceinline__ void stage_floats(const float* src, int n, float* strip) {
+    const int lane = threadIdx.x & 63;
+    for (int c0 = 0; c0 < n; c0 += 512) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int c = c0 + 64 * u + lane;
+            v[u] = c < n ? src[c] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int c = c0 + 64 * u + lane;
+            if (c < n) strip[c] = v[u];
+        }
+    }
+}
+
+// Probability mass of the rounds (lane mod SEG) + SEG k for one query token and head from its row of log-sum-exps:
+// softmax over the history rounds and, if has_cur, the current round's values behind them.  Zeros where the token sees
+// no key.
+template <int SEG, int KPL>
+__device__ __forceinline__ void round_masses(const float* row, const int (&lo)[KPL], const int (&hi)[KPL], bool has_cur,
+                                             int cur_lo, int cur_hi, float (&e)[KPL]) {
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) {
+        e[k] = lse_range(row, lo[k], hi[k]);
+        mx = fmaxf(mx, e[k]);
+    }
+    const float lc = has_cur ? lse_range(row, cur_lo, cur_hi) : -__builtin_inff();
+    mx = fmaxf(wave_max<SEG>(mx), lc);
+    const bool none = mx == -__builtin_inff();
+    float sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) {
+        e[k] = none ? 0.f : __expf(e[k] - mx);
+        sum += e[k];
+    }
+    const float z = wave_sum<SEG>(sum) + (none ? 1.f : __expf(lc - mx));
+    const float inv = 1.f / z;
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) e[k] *= inv;
+}
+
+// One query token per sequence: grid (B), 4 to 16 waves.  A wave takes groups of P = 64 / SEG consecutive heads: group w,
+// w + W, ..., with the rows of HB groups asked for together.  P goes to p_out [B][Hq][R_max] if wanted; the head mean
+// is accumulated per wave in registers and reduced over the waves through LDS in a fixed order.
+constexpr int kFinishWaves = 8;              // of the kernels that finish a head per workgroup
+constexpr size_t kFinishLdsMax = 96 * 1024;  // dynamic LDS of a finishing kernel (the selection's 13 KB come on top)
+
+template <int SEG, int KPL, int HB, bool STAGED>
+__global__ __launch_bounds__(1024) void scores_finish_kernel(FinishArgs a) {
+    constexpr int P = 64 / SEG;
     extern __shared__ __align__(16) char smem[];
     int* cum = reinterpret_cast<int*>(smem);                       // [R_max + 2] chunk prefix of the history rounds
     float* hs = reinterpret_cast<float*>(smem) + (a.R_max + 2);    // [W][R_max] per-wave head sums
-    float* rowbuf = hs + W * a.R_max;                   // [W][n_chunks_max] if staged
+    const int W = blockDim.x >> 6;
     const int b = blockIdx.x;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    // The first row this wave needs is fetched (whole, whatever the number of chunks turns out to be) while the
-    // round lengths are on their way: one memory round trip less on the path of this latency-bound kernel.
-    const bool prefetched = stage_rows && wave < a.Hq;
-    if (prefetched) {
-        const float* row = a.part + ((size_t)b * a.Hq + wave) * a.q_len * a.n_chunks_max;
-        float* mybuf = rowbuf + (size_t)wave * a.n_chunks_max;
-        for (int c = lane; c < a.n_chunks_max; c += 64) mybuf[c] = row[c];
-    }
-    const int R = min(max(a.n_rounds[b], 0), a.R_max);
-    for (int r = tid; r < a.R_max; r += W * 64) {
-        const int len = a.seg_len[(size_t)b * a.R_max + r];  // (loaded whether or not r < R: no wait for R)
-        if (r < R) cum[r] = chunks_of(max(len, 0), a.chunk_tokens);
-    }
-    exclusive_scan_units(cum, R);
-    const int hist_chunks = R > 0 ? cum[R] : 0;
-    const bool overflow = hist_chunks + (a.has_cur ? chunks_of(a.cur_len, a.chunk_tokens) : 0) > a.n_chunks_max;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int seg = lane / SEG, rl = lane & (SEG - 1);
+    const int n = a.n_chunks_max;
+    float* strip = hs + W * a.R_max + (size_t)wave * HB * P * n;  // [HB][P][n] of this wave if staged
+    const float* part_b = a.part + (size_t)b * a.Hq * n;
+    float av[HB][KPL];  // running masses of earlier calls
+    auto fetch = [&](int h0) {
+#pragma unroll
+        for (int j = 0; j < HB; ++j) {
+            const int hj = h0 + j * W * P, h = hj + seg;
+#pragma unroll
+            for (int k = 0; k < KPL; ++k) {
+                const int r = rl + SEG * k;
+                av[j][k] = a.acc && h < a.Hq && r < a.R_max ? a.acc[((size_t)b * a.Hq + h) * a.R_max + r] : 0.f;
+            }
+            if constexpr (STAGED)
+                if (hj < a.Hq) stage_floats(part_b + (size_t)hj * n, min(P, a.Hq - hj) * n, strip + j * P * n);
+        }
+        __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
+    };
+    fetch(wave * P);
+    int R, lo[KPL], hi[KPL];
+    const int hist_chunks = round_places<SEG, KPL>(a, b, R, cum, lo, hi);
+    const int cur_chunks = a.has_cur ? (a.cur_len + (1 << a.chunk_shift) - 1) >> a.chunk_shift : 0;
+    const bool overflow = hist_chunks + cur_chunks > n;
 
     float hsum[KPL];
 #pragma unroll
     for (int k = 0; k < KPL; ++k) hsum[k] = 0.f;
-    for (int h = wave; h < a.Hq; h += W) {
-        float qatt[KPL];
+    for (int h0 = wave * P; h0 < a.Hq; h0 += HB * W * P) {
+        if (h0 != wave * P) fetch(h0);
 #pragma unroll
-        for (int k = 0; k < KPL; ++k) qatt[k] = 0.f;
-        for (int i = 0; i < a.q_len && !overflow; ++i) {
-            const float* row = a.part + (((size_t)b * a.Hq + h) * a.q_len + i) * a.n_chunks_max;
-            if (stage_rows) {  // one coalesced pass over the row instead of dependent loads per round
-                float* mybuf = rowbuf + (size_t)(tid >> 6) * a.n_chunks_max;
-                __builtin_amdgcn_wave_barrier();
-                if (!(prefetched && h == wave && i == 0))
-                    for (int c = lane; c < hist_chunks + (a.has_cur ? chunks_of(a.cur_len, a.chunk_tokens) : 0); c += 64)
-                        mybuf[c] = row[c];
-                __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
-                row = mybuf;
-            }
-            float lv[KPL];
-            float mx = -__builtin_inff();
+        for (int j = 0; j < HB; ++j) {
+            const int hj = h0 + j * W * P, h = hj + seg;
+            if (hj >= a.Hq) continue;
+            const bool mine = h < a.Hq;  // a segment past the last head repeats the group's first one, unused
+            const int hs_in = mine ? seg : 0;
+            float qatt[KPL];
+            if (!overflow)
+                round_masses<SEG>(STAGED ? strip + (j * P + hs_in) * n : part_b + (size_t)(hj + hs_in) * n, lo, hi, a.has_cur,
+                                  hist_chunks, hist_chunks + cur_chunks, qatt);
+            float tot = 0.f;
 #pragma unroll
             for (int k = 0; k < KPL; ++k) {
-                const int r = lane + 64 * k;
-                lv[k] = r < R ? lse_range(row, cum[r], cum[r + 1]) : -__builtin_inff();
-                mx = fmaxf(mx, lv[k]);
-            }
-            float lc = -__builtin_inff();
-            if (a.has_cur) lc = lse_range(row, hist_chunks, hist_chunks + chunks_of(a.cur_len, a.chunk_tokens));
-            mx = fmaxf(wave_max(mx), lc);
-            if (mx == -__builtin_inff()) continue;  // this query token sees no key at all
-            float e[KPL], sum = 0.f;
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
-                e[k] = __expf(lv[k] - mx);
-                sum += e[k];
-            }
-            const float z = wave_sum(sum) + __expf(lc - mx);
-            const float inv = 1.f / z;
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) qatt[k] = __builtin_fmaf(e[k], inv, qatt[k]);
-        }
-        if (a.acc && !overflow) {
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
-                const int r = lane + 64 * k;
-                if (r < R) {
-                    float* slot = a.acc + ((size_t)b * a.Hq + h) * a.R_max + r;
-                    qatt[k] += *slot;
-                    *slot = qatt[k];
+                const int r = rl + SEG * k;
+                if (overflow) qatt[k] = 0.f;
+                if (a.acc && !overflow && r < R && mine) {
+                    qatt[k] += av[j][k];
+                    a.acc[((size_t)b * a.Hq + h) * a.R_max + r] = qatt[k];
                 }
+                tot += qatt[k];
             }
-        }
-        float tot = 0.f;
+            tot = wave_sum<SEG>(tot);
+            const float inv = tot > 0.f ? 1.f / tot : 0.f;
 #pragma unroll
-        for (int k = 0; k < KPL; ++k) tot += qatt[k];
-        tot = wave_sum(tot);
-        const float inv = tot > 0.f ? 1.f / tot : 0.f;
-#pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            const int r = lane + 64 * k;
-            // a max_tokens that understates the cache would leave chunks unscored: make that loud
-            const float val = overflow ? __builtin_nanf("") : (r < R ? qatt[k] * inv : 0.f);
-            hsum[k] += val;
-            if (a.p_out && r < a.R_max) a.p_out[((size_t)b * a.Hq + h) * a.R_max + r] = val;
+            for (int k = 0; k < KPL; ++k) {
+                const int r = rl + SEG * k;
+                // a max_tokens that understates the cache would leave chunks unscored: make that loud
+                const float val = overflow ? __builtin_nanf("") : (r < R ? qatt[k] * inv : 0.f);
+                hsum[k] += mine ? val : 0.f;
+                if (a.p_out && mine && r < a.R_max) a.p_out[((size_t)b * a.Hq + h) * a.R_max + r] = val;
+            }
         }
     }
 #pragma unroll
     for (int k = 0; k < KPL; ++k) {
-        const int r = lane + 64 * k;
-        if (r < a.R_max) hs[wave * a.R_max + r] = hsum[k];
+        const int r = rl + SEG * k;
+        const float sum = sum_segments<SEG>(hsum[k]);
+        if (seg == 0 && r < a.R_max) hs[wave * a.R_max + r] = sum;
     }
-    __syncthreads();
+    lds_barrier();
     const float inv_h = 1.f / (float)a.Hq;
     float* svec = reinterpret_cast<float*>(cum);  // the sequence's scores, for the selection (cum is no longer read)
     for (int r = tid; r < a.R_max; r += W * 64) {
         float s = 0.f;
-#pragma unroll
+#pragma unroll 4
         for (int w = 0; w < W; ++w) s += hs[w * a.R_max + r];
         const float val = s * inv_h;
         a.s_out[(size_t)b * a.R_max + r] = val;
         if (a.with_select) svec[r] = val;
     }
     if (a.with_select) {  // Sec. 3.3 on the scores just written, same bits
-        __shared__ SelectShared<W> sh;
-        __syncthreads();
-        select_rounds_block<W>(svec, R, a.R_max, a.sel, a.sel_idx + (size_t)b * a.R_max, a.n_sel + b, sh);
+        __shared__ SelectShared sh;
+        lds_barrier();
+        select_rounds_block(svec, R, a.R_max, a.sel, a.sel_idx + (size_t)b * a.R_max, a.n_sel + b, sh);
     }
 }
 
-// Finishing kernel for several query tokens: grid (B, Hq, Z), block 512.  Z workgroups per (sequence, head);
-// the eight waves of workgroup z take the query tokens i = 8*z + wave, + 8*Z, ...  A wave first copies token
-// i's row of chunk log-sum-exps into its own LDS strip with coalesced loads (when it fits), then every lane
-// folds the chunks of its rounds.  The per-wave round masses are summed over the waves in LDS in a fixed
-// order and written, not yet normalised, to p_part [B][Hq][Z][R_max]; scores_heads_kernel finishes.
-
-template <int KPL>
-__global__ __launch_bounds__(kFinishWaves * 64) void scores_finish_rows_kernel(FinishArgs a, float* p_part,
-                                                                                bool stage_rows) {
+// Several query tokens: grid (B, Hq, Z), eight waves.  Z workgroups per (sequence, head); wave w of workgroup z takes
+// the groups of P = 64 / SEG consecutive query tokens 8 z + w, + 8 Z, ..., the rows of TB groups asked for together.  The
+// per-wave round masses are summed over the waves in LDS in a fixed order and written, not yet normalised, to p_part
+// [B][Hq][Z][R_max]; scores_heads_kernel finishes.
+template <int SEG, int KPL, int TB, bool STAGED>
+__global__ __launch_bounds__(kFinishWaves * 64) void scores_finish_rows_kernel(FinishArgs a, float* p_part) {
+    constexpr int P = 64 / SEG;
     extern __shared__ __align__(16) char smem[];
     int* cum = reinterpret_cast<int*>(smem);                        // [R_max + 2]
     float* hs = reinterpret_cast<float*>(smem) + (a.R_max + 2);     // [kFinishWaves][R_max]
-    float* rowbuf = hs + kFinishWaves * a.R_max;                    // [kFinishWaves][n_chunks_max] if staged
     const int b = blockIdx.x, h = blockIdx.y;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int R = min(max(a.n_rounds[b], 0), a.R_max);
-    for (int r = tid; r < R; r += kFinishWaves * 64) cum[r] = chunks_of(max(a.seg_len[(size_t)b * a.R_max + r], 0), a.chunk_tokens);
-    exclusive_scan_units(cum, R);
-    const int hist_chunks = R > 0 ? cum[R] : 0;
-    const int all_chunks = hist_chunks + (a.has_cur ? chunks_of(a.cur_len, a.chunk_tokens) : 0);
-    const bool overflow = all_chunks > a.n_chunks_max;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int seg = lane / SEG, rl = lane & (SEG - 1);
+    const int n = a.n_chunks_max;
+    float* strip = hs + kFinishWaves * a.R_max + (size_t)wave * TB * P * n;  // [TB][P][n] if staged
+    const float* part_h = a.part + ((size_t)b * a.Hq + h) * a.q_len * n;
+    const int step = kFinishWaves * gridDim.z * P;
+    auto fetch = [&](int i0) {
+        if constexpr (STAGED) {
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                const int ij = i0 + j * step;
+                if (ij < a.q_len) stage_floats(part_h + (size_t)ij * n, min(P, a.q_len - ij) * n, strip + j * P * n);
+            }
+            __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
+        }
+    };
+    const int i_first = (blockIdx.z * kFinishWaves + wave) * P;
+    fetch(i_first);
+    int R, lo[KPL], hi[KPL];
+    const int hist_chunks = round_places<SEG, KPL>(a, b, R, cum, lo, hi);
+    const int all_chunks = hist_chunks + (a.has_cur ? (a.cur_len + (1 << a.chunk_shift) - 1) >> a.chunk_shift : 0);
+    const bool overflow = all_chunks > n;
 
     float qatt[KPL];
 #pragma unroll
     for (int k = 0; k < KPL; ++k) qatt[k] = 0.f;
-    float* mybuf = rowbuf + (size_t)wave * a.n_chunks_max;
-    // One query token (then gridDim.z is 1): instead of leaving seven waves idle and one lane per round walking its
-    // values one after the other, the eight waves share the rounds, and a wave folds a round's values with all its
-    // lanes (coalesced reads; the second pass over the same values comes from cache).  The round's log-sum-exps meet
-    // in LDS and wave 0 normalises them as below.
-    const bool one_token = a.q_len == 1 && !a.has_cur;
-    if (one_token && !overflow) {
-        const float* row = a.part + ((size_t)b * a.Hq + h) * a.n_chunks_max;
-        if (stage_rows) {  // the whole row into LDS with one round trip (the launch made room for it)
-            for (int c = tid; c < hist_chunks; c += kFinishWaves * 64) rowbuf[c] = row[c];
-            __syncthreads();
-            row = rowbuf;
-        }
-        float* round_lse = hs;  // [R_max] of the [kFinishWaves][R_max] floats; rewritten below after a barrier
-        for (int r = wave; r < R; r += kFinishWaves) {
-            const int lo = cum[r], hi = cum[r + 1];
-            float mx = -__builtin_inff();
-            for (int k = lo + lane; k < hi; k += 64) mx = fmaxf(mx, row[k]);
-            mx = wave_max(mx);
-            float sum = 0.f;
-            if (mx != -__builtin_inff())
-                for (int k = lo + lane; k < hi; k += 64) sum += __expf(row[k] - mx);
-            sum = wave_sum(sum);
-            if (lane == 0) round_lse[r] = mx == -__builtin_inff() ? mx : mx + __logf(sum);
-        }
-        __syncthreads();
-        if (wave == 0) {
-            float lv[KPL];
-            float mx = -__builtin_inff();
+    for (int i0 = i_first; i0 < a.q_len && !overflow; i0 += TB * step) {
+        if (i0 != i_first) fetch(i0);
+        for (int j = 0; j < TB; ++j) {
+            const int ij = i0 + j * step;
+            if (ij >= a.q_len) break;
+            const bool mine = ij + seg < a.q_len;  // a segment past the last token repeats the group's first one, unused
+            const int in = mine ? seg : 0;
+            float e[KPL];
+            round_masses<SEG>(STAGED ? strip + (j * P + in) * n : part_h + (size_t)(ij + in) * n, lo, hi, a.has_cur,
+                              hist_chunks, all_chunks, e);
 #pragma unroll
-            for (int k = 0; k < KPL; ++k) {
-                const int r = lane + 64 * k;
-                lv[k] = r < R ? round_lse[r] : -__builtin_inff();
-                mx = fmaxf(mx, lv[k]);
-            }
-            mx = wave_max(mx);
-            if (mx != -__builtin_inff()) {
-                float e[KPL], sum = 0.f;
-#pragma unroll
-                for (int k = 0; k < KPL; ++k) {
-                    e[k] = __expf(lv[k] - mx);
-                    sum += e[k];
-                }
-                const float inv = 1.f / wave_sum(sum);
-#pragma unroll
-                for (int k = 0; k < KPL; ++k) qatt[k] = e[k] * inv;
-            }
+            for (int k = 0; k < KPL; ++k) qatt[k] += mine ? e[k] : 0.f;
         }
-        __syncthreads();  // round_lse is part of hs, which every wave writes next
-    }
-    for (int i = blockIdx.z * kFinishWaves + wave; i < a.q_len && !overflow && !one_token; i += kFinishWaves * gridDim.z) {
-        const float* row = a.part + (((size_t)b * a.Hq + h) * a.q_len + i) * a.n_chunks_max;
-        if (stage_rows) {
-            for (int c = lane; c < all_chunks; c += 64) mybuf[c] = row[c];
-            __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
-            row = mybuf;
-        }
-        float lv[KPL];
-        float mx = -__builtin_inff();
-#pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            const int r = lane + 64 * k;
-            lv[k] = r < R ? lse_range(row, cum[r], cum[r + 1]) : -__builtin_inff();
-            mx = fmaxf(mx, lv[k]);
-        }
-        float lc = -__builtin_inff();
-        if (a.has_cur) lc = lse_range(row, hist_chunks, all_chunks);
-        __builtin_amdgcn_wave_barrier();
-        mx = fmaxf(wave_max(mx), lc);
-        if (mx == -__builtin_inff()) continue;  // this query token sees no key at all
-        float e[KPL], sum = 0.f;
-#pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            e[k] = __expf(lv[k] - mx);
-            sum += e[k];
-        }
-        const float inv = 1.f / (wave_sum(sum) + __expf(lc - mx));
-#pragma unroll
-        for (int k = 0; k < KPL; ++k) qatt[k] = __builtin_fmaf(e[k], inv, qatt[k]);
     }
 #pragma unroll
     for (int k = 0; k < KPL; ++k) {
-        const int r = lane + 64 * k;
-        if (r < a.R_max) hs[wave * a.R_max + r] = qatt[k];
+        const int r = rl + SEG * k;
+        const float sum = sum_segments<SEG>(qatt[k]);
+        if (seg == 0 && r < a.R_max) hs[wave * a.R_max + r] = sum;
     }
-    __syncthreads();
-    if (wave == 0) {
+    lds_barrier();
+    for (int r = tid; r < a.R_max; r += kFinishWaves * 64) {
+        float tot = 0.f;
+        if (r < R)
 #pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            const int r = lane + 64 * k;
-            float tot = 0.f;
-            if (r < R)
-                for (int w = 0; w < kFinishWaves; ++w) tot += hs[w * a.R_max + r];
-            if (r < a.R_max)
-                p_part[(((size_t)b * a.Hq + h) * gridDim.z + blockIdx.z) * a.R_max + r] = overflow ? __builtin_nanf("") : tot;
-        }
+            for (int w = 0; w < kFinishWaves; ++w) tot += hs[w * a.R_max + r];
+        p_part[(((size_t)b * a.Hq + h) * gridDim.z + blockIdx.z) * a.R_max + r] = overflow ? __builtin_nanf("") : tot;
     }
 }
 
-// grid (B), block 1024: per head, the Z partial round masses are added in order and normalised over the rounds
-// (Eq. 1; written to p_out [B][Hq][R_max] if given); scores[b][r] is the mean over heads.  A wave takes heads
-// wave, wave + 16, ... and a lane the rounds lane, lane + 64, ..., so all sums run in a fixed order.
-constexpr int kHeadsWaves = 16;
+// One query token whose heads have many values per round (the watershed layer's, one per 32-token tile): grid (B, Hq),
+// eight waves share the rounds, four at a time each, and a wave folds a round's values with all its lanes.  The rounds'
+// log-sum-exps meet in LDS, the first wave turns them into masses; output as above with Z = 1.
+template <int KPL>
+__global__ __launch_bounds__(kFinishWaves * 64) void scores_finish_tiles_kernel(FinishArgs a, float* p_part) {
+    extern __shared__ __align__(16) char smem[];
+    int* cum = reinterpret_cast<int*>(smem);                                // [R_max + 2]
+    float* round_lse = reinterpret_cast<float*>(smem) + (a.R_max + 2);      // [R_max]
+    const int b = blockIdx.x, h = blockIdx.y;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    int R, lo[KPL], hi[KPL];
+    const int hist_chunks = round_places<64, KPL>(a, b, R, cum, lo, hi);
+    const bool overflow = hist_chunks > a.n_chunks_max;
+    if (!overflow) {
+        const float* row = a.part + ((size_t)b * a.Hq + h) * a.n_chunks_max;
+        for (int r0 = wave; r0 < R; r0 += 4 * kFinishWaves) {
+            int first[4], end[4];
+            float v[4], mx[4], sum[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = r0 + j * kFinishWaves;
+                first[j] = end[j] = 0;
+                if (r < R) {
+                    if constexpr (KPL == 1) {
+                        first[j] = __builtin_amdgcn_readlane(lo[0], r);
+                        end[j] = __builtin_amdgcn_readlane(hi[0], r);
+                    } else {
+                        first[j] = cum[r];
+                        end[j] = cum[r + 1];
+                    }
+                }
+                v[j] = first[j] + lane < end[j] ? row[first[j] + lane] : -__builtin_inff();
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                mx[j] = v[j];
+                for (int c = first[j] + 64 + lane; c < end[j]; c += 64) mx[j] = fmaxf(mx[j], row[c]);
+                mx[j] = wave_max(mx[j]);
+                const bool none = mx[j] == -__builtin_inff();
+                sum[j] = none ? 0.f : __expf(v[j] - mx[j]);
+                if (!none)
+                    for (int c = first[j] + 64 + lane; c < end[j]; c += 64) sum[j] += __expf(row[c] - mx[j]);
+                sum[j] = wave_sum(sum[j]);
+                if (lane == 0 && r0 + j * kFinishWaves < R)
+                    round_lse[r0 + j * kFinishWaves] = none ? mx[j] : mx[j] + __logf(sum[j]);
+            }
+        }
+    }
+    lds_barrier();
+    if (wave != 0) return;
+    float lv[KPL], mx = -__builtin_inff(), sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) {
+        const int r = lane + 64 * k;
+        lv[k] = !overflow && r < R ? round_lse[r] : -__builtin_inff();
+        mx = fmaxf(mx, lv[k]);
+    }
+    mx = wave_max(mx);
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) {
+        lv[k] = mx == -__builtin_inff() ? 0.f : __expf(lv[k] - mx);
+        sum += lv[k];
+    }
+    sum = wave_sum(sum);
+    const float inv = sum > 0.f ? 1.f / sum : 0.f;
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) {
+        const int r = lane + 64 * k;
+        if (r < a.R_max) p_part[((size_t)b * a.Hq + h) * a.R_max + r] = overflow ? __builtin_nanf("") : lv[k] * inv;
+    }
+}
+
+// grid (B), 4 to 16 waves: per head, the Z partial round masses are added in order and normalised over the rounds
+// (Eq. 1; written to p_out [B][Hq][R_max] if given); scores[b][r] is the mean over heads.  Heads go to waves and lanes as
+// in the one-token kernel, so all sums run in a fixed order.
 struct HeadsSelect {
     bool with_select;
     ra_select_params sel;
@@ -447,59 +557,81 @@ struct HeadsSelect {
     int32_t* sel_idx;
     int32_t* n_sel;
 };
-__global__ __launch_bounds__(kHeadsWaves * 64) void scores_heads_kernel(const float* p_part, int Z, int R_max, int Hq,
-                                                                        float* p_out, float* s_out, float* acc,
-                                                                        HeadsSelect hsel) {
+constexpr int kMaxSplits = 8;  // most partial masses per head (scores_finish_splits)
+template <int SEG, int KPL, int HB>
+__global__ __launch_bounds__(1024) void scores_heads_kernel(const float* p_part, int Z, int R_max, int Hq, float* p_out,
+                                                            float* s_out, float* acc, HeadsSelect hsel) {
+    constexpr int P = 64 / SEG;
     extern __shared__ __align__(16) char smem[];
-    float* sacc = reinterpret_cast<float*>(smem);  // [kHeadsWaves][R_max]
-    constexpr int KPL = kMaxRounds / 64;
-    const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    float mine[KPL];  // this wave's sum over its heads of the normalised masses of rounds lane + 64 k
+    float* sacc = reinterpret_cast<float*>(smem);  // [W][R_max]
+    const int W = blockDim.x >> 6;
+    const int b = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int seg = lane / SEG, rl = lane & (SEG - 1);
+    float mine[KPL];  // this wave's sum over its heads of the normalised masses of this lane's rounds
 #pragma unroll
     for (int k = 0; k < KPL; ++k) mine[k] = 0.f;
-    for (int h = wave; h < Hq; h += kHeadsWaves) {
-        const float* ph = p_part + ((size_t)b * Hq + h) * Z * R_max;
-        float tot[KPL], all = 0.f;
+    for (int h0 = wave * P; h0 < Hq; h0 += HB * W * P) {
+        float tot[HB][KPL];
 #pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            const int r = lane + 64 * k;
-            tot[k] = 0.f;
-            if (r < R_max)
-                for (int z = 0; z < Z; ++z) tot[k] += ph[(size_t)z * R_max + r];
-            if (acc && r < R_max && tot[k] == tot[k]) {  // (an undersized pass leaves the running masses alone)
-                float* slot = acc + ((size_t)b * Hq + h) * R_max + r;
-                tot[k] += *slot;
-                *slot = tot[k];
+        for (int j = 0; j < HB; ++j)
+#pragma unroll
+            for (int k = 0; k < KPL; ++k) {
+                const int h = h0 + j * W * P + seg, r = rl + SEG * k;
+                const bool ok = h < Hq && r < R_max;
+                const float* ph = p_part + ((size_t)b * Hq + (ok ? h : 0)) * Z * R_max + (ok ? r : 0);
+                float v[kMaxSplits];
+#pragma unroll
+                for (int z = 0; z < kMaxSplits; ++z) v[z] = ok && z < Z ? ph[(size_t)z * R_max] : 0.f;
+                tot[j][k] = 0.f;
+#pragma unroll
+                for (int z = 0; z < kMaxSplits; ++z) tot[j][k] += v[z];
             }
-            all += tot[k];
-        }
-        all = wave_sum(all);
-        const float inv = all > 0.f ? 1.f / all : (all == all ? 0.f : all);  // (NaN marks an undersized pass)
 #pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            const int r = lane + 64 * k;
-            const float p = tot[k] * inv;
-            if (p_out && r < R_max) p_out[((size_t)b * Hq + h) * R_max + r] = p;
-            mine[k] += p;
+        for (int j = 0; j < HB; ++j) {
+            const int h = h0 + j * W * P + seg;
+            float all = 0.f;
+#pragma unroll
+            for (int k = 0; k < KPL; ++k) {
+                const int r = rl + SEG * k;
+                if (acc && h < Hq && r < R_max && tot[j][k] == tot[j][k]) {  // (an undersized pass leaves the running masses alone)
+                    float* slot = acc + ((size_t)b * Hq + h) * R_max + r;
+                    tot[j][k] += *slot;
+                    *slot = tot[j][k];
+                }
+                all += tot[j][k];
+            }
+            all = wave_sum<SEG>(all);
+            const float inv = all > 0.f ? 1.f / all : (all == all ? 0.f : all);  // (NaN marks an undersized pass)
+#pragma unroll
+            for (int k = 0; k < KPL; ++k) {
+                const int r = rl + SEG * k;
+                const float p = tot[j][k] * inv;
+                if (p_out && h < Hq && r < R_max) p_out[((size_t)b * Hq + h) * R_max + r] = p;
+                mine[k] += p;  // (zero for a segment past the last head)
+            }
         }
     }
 #pragma unroll
-    for (int k = 0; k < KPL; ++k)
-        if (lane + 64 * k < R_max) sacc[wave * R_max + lane + 64 * k] = mine[k];
-    __syncthreads();
+    for (int k = 0; k < KPL; ++k) {
+        const int r = rl + SEG * k;
+        const float sum = sum_segments<SEG>(mine[k]);
+        if (seg == 0 && r < R_max) sacc[wave * R_max + r] = sum;
+    }
+    lds_barrier();
     const float inv_h = 1.f / (float)Hq;
-    for (int r = threadIdx.x; r < R_max; r += kHeadsWaves * 64) {
+    for (int r = threadIdx.x; r < R_max; r += blockDim.x) {
         float s = 0.f;
-        for (int w = 0; w < kHeadsWaves; ++w) s += sacc[w * R_max + r];
+#pragma unroll 4
+        for (int w = 0; w < W; ++w) s += sacc[w * R_max + r];
         const float val = s * inv_h;
         s_out[(size_t)b * R_max + r] = val;
         if (hsel.with_select) sacc[r] = val;  // (a thread only ever touches its own column r of sacc)
     }
     if (hsel.with_select) {  // Sec. 3.3 on the scores just written, same bits
-        __shared__ SelectShared<kHeadsWaves> sh;
-        __syncthreads();
+        __shared__ SelectShared sh;
+        lds_barrier();
         const int R = min(max(hsel.n_rounds[b], 0), R_max);
-        select_rounds_block<kHeadsWaves>(sacc, R, R_max, hsel.sel, hsel.sel_idx + (size_t)b * R_max, hsel.n_sel + b, sh);
+        select_rounds_block(sacc, R, R_max, hsel.sel, hsel.sel_idx + (size_t)b * R_max, hsel.n_sel + b, sh);
     }
 }
 
@@ -530,61 +662,94 @@ namespace ra {
 // Several query tokens: Z workgroups per (sequence, head) leave partial round masses in p_part
 // [B][Hq][Z][R_max], a second kernel adds, normalises and averages them.
 int scores_finish_splits(int q_len, int B, int Hq) {
-    int Z = q_len / 32 < 1 ? 1 : (q_len / 32 > 8 ? 8 : q_len / 32);
+    int Z = q_len / 32 < 1 ? 1 : (q_len / 32 > kMaxSplits ? kMaxSplits : q_len / 32);
     while (Z > 1 && (int64_t)B * Hq * Z > 2048) --Z;
     return Z;
 }
-void launch_scores_finish_rows(const FinishArgs& f, int B, float* p_part, int Z, hipStream_t st) {
-    const int R_max = f.R_max, Hq = f.Hq, n_chunks_max = f.n_chunks_max;
-    const size_t fin_smem = (size_t)(R_max + 2) * sizeof(int) + (size_t)kFinishWaves * R_max * sizeof(float);
-    const dim3 fin_block(kFinishWaves * 64);
-    bool stage_rows =
-        n_chunks_max <= kRowBufMax && fin_smem + (size_t)kFinishWaves * n_chunks_max * sizeof(float) <= 60 * 1024;
-    size_t smem = fin_smem + (stage_rows ? (size_t)kFinishWaves * n_chunks_max * sizeof(float) : 0);
-    if (f.q_len == 1 && !f.has_cur) {  // one row per workgroup, shared by its waves: staged whole if it fits
-        stage_rows = fin_smem + (size_t)n_chunks_max * sizeof(float) <= 60 * 1024;
-        smem = fin_smem + (stage_rows ? (size_t)n_chunks_max * sizeof(float) : 0);
-    }
-    const dim3 fgrid(B, Hq, Z);
-    if (R_max <= 64)
-        hipLaunchKernelGGL((scores_finish_rows_kernel<1>), fgrid, fin_block, smem, st, f, p_part, stage_rows);
-    else if (R_max <= 256)
-        hipLaunchKernelGGL((scores_finish_rows_kernel<4>), fgrid, fin_block, smem, st, f, p_part, stage_rows);
+
+// Lanes a head's rounds take in the finishing kernels, and rounds per lane.
+#define RA_FINISH_SHAPE(R_max, LAUNCH)                            \
+    do {                                                          \
+        if ((R_max) <= 16) LAUNCH(16, 1);                         \
+        else if ((R_max) <= 32) LAUNCH(32, 1);                    \
+        else if ((R_max) <= 64) LAUNCH(64, 1);                    \
+        else if ((R_max) <= 256) LAUNCH(64, 4);                   \
+        else LAUNCH(64, kMaxRounds / 64);                         \
+    } while (0)
+
+// Waves of a workgroup that finishes `groups` groups of heads of one sequence: 4 to 16, and as the LDS allows.
+static int head_waves(int groups, int R_max) {
+    int W = groups < 4 ? 4 : (groups > kSelectWaves ? kSelectWaves : groups);
+    while (W > 4 && (size_t)(W + 1) * (R_max + 2) * sizeof(float) > kFinishLdsMax) --W;
+    return W;
+}
+
+template <int SEG, int KPL, int TB>
+static void launch_rows(const FinishArgs& f, int B, float* p_part, int Z, hipStream_t st) {
+    const size_t base = (size_t)(f.R_max + 2) * sizeof(int) + (size_t)kFinishWaves * f.R_max * sizeof(float);
+    const size_t staged = base + (size_t)kFinishWaves * TB * (64 / SEG) * f.n_chunks_max * sizeof(float);
+    const dim3 grid(B, f.Hq, Z), block(kFinishWaves * 64);
+    if (staged <= kFinishLdsMax / 2)  // two workgroups per compute unit
+        hipLaunchKernelGGL((scores_finish_rows_kernel<SEG, KPL, TB, true>), grid, block, staged, st, f, p_part);
+    else if (TB > 1)
+        launch_rows<SEG, KPL, 1>(f, B, p_part, Z, st);
     else
-        hipLaunchKernelGGL((scores_finish_rows_kernel<kMaxRounds / 64>), fgrid, fin_block, smem, st, f, p_part,
-                           stage_rows);
+        hipLaunchKernelGGL((scores_finish_rows_kernel<SEG, KPL, 1, false>), grid, block, base, st, f, p_part);
+}
+
+template <int SEG, int KPL, int HB>
+static void launch_heads(const FinishArgs& f, int B, const float* p_part, int Z, hipStream_t st) {
     HeadsSelect hsel;
     hsel.with_select = f.with_select;
     hsel.sel = f.sel;
     hsel.n_rounds = f.n_rounds;
     hsel.sel_idx = f.sel_idx;
     hsel.n_sel = f.n_sel;
-    hipLaunchKernelGGL(scores_heads_kernel, dim3(B), dim3(kHeadsWaves * 64), (size_t)kHeadsWaves * R_max * sizeof(float),
-                       st, p_part, Z, R_max, Hq, f.p_out, f.s_out, f.acc, hsel);
+    const int W = head_waves((f.Hq * SEG + 63) / 64, f.R_max);
+    hipLaunchKernelGGL((scores_heads_kernel<SEG, KPL, HB>), dim3(B), dim3(W * 64), (size_t)W * f.R_max * sizeof(float), st,
+                       p_part, Z, f.R_max, f.Hq, f.p_out, f.s_out, f.acc, hsel);
 }
 
-// One query token: the finishing kernel for B sequences (a.q_len must be 1).
-void launch_scores_finish_single(const FinishArgs& f, int B, hipStream_t st) {
-    const int R_max = f.R_max, Hq = f.Hq, n_chunks_max = f.n_chunks_max;
-    const size_t fin_smem = (size_t)(R_max + 2) * sizeof(int) + (size_t)kFinishWaves * R_max * sizeof(float);
-    const dim3 fin_block(kFinishWaves * 64);
-    const bool stage_rows =
-        n_chunks_max <= kRowBufMax && fin_smem + (size_t)kFinishWaves * n_chunks_max * sizeof(float) <= 60 * 1024;
-    const size_t smem = fin_smem + (stage_rows ? (size_t)kFinishWaves * n_chunks_max * sizeof(float) : 0);
-    // sixteen waves (two heads each at Hq = 32) when the per-wave LDS strips still fit
-    const size_t smem16 = (size_t)(R_max + 2) * sizeof(int) + (size_t)16 * R_max * sizeof(float) +
-                          (stage_rows ? (size_t)16 * n_chunks_max * sizeof(float) : 0);
-    if (R_max <= 64 && Hq > 8 && smem16 <= 60 * 1024)
-        hipLaunchKernelGGL((scores_finish_kernel<1, 16>), dim3(B), dim3(1024), smem16, st, f, stage_rows);
-    else if (R_max <= 64)
-        hipLaunchKernelGGL((scores_finish_kernel<1, kFinishWaves>), dim3(B), fin_block, smem, st, f, stage_rows);
-    else if (R_max <= 256 && Hq > 8 && smem16 <= 60 * 1024)
-        hipLaunchKernelGGL((scores_finish_kernel<4, 16>), dim3(B), dim3(1024), smem16, st, f, stage_rows);
-    else if (R_max <= 256)
-        hipLaunchKernelGGL((scores_finish_kernel<4, kFinishWaves>), dim3(B), fin_block, smem, st, f, stage_rows);
+void launch_scores_finish_rows(const FinishArgs& f, int B, float* p_part, int Z, hipStream_t st) {
+    if (f.q_len == 1 && !f.has_cur) {
+        const dim3 grid(B, f.Hq), block(kFinishWaves * 64);
+        const size_t smem = (size_t)(2 * f.R_max + 2) * sizeof(int);
+        if (f.R_max <= 64) hipLaunchKernelGGL((scores_finish_tiles_kernel<1>), grid, block, smem, st, f, p_part);
+        else if (f.R_max <= 256) hipLaunchKernelGGL((scores_finish_tiles_kernel<4>), grid, block, smem, st, f, p_part);
+        else hipLaunchKernelGGL((scores_finish_tiles_kernel<kMaxRounds / 64>), grid, block, smem, st, f, p_part);
+    } else {
+        const bool several = f.q_len > kFinishWaves * Z;  // a wave may have more than one group of tokens
+#define RA_ROWS(SEG, KPL)                                                              \
+    do {                                                                               \
+        if (several) launch_rows<SEG, KPL, (KPL) == 1 ? 4 : 1>(f, B, p_part, Z, st);   \
+        else launch_rows<SEG, KPL, 1>(f, B, p_part, Z, st);                            \
+    } while (0)
+        RA_FINISH_SHAPE(f.R_max, RA_ROWS);
+#undef RA_ROWS
+    }
+#define RA_HEADS(SEG, KPL) launch_heads<SEG, KPL, (SEG) == 64 && (KPL) == 1 ? 2 : 1>(f, B, p_part, Z, st)
+    RA_FINISH_SHAPE(f.R_max, RA_HEADS);
+#undef RA_HEADS
+}
+
+// One query token: the finishing kernel for B sequences (f.q_len must be 1).  As many of a wave's groups of heads
+// fetched together as it has and as their rows fit into LDS; rows that do not fit even so are read from memory.
+template <int SEG, int KPL, int HB>
+static void launch_single(const FinishArgs& f, int B, hipStream_t st) {
+    const int groups = (f.Hq * SEG + 63) / 64, W = head_waves(groups, f.R_max);
+    const size_t base = (size_t)(f.R_max + 2) * sizeof(int) + (size_t)W * f.R_max * sizeof(float);
+    const size_t staged = base + (size_t)W * HB * (64 / SEG) * f.n_chunks_max * sizeof(float);
+    if (HB > 1 && (groups <= W * (HB / 2) || staged > kFinishLdsMax))
+        launch_single<SEG, KPL, (HB > 1 ? HB / 2 : 1)>(f, B, st);
+    else if (staged <= kFinishLdsMax)
+        hipLaunchKernelGGL((scores_finish_kernel<SEG, KPL, HB, true>), dim3(B), dim3(W * 64), staged, st, f);
     else
-        hipLaunchKernelGGL((scores_finish_kernel<kMaxRounds / 64, kFinishWaves>), dim3(B), fin_block, smem, st, f,
-                           stage_rows);
+        hipLaunchKernelGGL((scores_finish_kernel<SEG, KPL, 1, false>), dim3(B), dim3(W * 64), base, st, f);
+}
+void launch_scores_finish_single(const FinishArgs& f, int B, hipStream_t st) {
+#define RA_SINGLE(SEG, KPL) launch_single<SEG, KPL, (KPL) == 1 && (SEG) == 64 ? 4 : (KPL) <= 4 ? 2 : 1>(f, B, st)
+    RA_FINISH_SHAPE(f.R_max, RA_SINGLE);
+#undef RA_SINGLE
 }
 void launch_scores_finish(const FinishArgs& f, int B, float* p_part, hipStream_t st) {
     if (scores_finish_by_rows(f.q_len, f.Hq, f.n_chunks_max))
@@ -686,7 +851,7 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
     f.q_len = q_len;
     f.cur_len = a.cur_len;
     f.n_chunks_max = n_chunks_max;
-    f.chunk_tokens = chunk_tokens;
+    f.chunk_shift = 8;
     f.has_cur = use_cur;
     f.p_out = scores_head;
     f.s_out = scores;

@@ -28,7 +28,8 @@ struct FinishArgs {
     const float* part;         // [B][Hq][q_len][n_chunks_max]
     const int32_t* n_rounds;
     const int32_t* seg_len;
-    int R_max, Hq, q_len, cur_len, n_chunks_max, chunk_tokens;
+    int R_max, Hq, q_len, cur_len, n_chunks_max;
+    int chunk_shift;           // tokens per value: 1 << chunk_shift (8: the score pass's chunks, 5: key tiles)
     bool has_cur;
     float* p_out;  // may be null
     float* s_out;

@@ -15,8 +15,8 @@ struct SelectArgs {
 };
 
 __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
-    __shared__ float s[kMaxRounds];
-    __shared__ SelectShared<4> sh;
+    __shared__ __align__(16) float s[kMaxRounds];
+    __shared__ SelectShared sh;
     const int b = blockIdx.x, tid = threadIdx.x;
     const int R = min(max(a.n_rounds[b], 0), a.R_max);
     for (int r = tid; r < a.R_max; r += 256) {
@@ -24,7 +24,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
         if (r < R) s[r] = v;
     }
     __syncthreads();
-    select_rounds_block<4>(s, R, a.R_max, a.p, a.sel_idx + (size_t)b * a.R_max, a.n_sel + b, sh);
+    select_rounds_block(s, R, a.R_max, a.p, a.sel_idx + (size_t)b * a.R_max, a.n_sel + b, sh);
 }
 
 int check_select_params(const ra_select_params* params, const char* who) {

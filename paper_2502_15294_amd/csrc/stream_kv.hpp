@@ -189,6 +189,30 @@ __device__ __forceinline__ PlanHeader load_plan(const char* plan_b, int cap, Slo
     return hdr;
 }
 
+// Inclusive prefix sum over every SEG consecutive lanes (16, 32 or 64) of a wave: shifts inside the rows of 16 lanes
+// (zeros come in at a row's start), then the totals of the rows before added from scalar registers; no trip through LDS.
+template <int SEG = 64>
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    const int lane = threadIdx.x & 63;
+    if constexpr (SEG == 16) return v;
+    const int t0 = __builtin_amdgcn_readlane(v, 15), t2 = __builtin_amdgcn_readlane(v, 47);
+    if constexpr (SEG == 32) return v + (lane & 16 ? (lane & 32 ? t2 : t0) : 0);
+    const int t1 = __builtin_amdgcn_readlane(v, 31);
+    return v + (lane < 16 ? 0 : (lane < 32 ? t0 : (lane < 48 ? t0 + t1 : t0 + t1 + t2)));
+}
+
+// Barrier of a workgroup for what it exchanges through LDS: unlike __syncthreads it does not wait for outstanding
+// global loads and for the acknowledgement of global stores, which no other wave of the workgroup reads.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Exclusive prefix sum, in place, of cum[0..n) by the first wavefront; cum[n] receives the total.
 // Must be called by all threads of the workgroup (it synchronises).
 __device__ inline void exclusive_scan_units(int* cum, int n) {
