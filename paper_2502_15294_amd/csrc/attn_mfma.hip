@@ -30,6 +30,8 @@
 #include "mfma_util.hpp"
 #include "range_schedule.hpp"
 
+#include <type_traits>
+
 namespace ra {
 
 constexpr int kTile = 32;  // tokens per key tile (two 16-token halves)
@@ -292,6 +294,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
 
     const RangeCut cut = range_cut((unsigned)total, a.min_units, a.max_ranges, a.range_skew);
     const int n_items = (int)cut.n_ranges * inner;
+    const bool long_ranges = cut.total > (kMfmaMinUnits + 1) * cut.n_ranges;
     if (blockIdx.x == 0)  // for the merge kernel: first record and number of records of every sequence
         for (int b = tid; b < B; b += 256) {
             SeqParts sp = {0, 0};
@@ -439,7 +442,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
 
             // Loads of a tile.  Halves that lie past the segment's end re-read its last 16-token block (their
             // scores are masked), so every address stays inside the segment.
-            auto issue = [&](const TileRef& r, KVTile& t) {
+            auto issue = [&](auto stream_values, const TileRef& r, KVTile& t) {
                 const int len = r.len;
                 const int nblk = (len + 15) >> 4;
 #pragma unroll
@@ -478,14 +481,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
 #pragma unroll
                         for (int kk = 0; kk < 4; ++kk) t.k[h][kk] = kq[kk * 4 + q4];
                         const uint2* vq = reinterpret_cast<const uint2*>(vp);
-#pragma unroll
                         // 4 x 8 bytes per channel: an instruction reads 512 contiguous bytes, whole cache lines, which is
-                        // what the non-temporal hint needs to pay (see load_once).  The variant for small batches keeps
-                        // ordinary loads: it is bound by latency, not bandwidth, and was 6 % slower with the hint
-                        // (16.4 -> 17.4 microseconds on the small-batch workload).
+                        // what the non-temporal hint needs to pay (see load_once).
+#pragma unroll
                         for (int dt = 0; dt < 8; ++dt) {
-                            if constexpr (INLINE_PLAN) t.v[dt][h] = vq[(dt * 16 + n) * 4 + q4];
-                            else t.v[dt][h] = load_once(vq + (dt * 16 + n) * 4 + q4);
+                            if constexpr (decltype(stream_values)::value) t.v[dt][h] = load_once(vq + (dt * 16 + n) * 4 + q4);
+                            else t.v[dt][h] = vq[(dt * 16 + n) * 4 + q4];
                         }
                     }
                 }
@@ -577,18 +578,18 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             // first product: both tiles are requested back to back and arrive together.  A form of this loop whose
             // waits leave the other tile's loads outstanding was measured and is no faster: the memory system is
             // full either way.
-            {
+            auto stream = [&](auto stream_values) {
                 KVTile ta, tb;
                 TileRef ref_a, ref_b;
                 int u = u_lo;
                 ref_a = tile_at(u);
-                issue(ref_a, ta);
+                issue(stream_values, ref_a, ta);
                 while (true) {
                     ++u;
                     const bool have_b = u < u_hi;
                     if (have_b) {
                         ref_b = tile_at(u);
-                        issue(ref_b, tb);
+                        issue(stream_values, ref_b, tb);
                     }
                     consume(ta, ref_a);
                     if (!have_b) break;
@@ -596,7 +597,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                     const bool have_a = u < u_hi;
                     if (have_a) {
                         ref_a = tile_at(u);
-                        issue(ref_a, ta);
+                        issue(stream_values, ref_a, ta);
                     }
                     consume(tb, ref_b);
                     if (!have_a) break;
@@ -605,7 +606,14 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                     const int done = u_hi - u_lo;
                     if (done & 63) flush_tile_lse(done & ~63, done & 63);
                 }
-            }
+            };
+            // Non-temporal value loads, except in small launches.  The planning kernel's launches are large; one that
+            // plans inline tells by the length of its ranges: while they are as short as ranges get the launch is bound
+            // by latency and the hint costs (39 MB of keys and values: 16.2 -> 17.1 microseconds; 59 MB, four tiles a
+            // range: 18.9 and 19.1), longer ones are bandwidth (118 MB: 30.4 -> 28.0; 0.7 GB: 135 -> 125; 2.4 GB: 419 ->
+            // 378).  Whole loops, not a choice at each load: the loads of a tile would sit in separate branches.
+            if (INLINE_PLAN && !long_ranges) stream(std::false_type());
+            else stream(std::true_type());
 
             // ---- the four lane groups hold partial sums of the same rows -------------------------------------
             l = xrow_sum4(l);
