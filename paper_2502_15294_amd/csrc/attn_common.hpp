@@ -75,7 +75,7 @@ inline AttnWorkspace attn_workspace(size_t rows, int S, int D, int B, int R_max)
 void launch_plan(const AttnArgs& a, int unit_tokens, hipStream_t st);
 int attn_min_units();  // smallest piece of a sequence's key set, in 32-token tiles
 
-// bf16, d = 128, Hq/Hkv <= 16, up to 32 query rows per KV head (decode, short questions): matrix-core streaming
+// bf16, d = 128 (one query token: also 64), Hq/Hkv <= 16, up to 32 query rows per KV head: matrix-core streaming
 // kernel, one wavefront per (range of the batch's key tiles, KV head, block of 16 query rows).
 int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st);
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st);  // ... and its second step
@@ -95,7 +95,7 @@ struct MfmaDecodeShape {
     int n_rowblocks, inner, grid, max_ranges, records;
     size_t rec_bytes, ml_bytes;
 };
-inline MfmaDecodeShape mfma_decode_shape(int num_cu, int B, int R_max, int Hkv, int rows_total, long long max_tiles) {
+inline MfmaDecodeShape mfma_decode_shape(int num_cu, int B, int Hkv, int D, int rows_total, long long max_tiles) {
     MfmaDecodeShape s;
     s.n_rowblocks = (rows_total + 15) / 16;
     s.inner = Hkv * s.n_rowblocks;
@@ -107,7 +107,9 @@ inline MfmaDecodeShape mfma_decode_shape(int num_cu, int B, int R_max, int Hkv, 
     // and finish a quarter later, while the sum stays what the memory system gives.  Alone on its SIMD every wave
     // runs at the same rate, and there are half as many records to merge (headline decode kernel 198.7 -> 194.6
     // microseconds, 85.1 -> 82.8 at 6 % of the tokens kept, 415.8 -> 410.4 per layer of the long-context workload).
-    const long long full = num_cu > 512 ? 512 : num_cu;
+    // (With 64 channels a tile is half the bytes and half the registers, and two workgroups keep as much in flight: 18.3 ->
+    // 17.5 microseconds for 60 MB, 27.6 -> 26.0 for 130 MB, alike for larger launches.)
+    const long long full = (num_cu > 512 ? 512 : num_cu) * (D == 64 ? 2 : 1);
     if (grid > full) grid = full;
     if (grid < 1) grid = 1;
     s.grid = (int)grid;
@@ -115,7 +117,7 @@ inline MfmaDecodeShape mfma_decode_shape(int num_cu, int B, int R_max, int Hkv, 
     if (ranges > want) ranges = want;
     s.max_ranges = (int)(ranges < 1 ? 1 : ranges);
     s.records = s.max_ranges + B;
-    s.rec_bytes = align_up((size_t)s.records * s.inner * 16 * 128 * sizeof(float), 256);
+    s.rec_bytes = align_up((size_t)s.records * s.inner * 16 * D * sizeof(float), 256);
     s.ml_bytes = align_up((size_t)s.records * s.inner * 16 * 2 * sizeof(float), 256);
     return s;
 }

@@ -1,4 +1,4 @@
-// Round-sparse attention over the selected rounds, bf16 / head_dim 128, on the matrix cores
+// Round-sparse attention over the selected rounds, bf16 / head_dim 128 (decode also 64), on the matrix cores
 // (paper Sec. 3.2 steps 4 and 5: question prefill and decode after the watershed layer).
 //
 // This kernel serves decode and short questions; long questions use the kernel that shares key tiles
@@ -17,7 +17,9 @@
 // never leave the lane except for one max over the four lane groups.  Values are stored transposed in
 // 16-token tiles so that the V^T operand is a plain 8-byte load per lane.
 //
-// P is rounded to bf16 twice (P = hi + lo, both bf16) so that the product carries ~16 bits of P.
+// P is rounded to bf16 twice (P = hi + lo, both bf16) so that the product carries ~16 bits of P; with 64 channels three
+// times (hi + mid + lo: all 24 bits), since those calls used to run on the vector ALU in fp32 and the matrix cores have
+// the time (half the products per token).
 //
 // Work decomposition (range_schedule.hpp): the key tiles of the whole batch are cut into equal ranges, and ONE
 // WAVEFRONT streams one range for one (KV head, block of 16 query rows), two tiles in flight, everything it
@@ -35,12 +37,12 @@
 namespace ra {
 
 constexpr int kTile = 32;  // tokens per key tile (two 16-token halves)
-constexpr int D128 = 128;
 constexpr int kLsePitch = 65;  // floats per row of a wave's strip of staged tile log-sum-exps
 
+template <int D>
 struct KVTile {
-    uint4 k[2][4];  // [half][kk]: 8 channels kk*32 + 8*(lane/16) .. of token half*16 + lane%16
-    uint2 v[8][2];  // [dt][half]: tokens 4*(lane/16) .. +3 of that half, channel dt*16 + lane%16
+    uint4 k[2][D / 32];  // [half][kk]: 8 channels kk*32 + 8*(lane/16) .. of token half*16 + lane%16
+    uint2 v[D / 16][2];  // [dt][half]: tokens 4*(lane/16) .. +3 of that half, channel dt*16 + lane%16
 };
 
 // Where a key tile lies; every field is the same in all lanes of the wave.
@@ -73,14 +75,15 @@ __device__ __forceinline__ int wave_exclusive_scan(int v, int lane, int& total) 
     return incl - v;
 }
 
-// Merge of the records (a record: the accumulators of the 16 rows of a block, row-major [16][128], and (max, sum)
+// Merge of the records (a record: the accumulators of the 16 rows of a block, row-major [16][D], and (max, sum)
 // per row) of every (sequence, KV head, row block) that was cut; grid (B * inner), block 256.
-// Thread = (group, row, four channels): the rows of the block (at most eight per pass) times 32 channel quads fill
-// 32 .. 256 threads, and when they fill fewer the remaining threads form further groups that take every NG-th
+// Thread = (group, row, four channels): the rows of the block (at most eight per pass) times D / 4 channel quads fill
+// 16 .. 256 threads, and when they fill fewer the remaining threads form further groups that take every NG-th
 // record; the groups are then merged through LDS.  Four records per thread are in flight at a time.
+template <int D>
 __global__ __launch_bounds__(256) void merge_records_kernel(AttnArgs a, int n_rowblocks) {
-    __shared__ float sh_num[8][8][D128];  // [group][row][channel]
-    __shared__ float sh_ml[8][8][2];
+    __shared__ float sh_num[1024 / D][8][D];  // [group][row][channel]
+    __shared__ float sh_ml[1024 / D][8][2];
     const int Hkv = a.view.Hkv, inner = Hkv * n_rowblocks;
     const int b = blockIdx.x / inner, gi = blockIdx.x - b * inner;
     const int g = gi % Hkv, rowblock = gi / Hkv;
@@ -91,9 +94,10 @@ __global__ __launch_bounds__(256) void merge_records_kernel(AttnArgs a, int n_ro
     for (int row0 = 0; row0 < rows_here; row0 += 8) {
         const int R = min(8, rows_here - row0);
         const int rp_log2 = R <= 1 ? 0 : (R <= 2 ? 1 : (R <= 4 ? 2 : 3));
-        const int group_threads = 32 << rp_log2, NG = 256 >> (5 + rp_log2);
-        const int grp = t >> (5 + rp_log2), tt = t & (group_threads - 1);
-        const int r = tt >> 5, c4 = tt & 31;
+        constexpr int kQuadsLog2 = D == 128 ? 5 : 4;  // threads of a row
+        const int group_threads = 1 << (kQuadsLog2 + rp_log2), NG = 256 >> (kQuadsLog2 + rp_log2);
+        const int grp = t >> (kQuadsLog2 + rp_log2), tt = t & (group_threads - 1);
+        const int r = tt >> kQuadsLog2, c4 = tt & (D / 4 - 1);
         const bool active = r < R;
         const int row = row0 + (active ? r : 0);
         float M = kNegBig, den = 0.f;
@@ -108,7 +112,7 @@ __global__ __launch_bounds__(256) void merge_records_kernel(AttnArgs a, int n_ro
                 ml[j] = make_float2(kNegBig, 0.f);
                 if (p < n_parts && active) {
                     const size_t rrow = ((size_t)(rec0 + p) * inner + gi) * 16 + row;
-                    v[j] = *reinterpret_cast<const floatx4_t*>(a.rec_acc + rrow * D128 + c4 * 4);
+                    v[j] = *reinterpret_cast<const floatx4_t*>(a.rec_acc + rrow * D + c4 * 4);
                     ml[j] = *reinterpret_cast<const float2*>(a.rec_ml + rrow * 2);
                 }
             }
@@ -142,7 +146,7 @@ __global__ __launch_bounds__(256) void merge_records_kernel(AttnArgs a, int n_ro
             const int rw = rowblock * 16 + row, qi = rw / a.G;
             const size_t rid = ((size_t)b * a.q_len + qi) * a.Hq + (size_t)g * a.G + (rw - qi * a.G);
             const float inv = d > 0.f ? 1.f / d : 0.f;
-            *reinterpret_cast<floatx4_t*>(a.out + rid * D128 + c4 * 4) = o * inv;
+            *reinterpret_cast<floatx4_t*>(a.out + rid * D + c4 * 4) = o * inv;
             if (a.lse && c4 == 0) a.lse[rid] = d > 0.f ? __builtin_fmaf(Mx, a.scale, __builtin_logf(d)) : -__builtin_inff();
         }
         __syncthreads();  // the next pass reuses the buffers
@@ -152,8 +156,10 @@ __global__ __launch_bounds__(256) void merge_records_kernel(AttnArgs a, int n_ro
 // TILE_LSE: also one log-sum-exp per (query row, key tile), the raw material of the round scores at the watershed
 // layer; staged per wave in LDS and written out in runs of up to 64 tiles per row.
 // INLINE_PLAN: the workgroup resolves the batch's selections itself instead of reading the planning kernel's tables.
-template <bool PAGED, bool TILE_LSE, bool INLINE_PLAN>
+template <int D, bool PAGED, bool TILE_LSE, bool INLINE_PLAN>
 __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_rowblocks) {
+    constexpr int KK = D / 32, DT = D / 16, kParts = D == 64 ? 3 : 2;  // contraction steps of Q.K^T, 16-channel tiles of the output,
+                                                                        // bf16 numbers a probability is carried as
     extern __shared__ __align__(16) char smem[];
     __shared__ int sU[kMaxBatch], sps[kMaxBatch + 1];
     const DevView& vw = a.view;
@@ -281,7 +287,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
         const int rows_seq = q_len * a.Hq;
         for (int b = wave; b < B; b += 4) {
             if (sU[b] != 0) continue;
-            for (int i = lane; i < rows_seq * D128; i += 64) a.out[(size_t)b * rows_seq * D128 + i] = 0.f;
+            for (int i = lane; i < rows_seq * D; i += 64) a.out[(size_t)b * rows_seq * D + i] = 0.f;
             if (a.lse)
                 for (int i = lane; i < rows_seq; i += 64) a.lse[(size_t)b * rows_seq + i] = -__builtin_inff();
         }
@@ -336,11 +342,11 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             const int rr = row_ok ? row : 0;
             const int qtok = rr / G;
             const size_t rowid = ((size_t)b * q_len + qtok) * a.Hq + (size_t)g * G + (rr - qtok * G);
-            uint4 qf[4];
+            uint4 qf[KK];
             {
-                const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + rowid * D128 * 2);
+                const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + rowid * D * 2);
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) qf[kk] = row_ok ? qp[kk * 4 + q4] : make_uint4(0, 0, 0, 0);
+                for (int kk = 0; kk < KK; ++kk) qf[kk] = row_ok ? qp[kk * 4 + q4] : make_uint4(0, 0, 0, 0);
             }
 
             // ---- the sequence's segment table: a window of 64 entries in this wave's registers -------------
@@ -435,14 +441,14 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 return t;
             };
 
-            floatx4_t acc[8];
+            floatx4_t acc[DT];
             float m = kNegBig, l = 0.f;
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) acc[dt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+            for (int dt = 0; dt < DT; ++dt) acc[dt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
             // Loads of a tile.  Halves that lie past the segment's end re-read its last 16-token block (their
             // scores are masked), so every address stays inside the segment.
-            auto issue = [&](auto stream_values, const TileRef& r, KVTile& t) {
+            auto issue = [&](auto stream_values, const TileRef& r, KVTile<D>& t) {
                 const int len = r.len;
                 const int nblk = (len + 15) >> 4;
 #pragma unroll
@@ -450,19 +456,19 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                     const int blk = min(r.uin * 2 + h, nblk - 1);  // uniform
                     const int rin = min(n, len - 1 - blk * 16);    // row inside the block, clamped
                     if (r.is_cur) {
-                        const size_t e0 = (((size_t)b * a.cur_cap + blk * 16 + rin) * Hkv + g) * D128;
+                        const size_t e0 = (((size_t)b * a.cur_cap + blk * 16 + rin) * Hkv + g) * D;
                         const uint4* kp = reinterpret_cast<const uint4*>(ck + e0 * 2);
 #pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) t.k[h][kk] = kp[kk * 4 + q4];
+                        for (int kk = 0; kk < KK; ++kk) t.k[h][kk] = kp[kk * 4 + q4];
                         // token-major values: gather 4 tokens of one channel with 2-byte loads
                         const unsigned short* vp = reinterpret_cast<const unsigned short*>(cv);
 #pragma unroll
-                        for (int dt = 0; dt < 8; ++dt) {
+                        for (int dt = 0; dt < DT; ++dt) {
                             uint32_t e[4];
 #pragma unroll
                             for (int j = 0; j < 4; ++j) {
                                 const int tok = min(blk * 16 + q4 * 4 + j, len - 1);
-                                e[j] = vp[(((size_t)b * a.cur_cap + tok) * Hkv + g) * D128 + dt * 16 + n];
+                                e[j] = vp[(((size_t)b * a.cur_cap + tok) * Hkv + g) * D + dt * 16 + n];
                             }
                             t.v[dt][h] = make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16));
                         }
@@ -470,21 +476,21 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                         const char *kp, *vp;
                         if (PAGED) {
                             const int pb = h ? r.pb1 : r.pb0;
-                            kp = kbase + ((((size_t)pb * Hkv + g) * 16 + rin) * D128) * 2;
-                            vp = vbase + (((size_t)pb * Hkv + g) * D128 * 16) * 2;
+                            kp = kbase + ((((size_t)pb * Hkv + g) * 16 + rin) * D) * 2;
+                            vp = vbase + (((size_t)pb * Hkv + g) * D * 16) * 2;
                         } else {
                             const size_t L16 = (size_t)nblk * 16;
-                            kp = kbase + ((((size_t)r.ok * Hkv + (size_t)g * len + blk * 16 + rin) * D128)) * 2;
-                            vp = vbase + ((((size_t)r.ov * Hkv + (size_t)g * L16 + (size_t)blk * 16) * D128)) * 2;
+                            kp = kbase + ((((size_t)r.ok * Hkv + (size_t)g * len + blk * 16 + rin) * D)) * 2;
+                            vp = vbase + ((((size_t)r.ov * Hkv + (size_t)g * L16 + (size_t)blk * 16) * D)) * 2;
                         }
                         const uint4* kq = reinterpret_cast<const uint4*>(kp);
 #pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) t.k[h][kk] = kq[kk * 4 + q4];
+                        for (int kk = 0; kk < KK; ++kk) t.k[h][kk] = kq[kk * 4 + q4];
                         const uint2* vq = reinterpret_cast<const uint2*>(vp);
                         // 4 x 8 bytes per channel: an instruction reads 512 contiguous bytes, whole cache lines, which is
                         // what the non-temporal hint needs to pay (see load_once).
 #pragma unroll
-                        for (int dt = 0; dt < 8; ++dt) {
+                        for (int dt = 0; dt < DT; ++dt) {
                             if constexpr (decltype(stream_values)::value) t.v[dt][h] = load_once(vq + (dt * 16 + n) * 4 + q4);
                             else t.v[dt][h] = vq[(dt * 16 + n) * 4 + q4];
                         }
@@ -507,7 +513,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 __builtin_amdgcn_wave_barrier();
             };
 
-            auto consume = [&](const KVTile& t, const TileRef& r) {
+            auto consume = [&](const KVTile<D>& t, const TileRef& r) {
                 const int tok0 = r.uin * kTile, len = r.len;
                 const bool full = !r.is_cur && (len - tok0 >= kTile);
                 floatx4_t sc[2];
@@ -515,7 +521,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 for (int h = 0; h < 2; ++h) {
                     sc[h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) sc[h] = mfma16(t.k[h][kk], qf[kk], sc[h]);
+                    for (int kk = 0; kk < KK; ++kk) sc[h] = mfma16(t.k[h][kk], qf[kk], sc[h]);
                 }
                 if (!full) {
                     // tokens this row may see: the segment's length, or inside the current round the causal limit
@@ -536,7 +542,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                     const float alpha = fast_exp2((m - m_new) * a.c);
                     l *= alpha;
 #pragma unroll
-                    for (int dt = 0; dt < 8; ++dt) acc[dt] *= alpha;
+                    for (int dt = 0; dt < DT; ++dt) acc[dt] *= alpha;
                     m = m_new;
                 }
                 const float mc = m * a.c;
@@ -555,20 +561,23 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                             pt > 0.f ? kLn2 * __builtin_fmaf(m, a.c, fast_log2(pt)) : -__builtin_inff();
                     if ((ut & 63) == 63) flush_tile_lse(ut - 63, 64);
                 }
-                uint4 phi, plo;
-                phi.x = pack_trunc(p[0], p[1]);
-                phi.y = pack_trunc(p[2], p[3]);
-                phi.z = pack_trunc(p[4], p[5]);
-                phi.w = pack_trunc(p[6], p[7]);
-                plo.x = pack_trunc(p[0] - trunc_bf16(p[0]), p[1] - trunc_bf16(p[1]));
-                plo.y = pack_trunc(p[2] - trunc_bf16(p[2]), p[3] - trunc_bf16(p[3]));
-                plo.z = pack_trunc(p[4] - trunc_bf16(p[4]), p[5] - trunc_bf16(p[5]));
-                plo.w = pack_trunc(p[6] - trunc_bf16(p[6]), p[7] - trunc_bf16(p[7]));
+                // P as a sum of bf16 numbers by truncation, and O^T += V^T . (each of them)
+                uint4 ph[kParts];
 #pragma unroll
-                for (int dt = 0; dt < 8; ++dt) {
+                for (int i = 0; i < kParts; ++i) {
+                    ph[i].x = pack_trunc(p[0], p[1]);
+                    ph[i].y = pack_trunc(p[2], p[3]);
+                    ph[i].z = pack_trunc(p[4], p[5]);
+                    ph[i].w = pack_trunc(p[6], p[7]);
+                    if (i + 1 < kParts)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) p[j] -= trunc_bf16(p[j]);
+                }
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
                     const uint4 vf = make_uint4(t.v[dt][0].x, t.v[dt][0].y, t.v[dt][1].x, t.v[dt][1].y);
-                    acc[dt] = mfma16(vf, phi, acc[dt]);
-                    acc[dt] = mfma16(vf, plo, acc[dt]);
+#pragma unroll
+                    for (int i = 0; i < kParts; ++i) acc[dt] = mfma16(vf, ph[i], acc[dt]);
                 }
             };
 
@@ -579,7 +588,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             // waits leave the other tile's loads outstanding was measured and is no faster: the memory system is
             // full either way.
             auto stream = [&](auto stream_values) {
-                KVTile ta, tb;
+                KVTile<D> ta, tb;
                 TileRef ref_a, ref_b;
                 int u = u_lo;
                 ref_a = tile_at(u);
@@ -621,8 +630,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 if (row_ok) {
                     const float inv = l > 0.f ? 1.f / l : 0.f;
 #pragma unroll
-                    for (int dt = 0; dt < 8; ++dt)
-                        *reinterpret_cast<floatx4_t*>(a.out + rowid * D128 + dt * 16 + q4 * 4) = acc[dt] * inv;
+                    for (int dt = 0; dt < DT; ++dt)
+                        *reinterpret_cast<floatx4_t*>(a.out + rowid * D + dt * 16 + q4 * 4) = acc[dt] * inv;
                     if (a.lse && q4 == 0)
                         a.lse[rowid] = l > 0.f ? __builtin_fmaf(m, a.scale, __builtin_logf(l)) : -__builtin_inff();
                 }
@@ -633,22 +642,17 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             if (row_ok) {
                 const size_t rrow = ((size_t)rec * inner + gi) * 16 + n;
 #pragma unroll
-                for (int dt = 0; dt < 8; ++dt)
-                    *reinterpret_cast<floatx4_t*>(a.rec_acc + rrow * D128 + dt * 16 + q4 * 4) = acc[dt];
+                for (int dt = 0; dt < DT; ++dt)
+                    *reinterpret_cast<floatx4_t*>(a.rec_acc + rrow * D + dt * 16 + q4 * 4) = acc[dt];
                 if (q4 == 0) *reinterpret_cast<float2*>(a.rec_ml + rrow * 2) = make_float2(m, l);
             }
         }
     }
 }
 
-int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) {
-    const int rows_total = a.q_len * a.G;
-    const int B = a.view.B, Hkv = a.view.Hkv;
-    if (a.G > 16) return fail(RA_ERR_UNSUPPORTED, "attention: Hq / Hkv = %d exceeds 16", a.G);
-    if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "attention: batch %d exceeds %d", B, kMaxBatch);
-    const MfmaDecodeShape s =
-        mfma_decode_shape(num_cu, B, a.view.R_max, Hkv, rows_total, mfma_max_tiles(B, a.max_tokens, a.view.R_max, a.cur_cap));
-    if (a.max_ranges != s.max_ranges) return fail(RA_ERR_INVALID_ARG, "attention: launch shape mismatch");
+template <int D>
+static void launch_attn_mfma_d(const AttnArgs& a, bool paged, const MfmaDecodeShape& s, hipStream_t st) {
+    const int B = a.view.B;
     const bool inline_plan = attn_mfma_plans_inline(B, a.view.R_max);
     const bool tile_lse = a.tile_lse != nullptr;
     const size_t smem = (tile_lse ? (size_t)4 * 16 * kLsePitch * sizeof(float) : 0) +
@@ -656,22 +660,39 @@ int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) 
     const dim3 g((unsigned)s.grid), blk(256);
 #define RA_ATTN_CASE(P_, L_, I_)                                                                          \
     if (paged == P_ && tile_lse == L_ && inline_plan == I_) {                                             \
-        RA_LAUNCH_TIMED((attn_mfma_kernel<P_, L_, I_>), g, blk, smem, st, a, s.n_rowblocks);              \
-        return RA_OK;                                                                                     \
+        RA_LAUNCH_TIMED((attn_mfma_kernel<D, P_, L_, I_>), g, blk, smem, st, a, s.n_rowblocks);           \
+        return;                                                                                           \
     }
     RA_ATTN_CASE(false, false, false) RA_ATTN_CASE(false, false, true) RA_ATTN_CASE(true, false, false)
-    RA_ATTN_CASE(true, false, true) RA_ATTN_CASE(false, true, false) RA_ATTN_CASE(false, true, true)
-    RA_ATTN_CASE(true, true, false) RA_ATTN_CASE(true, true, true)
+    RA_ATTN_CASE(true, false, true)
+    if constexpr (D == 128) {  // scores from the attention pass: 128 channels only
+        RA_ATTN_CASE(false, true, false) RA_ATTN_CASE(false, true, true) RA_ATTN_CASE(true, true, false)
+        RA_ATTN_CASE(true, true, true)
+    }
 #undef RA_ATTN_CASE
+}
+
+int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) {
+    const int rows_total = a.q_len * a.G;
+    const int B = a.view.B, Hkv = a.view.Hkv, D = a.view.d;
+    if (a.G > 16) return fail(RA_ERR_UNSUPPORTED, "attention: Hq / Hkv = %d exceeds 16", a.G);
+    if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "attention: batch %d exceeds %d", B, kMaxBatch);
+    const MfmaDecodeShape s =
+        mfma_decode_shape(num_cu, B, Hkv, D, rows_total, mfma_max_tiles(B, a.max_tokens, a.view.R_max, a.cur_cap));
+    if (a.max_ranges != s.max_ranges) return fail(RA_ERR_INVALID_ARG, "attention: launch shape mismatch");
+    if (D == 128) launch_attn_mfma_d<128>(a, paged, s, st);
+    else launch_attn_mfma_d<64>(a, paged, s, st);
     return RA_OK;
 }
 
 // Second step of the matrix-core kernel above: merges the records of the sequences that were cut.
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st) {
-    const MfmaDecodeShape s = mfma_decode_shape(num_cu, a.view.B, a.view.R_max, a.view.Hkv, a.q_len * a.G,
+    const MfmaDecodeShape s = mfma_decode_shape(num_cu, a.view.B, a.view.Hkv, a.view.d, a.q_len * a.G,
                                                 mfma_max_tiles(a.view.B, a.max_tokens, a.view.R_max, a.cur_cap));
     if (s.max_ranges <= 1) return;  // a single range never cuts a sequence
-    hipLaunchKernelGGL(merge_records_kernel, dim3((unsigned)(a.view.B * s.inner)), dim3(256), 0, st, a, s.n_rowblocks);
+    const dim3 g((unsigned)(a.view.B * s.inner)), blk(256);
+    if (a.view.d == 128) hipLaunchKernelGGL((merge_records_kernel<128>), g, blk, 0, st, a, s.n_rowblocks);
+    else hipLaunchKernelGGL((merge_records_kernel<64>), g, blk, 0, st, a, s.n_rowblocks);
 }
 
 }  // namespace ra

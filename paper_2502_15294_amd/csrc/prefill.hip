@@ -46,7 +46,7 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     if (few_rows) {
         const long long max_tiles = mfma_max_tiles(B, layer->max_tokens, layer->R_max, cur_len);
         RA_REQUIRE(max_tiles < ((long long)1 << 30), RA_ERR_UNSUPPORTED, "prefill: max_tokens too large for this batch");
-        shape = mfma_decode_shape(ctx->num_cu, B, layer->R_max, layer->Hkv, q_len * G, max_tiles);
+        shape = mfma_decode_shape(ctx->num_cu, B, layer->Hkv, D, q_len * G, max_tiles);
         mw = mfma_decode_workspace(shape, B, layer->R_max);
         plan_off = mw.plan_off;
         scratch_total = mw.total;

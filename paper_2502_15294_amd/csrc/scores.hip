@@ -786,7 +786,7 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
     // normalisation over history rounds, so its keys need not be read at all -- unless the masses are
     // added to those of other tokens, each with its own share.
     const bool use_cur = cur_k != nullptr && (q_len > 1 || acc != nullptr);
-    const bool mfma = watershed->dtype == RA_BF16 && D == 128;
+    bool mfma = watershed->dtype == RA_BF16 && D == 128;
     const int chunk_tokens = kChunkTokens;
     const int64_t nc64 = watershed->max_tokens / chunk_tokens + R_max + (use_cur ? (cur_len + chunk_tokens - 1) / chunk_tokens : 0);
     RA_REQUIRE(nc64 <= (int64_t)1 << 24, RA_ERR_UNSUPPORTED, "round_scores: max_tokens too large");
@@ -801,7 +801,15 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
     if (many_rows) RA_REQUIRE(B <= kMaxBatch, RA_ERR_UNSUPPORTED, "round_scores: batch %d exceeds %d", B, kMaxBatch);
     const size_t plan_bytes = many_rows ? align_up((size_t)B * plan_stride(R_max + 1), 256) : 0;
     // few rows on the matrix cores: one 16-byte descriptor per (sequence, chunk)
-    const size_t desc_bytes = mfma && !many_rows ? align_up((size_t)B * n_chunks_max * 16, 256) : 0;
+    size_t desc_bytes = mfma && !many_rows ? align_up((size_t)B * n_chunks_max * 16, 256) : 0;
+    // 64 channels run there too as long as there are few rows, the descriptors fit and the 16-byte loads are aligned
+    // (16 dialogues of 12 000 tokens, 196 MB of keys: 63 -> 33 microseconds); the generic kernel takes what is left
+    if (watershed->dtype == RA_BF16 && D == 64 && q_len * G <= 16 && (G & (G - 1)) == 0 && G <= 8 &&
+        (((uintptr_t)q | (uintptr_t)watershed->k | (uintptr_t)cur_k) & 15) == 0) {
+        const size_t bytes = align_up((size_t)B * n_chunks_max * 16, 256);
+        mfma = ctx->ws.base != nullptr && ctx->ws.bytes >= kWsReserved + part_bytes + p_bytes + bytes;
+        if (mfma) desc_bytes = bytes;
+    }
     RA_REQUIRE(ctx->ws.base != nullptr && ctx->ws.bytes >= kWsReserved + part_bytes + p_bytes + plan_bytes + desc_bytes,
                RA_ERR_WORKSPACE, "round_scores: workspace has %zu bytes, this call needs %zu", ctx->ws.bytes,
                kWsReserved + part_bytes + p_bytes + plan_bytes + desc_bytes);

@@ -1,5 +1,5 @@
 // Round scores (paper Sec. 3.1, Eq. 1), streaming pass over the watershed layer's keys for bf16 /
-// head_dim 128 on the matrix cores.  Same roles as in the attention kernel: the query rows of a KV
+// head_dim 128 or 64 on the matrix cores.  Same roles as in the attention kernel: the query rows of a KV
 // head (query token i, head h of the group; row = i * G + h) are handled in tiles of 16, keys in
 // tiles of 32 tokens, S^T[16 tokens x 16 rows] = K . Q^T with four mfma 16x16x32 per 16 tokens, and
 // lane%16 is the query row, so the running (max, sum-exp) of a row stays in its lane.
@@ -33,10 +33,11 @@ constexpr long long kDescMinWorkgroupsFewRounds = 32768;
 constexpr size_t kDescLdsPad = 12 * 1024;
 constexpr long long kDescPadMinWorkgroups = 16384;  // launches of at least this many workgroups get the padding
 
-// A 32-token key tile on its way from memory: load j holds 16 bytes (chunk lane%16) of the row of token
-// 4 j + lane/16, so that one load instruction reads four whole rows (eight whole cache lines).
+// A 32-token key tile on its way from memory: a row is C = D / 8 chunks of 16 bytes, load j holds chunk lane%C of the
+// row of token (64 / C) j + lane/C, so that one load instruction reads 1 KB of whole rows (eight whole cache lines).
+template <int D>
 struct KTile {
-    uint4 r[8];
+    uint4 r[D / 16];
 };
 
 // Where chunk c of a sequence lies: written once per call by scores_chunks_kernel for the large launches, whose
@@ -121,12 +122,14 @@ constexpr int kDescriptors = 1;   // one scalar load of what scores_chunks_kerne
 constexpr int kTableScalar = 2;   // at most kScalarRounds rounds: their lengths by scalar loads, the prefix in
 constexpr int kScalarRounds = 32; // scalar registers: no LDS, no barrier, no vector load, and no kernel before
 
-template <bool PAGED, int TAB>
-__global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
+template <int D, bool PAGED, int TAB>
+__device__ __forceinline__ void score_chunk(const ScoreArgs& a) {
+    constexpr int KK = D / 32, C = D / 8, RPL = 64 / C;  // contraction steps, 16-byte chunks of a row, rows per load
+    constexpr int kRow = 2 * D;                          // bytes of a row
     constexpr bool DESC = TAB != kTableInLds;  // the table's loads go the scalar way
     extern __shared__ __align__(16) char smem[];
     __shared__ float sm[4][16], sl[4][16];
-    __shared__ uint4 strip[4][512];  // per wave: one key tile, row-major, the 16-byte chunks of row r rotated by r
+    __shared__ uint4 strip[4][32 * C];  // per wave: one key tile, row-major, the 16-byte chunks of row r rotated by r
     const DevView& vw = a.view;
     const int Hkv = vw.Hkv;
     const int c = blockIdx.x, b = blockIdx.z;
@@ -134,6 +137,7 @@ __global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 15, q4 = lane >> 4;
+    const int ch = lane & (C - 1), lr = lane / C;  // loads: this lane's chunk of its row, its row among a load's
     const int G = a.Hq / Hkv, q_len = a.q_len;
     const int rows_total = q_len * G;
     constexpr int NT = 1, RB = 16;
@@ -195,7 +199,7 @@ __global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
     int lim[NT];
     bool row_ok[NT];
     size_t rowid[NT];
-    uint4 qf[NT][4];
+    uint4 qf[NT][KK];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int row = rowblock * RB + nt * 16 + n;
@@ -204,9 +208,9 @@ __global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
         const int qtok = rr / G;
         rowid[nt] = ((size_t)b * a.Hq + (size_t)g * G + (rr - qtok * G)) * q_len + qtok;  // [B][Hq][q_len]
         const size_t qrow = ((size_t)b * q_len + qtok) * a.Hq + (size_t)g * G + (rr - qtok * G);
-        const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + qrow * 256);
+        const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + qrow * kRow);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = row_ok[nt] ? qp[kk * 4 + q4] : make_uint4(0, 0, 0, 0);
+        for (int kk = 0; kk < KK; ++kk) qf[nt][kk] = row_ok[nt] ? qp[kk * 4 + q4] : make_uint4(0, 0, 0, 0);
         // tokens of this segment the row may see (causal inside the current round)
         lim[nt] = is_cur ? cur_visible(len, q_len, qtok) : len;
         if (!row_ok[nt]) lim[nt] = 0;
@@ -230,7 +234,7 @@ __global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
     struct TileBase {
         const char* base[2];
     };
-    const long long pitch = is_cur ? (long long)Hkv * 256 : 256;
+    const long long pitch = is_cur ? (long long)Hkv * kRow : kRow;
     const int mask = (PAGED && !is_cur) ? 15 : -1;
     auto bases_of = [&](const int (&tok0)[2], TileBase (&tb)[2]) {
         if constexpr (PAGED) {
@@ -252,38 +256,38 @@ __global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int hh = 0; hh < 2; ++hh)
-                    tb[j].base[hh] = kbase + ((size_t)max(pb[j][hh], 0) * Hkv + g) * 16 * 256;
+                    tb[j].base[hh] = kbase + ((size_t)max(pb[j][hh], 0) * Hkv + g) * 16 * kRow;
         } else {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) tb[j].base[0] = tb[j].base[1] = kbase + ((size_t)off * Hkv + (size_t)g * len) * 256;
+            for (int j = 0; j < 2; ++j) tb[j].base[0] = tb[j].base[1] = kbase + ((size_t)off * Hkv + (size_t)g * len) * kRow;
         }
         if (is_cur) {
 #pragma unroll
             for (int j = 0; j < 2; ++j)
                 tb[j].base[0] = tb[j].base[1] =
-                    reinterpret_cast<const char*>(a.cur_k) + ((size_t)b * a.cur_len * Hkv + g) * 256;
+                    reinterpret_cast<const char*>(a.cur_k) + ((size_t)b * a.cur_len * Hkv + g) * kRow;
         }
     };
-    auto issue = [&](int tok0, const TileBase& tb, KTile& t) {
+    auto issue = [&](int tok0, const TileBase& tb, KTile<D>& t) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int tok = min(tok0 + 4 * j + q4, len - 1);
-            const char* kp = tb.base[j >> 2] + (long long)(tok & mask) * pitch;
-            t.r[j] = load_once(reinterpret_cast<const uint4*>(kp) + n);
+        for (int j = 0; j < D / 16; ++j) {
+            const int tok = min(tok0 + RPL * j + lr, len - 1);
+            const char* kp = tb.base[j >= D / 32] + (long long)(tok & mask) * pitch;
+            t.r[j] = load_once(reinterpret_cast<const uint4*>(kp) + ch);
         }
     };
-    auto consume = [&](const KTile& t, int tok0) {
+    auto consume = [&](const KTile<D>& t, int tok0) {
         const bool full = !is_cur && (len - tok0 >= kTileS);
         // through the wave's LDS strip into the operand layout: lane (n, q4) needs chunk kk*4 + q4 of row h*16 + n.
         // (Same wave: LDS operations complete in program order, so the next tile's writes follow these reads.)
         uint4* st = strip[wave];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) st[(4 * j + q4) * 16 + ((n + 4 * j + q4) & 15)] = t.r[j];
-        uint4 kf[2][4];
+        for (int j = 0; j < D / 16; ++j) st[(RPL * j + lr) * C + ((ch + RPL * j + lr) & (C - 1))] = t.r[j];
+        uint4 kf[2][KK];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) kf[h][kk] = st[(h * 16 + n) * 16 + ((kk * 4 + q4 + n) & 15)];
+            for (int kk = 0; kk < KK; ++kk) kf[h][kk] = st[(h * 16 + n) * C + ((kk * 4 + q4 + n) & (C - 1))];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             floatx4_t sc[2];
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
             for (int h = 0; h < 2; ++h) {
                 sc[h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) sc[h] = mfma16(kf[h][kk], qf[nt][kk], sc[h]);
+                for (int kk = 0; kk < KK; ++kk) sc[h] = mfma16(kf[h][kk], qf[nt][kk], sc[h]);
             }
             if (!full) {
 #pragma unroll
@@ -318,7 +322,7 @@ __global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
     };
 
     {
-        KTile t[2];
+        KTile<D> t[2];
         int tok0[2];
         TileBase tb[2];
 #pragma unroll
@@ -360,6 +364,25 @@ __global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {
     }
 }
 
+template <bool PAGED, int TAB>
+__global__ __launch_bounds__(256) void scores_mfma_kernel(ScoreArgs a) {  // 128 channels
+    score_chunk<128, PAGED, TAB>(a);
+}
+template <bool PAGED, int TAB>
+__global__ __launch_bounds__(256) void scores_head64_kernel(ScoreArgs a) {
+    score_chunk<64, PAGED, TAB>(a);
+}
+
+template <int TAB>
+static void launch_scores_mfma_tab(const ScoreArgs& a, bool paged, dim3 grid, size_t smem, hipStream_t st) {
+    if (a.view.d == 128) {
+        if (paged) RA_LAUNCH_TIMED((scores_mfma_kernel<true, TAB>), grid, dim3(256), smem, st, a);
+        else RA_LAUNCH_TIMED((scores_mfma_kernel<false, TAB>), grid, dim3(256), smem, st, a);
+    } else {
+        if (paged) RA_LAUNCH_TIMED((scores_head64_kernel<true, TAB>), grid, dim3(256), smem, st, a);
+        else RA_LAUNCH_TIMED((scores_head64_kernel<false, TAB>), grid, dim3(256), smem, st, a);
+    }
+}
 
 int launch_scores_mfma(const ScoreArgs& a, bool paged, int /*num_cu*/, hipStream_t st) {
     const int G = a.Hq / a.view.Hkv;
@@ -373,24 +396,13 @@ int launch_scores_mfma(const ScoreArgs& a, bool paged, int /*num_cu*/, hipStream
     if (a.chunks && n_wg >= (a.view.R_max <= kScalarRounds ? kDescMinWorkgroupsFewRounds : kDescMinWorkgroups)) {
         hipLaunchKernelGGL(scores_chunks_kernel, dim3(a.view.B), dim3(256), tab_bytes, st, a,
                            reinterpret_cast<ChunkDesc*>(a.chunks));
-        const size_t pad = n_wg >= kDescPadMinWorkgroups ? kDescLdsPad : 0;
-        if (paged)
-            RA_LAUNCH_TIMED((scores_mfma_kernel<true, kDescriptors>), grid, dim3(256), pad, st, a);
-        else
-            RA_LAUNCH_TIMED((scores_mfma_kernel<false, kDescriptors>), grid, dim3(256), pad, st, a);
-        return RA_OK;
+        const size_t pad = a.view.d == 128 && n_wg >= kDescPadMinWorkgroups ? kDescLdsPad : 0;
+        launch_scores_mfma_tab<kDescriptors>(a, paged, grid, pad, st);
+    } else if (a.view.R_max <= kScalarRounds) {
+        launch_scores_mfma_tab<kTableScalar>(a, paged, grid, 0, st);
+    } else {
+        launch_scores_mfma_tab<kTableInLds>(a, paged, grid, tab_bytes, st);
     }
-    if (a.view.R_max <= kScalarRounds) {
-        if (paged)
-            RA_LAUNCH_TIMED((scores_mfma_kernel<true, kTableScalar>), grid, dim3(256), 0, st, a);
-        else
-            RA_LAUNCH_TIMED((scores_mfma_kernel<false, kTableScalar>), grid, dim3(256), 0, st, a);
-        return RA_OK;
-    }
-    if (paged)
-        RA_LAUNCH_TIMED((scores_mfma_kernel<true, kTableInLds>), grid, dim3(256), tab_bytes, st, a);
-    else
-        RA_LAUNCH_TIMED((scores_mfma_kernel<false, kTableInLds>), grid, dim3(256), tab_bytes, st, a);
     return RA_OK;
 }
 
