@@ -53,6 +53,8 @@ struct AttnArgs {
     int* seq_rec;     // [B][2] first record and number of records of every sequence (written by the kernel)
     int max_ranges;   // most ranges the batch's key tiles are cut into
     int range_skew;   // in 1/1000: how much more than half of the tiles the first half of the ranges gets (see RangeCut)
+    int num_cu;       // compute units of the device (many-row kernel)
+    int plan_inline;  // many-row kernel: it plans itself, no planning kernel ran
     int p_half;       // many-row kernel: probabilities as one fp16 operand instead of two bf16 (ra_set_prefill_precision)
 };
 

@@ -33,6 +33,8 @@
 #include "mfma_util.hpp"
 #include "stream_kv.hpp"
 
+#include <type_traits>
+
 namespace ra {
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
@@ -61,7 +63,8 @@ constexpr int kTileP = 32;                      // tokens per key tile
 constexpr int kNTP = 2;                         // 16-row tiles per wave
 constexpr int kRowsPerItem = 4 * kNTP * 16;     // 128
 constexpr int kTileBytes = 16384;               // 8 K fragments of 1 KB + 16 V fragments of 512 B
-constexpr int kPiecesPerWorkgroupP = 4;
+constexpr int kPiecesPerWorkgroupP = 4;            // large batches, planned by a kernel of their own
+__device__ constexpr int kRangeWeightsP[2] = {1180, 820};  // see TileRanges
 
 // A wave's quarter of a key/value tile on its way from global memory to LDS.
 struct Share {
@@ -69,10 +72,12 @@ struct Share {
     bool pending;  // the values are in these registers (current round, or fp16 mode) and still have to go to LDS
 };
 
-template <bool PAGED, bool TILE_LSE, bool P_HALF>
+// INLINE_PLAN: the workgroup reads the batch's segment lists and plans itself (small batches, no planning kernel before).
+template <bool PAGED, bool TILE_LSE, bool P_HALF, bool INLINE_PLAN>
 __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, int n_rowblocks) {
     extern __shared__ __align__(16) char smem[];
-    __shared__ int sU[kMaxBatch], sps[kMaxBatch + 1];
+    __shared__ int sU[INLINE_PLAN ? kInlineBatch : kMaxBatch], sps[INLINE_PLAN ? 1 : kMaxBatch + 1];
+    __shared__ typename std::conditional<INLINE_PLAN, TileRanges, int>::type ranges;
     const DevView& vw = a.view;
     const int Hkv = vw.Hkv;
     const int tid = threadIdx.x;
@@ -89,36 +94,91 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
     int* ccum = reinterpret_cast<int*>(tiles + 2 * kTileBytes);        // [cap + 1] chunk prefix (score output only)
 
     const int inner = Hkv * n_rowblocks;
-    const long long slots = ((long long)gridDim.x * kPiecesPerWorkgroupP + inner - 1) / inner;
-    const int P = build_schedule(a.plan, cap, vw.B, a.S, a.min_units, slots, sU, sps);
-    if (blockIdx.x == 0)
-        for (int b = tid; b < vw.B; b += 256) a.n_parts[b] = sps[b + 1] - sps[b];
+    int P;
+    BatchLists lists;
+    if constexpr (INLINE_PLAN) {
+        lists.load(reinterpret_cast<char*>(ccum) + (TILE_LSE ? align16((cap + 1) * (int)sizeof(int)) : 0), vw, a.sel_idx, a.n_sel,
+                   [&](int) { return a.cur_k ? a.cur_len_host : 0; });
+        lists.count_tiles(vw.B, sU);
+        P = cut_tiles<2>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, a.S,
+                         gridDim.x >= 2u * (unsigned)a.num_cu, kRangeWeightsP);
+        if (blockIdx.x == 0) {
+            if (tid < vw.B) a.n_parts[tid] = ranges.parts[tid];
+            // a sequence with an empty key set lies in no range: its rows are written here
+            for (int b = 0; b < vw.B; ++b) {
+                if (sU[b] != 0) continue;
+                const size_t rows = (size_t)q_len * a.Hq;
+                for (size_t i = tid; i < rows * 128; i += 256) a.out[(size_t)b * rows * 128 + i] = 0.f;
+                if (a.lse)
+                    for (size_t i = tid; i < rows; i += 256) a.lse[(size_t)b * rows + i] = -__builtin_inff();
+            }
+        }
+    } else {
+        const int slots = max((int)gridDim.x * kPiecesPerWorkgroupP / inner, 1);
+        P = build_schedule(a.plan, cap, vw.B, a.S, a.min_units, slots, sU, sps);
+        if (blockIdx.x == 0)
+            for (int b = tid; b < vw.B; b += 256) a.n_parts[b] = sps[b + 1] - sps[b];
+    }
 
+    auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
     const char* kbase = reinterpret_cast<const char*>(vw.k);
     const char* vbase = reinterpret_cast<const char*>(vw.v);
     const char* ck = reinterpret_cast<const char*>(a.cur_k);
     const char* cv = reinterpret_cast<const char*>(a.cur_v);
-    const long long n_items = (long long)P * inner;
+    const int n_items = P * inner;
 
-    for (long long item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const int piece = (int)(item / inner);
-        const int rest = (int)(item - (long long)piece * inner);
-        const int g = rest % Hkv, rowblock = rest / Hkv;
-        const int b = find_slot(sps, vw.B, piece);
-        const int s = piece - sps[b];
-        const int S_eff = sps[b + 1] - sps[b];
+    // One pass per (item, sequence that its range meets); planned apart an item is a piece of one sequence.  A single loop:
+    // with the passes in a loop of their own the compiler keeps what only depends on the item in registers all through.
+    int reached = 0;  // tiles of the item's range that earlier passes took end here
+    bool first = true;
+    for (int item = blockIdx.x; item < n_items;) {
+        const int piece = uniform(item / inner), rest = item - piece * inner;
+        const int rowblock = uniform(rest / Hkv), g = rest - rowblock * Hkv;
+        int b, s, S_eff, u_lo, u_hi;
+        if constexpr (INLINE_PLAN) {
+            const int r = range_at<2>(piece, P);
+            const int t_lo = max(uniform(ranges.bound[r]), reached), t_hi = uniform(ranges.bound[r + 1]);
+            if (t_lo >= t_hi) {  // (an empty range)
+                item += gridDim.x;
+                continue;
+            }
+            b = sequence_of_tile(ranges, vw.B, t_lo);
+            const int seq_lo = uniform(ranges.seq[b]);
+            const int end = min(t_hi, seq_lo + uniform(sU[b]));
+            s = r - uniform(ranges.part0[b]);
+            S_eff = uniform(ranges.parts[b]);
+            u_lo = t_lo - seq_lo;
+            u_hi = end - seq_lo;
+            reached = end < t_hi ? end : 0;
+        } else {
+            b = uniform(find_slot(sps, vw.B, piece));
+            s = piece - sps[b];
+            S_eff = sps[b + 1] - sps[b];
+            u_lo = (int)(((long long)sU[b] * s) / S_eff);
+            u_hi = (int)(((long long)sU[b] * (s + 1)) / S_eff);
+        }
+        if (reached == 0) item += gridDim.x;
         const int U = sU[b];
-        int u_lo = (int)(((long long)U * s) / S_eff);
-        int u_hi = (int)(((long long)U * (s + 1)) / S_eff);
 
-        __syncthreads();  // the previous item's readers of the table and the tile buffers are done
-        const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
-        const int n_slots = __builtin_amdgcn_readfirstlane(hdr.n_slots), n_hist = __builtin_amdgcn_readfirstlane(hdr.n_hist);
-        __syncthreads();
+        int n_slots, n_hist;
+        if (!INLINE_PLAN || !first) __syncthreads();  // the previous pass's readers of the table and the tile buffers are done
+        first = false;
+        if constexpr (INLINE_PLAN) {
+            n_hist = __builtin_amdgcn_readfirstlane(lists.meta[3 * b + 1]);
+            n_slots = n_hist + (__builtin_amdgcn_readfirstlane(lists.meta[3 * b + 2]) > 0 ? 1 : 0);
+            lists.table<TILE_LSE>(b, tab, ccum);
+        } else {
+            const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
+            n_slots = __builtin_amdgcn_readfirstlane(hdr.n_slots);
+            n_hist = __builtin_amdgcn_readfirstlane(hdr.n_hist);
+            __syncthreads();
+        }
         if constexpr (TILE_LSE) {
             // chunk prefix of the sequence's segments (a chunk = 256 tokens = 8 tiles, never crossing a segment)
-            for (int i = tid; i < cap; i += 256) ccum[i] = i < n_slots ? (tab.len[i] + 255) >> 8 : 0;
-            exclusive_scan_units(ccum, cap);
+            if constexpr (!INLINE_PLAN) {
+                for (int i = tid; i < cap; i += 256) ccum[i] = i < n_slots ? (tab.len[i] + 255) >> 8 : 0;
+                exclusive_scan_units(ccum, cap);
+            }
             // a piece owns whole chunks: its ends move down to the chunk start at or before them
             auto snap = [&](int u) {
                 if (u <= 0 || u >= U) return u <= 0 ? 0 : U;
@@ -143,7 +203,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
             rowid[nt] = ((size_t)b * q_len + qtok[nt]) * a.Hq + (size_t)g * G + (rr - qtok[nt] * G);
             const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + rowid[nt] * 256);
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = row_ok[nt] ? qp[kk * 4 + q4] : make_uint4(0, 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = qp[kk * 4 + q4];  // rows past the last repeat row 0, unused: no wait here
         }
         floatx4_t acc[kNTP][8];
         float m[kNTP], l[kNTP];
@@ -205,8 +265,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
             off_k[1] = (unsigned)k_tok[1] * kstride + k_chunk[1];
             const int uin = u - seg_first;
             rows_left = seg_len - uin * kTileP;
-            tile_k = seg_k + (size_t)uin * kTileP * kstride;
-            tile_v = seg_v + (size_t)uin * 8192;
+            tile_k = reinterpret_cast<const char*>(uni64(reinterpret_cast<long long>(seg_k + (size_t)uin * kTileP * kstride)));
+            tile_v = reinterpret_cast<const char*>(uni64(reinterpret_cast<long long>(seg_v + (size_t)uin * 8192)));
         };
         // This wave's quarter of the next tile goes to `buf`: two K fragments and two V^T fragments.  Keys and the
         // values of history rounds travel from global memory straight into LDS; the values of the current round
@@ -491,8 +551,10 @@ int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, int num_cu, hipStrea
     if (a.G > 16) return fail(RA_ERR_UNSUPPORTED, "prefill: Hq / Hkv = %d exceeds 16", a.G);
     if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "prefill: batch %d exceeds %d", B, kMaxBatch);
     const int n_rowblocks = (rows_total + kRowsPerItem - 1) / kRowsPerItem;
+    const bool plan_inline = a.plan_inline != 0;
     const size_t smem = align_up(SlotTable::bytes(a.view.R_max + 1), 16) + 2 * kTileBytes +
-                        (a.tile_lse ? (size_t)(a.view.R_max + 3) * sizeof(int) : 0);
+                        (a.tile_lse ? align_up((size_t)(a.view.R_max + 2) * sizeof(int), 16) : 0) +
+                        (plan_inline ? BatchLists::bytes(B, a.view.R_max) : 0);
     const long long max_tiles = (long long)B * (a.max_tokens / kTileP + a.view.R_max + 1 + a.cur_cap / kTileP + 1);
     long long max_pieces = (long long)B + max_tiles / a.min_units;
     if (max_pieces > (long long)B * a.S) max_pieces = (long long)B * a.S;
@@ -500,14 +562,16 @@ int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, int num_cu, hipStrea
     if (grid > max_pieces * Hkv * n_rowblocks) grid = max_pieces * Hkv * n_rowblocks;
     if (grid < 1) grid = 1;
     const bool lse = a.tile_lse != nullptr, half = a.p_half != 0;
-#define RA_PREFILL_CASE(P_, L_, H_)                                                                                  \
-    if (paged == P_ && lse == L_ && half == H_) {                                                                    \
-        RA_LAUNCH_TIMED((attn_prefill_mfma_kernel<P_, L_, H_>), dim3((unsigned)grid), dim3(256), smem, st, a, n_rowblocks); \
+#define RA_PREFILL_CASE(P_, L_, H_, I_)                                                                              \
+    if (paged == P_ && lse == L_ && half == H_ && plan_inline == I_) {                                               \
+        RA_LAUNCH_TIMED((attn_prefill_mfma_kernel<P_, L_, H_, I_>), dim3((unsigned)grid), dim3(256), smem, st, a, n_rowblocks); \
         return RA_OK;                                                                                                \
     }
-    RA_PREFILL_CASE(false, false, false) RA_PREFILL_CASE(false, true, false) RA_PREFILL_CASE(true, false, false)
-    RA_PREFILL_CASE(true, true, false) RA_PREFILL_CASE(false, false, true) RA_PREFILL_CASE(false, true, true)
-    RA_PREFILL_CASE(true, false, true) RA_PREFILL_CASE(true, true, true)
+#define RA_PREFILL_CASES(L_, H_)                                                                                     \
+    RA_PREFILL_CASE(false, L_, H_, false) RA_PREFILL_CASE(true, L_, H_, false)                                       \
+    RA_PREFILL_CASE(false, L_, H_, true) RA_PREFILL_CASE(true, L_, H_, true)
+    RA_PREFILL_CASES(false, false) RA_PREFILL_CASES(true, false) RA_PREFILL_CASES(false, true) RA_PREFILL_CASES(true, true)
+#undef RA_PREFILL_CASES
 #undef RA_PREFILL_CASE
     return RA_OK;
 }

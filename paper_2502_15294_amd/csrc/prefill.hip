@@ -3,6 +3,7 @@
 // KV.  Entry point only; the arithmetic is in the matrix-core kernels.
 #include "attn_common.hpp"
 #include "scores_common.hpp"
+#include "stream_kv.hpp"
 
 using namespace ra;
 
@@ -38,10 +39,22 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     // otherwise the kernel whose waves own different rows and share each key tile through LDS.
     const bool few_rows = q_len * G <= 32;
     const size_t rows = (size_t)B * q_len * Hq;
+    const bool with_scores = scores != nullptr;
+    RA_REQUIRE(!with_scores || layer->R_max > 0, RA_ERR_INVALID_ARG, "watershed prefill: R_max is 0, there is nothing to score");
+    // score output: one entry per 32-token tile (decode kernel) or per 256-token chunk (many-row kernel) of a
+    // sequence's table: history rounds (each rounded up), then the current round
+    const int score_unit = few_rows ? 32 : 256;
+    const int64_t n_tiles64 = layer->max_tokens / score_unit + layer->R_max + cur_len / score_unit + 1;
+    RA_REQUIRE(!with_scores || n_tiles64 <= (int64_t)1 << 24, RA_ERR_UNSUPPORTED, "watershed prefill: max_tokens too large");
+    const int n_tiles_max = (int)n_tiles64;
+    const size_t tile_bytes = with_scores ? align_up(rows * n_tiles_max * sizeof(float), 256) : 0;
+    const size_t p_bytes = with_scores ? scores_finish_part_bytes(q_len, B, Hq, layer->R_max, n_tiles_max) : 0;
+    const size_t score_bytes = tile_bytes + p_bytes;
     MfmaDecodeShape shape = {};
     MfmaDecodeWorkspace mw = {};
     AttnWorkspace w = {};
     int S = 1;
+    bool plan_inline = few_rows && attn_mfma_plans_inline(B, layer->R_max);
     size_t plan_off, scratch_total;
     if (few_rows) {
         const long long max_tiles = mfma_max_tiles(B, layer->max_tokens, layer->R_max, cur_len);
@@ -53,21 +66,22 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     } else {
         S = mfma_max_pieces(layer->max_tokens + cur_len, attn_min_units(), 8);
         w = attn_workspace(rows, S, D, B, layer->R_max);
+        // Small batches: the kernel plans itself and cuts the batch into ranges, whose ends a sequence shares with its
+        // neighbours (two parts more).  A workspace that only fits the other schedule gets that one.
+        if (prefill_plans_inline(B, layer->R_max)) {
+            const int S_ranges = mfma_max_pieces(layer->max_tokens + cur_len, attn_min_units(), 16) + 2;
+            const AttnWorkspace w_ranges = attn_workspace(rows, S_ranges, D, B, layer->R_max);
+            plan_inline = ctx->ws.bytes >= w_ranges.total + score_bytes;
+            if (plan_inline) {
+                S = S_ranges;
+                w = w_ranges;
+            }
+        }
         plan_off = w.plan_off;
         scratch_total = w.total;
     }
-    const bool with_scores = scores != nullptr;
-    RA_REQUIRE(!with_scores || layer->R_max > 0, RA_ERR_INVALID_ARG, "watershed prefill: R_max is 0, there is nothing to score");
-    // score output: one entry per 32-token tile (decode kernel) or per 256-token chunk (many-row kernel) of a
-    // sequence's table: history rounds (each rounded up), then the current round
-    const int score_unit = few_rows ? 32 : 256;
-    const int64_t n_tiles64 = layer->max_tokens / score_unit + layer->R_max + cur_len / score_unit + 1;
-    RA_REQUIRE(!with_scores || n_tiles64 <= (int64_t)1 << 24, RA_ERR_UNSUPPORTED, "watershed prefill: max_tokens too large");
-    const int n_tiles_max = (int)n_tiles64;
-    const size_t tile_bytes = with_scores ? align_up(rows * n_tiles_max * sizeof(float), 256) : 0;
-    const size_t p_bytes = with_scores ? scores_finish_part_bytes(q_len, B, Hq, layer->R_max, n_tiles_max) : 0;
-    RA_REQUIRE(ctx->ws.base != nullptr && ctx->ws.bytes >= scratch_total + tile_bytes + p_bytes, RA_ERR_WORKSPACE,
-               "prefill: workspace has %zu bytes, this call needs %zu", ctx->ws.bytes, scratch_total + tile_bytes + p_bytes);
+    RA_REQUIRE(ctx->ws.base != nullptr && ctx->ws.bytes >= scratch_total + score_bytes, RA_ERR_WORKSPACE,
+               "prefill: workspace has %zu bytes, this call needs %zu", ctx->ws.bytes, scratch_total + score_bytes);
 
     AttnArgs a = {};
     a.view = to_dev(layer);
@@ -101,9 +115,11 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     a.seq_rec = reinterpret_cast<int*>(ctx->ws.base + kWsSeqRecOff);
     a.max_ranges = shape.max_ranges;
     a.range_skew = kRangeSkew;
+    a.num_cu = ctx->num_cu;
     a.p_half = with_scores ? 0 : ctx->prefill_p_half;  // the watershed call's scores decide the selection: full precision
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (!(few_rows && attn_mfma_plans_inline(B, layer->R_max))) launch_plan(a, 32, st);
+    a.plan_inline = plan_inline;
+    if (!plan_inline) launch_plan(a, 32, st);
     {
         KernelTimer timer(ctx, st);
         if (int rc = few_rows ? launch_attn_mfma(a, layer->block_size != 0, ctx->num_cu, st)

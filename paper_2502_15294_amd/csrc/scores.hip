@@ -827,6 +827,7 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
     a.part = reinterpret_cast<float*>(ctx->ws.base + kWsReserved);
     a.plan = ctx->ws.base + kWsReserved + part_bytes + p_bytes;
     a.chunks = desc_bytes ? ctx->ws.base + kWsReserved + part_bytes + p_bytes + plan_bytes : nullptr;
+    a.num_cu = ctx->num_cu;
     a.S = 1 << 20;
     a.min_units = 16;
 
@@ -835,7 +836,6 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
     const size_t tab_bytes = (size_t)(R_max + 1) * 16 + 16;
     const bool paged = watershed->block_size != 0;
     int rc;
-    if (many_rows) launch_scores_plan(a, st);
     {
         KernelTimer timer(ctx, st);
         if (many_rows)

@@ -20,6 +20,8 @@
 #include "mfma_util.hpp"
 #include "stream_kv.hpp"
 
+#include <type_traits>
+
 namespace ra {
 
 constexpr int kTileSP = 32;                      // tokens per key tile
@@ -29,6 +31,7 @@ constexpr int kTilesPerChunk = kChunkTokens / kTileSP;
 constexpr int kKTileBytes = 8192;
 constexpr int kPiecesPerWorkgroupS = 1;  // measured on the 4 x 32 K-token question-prefill workload: 1: 167-172 us, 2: 174-180, 3: 176
 constexpr int kWorkgroupsPerCuS = 3;
+__device__ constexpr int kRangeWeightsS[kWorkgroupsPerCuS] = {1370, 1080, 550};  // see TileRanges
 
 // Planning kernel, grid (B): the table of segments of sequence b (all history rounds, then the current round)
 // in the layout the attention kernels use, with cum = prefix sum of the segments' chunk counts, the unused
@@ -75,10 +78,12 @@ __global__ __launch_bounds__(256) void scores_plan_kernel(ScoreArgs a, char* pla
     }
 }
 
-template <bool PAGED>
+// INLINE_PLAN: the workgroup reads the batch's segment lists and plans itself (small batches, no planning kernel before).
+template <bool PAGED, bool INLINE_PLAN>
 __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_kernel(ScoreArgs a, int n_rowblocks) {
     extern __shared__ __align__(16) char smem[];
-    __shared__ int sU[kMaxBatch], sps[kMaxBatch + 1];
+    __shared__ int sU[INLINE_PLAN ? kInlineBatch : kMaxBatch], sps[INLINE_PLAN ? 1 : kMaxBatch + 1];
+    __shared__ typename std::conditional<INLINE_PLAN, TileRanges, int>::type ranges;
     const DevView& vw = a.view;
     const int Hkv = vw.Hkv;
     const int tid = threadIdx.x;
@@ -94,34 +99,78 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
     const unsigned tiles_lds = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)tiles);
 
     const int inner = Hkv * n_rowblocks;
-    const long long slots = ((long long)gridDim.x * kPiecesPerWorkgroupS + inner - 1) / inner;
-    const int P = build_schedule(a.plan, cap, vw.B, a.S, a.min_units, slots, sU, sps);
+    int P;
+    BatchLists lists;
+    int* tcum = reinterpret_cast<int*>(tiles + 2 * kKTileBytes);  // [cap + 1] prefix of the segments' key tiles
+    if constexpr (INLINE_PLAN) {
+        lists.load(reinterpret_cast<char*>(tcum) + align16((cap + 1) * (int)sizeof(int)), vw, nullptr, nullptr,
+                   [&](int) { return a.cur_k ? a.cur_len : 0; });
+        lists.count_tiles(vw.B, sU);
+        P = cut_tiles<kWorkgroupsPerCuS>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, kMaxRanges + 2,
+                                         gridDim.x >= kWorkgroupsPerCuS * (unsigned)a.num_cu, kRangeWeightsS);
+    } else {
+        const int slots = max((int)gridDim.x * kPiecesPerWorkgroupS / inner, 1);
+        P = build_schedule(a.plan, cap, vw.B, a.S, a.min_units, slots, sU, sps);
+    }
 
     const char* kbase = reinterpret_cast<const char*>(vw.k);
     const char* ck = reinterpret_cast<const char*>(a.cur_k);
-    const long long n_items = (long long)P * inner;
+    const int n_items = P * inner;
     const float slack = 16.f / a.c;
     auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
     auto uni64 = [&](long long x) { return ((long long)uni((int)(x >> 32)) << 32) | (unsigned)uni((int)x); };
 
-    for (long long item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const int piece = (int)(item / inner);
-        const int rest = (int)(item - (long long)piece * inner);
-        const int g = rest % Hkv, rowblock = rest / Hkv;
-        const int b = find_slot(sps, vw.B, piece);
-        const int s = piece - sps[b];
-        const int S_eff = sps[b + 1] - sps[b];
-        const int T = sU[b];  // key tiles of sequence b; the piece is tiles [t_lo, t_hi) moved to chunk starts
-        const int t_lo = (int)(((long long)T * s) / S_eff), t_hi = (int)(((long long)T * (s + 1)) / S_eff);
+    // One pass per (item, sequence that its range meets); planned apart an item is a piece of one sequence.  A single loop:
+    // with the passes in a loop of their own the compiler keeps what only depends on the item in registers all through.
+    int reached = 0;  // tiles of the item's range that earlier passes took end here
+    bool first = true;
+    for (int item = blockIdx.x; item < n_items;) {
+        const int piece = uni(item / inner), rest = item - piece * inner;
+        const int rowblock = uni(rest / Hkv), g = rest - rowblock * Hkv;
+        int b, t_lo, t_hi;  // the pass: tiles [t_lo, t_hi) of sequence b, moved to chunk starts
+        if constexpr (INLINE_PLAN) {
+            const int r = range_at<kWorkgroupsPerCuS>(piece, P);
+            const int g_lo = max(uni(ranges.bound[r]), reached), g_hi = uni(ranges.bound[r + 1]);
+            if (g_lo >= g_hi) {  // (an empty range)
+                item += gridDim.x;
+                continue;
+            }
+            b = sequence_of_tile(ranges, vw.B, g_lo);
+            const int seq_lo = uni(ranges.seq[b]), end = min(g_hi, seq_lo + uni(sU[b]));
+            t_lo = g_lo - seq_lo;
+            t_hi = end - seq_lo;
+            reached = end < g_hi ? end : 0;
+        } else {
+            b = uni(find_slot(sps, vw.B, piece));
+            const int s = piece - sps[b], S_eff = sps[b + 1] - sps[b];
+            t_lo = (int)(((long long)sU[b] * s) / S_eff);
+            t_hi = (int)(((long long)sU[b] * (s + 1)) / S_eff);
+        }
+        if (reached == 0) item += gridDim.x;
+        const int T = sU[b];
 
-        __syncthreads();  // the previous item's readers of the table and the tile buffers are done
-        const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
-        const int n_slots = uni(hdr.n_slots), n_hist = uni(hdr.n_hist);
-        __syncthreads();
+        int n_slots, n_hist;
+        if (!INLINE_PLAN || !first) __syncthreads();  // the previous pass's readers of the table and the tile buffers are done
+        first = false;
+        if constexpr (INLINE_PLAN) {
+            n_hist = uni(lists.meta[3 * b + 1]);
+            n_slots = n_hist + (uni(lists.meta[3 * b + 2]) > 0 ? 1 : 0);
+            SlotTable by_tile = tab;  // `cum` of the table is the chunk prefix here
+            by_tile.cum = tcum;
+            lists.table<true>(b, by_tile, tab.cum);
+        } else {
+            const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
+            n_slots = uni(hdr.n_slots);
+            n_hist = uni(hdr.n_hist);
+            __syncthreads();
+            for (int i = tid; i < cap; i += 256) tcum[i] = (int)tab.off_v[i];  // where the planning kernel put it
+            if (tid == 0) tcum[cap] = T;
+            __syncthreads();
+        }
         auto chunk_of_tile = [&](int t) {  // index of the chunk that holds tile t (the chunk count for t == T)
             if (t >= T) return uni(tab.cum[n_slots]);
-            const int sl = find_slot(tab.off_v, n_slots, (long long)t);
-            return uni(tab.cum[sl] + (t - (int)tab.off_v[sl]) / kTilesPerChunk);
+            const int sl = find_slot(tcum, n_slots, t);
+            return uni(tab.cum[sl] + (t - tcum[sl]) / kTilesPerChunk);
         };
         const int u_lo = chunk_of_tile(t_lo), u_hi = chunk_of_tile(t_hi);  // chunks [u_lo, u_hi) of sequence b
         if (u_lo >= u_hi) continue;
@@ -138,7 +187,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
             const size_t qrow = ((size_t)b * q_len + qtok) * a.Hq + (size_t)g * G + (rr - qtok * G);
             const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + qrow * 256);
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = row < rows_total ? qp[kk * 4 + q4] : make_uint4(0, 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = qp[kk * 4 + q4];  // rows past the last repeat row 0, unused: no wait here
         }
         float m[kNTS], l[kNTS];
 #pragma unroll
@@ -178,7 +227,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
         auto open_chunk = [&](int u) {  // of the open segment
             const int tok0 = (u - seg_first) * kChunkTokens;
             rows_left = seg_len - tok0;
-            tile_k = seg_k + (size_t)tok0 * kstride;
+            tile_k = reinterpret_cast<const char*>(uni64(reinterpret_cast<long long>(seg_k + (size_t)tok0 * kstride)));
         };
         // This wave's quarter (rows 8*wave .. +7) of the next key tile goes to the buffer at LDS address `buf_lds`;
         // afterwards the loader stands at the tile that follows.  Rows past the segment's end re-read its last row
@@ -190,7 +239,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                 const int blk = min((tok0 >> 4) + (wave >> 1), (seg_len - 1) >> 4);
                 const long long si = min(max(seg_tab + blk, 0ll), (long long)vw.max_blocks - 1);
                 const int pb = max(uni(vw.block_table[(size_t)b * vw.max_blocks + si]), 0);
-                const char* kb = kbase + ((size_t)pb * Hkv + g) * 4096;
+                const char* kb = reinterpret_cast<const char*>(uni64(reinterpret_cast<long long>(kbase + ((size_t)pb * Hkv + g) * 4096)));
                 const int last_row = seg_len - 1 - blk * 16;
                 const int r0 = min(8 * (wave & 1) + q4, last_row), r1 = min(8 * (wave & 1) + 4 + q4, last_row);
                 load_to_lds(kb, (unsigned)r0 * 256u + chunk_a, kd);
@@ -260,23 +309,34 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                 l[nt] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
             }
         };
-        // End of chunk u: merge the four lane groups of every row, write the chunk's log-sum-exp, start afresh.
+        // End of chunk u: merge the four lane groups of every row into the chunk's log-sum-exp.  It is stored behind the
+        // request for the tile after next (store_chunk): at once, the wait for that tile's loads, which counts stores
+        // too, would sit out the whole trip of the stores, once per chunk.  The reference logit stays: a later chunk's
+        // sum underflows only where its share of the row's softmax is below 2^-126.
+        float done[kNTS];
+        int done_u = -1;
         auto finish_chunk = [&](int u) {
 #pragma unroll
             for (int nt = 0; nt < kNTS; ++nt) {
                 const float M = xrow_max4(m[nt]);
-                float lv = l[nt] * fast_exp2((m[nt] - M) * a.c);
-                lv = xrow_sum4(lv);
-                const int row = row0 + nt * 16;
-                if (row < rows_total && q4 == 0 && u < a.n_chunks_max) {  // (a caller that understated max_tokens loses chunks)
-                    const int qtok = row / G;
-                    const size_t rowid = ((size_t)b * a.Hq + (size_t)g * G + (row - qtok * G)) * q_len + qtok;  // [B][Hq][q_len]
-                    a.part[rowid * a.n_chunks_max + u] =
-                        lv > 0.f ? kLn2 * __builtin_fmaf(M, a.c, fast_log2(lv)) : -__builtin_inff();
-                }
-                m[nt] = kNegBig;
+                const float lv = xrow_sum4(l[nt] * fast_exp2((m[nt] - M) * a.c));
+                done[nt] = lv > 0.f ? kLn2 * __builtin_fmaf(M, a.c, fast_log2(lv)) : -__builtin_inff();
                 l[nt] = 0.f;
             }
+            done_u = u;
+        };
+        auto store_chunk = [&]() {
+            if (done_u < 0) return;
+#pragma unroll
+            for (int nt = 0; nt < kNTS; ++nt) {
+                const int row = row0 + nt * 16;
+                if (row < rows_total && q4 == 0 && done_u < a.n_chunks_max) {  // (a caller that understated max_tokens loses chunks)
+                    const int qtok = row / G;
+                    const size_t rowid = ((size_t)b * a.Hq + (size_t)g * G + (row - qtok * G)) * q_len + qtok;  // [B][Hq][q_len]
+                    a.part[rowid * a.n_chunks_max + done_u] = done[nt];
+                }
+            }
+            done_u = -1;
         };
         // ---- walk the key tiles of chunks [u_lo, u_hi): the whole workgroup in lockstep ------------------------
         int slot = find_slot(tab.cum, n_slots, u_lo);
@@ -310,16 +370,18 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                 c_tok0 = seg_len - rows_left;
                 load_tile(tiles_lds + (bufsel ^ 1) * kKTileBytes);
             }
+            store_chunk();
             consume(buf, c_t, c_len, c_cur);
             if (c_last) finish_chunk(c_u);
             if (!more) break;
             bufsel ^= 1;
         }
+        store_chunk();
     }
 }
 
 
-void launch_scores_plan(const ScoreArgs& a, hipStream_t st) {
+static void launch_scores_plan(const ScoreArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(scores_plan_kernel, dim3(a.view.B), dim3(256), (size_t)(a.view.R_max + 2) * 2 * sizeof(int), st, a,
                        const_cast<char*>(a.plan));
 }
@@ -331,16 +393,21 @@ int launch_scores_prefill_mfma(const ScoreArgs& a, bool paged, int num_cu, hipSt
     if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "round_scores: batch %d exceeds %d", B, kMaxBatch);
     const int rows_total = a.q_len * G;
     const int n_rowblocks = (rows_total + kRowsPerItemS - 1) / kRowsPerItemS;
-    const size_t smem = align_up(SlotTable::bytes(a.view.R_max + 1), 16) + 2 * kKTileBytes;
+    const bool plan_inline = prefill_plans_inline(B, a.view.R_max);
+    const size_t smem = align_up(SlotTable::bytes(a.view.R_max + 1), 16) + 2 * kKTileBytes +
+                        align_up((size_t)(a.view.R_max + 2) * sizeof(int), 16) +
+                        (plan_inline ? BatchLists::bytes(B, a.view.R_max) : 0);
     long long max_pieces = (long long)B + (long long)B * a.n_chunks_max * kTilesPerChunk / a.min_units;
     if (max_pieces > (long long)B * a.S) max_pieces = (long long)B * a.S;
     long long grid = (long long)kWorkgroupsPerCuS * num_cu;
     if (grid > max_pieces * Hkv * n_rowblocks) grid = max_pieces * Hkv * n_rowblocks;
     if (grid < 1) grid = 1;
-    if (paged)
-        RA_LAUNCH_TIMED((scores_prefill_mfma_kernel<true>), dim3((unsigned)grid), dim3(256), smem, st, a, n_rowblocks);
-    else
-        RA_LAUNCH_TIMED((scores_prefill_mfma_kernel<false>), dim3((unsigned)grid), dim3(256), smem, st, a, n_rowblocks);
+    if (!plan_inline) launch_scores_plan(a, st);
+#define RA_SCORES_CASE(P_, I_)                                                                                       \
+    if (paged == P_ && plan_inline == I_)                                                                            \
+        RA_LAUNCH_TIMED((scores_prefill_mfma_kernel<P_, I_>), dim3((unsigned)grid), dim3(256), smem, st, a, n_rowblocks);
+    RA_SCORES_CASE(false, false) RA_SCORES_CASE(false, true) RA_SCORES_CASE(true, false) RA_SCORES_CASE(true, true)
+#undef RA_SCORES_CASE
     return RA_OK;
 }
 

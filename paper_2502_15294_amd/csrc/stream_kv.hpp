@@ -276,33 +276,39 @@ __device__ __forceinline__ void wait_for_loads_so_far() { __builtin_amdgcn_s_wai
 // ---- balanced schedule of a whole batch ------------------------------------------------------------
 // Every workgroup of a persistent attention launch derives the same schedule from the per-sequence
 // unit counts U_b the planning kernel left in the plan headers: sequence b is cut into
-//   n_b = clamp(ceil(U_b / T), 1, S)   pieces,   T = max(min_units, ceil(sum_b U_b / slots)),
-// so that pieces have about equal size whatever the selection sizes are, and the batch has about
-// `slots` pieces in total.  sU[b] = U_b, sps = exclusive prefix of n_b (sps[B] = number of pieces).
-// Must be called by all threads of the workgroup.
-// Same, from unit counts already in sU[0..B) (written by all threads before the call, no barrier needed).
-__device__ inline int schedule_from_counts(int B, int S, int min_units, long long slots, int* sU, int* sps);
-
-__device__ inline int build_schedule(const char* plan, int cap, int B, int S, int min_units, long long slots,
-                                     int* sU, int* sps) {
+//   n_b = clamp(ceil(U_b / T), 1, S)   pieces of about equal size whatever the selection sizes are.
+// T is the smallest piece (>= min_units) for which the batch has no more than `slots` pieces: one piece more than the
+// launch has workgroups for would run after all the others, alone on its compute unit and as long as they took
+// together (T = ceil(sum U_b / slots) leaves up to B - 1 such pieces: the score kernel of a 128-token question over four
+// dialogues of unequal length 220 -> @SCH@ microseconds).  Batches above 64 sequences, which are hardly cut, take that T.
+// sU[b] = U_b, sps = exclusive prefix of n_b (sps[B] = number of pieces).  Must be called by all threads of the
+// workgroup.
+__device__ inline int build_schedule(const char* plan, int cap, int B, int S, int min_units, int slots, int* sU, int* sps) {
+    __shared__ int s_fit;
     const size_t stride = plan_stride(cap);
+    if (threadIdx.x == 0) s_fit = 0x7fffffff;
     for (int b = threadIdx.x; b < B; b += blockDim.x)
-        sU[b] = reinterpret_cast<const PlanHeader*>(plan + (size_t)b * stride)->U;
-    return schedule_from_counts(B, S, min_units, slots, sU, sps);
-}
-
-__device__ inline int schedule_from_counts(int B, int S, int min_units, long long slots, int* sU, int* sps) {
-    __syncthreads();
-    for (int b = threadIdx.x; b < B; b += blockDim.x) sps[b] = sU[b];
+        sps[b] = sU[b] = reinterpret_cast<const PlanHeader*>(plan + (size_t)b * stride)->U;
     exclusive_scan_units(sps, B);
-    const long long total = sps[B];
-    long long T = (total + slots - 1) / (slots > 0 ? slots : 1);
+    const int total = sps[B];
+    auto pieces = [&](int U, int T) {
+        const int nb = (int)(((unsigned)U + (unsigned)T - 1) / (unsigned)T);
+        return nb < 1 ? 1 : (nb > S ? S : nb);
+    };
+    int T = (int)(((unsigned)total + (unsigned)slots - 1) / (unsigned)slots);
     if (T < min_units) T = min_units;
-    __syncthreads();
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
-        long long nb = (sU[b] + T - 1) / T;
-        sps[b] = (int)(nb < 1 ? 1 : (nb > S ? S : nb));
+    if (B > 1 && B <= 64 && slots > B) {
+        // every thread tries one T between that and the one that fits for certain; the smallest that fits is taken
+        const int most = (int)(((unsigned)total + (unsigned)(slots - B) - 1) / (unsigned)(slots - B));
+        const int mine = T + (int)((unsigned)max(most - T, 0) * threadIdx.x / (blockDim.x - 1));
+        int n = 0;
+        for (int b = 0; b < B; ++b) n += pieces(sU[b], mine);
+        if (n <= slots) atomicMin(&s_fit, mine);
+        __syncthreads();
+        if (s_fit != 0x7fffffff) T = s_fit;
     }
+    __syncthreads();
+    for (int b = threadIdx.x; b < B; b += blockDim.x) sps[b] = pieces(sU[b], T);
     exclusive_scan_units(sps, B);
     return sps[B];
 }
@@ -316,6 +322,197 @@ __device__ __forceinline__ int find_slot(const T* cum, int n, T u) {
         if (cum[mid] <= u) lo = mid; else hi = mid;
     }
     return lo;
+}
+
+// ---- planning inside a launch, for small batches ------------------------------------------------------
+// The segment lists of the whole batch in LDS, read in one memory round trip: a kernel that has them needs no planning
+// kernel before it and no second trip for the tables that one would have written.
+constexpr int kInlineBatch = 64, kInlineRounds = 1024;  // most sequences; most of them times R_max
+inline bool prefill_plans_inline(int B, int R_max) { return B <= kInlineBatch && (long long)B * R_max <= kInlineRounds; }
+__device__ constexpr int align16(int x) { return (x + 15) & ~15; }
+struct BatchLists {
+    long long *ok, *ov;  // [B][R_max] starts of the rounds' keys / values, by round index
+    int *len, *sel;      // [B][R_max] tokens of the rounds; the listed rounds
+    int* meta;           // [B][3] rounds of the sequence, listed rounds, length of the current round
+    int R_max;
+    __host__ __device__ static size_t bytes(int B, int R_max) { return ((size_t)B * R_max * 24 + (size_t)B * 12 + 15) & ~(size_t)15; }
+    // sel_idx null: every round; cur_len(b): the current round's tokens.  All threads call it; ends with a barrier.
+    template <typename CurLen>
+    __device__ __forceinline__ void load(char* smem, const DevView& vw, const int32_t* sel_idx, const int32_t* n_sel,
+                                         CurLen cur_len) {
+        R_max = vw.R_max;
+        const int n = vw.B * R_max;
+        ok = reinterpret_cast<long long*>(smem);
+        ov = ok + n;
+        len = reinterpret_cast<int*>(ov + n);
+        sel = len + n;
+        meta = sel + n;
+        for (int i = threadIdx.x; i < n; i += blockDim.x) {
+            len[i] = vw.seg_len[i];
+            ok[i] = vw.seg_off[i];
+            ov[i] = vw.seg_off_v[i];
+            if (sel_idx) sel[i] = sel_idx[i];
+        }
+        for (int b = threadIdx.x; b < vw.B; b += blockDim.x) {
+            const int n_rounds = min(max(vw.n_rounds[b], 0), R_max);
+            meta[3 * b] = n_rounds;
+            meta[3 * b + 1] = sel_idx ? min(max(n_sel[b], 0), R_max) : n_rounds;
+            meta[3 * b + 2] = cur_len(b);
+        }
+        listed = sel_idx != nullptr;
+        __syncthreads();
+    }
+    // Segment i of sequence b's table, as the planning kernel defines it: the i-th listed round (entries that are not
+    // rounds of the sequence count as empty), then the current round.
+    __device__ __forceinline__ int entry(int b, int i, long long& k, long long& v) const {
+        k = v = 0;
+        if (i < meta[3 * b + 1]) {
+            const int r = listed ? sel[b * R_max + i] : i;
+            if (r < 0 || r >= meta[3 * b]) return 0;
+            k = ok[b * R_max + r];
+            v = ov[b * R_max + r];
+            return max(len[b * R_max + r], 0);
+        }
+        return i == meta[3 * b + 1] ? max(meta[3 * b + 2], 0) : 0;
+    }
+    // Key tiles of every sequence into sU[0..B): a wave per sequence.  Ends with a barrier.
+    __device__ __forceinline__ void count_tiles(int B, int* sU) const {
+        const int lane = threadIdx.x & 63;
+        for (int b = threadIdx.x >> 6; b < B; b += blockDim.x >> 6) {
+            int tiles = 0;
+            for (int i = lane; i <= R_max; i += 64) {
+                long long k, v;
+                tiles += (entry(b, i, k, v) + 31) >> 5;
+            }
+            tiles = __builtin_amdgcn_readlane(wave_inclusive_sum(tiles), 63);
+            if (lane == 0) sU[b] = tiles;
+        }
+        lds_barrier();
+    }
+    // Sequence b's table by the first wave, cum the prefix of the segments' key tiles; with CHUNKS the prefix of their
+    // 256-token chunks goes to ccum.  Ends with a barrier.
+    template <bool CHUNKS>
+    __device__ __forceinline__ void table(int b, const SlotTable& tab, int* ccum) const {
+        if (threadIdx.x < 64) {
+            const int lane = threadIdx.x, cap = R_max + 1;
+            int t0 = 0, c0 = 0;
+            for (int i0 = 0; i0 < cap; i0 += 64) {
+                const int i = i0 + lane;
+                long long k = 0, v = 0;
+                const int n = i < cap ? entry(b, i, k, v) : 0;
+                const int tiles = (n + 31) >> 5, t = wave_inclusive_sum(tiles);
+                if (i < cap) {
+                    tab.off_k[i] = k;
+                    tab.off_v[i] = v;
+                    tab.len[i] = n;
+                    tab.cum[i] = t0 + t - tiles;
+                }
+                t0 += __builtin_amdgcn_readlane(t, 63);
+                if constexpr (CHUNKS) {
+                    const int chunks = (n + 255) >> 8, c = wave_inclusive_sum(chunks);
+                    if (i < cap) ccum[i] = c0 + c - chunks;
+                    c0 += __builtin_amdgcn_readlane(c, 63);
+                }
+            }
+            if (lane == 0) {
+                tab.cum[cap] = t0;
+                if constexpr (CHUNKS) ccum[cap] = c0;
+            }
+        }
+        lds_barrier();
+    }
+    bool listed;
+};
+
+// Cut of the batch's key tiles into ranges, one per (group of) workgroup(s), for at most 64 sequences.  The tiles of all
+// sequences form one list, and a range may end inside a sequence and go on with the next: cutting every sequence by
+// itself leaves pieces of unequal size (four pieces a sequence: a quarter of a sequence too much here and there), and
+// the longest one is the launch.
+// The ranges are sized by how the hardware serves the workgroups that stream them.  Of the C workgroups that share a
+// compute unit the one dispatched first is the older one on every SIMD and gets the issue port first for the whole
+// kernel; with equal ranges it ends early and the last one runs alone, with nothing left to overlap its softmax with
+// (128-token question over four dialogues of 32 000 tokens: the classes of the score kernel ended after 118, 140 and
+// 187 microseconds, of the attention kernel after 121 and 154).  A launch that fills the chip C deep therefore deals the
+// ranges out to C classes in turn (class k = the k-th workgroup to land on a unit) and sizes them by `weight`.
+constexpr int kMaxRanges = 1024;
+struct TileRanges {
+    int bound[kMaxRanges + 1];   // range r is the tiles bound[r] .. bound[r + 1] - 1 of the batch's list
+    int seq[kInlineBatch];       // first tile of every sequence
+    int part0[kInlineBatch], parts[kInlineBatch];  // first range that meets a sequence, number of them
+};
+// Fills `tr` (in LDS) from the sequences' tiles sU; returns the number of ranges: at most `slots`, each of about
+// min_tiles tiles or more, and at most max_parts (> 2) of them meet one sequence.  All threads call it; no barrier
+// behind the counts needed before it, one at its end.
+template <int C>
+__device__ __forceinline__ int cut_tiles(TileRanges& tr, const int* sU, int B, int slots, int min_tiles, int max_parts, bool full,
+                                         const int (&weights)[C]) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int U = lane < B ? sU[lane] : 0;
+    const int incl = wave_inclusive_sum(U);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    float top = (float)U;  // (exact: a sequence has fewer than 2^24 tiles)
+    top = vmax(top, dpp_mov<0xB1>(top));
+    top = vmax(top, dpp_mov<0x4E>(top));
+    top = vmax(top, dpp_mov<0x141>(top));
+    top = xrow_max4(vmax(top, dpp_mov<0x140>(top)));
+    const int most = __builtin_amdgcn_readfirstlane((int)top);
+    if (slots > kMaxRanges) slots = kMaxRanges;
+    int len = max(min_tiles, (total + slots - 1) / slots);
+    len = max(len, (most + max_parts - 3) / (max_parts - 2));
+    const int P = max(1, (total + len - 1) / len);
+    // A launch that does not fill the chip anyway, its ranges as short as they get: every sequence by itself, so that no
+    // workgroup starts twice.
+    const int cuts = U > 0 ? (U + len - 1) / len : 0, cuts_incl = wave_inclusive_sum(cuts);
+    const int P_apart = __builtin_amdgcn_readlane(cuts_incl, 63);
+    if (len == min_tiles && P_apart <= slots && P_apart > 0) {
+        if (tid < B) {
+            tr.seq[tid] = incl - U;
+            tr.part0[tid] = cuts_incl - cuts;
+            tr.parts[tid] = cuts;
+            for (int j = 0; j < cuts; ++j) tr.bound[cuts_incl - cuts + j] = incl - U + U * j / cuts;
+        }
+        if (tid == 0) tr.bound[P_apart] = total;
+        lds_barrier();
+        return P_apart;
+    }
+    int w[C], sum = 0;
+#pragma unroll
+    for (int k = 0; k < C; ++k) sum += w[k] = full && P == slots ? weights[k] : 1000;
+    auto weight_before = [&](int r) {  // of the ranges 0 .. r - 1
+        int x = r / C * sum;
+#pragma unroll
+        for (int k = 0; k + 1 < C; ++k) x += k < r % C ? w[k] : 0;
+        return x;
+    };
+    const float per_weight = (float)total / (float)weight_before(P);
+    // monotone, as the rounding of the product is
+    for (int r = tid; r <= P; r += blockDim.x) tr.bound[r] = r == P ? total : min((int)((float)weight_before(r) * per_weight), total);
+    lds_barrier();
+    if (tid < B) {  // (the first wave)
+        const int lo = incl - U, hi = incl - 1;
+        tr.seq[tid] = lo;
+        const int first = U > 0 ? find_slot(tr.bound, P, lo) : 0;
+        tr.part0[tid] = first;
+        tr.parts[tid] = U > 0 ? find_slot(tr.bound, P, hi) - first + 1 : 0;
+    }
+    lds_barrier();
+    return P;
+}
+// The sequence that tile t lies in: the last one that begins at or before it.
+__device__ __forceinline__ int sequence_of_tile(const TileRanges& tr, int B, int t) {
+    const int lane = threadIdx.x & 63;
+    return __popcll(__ballot(lane < B && tr.seq[lane < B ? lane : 0] <= t)) - 1;
+}
+// The range that the position-th group of workgroups takes: class 0's ranges first, then class 1's, ...
+template <int C>
+__device__ __forceinline__ int range_at(int position, int P) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        const int n = (P - k + C - 1) / C;
+        if (position < n) return position * C + k;
+        position -= n;
+    }
+    return P - 1;
 }
 
 }  // namespace ra
