@@ -120,6 +120,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
             for (int b = tid; b < vw.B; b += 256) a.n_parts[b] = sps[b + 1] - sps[b];
     }
 
+    // Row blocks of equal size (to within one 16-row tile): a block is at most kRowTiles tiles, 8 KB of keys and 8 KB of
+    // values read for every one of them.
+    const int row_tiles = (rows_total + 15) / 16, tiles_per_block = (row_tiles + n_rowblocks - 1) / n_rowblocks;
+    auto block_tiles = [&](int rowblock) { return min(tiles_per_block, row_tiles - rowblock * tiles_per_block); };
     auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
     const char* kbase = reinterpret_cast<const char*>(vw.k);
     const char* vbase = reinterpret_cast<const char*>(vw.v);
@@ -189,15 +193,17 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
             u_hi = __builtin_amdgcn_readfirstlane(snap(u_hi));
         }
 
-        // ---- this wave's query rows -------------------------------------------------------------------
+        // ---- this wave's query rows: the block's 16-row tiles are dealt out to the waves in turn -------------------------
+        const int wv = (wave + rowblock + piece) & 3;  // not always the same SIMD gets the odd tile
+        const int my_tiles = (wv < block_tiles(rowblock) ? 1 : 0) + (wv + 4 < block_tiles(rowblock) ? 1 : 0);
         int qtok[kNTP];
         bool row_ok[kNTP];
         size_t rowid[kNTP];
         uint4 qf[kNTP][4];
 #pragma unroll
         for (int nt = 0; nt < kNTP; ++nt) {
-            const int row = rowblock * kRowsPerItem + wave * kNTP * 16 + nt * 16 + n;
-            row_ok[nt] = row < rows_total;
+            const int row = (rowblock * tiles_per_block + nt * 4 + wv) * 16 + n;
+            row_ok[nt] = nt < my_tiles && row < rows_total;
             const int rr = row_ok[nt] ? row : 0;
             qtok[nt] = rr / G;
             rowid[nt] = ((size_t)b * q_len + qtok[nt]) * a.Hq + (size_t)g * G + (rr - qtok[nt] * G);
@@ -354,7 +360,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
                 vd[64] = sh.v1;
             }
         };
-        auto consume = [&](const char* buf, int tok0, int len, bool is_cur) {
+        // N: row tiles of this wave (1 or 2)
+        auto consume = [&](auto n_tiles, const char* buf, int tok0, int len, bool is_cur) {
+            constexpr int N = decltype(n_tiles)::value;
             const bool full = !is_cur && (len - tok0 >= kTileP);
             const uint4* kb = reinterpret_cast<const uint4*>(buf);
             const uint4* vb = reinterpret_cast<const uint4*>(buf + 8192);
@@ -363,17 +371,17 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
             for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) kf[h][kk] = kb[(h * 16 + n) * 16 + ((kk * 4 + q4 + n) & 15)];
-            floatx4_t sc[kNTP][2];
+            floatx4_t sc[N][2];
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk)  // four independent chains interleaved: no instruction waits for the one before
 #pragma unroll
-                for (int nt = 0; nt < kNTP; ++nt)
+                for (int nt = 0; nt < N; ++nt)
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
                         sc[nt][h] = mfma16(kf[h][kk], qf[nt][kk], kk ? sc[nt][h] : floatx4_t{0.f, 0.f, 0.f, 0.f});
             if (!full) {
 #pragma unroll
-                for (int nt = 0; nt < kNTP; ++nt) {
+                for (int nt = 0; nt < N; ++nt) {
                     // tokens this row may see: the segment's length, or inside the current round the causal limit
                     int lim = len;
                     if (is_cur) lim = min(len, max(len - q_len + qtok[nt] + 1, 0));
@@ -388,16 +396,16 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
             // The reference logit m of a row is only raised when some logit exceeds it by more than `slack`
             // (2^16 after scaling), which a lane can tell from its own eight logits: the common tile has no
             // cross-lane traffic and no rescale, and P stays far inside the fp32 / bf16 range.
-            float mx[kNTP];
+            float mx[N];
             bool raise = false;
 #pragma unroll
-            for (int nt = 0; nt < kNTP; ++nt) {
+            for (int nt = 0; nt < N; ++nt) {
                 mx[nt] = max8(sc[nt][0], sc[nt][1]);
                 raise |= mx[nt] > m[nt] + slack;
             }
             if (__any(raise)) {
 #pragma unroll
-                for (int nt = 0; nt < kNTP; ++nt) {
+                for (int nt = 0; nt < N; ++nt) {
                     const float r = xrow_max4(mx[nt]);
                     const float m_new = vmax(m[nt], r);
                     const float alpha = fast_exp2((m[nt] - m_new) * a.c);
@@ -456,11 +464,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
             };
             // Row tile by row tile: the first tile's products can run on the matrix cores while the vector ALU
             // turns the second tile's logits into probabilities.
-            uint4 phi0, plo0, phi1, plo1;
-            probabilities(0, phi0, plo0);
-            accumulate(0, phi0, plo0);
-            probabilities(1, phi1, plo1);
-            accumulate(1, phi1, plo1);
+#pragma unroll
+            for (int nt = 0; nt < N; ++nt) {
+                uint4 phi, plo;
+                probabilities(nt, phi, plo);
+                accumulate(nt, phi, plo);
+            }
         };
 
         // ---- walk the key tiles: the whole workgroup in lockstep -----------------------------------------
@@ -486,7 +495,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
                     c_tok0 = seg_len - rows_left;
                     sh = load_tile(tiles_lds + (bufsel ^ 1) * kTileBytes);
                 }
-                consume(buf, tok0, len, is_cur);
+                if (my_tiles == 2) consume(std::integral_constant<int, 2>(), buf, tok0, len, is_cur);
+                else if (my_tiles == 1) consume(std::integral_constant<int, 1>(), buf, tok0, len, is_cur);
                 if constexpr (TILE_LSE) {
                     const int uin = u - t_first;
                     if ((uin & 7) == 7 || u + 1 == t_end || u + 1 == u_hi) {  // the chunk ends with this tile

@@ -79,7 +79,9 @@ __global__ __launch_bounds__(256) void scores_plan_kernel(ScoreArgs a, char* pla
 }
 
 // INLINE_PLAN: the workgroup reads the batch's segment lists and plans itself (small batches, no planning kernel before).
-template <bool PAGED, bool INLINE_PLAN>
+// RAGGED: some wave of some row block has fewer than four row tiles.  (A variant of its own: with the choice of tile counts
+// in its loop the kernel takes 205 instead of 194 microseconds for the 512 rows of a 128-token question, which need none.)
+template <bool PAGED, bool INLINE_PLAN, bool RAGGED>
 __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_kernel(ScoreArgs a, int n_rowblocks) {
     extern __shared__ __align__(16) char smem[];
     __shared__ int sU[INLINE_PLAN ? kInlineBatch : kMaxBatch], sps[INLINE_PLAN ? 1 : kMaxBatch + 1];
@@ -117,6 +119,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
     const char* ck = reinterpret_cast<const char*>(a.cur_k);
     const int n_items = P * inner;
     const float slack = 16.f / a.c;
+    // row blocks of equal size (to within one 16-row tile)
+    const int row_tiles = (rows_total + 15) / 16, tiles_per_block = (row_tiles + n_rowblocks - 1) / n_rowblocks;
     auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
     auto uni64 = [&](long long x) { return ((long long)uni((int)(x >> 32)) << 32) | (unsigned)uni((int)x); };
 
@@ -176,12 +180,15 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
         if (u_lo >= u_hi) continue;
 
         // ---- this wave's query rows -------------------------------------------------------------------
-        // (row nt of this lane is row0 + 16*nt; whatever else is needed of it is recomputed where it is used)
-        const int row0 = rowblock * kRowsPerItemS + wave * kNTS * 16 + n;
+        // The block's 16-row tiles are dealt out to the waves in turn: row nt of this lane is row0 + 64 nt (whatever else is
+        // needed of it is recomputed where it is used).
+        const int wv = (wave + rowblock + piece) & 3;  // not always the same SIMD gets the odd tile
+        const int row0 = (rowblock * tiles_per_block + wv) * 16 + n;
+        const int my_tiles = !RAGGED ? 4 : (min(tiles_per_block, row_tiles - rowblock * tiles_per_block) - wv + 3) >> 2;
         uint4 qf[kNTS][4];
 #pragma unroll
         for (int nt = 0; nt < kNTS; ++nt) {
-            const int row = row0 + nt * 16;
+            const int row = row0 + nt * 64;
             const int rr = row < rows_total ? row : 0;
             const int qtok = rr / G;
             const size_t qrow = ((size_t)b * q_len + qtok) * a.Hq + (size_t)g * G + (rr - qtok * G);
@@ -254,10 +261,12 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
             rows_left -= kTileSP;
             tile_k += (size_t)kTileSP * kstride;
         };
-        auto consume = [&](const char* buf, int tok0, int len, bool is_cur) {
+        // N: row tiles of this wave (1 .. 4)
+        auto consume = [&](auto n_tiles, const char* buf, int tok0, int len, bool is_cur) {
+            constexpr int N = decltype(n_tiles)::value;
             const bool full = !is_cur && (len - tok0 >= kTileSP);
             const uint4* kb = reinterpret_cast<const uint4*>(buf);
-            floatx4_t sc[kNTS][2];
+            floatx4_t sc[N][2];
             uint4 kf[2][4];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -269,13 +278,13 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk)  // the four row tiles' chains interleaved: no instruction waits for the one before
 #pragma unroll
-                    for (int nt = 0; nt < kNTS; ++nt)
+                    for (int nt = 0; nt < N; ++nt)
                         sc[nt][h] = mfma16(kf[h][kk], qf[nt][kk], kk ? sc[nt][h] : floatx4_t{0.f, 0.f, 0.f, 0.f});
             if (!full) {
 #pragma unroll
-                for (int nt = 0; nt < kNTS; ++nt) {
+                for (int nt = 0; nt < N; ++nt) {
                     // tokens of this segment the row may see (causal inside the current round)
-                    const int lim = is_cur ? cur_visible(len, q_len, min(row0 + nt * 16, rows_total - 1) / G) : len;
+                    const int lim = is_cur ? cur_visible(len, q_len, min(row0 + nt * 64, rows_total - 1) / G) : len;
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -283,23 +292,23 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                             if (tok0 + h * 16 + q4 * 4 + i >= lim) sc[nt][h][i] = -__builtin_inff();
                 }
             }
-            float mx[kNTS];
+            float mx[N];
             bool raise = false;
 #pragma unroll
-            for (int nt = 0; nt < kNTS; ++nt) {
+            for (int nt = 0; nt < N; ++nt) {
                 mx[nt] = max8(sc[nt][0], sc[nt][1]);
                 raise |= mx[nt] > m[nt] + slack;
             }
             if (__any(raise)) {  // each lane keeps its own reference: the four lane groups of a row are merged per chunk
 #pragma unroll
-                for (int nt = 0; nt < kNTS; ++nt) {
+                for (int nt = 0; nt < N; ++nt) {
                     const float m_new = vmax(m[nt], mx[nt]);
                     l[nt] *= fast_exp2((m[nt] - m_new) * a.c);
                     m[nt] = m_new;
                 }
             }
 #pragma unroll
-            for (int nt = 0; nt < kNTS; ++nt) {
+            for (int nt = 0; nt < N; ++nt) {
                 const float mc = m[nt] * a.c;
                 float p[8];
 #pragma unroll
@@ -329,8 +338,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
             if (done_u < 0) return;
 #pragma unroll
             for (int nt = 0; nt < kNTS; ++nt) {
-                const int row = row0 + nt * 16;
-                if (row < rows_total && q4 == 0 && done_u < a.n_chunks_max) {  // (a caller that understated max_tokens loses chunks)
+                const int row = row0 + nt * 64;
+                if (nt < my_tiles && row < rows_total && q4 == 0 && done_u < a.n_chunks_max) {  // (a caller that understated max_tokens loses chunks)
                     const int qtok = row / G;
                     const size_t rowid = ((size_t)b * a.Hq + (size_t)g * G + (row - qtok * G)) * q_len + qtok;  // [B][Hq][q_len]
                     a.part[rowid * a.n_chunks_max + done_u] = done[nt];
@@ -371,7 +380,10 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                 load_tile(tiles_lds + (bufsel ^ 1) * kKTileBytes);
             }
             store_chunk();
-            consume(buf, c_t, c_len, c_cur);
+            if (!RAGGED || my_tiles == 4) consume(std::integral_constant<int, 4>(), buf, c_t, c_len, c_cur);
+            else if (my_tiles == 3) consume(std::integral_constant<int, 3>(), buf, c_t, c_len, c_cur);
+            else if (my_tiles == 2) consume(std::integral_constant<int, 2>(), buf, c_t, c_len, c_cur);
+            else if (my_tiles == 1) consume(std::integral_constant<int, 1>(), buf, c_t, c_len, c_cur);
             if (c_last) finish_chunk(c_u);
             if (!more) break;
             bufsel ^= 1;
@@ -403,10 +415,14 @@ int launch_scores_prefill_mfma(const ScoreArgs& a, bool paged, int num_cu, hipSt
     if (grid > max_pieces * Hkv * n_rowblocks) grid = max_pieces * Hkv * n_rowblocks;
     if (grid < 1) grid = 1;
     if (!plan_inline) launch_scores_plan(a, st);
-#define RA_SCORES_CASE(P_, I_)                                                                                       \
-    if (paged == P_ && plan_inline == I_)                                                                            \
-        RA_LAUNCH_TIMED((scores_prefill_mfma_kernel<P_, I_>), dim3((unsigned)grid), dim3(256), smem, st, a, n_rowblocks);
-    RA_SCORES_CASE(false, false) RA_SCORES_CASE(false, true) RA_SCORES_CASE(true, false) RA_SCORES_CASE(true, true)
+    const int row_tiles = (rows_total + 15) / 16;
+    const bool ragged = row_tiles != n_rowblocks * 4 * kNTS;
+#define RA_SCORES_CASE(P_, I_, R_)                                                                                   \
+    if (paged == P_ && plan_inline == I_ && ragged == R_)                                                            \
+        RA_LAUNCH_TIMED((scores_prefill_mfma_kernel<P_, I_, R_>), dim3((unsigned)grid), dim3(256), smem, st, a, n_rowblocks);
+    RA_SCORES_CASE(false, false, false) RA_SCORES_CASE(false, true, false) RA_SCORES_CASE(true, false, false)
+    RA_SCORES_CASE(true, true, false) RA_SCORES_CASE(false, false, true) RA_SCORES_CASE(false, true, true)
+    RA_SCORES_CASE(true, false, true) RA_SCORES_CASE(true, true, true)
 #undef RA_SCORES_CASE
     return RA_OK;
 }

@@ -280,7 +280,7 @@ __device__ __forceinline__ void wait_for_loads_so_far() { __builtin_amdgcn_s_wai
 // T is the smallest piece (>= min_units) for which the batch has no more than `slots` pieces: one piece more than the
 // launch has workgroups for would run after all the others, alone on its compute unit and as long as they took
 // together (T = ceil(sum U_b / slots) leaves up to B - 1 such pieces: the score kernel of a 128-token question over four
-// dialogues of unequal length 220 -> @SCH@ microseconds).  Batches above 64 sequences, which are hardly cut, take that T.
+// dialogues of unequal length 224 -> 197 microseconds).  Batches above 64 sequences, which are hardly cut, take that T.
 // sU[b] = U_b, sps = exclusive prefix of n_b (sps[B] = number of pieces).  Must be called by all threads of the
 // workgroup.
 __device__ inline int build_schedule(const char* plan, int cap, int B, int S, int min_units, int slots, int* sU, int* sps) {

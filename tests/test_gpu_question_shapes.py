@@ -1,0 +1,63 @@
+"""Questions at the sizes where their kernels change shape: row counts around the 16-row tiles and row blocks, batches that
+the launch plans itself and ones planned by a kernel of their own, launches that fill the chip (ranges that cross from
+one dialogue into the next) and ones that do not, dialogues without any key."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2502_15294_amd as ra
+from oracle import pipeline
+from oracle import round_attention as ora
+from synth import make_workload
+from synth.device import Engine, device_view, sel_to_device, to_device
+
+pytestmark = pytest.mark.gpu
+STREAM_TOL, SCORE_TOL = 5e-5, 1e-5  # the bars of the other parity tests: P carried to 16 bits, fp32 sums
+
+ROWS = [(9, 32, 8), (8, 64, 8), (16, 64, 8), (17, 64, 8), (48, 32, 8), (65, 32, 8), (50, 24, 8), (30, 32, 2)]
+BATCHES = {
+    "long": dict(lens=[[900, 3, 700, 250], [17, 640, 33], [1000, 900, 800, 31, 5]]),      # fills the chip at 16 items a range
+    "short_paged": dict(lens=[[5, 16, 17, 0, 33], [64, 3], [0, 0]], block_size=16),
+    "lists_of_1024": dict(B=64, R=16, length=("uniform", 0, 12)),                         # the most that is planned inline
+    "planned_apart": dict(B=30, R=40, length=("uniform", 0, 9), block_size=16),
+    "planned_apart_65": dict(B=65, R=2, length=("uniform", 1, 40)),
+}
+
+
+@pytest.mark.parametrize("batch", list(BATCHES))
+@pytest.mark.parametrize("q_len,Hq,Hkv", ROWS)
+def test_question(batch, q_len, Hq, Hkv):
+    over = dict(BATCHES[batch])
+    if "lens" in over:
+        over["B"] = len(over["lens"])
+    cur_len = 0 if (batch, q_len) == ("short_paged", 16) else q_len + (q_len & 3)
+    w = make_workload("cfg3", Hq=Hq, Hkv=Hkv, q_len=q_len, cur_len=cur_len, n_relevant=1, **over)
+    eng = Engine(w)
+    v0, v1 = device_view(w, 0), device_view(w, 1)
+    dev = lambda x: None if x is None else to_device(x, "bf16")  # noqa: E731
+    ck0, cv0, ck1, cv1 = dev(w.cur_k(0)), dev(w.cur_v(0)), dev(w.cur_k(1)), dev(w.cur_v(1))
+    P, S, sel, n = ra.ra_round_scores_select(eng.ctx, dev(w.q(0)), v0, cur_k=ck0, scale=w.scale)
+    rng = np.random.default_rng(q_len)
+    sels = [sorted(rng.choice(w.n_rounds(b), size=(w.n_rounds(b) + 1) // 2, replace=False).tolist()) for b in range(w.B)]
+    si, ns = sel_to_device(sels, v1.R_max)
+    out, lse = ra.ra_round_sparse_attn_prefill(eng.ctx, dev(w.q(1)), v1, si, ns, ck1, cv1, scale=w.scale)
+    again, _ = ra.ra_round_sparse_attn_prefill(eng.ctx, dev(w.q(1)), v1, si, ns, ck1, cv1, scale=w.scale)
+    out2, _, P2, S2 = ra.ra_watershed_attn_prefill(eng.ctx, dev(w.q(0)), v0, ck0, cv0, scale=w.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again)
+    P, S, out, lse, out2, S2 = (x.cpu().numpy() for x in (P, S, out, lse, out2, S2))
+    for b in sorted({0, 1, w.B // 2, w.B - 1}):
+        R = w.n_rounds(b)
+        if w.total_tokens(b):
+            rP, rS = pipeline.scores_for_sequence(w, b)
+            assert np.abs(P[b, :, :R] - rP).max() < SCORE_TOL and np.abs(S[b, :R] - rS).max() < SCORE_TOL, b
+            assert np.abs(S2[b, :R] - rS).max() < SCORE_TOL, b
+        if w.total_tokens(b) + cur_len:
+            assert ora.row_error(out2[b], pipeline.attention_for_sequence(w, b, 0, list(range(R)))[0]) < STREAM_TOL, b
+        if sum(int(w.lens[b][r]) for r in sels[b]) + cur_len == 0:
+            assert np.all(out[b] == 0) and np.all(np.isneginf(lse[b])), b
+            continue
+        ro, rl = pipeline.attention_for_sequence(w, b, 1, sels[b])
+        assert ora.row_error(out[b], ro) < STREAM_TOL, b
+        assert np.allclose(lse[b], rl, rtol=0, atol=2e-5 * max(1.0, np.abs(rl).max())), b
+    eng.close()
