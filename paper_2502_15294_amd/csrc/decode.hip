@@ -288,49 +288,63 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
     }
 }
 
-// Merge the pieces of every (sequence, query token, query head) row that was split; grid (rows), block D.
+// Merge the pieces of every (sequence, query token, query head) row that was split: D / 4 lanes per row, 16 bytes of a
+// piece each, and four pieces in flight with their (max, sum) pairs.  A workgroup takes as many rows as it has lanes for:
+// with one row and one channel per lane the merge of a 128-token question over four dialogues (16 384 rows of five
+// pieces, 50 MB) was 16 384 small workgroups, 12.2 microseconds, now 9.8.
 template <int D>
-__global__ __launch_bounds__(D) void combine_kernel(const float* part_acc, const float* part_m, const float* part_l,
-                                                   const int* n_parts, int S, int rows_per_seq, float c, float scale,
-                                                   float* out, float* lse) {
-    const size_t row = blockIdx.x;
+__global__ __launch_bounds__(256) void combine_kernel(const float* part_acc, const float* part_m, const float* part_l,
+                                                      const int* n_parts, int S, int rows_per_seq, int rows, float c, float scale,
+                                                      float* out, float* lse) {
+    constexpr int kLanes = D / 4, kRows = 256 / kLanes;
+    const int row = blockIdx.x * kRows + threadIdx.x / kLanes, c4 = threadIdx.x & (kLanes - 1);
+    if (row >= rows) return;
     const int n = n_parts[row / rows_per_seq];
     if (n <= 1) return;  // written directly by the streaming kernel
-    const int dim = threadIdx.x;
-    const float* pm = part_m + row * S;
-    const float* pl = part_l + row * S;
-    const float* pa = part_acc + row * S * D + dim;
-    float M = kNegBig;
-    for (int p = 0; p < n; ++p) M = fmaxf(M, pm[p]);
-    float num = 0.f, den = 0.f;
-    int p = 0;
-    for (; p + 4 <= n; p += 4) {
-        const float a0 = pa[(size_t)p * D], a1 = pa[(size_t)(p + 1) * D];
-        const float a2 = pa[(size_t)(p + 2) * D], a3 = pa[(size_t)(p + 3) * D];
-        const float f0 = fast_exp2((pm[p] - M) * c), f1 = fast_exp2((pm[p + 1] - M) * c);
-        const float f2 = fast_exp2((pm[p + 2] - M) * c), f3 = fast_exp2((pm[p + 3] - M) * c);
-        num = __builtin_fmaf(a0, f0, num); den = __builtin_fmaf(pl[p], f0, den);
-        num = __builtin_fmaf(a1, f1, num); den = __builtin_fmaf(pl[p + 1], f1, den);
-        num = __builtin_fmaf(a2, f2, num); den = __builtin_fmaf(pl[p + 2], f2, den);
-        num = __builtin_fmaf(a3, f3, num); den = __builtin_fmaf(pl[p + 3], f3, den);
+    const float* pm = part_m + (size_t)row * S;
+    const float* pl = part_l + (size_t)row * S;
+    const float* pa = part_acc + (size_t)row * S * D + c4 * 4;
+    float M = kNegBig, den = 0.f;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int p0 = 0; p0 < n; p0 += 4) {
+        float4 v[4];
+        float m[4], l[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int p = min(p0 + j, n - 1);
+            v[j] = *reinterpret_cast<const float4*>(pa + (size_t)p * D);
+            m[j] = pm[p];
+            l[j] = pl[p];
+        }
+        const float top = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])), m_new = fmaxf(M, top);
+        const float f_old = fast_exp2((M - m_new) * c);
+        den *= f_old;
+        num.x *= f_old, num.y *= f_old, num.z *= f_old, num.w *= f_old;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float f = p0 + j < n ? fast_exp2((m[j] - m_new) * c) : 0.f;
+            den = __builtin_fmaf(l[j], f, den);
+            num.x = __builtin_fmaf(v[j].x, f, num.x);
+            num.y = __builtin_fmaf(v[j].y, f, num.y);
+            num.z = __builtin_fmaf(v[j].z, f, num.z);
+            num.w = __builtin_fmaf(v[j].w, f, num.w);
+        }
+        M = m_new;
     }
-    for (; p < n; ++p) {
-        const float f = fast_exp2((pm[p] - M) * c);
-        num = __builtin_fmaf(pa[(size_t)p * D], f, num);
-        den = __builtin_fmaf(pl[p], f, den);
-    }
-    out[row * D + dim] = den > 0.f ? num / den : 0.f;
-    if (lse && dim == 0) lse[row] = den > 0.f ? __builtin_fmaf(M, scale, __builtin_logf(den)) : -__builtin_inff();
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    *reinterpret_cast<float4*>(out + (size_t)row * D + c4 * 4) = make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv);
+    if (lse && c4 == 0) lse[row] = den > 0.f ? __builtin_fmaf(M, scale, __builtin_logf(den)) : -__builtin_inff();
 }
 
 void launch_combine(const AttnArgs& a, int D, size_t rows, hipStream_t st) {
-    const int rows_per_seq = a.q_len * a.Hq;
+    const int rows_per_seq = a.q_len * a.Hq, per_wg = 1024 / D;
+    const dim3 grid((unsigned)((rows + per_wg - 1) / per_wg));
     if (D == 128)
-        hipLaunchKernelGGL((combine_kernel<128>), dim3((unsigned)rows), dim3(128), 0, st, a.part_acc, a.part_m, a.part_l,
-                           a.n_parts, a.S, rows_per_seq, a.c, a.scale, a.out, a.lse);
+        hipLaunchKernelGGL((combine_kernel<128>), grid, dim3(256), 0, st, a.part_acc, a.part_m, a.part_l, a.n_parts, a.S,
+                           rows_per_seq, (int)rows, a.c, a.scale, a.out, a.lse);
     else
-        hipLaunchKernelGGL((combine_kernel<64>), dim3((unsigned)rows), dim3(64), 0, st, a.part_acc, a.part_m, a.part_l,
-                           a.n_parts, a.S, rows_per_seq, a.c, a.scale, a.out, a.lse);
+        hipLaunchKernelGGL((combine_kernel<64>), grid, dim3(256), 0, st, a.part_acc, a.part_m, a.part_l, a.n_parts, a.S,
+                           rows_per_seq, (int)rows, a.c, a.scale, a.out, a.lse);
 }
 
 template <typename T, int D, int G>
