@@ -89,7 +89,11 @@ void launch_plan(const AttnArgs& a, int unit_tokens, hipStream_t st) {
 // Values are stored transposed in 16-token tiles ([D][16]), so for P.V lane `lane` owns channels
 // lane, lane + 64, ... and reads the 16 tokens of each with contiguous loads; the 16 x G probabilities
 // of the unit reach it as scalars (v_readlane), so P.V needs no cross-lane reduction.
-template <typename T, int D, int G, bool PAGED>
+// INLINE_PLAN (sequences of up to kGenericInlineRounds rounds): a workgroup builds its sequence's table itself, from one
+// round trip to the lists, and no planning kernel runs before it (3 microseconds and a launch of the smallest steps).
+constexpr int kGenericInlineRounds = 64;
+
+template <typename T, int D, int G, bool PAGED, bool INLINE_PLAN>
 __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
     constexpr int EPL = D / 16;
     using Ops = RowOps<T, EPL>;
@@ -110,9 +114,50 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
     SlotTable tab;
     tab.carve(smem, cap);
     float* red = reinterpret_cast<float*>(smem + ((SlotTable::bytes(cap) + 15) & ~(size_t)15));
-    const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
-    const int n_slots = hdr.n_slots, n_hist = hdr.n_hist, U = hdr.U, S_eff = hdr.S_eff;
-    if (s >= S_eff) return;
+    int n_slots, n_hist, U, S_eff;
+    if constexpr (INLINE_PLAN) {
+        // as plan_kernel defines it; every wave for itself: lane i holds round i, then list entry i
+        const size_t base = (size_t)b * vw.R_max;
+        const int in = min(lane, vw.R_max - 1);
+        const int raw_len = vw.R_max > 0 ? vw.seg_len[base + in] : 0;
+        const long long raw_k = vw.R_max > 0 ? vw.seg_off[base + in] : 0, raw_v = vw.R_max > 0 ? vw.seg_off_v[base + in] : 0;
+        const int listed = a.sel_idx && vw.R_max > 0 ? a.sel_idx[base + in] : lane;
+        const int n_rounds = min(max(vw.n_rounds[b], 0), vw.R_max);
+        n_hist = a.sel_idx ? min(max(a.n_sel[b], 0), vw.R_max) : n_rounds;
+        const int cur_len = a.cur_k ? min(max(a.cur_len_dev ? a.cur_len_dev[b] : a.cur_len_host, 0), a.cur_cap) : 0;
+        n_slots = n_hist + (cur_len > 0 ? 1 : 0);
+        const bool hist = lane < n_hist && listed >= 0 && listed < n_rounds;
+        const int src = hist ? listed : 0;
+        const int len_r = __shfl(raw_len, src, 64);
+        const long long k_r = __shfl(raw_k, src, 64), v_r = __shfl(raw_v, src, 64);
+        const int len = hist ? max(len_r, 0) : 0;
+        const int units = (len + kUnitTokens - 1) / kUnitTokens, incl = wave_inclusive_sum(units);
+        const int hist_units = __builtin_amdgcn_readlane(incl, 63);
+        U = hist_units + (cur_len + kUnitTokens - 1) / kUnitTokens;
+        S_eff = min(a.S, max(1, U / a.min_units));
+        if (s == 0 && g == 0 && tid == 0) a.n_parts[b] = S_eff;
+        if (s >= S_eff) return;
+        if (wave == 0) {
+            if (lane < n_hist) {
+                tab.off_k[lane] = hist ? k_r : 0;
+                tab.off_v[lane] = hist ? v_r : 0;
+                tab.len[lane] = len;
+                tab.cum[lane] = incl - units;
+            }
+            if (lane == 0) {  // the current round's segment, and the end of the prefix
+                if (cur_len > 0) {
+                    tab.off_k[n_hist] = tab.off_v[n_hist] = 0;
+                    tab.len[n_hist] = cur_len;
+                }
+                tab.cum[n_hist] = hist_units;
+                tab.cum[n_slots] = U;
+            }
+        }
+    } else {
+        const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
+        n_slots = hdr.n_slots, n_hist = hdr.n_hist, U = hdr.U, S_eff = hdr.S_eff;
+        if (s >= S_eff) return;
+    }
     __syncthreads();
     const int u_lo = (int)(((long long)U * s) / S_eff);
     const int u_hi = (int)(((long long)U * (s + 1)) / S_eff);
@@ -349,10 +394,11 @@ void launch_combine(const AttnArgs& a, int D, size_t rows, hipStream_t st) {
 
 template <typename T, int D, int G>
 static void launch_generic(bool paged, dim3 grid, size_t smem, hipStream_t st, const AttnArgs& a) {
-    if (paged)
-        RA_LAUNCH_TIMED((decode_generic_kernel<T, D, G, true>), grid, dim3(256), smem, st, a);
-    else
-        RA_LAUNCH_TIMED((decode_generic_kernel<T, D, G, false>), grid, dim3(256), smem, st, a);
+    const bool plan_inline = a.view.R_max <= kGenericInlineRounds;
+#define RA_GENERIC_CASE(P_, I_)                                                                               \
+    if (paged == P_ && plan_inline == I_) RA_LAUNCH_TIMED((decode_generic_kernel<T, D, G, P_, I_>), grid, dim3(256), smem, st, a);
+    RA_GENERIC_CASE(false, false) RA_GENERIC_CASE(false, true) RA_GENERIC_CASE(true, false) RA_GENERIC_CASE(true, true)
+#undef RA_GENERIC_CASE
 }
 
 template <typename T, int D>
@@ -490,7 +536,8 @@ static int decode_impl(ra_ctx* ctx, const Workspace* scratch, void* stream, cons
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const bool paged = layer->block_size != 0;
     int rc;
-    if (!(mfma && attn_mfma_plans_inline(B, layer->R_max))) launch_plan(a, mfma ? 32 : kUnitTokens, st);
+    if (mfma ? !attn_mfma_plans_inline(B, layer->R_max) : layer->R_max > kGenericInlineRounds)
+        launch_plan(a, mfma ? 32 : kUnitTokens, st);
     {
         KernelTimer timer(ctx, st);
         if (mfma) {
