@@ -92,7 +92,8 @@ inline bool attn_mfma_plans_inline(int B, int R_max) {
     return B <= 64 && (long long)B * R_max <= 1024;  // at most 29 KB of LDS beside the 17 KB of score staging
 }
 // Launch shape and scratch of that kernel.  `max_tiles` bounds the 32-token key tiles of the whole batch.
-constexpr int kMfmaMinUnits = 4;  // shortest range in key tiles (two tiles are in flight per wave; ranges of 2 and of 8 measured no better)
+constexpr int kMfmaMinUnits = 4;     // shortest range in key tiles (two tiles are in flight per wave; ranges of 2 and of 8 measured no better)
+constexpr int kMfmaSpreadUnits = 2;  // ... and while the launch has waves to spare for all of them
 struct MfmaDecodeShape {
     int n_rowblocks, inner, grid, max_ranges, records;
     size_t rec_bytes, ml_bytes;
@@ -101,7 +102,7 @@ inline MfmaDecodeShape mfma_decode_shape(int num_cu, int B, int Hkv, int D, int 
     MfmaDecodeShape s;
     s.n_rowblocks = (rows_total + 15) / 16;
     s.inner = Hkv * s.n_rowblocks;
-    long long want = max_tiles / kMfmaMinUnits;  // ranges the batch can have at most
+    long long want = max_tiles / kMfmaSpreadUnits;  // ranges the batch can have at most
     if (want < 1) want = 1;
     long long grid = (want * s.inner + 3) / 4;   // four waves per workgroup, at least one work item per wave
     // One workgroup per compute unit, i.e. one wave per SIMD.  With two, the hardware serves the older wave of a
