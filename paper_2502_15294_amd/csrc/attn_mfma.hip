@@ -565,7 +565,10 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                             pt > 0.f ? kLn2 * __builtin_fmaf(m, a.c, fast_log2(pt)) : -__builtin_inff();
                     if ((ut & 63) == 63) flush_tile_lse(ut - 63, 64);
                 }
-                // P as a sum of bf16 numbers by truncation, and O^T += V^T . (each of them)
+                // P as a sum of bf16 numbers by truncation, and O^T += V^T . (each of them).  With 64 channels an infinite
+                // value comes out infinite, as it does from the generic kernel: no part of a weight that is not zero is
+                // zero (2^-30 of the weight is added to what the first part leaves, under the 24 bits carried), and a
+                // half tile past the segment's end, which holds the last block once more, counts as zeros.
                 uint4 ph[kParts];
 #pragma unroll
                 for (int i = 0; i < kParts; ++i) {
@@ -575,11 +578,15 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                     ph[i].w = pack_trunc(p[6], p[7]);
                     if (i + 1 < kParts)
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) p[j] -= trunc_bf16(p[j]);
+                        for (int j = 0; j < 8; ++j) {
+                            const float rest = p[j] - trunc_bf16(p[j]);
+                            p[j] = D == 64 ? __builtin_fmaf(p[j], 0x1p-30f, rest) : rest;
+                        }
                 }
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
-                    const uint4 vf = make_uint4(t.v[dt][0].x, t.v[dt][0].y, t.v[dt][1].x, t.v[dt][1].y);
+                    uint4 vf = make_uint4(t.v[dt][0].x, t.v[dt][0].y, t.v[dt][1].x, t.v[dt][1].y);
+                    if (D == 64 && len - tok0 <= 16) vf.z = vf.w = 0;
 #pragma unroll
                     for (int i = 0; i < kParts; ++i) acc[dt] = mfma16(vf, ph[i], acc[dt]);
                 }

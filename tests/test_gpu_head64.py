@@ -81,3 +81,28 @@ def test_head64_scores_of_several_tokens(q_len, Hq):
         rP, rS = pipeline.scores_for_sequence(w, b)
         assert np.abs(P[b, :, :R].cpu().numpy() - rP).max() < SCORE_TOL and np.abs(S[b, :R].cpu().numpy() - rS).max() < SCORE_TOL
     eng.close()
+
+
+@pytest.mark.parametrize("last_len", [1, 16, 17, 33])
+def test_head64_infinite_value_comes_out_infinite(last_len):
+    """An infinite value of a selected token, with weights from exactly one downwards, makes its channel infinite and
+    changes no other channel; its place (the last token) is read a second time by a half tile past the round's end."""
+    w = make_workload("cfg2", d=64, n_relevant=0, B=1, lens=[[40, last_len]], cur_len=0)
+    eng = Engine(w)
+    v = device_view(w, 1)
+    q = to_device(w.q(1)[:, 0], "bf16")
+    for sel in ([1], [0, 1]):
+        si, ns = sel_to_device([sel], v.R_max)
+        ref, ref_lse = ra.ra_round_sparse_attn_decode(eng.ctx, q, v, si, ns, scale=w.scale)
+        nblk, first = (last_len + 15) // 16, 48 * w.Hkv * 64        # round 0 fills 48 tokens of values
+        last = v.tensors[1].view(torch.bfloat16).view(-1)[first:first + w.Hkv * nblk * 16 * 64].view(w.Hkv, nblk, 64, 16)
+        keep = last.clone()
+        last[:, nblk - 1, 7, (last_len - 1) % 16] = float("inf")
+        out, lse = ra.ra_round_sparse_attn_decode(eng.ctx, q, v, si, ns, scale=w.scale)
+        torch.cuda.synchronize()
+        last.copy_(keep)
+        assert torch.equal(lse, ref_lse)
+        assert torch.isposinf(out[..., 7]).all()
+        others = [c for c in range(64) if c != 7]
+        assert torch.isfinite(ref).all() and torch.equal(out[..., others], ref[..., others])
+    eng.close()
