@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 __builtin_amdgcn_wave_barrier();
             };
 
-            auto consume = [&](const KVTile<D>& t, const TileRef& r) {
+            auto consume = [&](KVTile<D>& t, const TileRef& r) {
                 const int tok0 = r.uin * kTile, len = r.len;
                 const bool full = !r.is_cur && (len - tok0 >= kTile);
                 floatx4_t sc[2];
@@ -528,6 +528,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                     for (int kk = 0; kk < KK; ++kk) sc[h] = mfma16(t.k[h][kk], qf[kk], sc[h]);
                 }
                 if (!full) {
+                    if (D == 64 && len - tok0 <= 16)
+#pragma unroll
+                        for (int dt = 0; dt < DT; ++dt) t.v[dt][1] = make_uint2(0, 0);
                     // tokens this row may see: the segment's length, or inside the current round the causal limit
                     int lim = len;
                     if (r.is_cur) lim = min(len, max(len - q_len + qtok + 1, 0));
@@ -567,8 +570,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 }
                 // P as a sum of bf16 numbers by truncation, and O^T += V^T . (each of them).  With 64 channels an infinite
                 // value comes out infinite, as it does from the generic kernel: no part of a weight that is not zero is
-                // zero (2^-30 of the weight is added to what the first part leaves, under the 24 bits carried), and a
-                // half tile past the segment's end, which holds the last block once more, counts as zeros.
+                // zero (each remainder carries 2^-23 of the part's weight more, which the sum of the weights is given too), and
+                // a half tile past the segment's end, which holds the last block once more, counts as zeros.
                 uint4 ph[kParts];
 #pragma unroll
                 for (int i = 0; i < kParts; ++i) {
@@ -578,15 +581,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                     ph[i].w = pack_trunc(p[6], p[7]);
                     if (i + 1 < kParts)
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            const float rest = p[j] - trunc_bf16(p[j]);
-                            p[j] = D == 64 ? __builtin_fmaf(p[j], 0x1p-30f, rest) : rest;
-                        }
+                        for (int j = 0; j < 8; ++j)
+                            p[j] = D == 64 ? __builtin_fmaf(p[j], 1.f + 0x1p-23f, -trunc_bf16(p[j])) : p[j] - trunc_bf16(p[j]);
                 }
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
-                    uint4 vf = make_uint4(t.v[dt][0].x, t.v[dt][0].y, t.v[dt][1].x, t.v[dt][1].y);
-                    if (D == 64 && len - tok0 <= 16) vf.z = vf.w = 0;
+                    const uint4 vf = make_uint4(t.v[dt][0].x, t.v[dt][0].y, t.v[dt][1].x, t.v[dt][1].y);
 #pragma unroll
                     for (int i = 0; i < kParts; ++i) acc[dt] = mfma16(vf, ph[i], acc[dt]);
                 }
@@ -636,7 +636,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             else stream(std::true_type());
 
             // ---- the four lane groups hold partial sums of the same rows -------------------------------------
-            l = xrow_sum4(l);
+            l = xrow_sum4(l) * (D == 64 ? 1.f + 0x1p-23f : 1.f);
             if (parts.n_parts == 1) {
                 if (row_ok) {
                     const float inv = l > 0.f ? 1.f / l : 0.f;
