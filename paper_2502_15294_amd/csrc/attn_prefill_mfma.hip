@@ -64,7 +64,6 @@ constexpr int kNTP = 2;                         // 16-row tiles per wave
 constexpr int kRowsPerItem = 4 * kNTP * 16;     // 128
 constexpr int kTileBytes = 16384;               // 8 K fragments of 1 KB + 16 V fragments of 512 B
 constexpr int kPiecesPerWorkgroupP = 4;            // large batches, planned by a kernel of their own
-__device__ constexpr int kRangeWeightsP[2] = {1180, 820};  // see TileRanges
 
 // A wave's quarter of a key/value tile on its way from global memory to LDS.
 struct Share {
@@ -101,7 +100,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
                    [&](int) { return a.cur_k ? a.cur_len_host : 0; });
         lists.count_tiles(vw.B, sU);
         P = cut_tiles<2>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, a.S,
-                         gridDim.x >= 2u * (unsigned)a.num_cu, kRangeWeightsP);
+                         gridDim.x >= 2u * (unsigned)a.num_cu, attn_range_weights());
         if (blockIdx.x == 0) {
             if (tid < vw.B) a.n_parts[tid] = ranges.parts[tid];
             // a sequence with an empty key set lies in no range: its rows are written here

@@ -31,7 +31,6 @@ constexpr int kTilesPerChunk = kChunkTokens / kTileSP;
 constexpr int kKTileBytes = 8192;
 constexpr int kPiecesPerWorkgroupS = 1;  // measured on the 4 x 32 K-token question-prefill workload: 1: 167-172 us, 2: 174-180, 3: 176
 constexpr int kWorkgroupsPerCuS = 3;
-__device__ constexpr int kRangeWeightsS[kWorkgroupsPerCuS] = {1370, 1080, 550};  // see TileRanges
 
 // Planning kernel, grid (B): the table of segments of sequence b (all history rounds, then the current round)
 // in the layout the attention kernels use, with cum = prefix sum of the segments' chunk counts, the unused
@@ -109,7 +108,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                    [&](int) { return a.cur_k ? a.cur_len : 0; });
         lists.count_tiles(vw.B, sU);
         P = cut_tiles<kWorkgroupsPerCuS>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, kMaxRanges + 2,
-                                         gridDim.x >= kWorkgroupsPerCuS * (unsigned)a.num_cu, kRangeWeightsS);
+                                         gridDim.x >= kWorkgroupsPerCuS * (unsigned)a.num_cu, score_range_weights());
     } else {
         const int slots = max((int)gridDim.x * kPiecesPerWorkgroupS / inner, 1);
         P = build_schedule(a.plan, cap, vw.B, a.S, a.min_units, slots, sU, sps);

@@ -9,6 +9,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "tile_ranges.hpp"
 
 namespace ra {
 
@@ -327,7 +328,7 @@ __device__ __forceinline__ int find_slot(const T* cum, int n, T u) {
 // ---- planning inside a launch, for small batches ------------------------------------------------------
 // The segment lists of the whole batch in LDS, read in one memory round trip: a kernel that has them needs no planning
 // kernel before it and no second trip for the tables that one would have written.
-constexpr int kInlineBatch = 64, kInlineRounds = 1024;  // most sequences; most of them times R_max
+constexpr int kInlineRounds = 1024;  // most sequences times R_max
 inline bool prefill_plans_inline(int B, int R_max) { return B <= kInlineBatch && (long long)B * R_max <= kInlineRounds; }
 __device__ constexpr int align16(int x) { return (x + 15) & ~15; }
 struct BatchLists {
@@ -424,28 +425,17 @@ struct BatchLists {
     bool listed;
 };
 
-// Cut of the batch's key tiles into ranges, one per (group of) workgroup(s), for at most 64 sequences.  The tiles of all
-// sequences form one list, and a range may end inside a sequence and go on with the next: cutting every sequence by
-// itself leaves pieces of unequal size (four pieces a sequence: a quarter of a sequence too much here and there), and
-// the longest one is the launch.
-// The ranges are sized by how the hardware serves the workgroups that stream them.  Of the C workgroups that share a
-// compute unit the one dispatched first is the older one on every SIMD and gets the issue port first for the whole
-// kernel; with equal ranges it ends early and the last one runs alone, with nothing left to overlap its softmax with
-// (128-token question over four dialogues of 32 000 tokens: the classes of the score kernel ended after 118, 140 and
-// 187 microseconds, of the attention kernel after 121 and 154).  A launch that fills the chip C deep therefore deals the
-// ranges out to C classes in turn (class k = the k-th workgroup to land on a unit) and sizes them by `weight`.
-constexpr int kMaxRanges = 1024;
+// The cut of the batch's key tiles into ranges (tile_ranges.hpp), in LDS.
 struct TileRanges {
     int bound[kMaxRanges + 1];   // range r is the tiles bound[r] .. bound[r + 1] - 1 of the batch's list
     int seq[kInlineBatch];       // first tile of every sequence
     int part0[kInlineBatch], parts[kInlineBatch];  // first range that meets a sequence, number of them
 };
-// Fills `tr` (in LDS) from the sequences' tiles sU; returns the number of ranges: at most `slots`, each of about
-// min_tiles tiles or more, and at most max_parts (> 2) of them meet one sequence.  All threads call it; no barrier
-// behind the counts needed before it, one at its end.
+// Fills `tr` from the sequences' tiles sU; returns the number of ranges.  All threads call it; no barrier behind the counts
+// needed before it, one at its end.
 template <int C>
 __device__ __forceinline__ int cut_tiles(TileRanges& tr, const int* sU, int B, int slots, int min_tiles, int max_parts, bool full,
-                                         const int (&weights)[C]) {
+                                         const RangeWeights<C>& weights) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int U = lane < B ? sU[lane] : 0;
     const int incl = wave_inclusive_sum(U);
@@ -457,14 +447,11 @@ __device__ __forceinline__ int cut_tiles(TileRanges& tr, const int* sU, int B, i
     top = xrow_max4(vmax(top, dpp_mov<0x140>(top)));
     const int most = __builtin_amdgcn_readfirstlane((int)top);
     if (slots > kMaxRanges) slots = kMaxRanges;
-    int len = max(min_tiles, (total + slots - 1) / slots);
-    len = max(len, (most + max_parts - 3) / (max_parts - 2));
-    const int P = max(1, (total + len - 1) / len);
-    // A launch that does not fill the chip anyway, its ranges as short as they get: every sequence by itself, so that no
-    // workgroup starts twice.
-    const int cuts = U > 0 ? (U + len - 1) / len : 0, cuts_incl = wave_inclusive_sum(cuts);
+    const TileCut<C> cut(total, most, slots, min_tiles, max_parts, full, weights);
+    const int P = cut.n_ranges;
+    const int cuts = cut.cuts(U), cuts_incl = wave_inclusive_sum(cuts);
     const int P_apart = __builtin_amdgcn_readlane(cuts_incl, 63);
-    if (len == min_tiles && P_apart <= slots && P_apart > 0) {
+    if (cut.apart(P_apart, slots, min_tiles)) {
         if (tid < B) {
             tr.seq[tid] = incl - U;
             tr.part0[tid] = cuts_incl - cuts;
@@ -475,18 +462,8 @@ __device__ __forceinline__ int cut_tiles(TileRanges& tr, const int* sU, int B, i
         lds_barrier();
         return P_apart;
     }
-    int w[C], sum = 0;
-#pragma unroll
-    for (int k = 0; k < C; ++k) sum += w[k] = full && P == slots ? weights[k] : 1000;
-    auto weight_before = [&](int r) {  // of the ranges 0 .. r - 1
-        int x = r / C * sum;
-#pragma unroll
-        for (int k = 0; k + 1 < C; ++k) x += k < r % C ? w[k] : 0;
-        return x;
-    };
-    const float per_weight = (float)total / (float)weight_before(P);
-    // monotone, as the rounding of the product is
-    for (int r = tid; r <= P; r += blockDim.x) tr.bound[r] = r == P ? total : min((int)((float)weight_before(r) * per_weight), total);
+    const double per_weight = cut.tiles_per_weight();
+    for (int r = tid; r <= P; r += blockDim.x) tr.bound[r] = cut.begin(r, per_weight);
     lds_barrier();
     if (tid < B) {  // (the first wave)
         const int lo = incl - U, hi = incl - 1;

@@ -1,0 +1,94 @@
+// Cut of the key tiles of a question's batch into ranges, one per group of workgroups (question prefill and its round
+// scores, paper Sec. 3.2 steps 2 to 4), for at most kInlineBatch sequences.
+//
+// The tiles of all sequences form one list, and a range may end inside a sequence and go on with the next: cutting every
+// sequence by itself leaves pieces of unequal size (four pieces a sequence: a quarter of a sequence too much here and
+// there), and the longest one is the launch.
+// The ranges are sized by how the hardware serves the workgroups that stream them.  Of the C workgroups that share a
+// compute unit the one dispatched first is the older one on every SIMD and gets the issue port first for the whole
+// kernel; with equal ranges it ends early and the last one runs alone, with nothing left to overlap its softmax with
+// (128-token question over four dialogues of 32 000 tokens: the classes of the score kernel ended after 118, 140 and
+// 187 microseconds, of the attention kernel after 121 and 154).  A launch that fills the chip C deep therefore deals the
+// ranges out to C classes in turn (class k = the k-th workgroup to land on a unit) and sizes them by `weight`.
+//
+// Plain arithmetic usable on host and device; tests/host_model/tile_ranges.cpp runs it on the CPU.
+#pragma once
+
+#ifndef RA_HD
+#ifdef __HIPCC__
+#define RA_HD __host__ __device__
+#else
+#define RA_HD
+#endif
+#endif
+
+namespace ra {
+
+constexpr int kInlineBatch = 64;  // most sequences
+constexpr int kMaxRanges = 1024;  // most ranges, whatever the launch
+
+template <int C>
+struct RangeWeights {
+    int w[C];  // in 1/1000 of an equal range
+};
+RA_HD constexpr RangeWeights<3> score_range_weights() { return {{1370, 1080, 550}}; }
+RA_HD constexpr RangeWeights<2> attn_range_weights() { return {{1180, 820}}; }
+
+// At most `slots` ranges of about `len` tiles, at least min_tiles, such that at most max_parts (> 2) of them meet one
+// sequence: the partial results of a row have room for that many.  A sequence that meets max_parts + 1 ranges holds the
+// max_parts - 1 between its first and its last one whole, and at least a tile of each of those two.
+//   * Equal ranges: len >= most / (max_parts - 2) and total > (n_ranges - 1) len, so max_parts - 1 of them hold more than
+//     `most` tiles as long as there are that many, and rounding the ends down takes less than one.
+//   * Ranges by weight: a run that begins and ends with the lightest class holds less than its share.  They are taken if
+//     there are no more than max_parts, or if the lightest run of max_parts - 1 holds `most` tiles all the same.
+template <int C>
+struct TileCut {
+    int total, len, n_ranges, w[C], sum;  // sum: weight of a turn of the classes
+
+    // most: tiles of the longest sequence; full: the launch fills the chip if it has as many ranges as it may have
+    RA_HD TileCut(int total_, int most, int slots, int min_tiles, int max_parts, bool full, const RangeWeights<C>& weights) {
+        total = total_;
+        len = (total + slots - 1) / slots;
+        if (len < min_tiles) len = min_tiles;
+        const int fewest = (most + max_parts - 3) / (max_parts - 2);
+        if (len < fewest) len = fewest;
+        n_ranges = (total + len - 1) / len;
+        if (n_ranges < 1) n_ranges = 1;
+        sum = 0;
+        for (int k = 0; k < C; ++k) sum += w[k] = weights.w[k];
+        const bool fits = n_ranges <= max_parts ||
+                          (long long)lightest_run(max_parts - 1) * total >= (long long)most * weight_before(n_ranges % C, n_ranges / C);
+        if (!(full && n_ranges == slots && fits)) {
+            for (int k = 0; k < C; ++k) w[k] = 1000;
+            sum = 1000 * C;
+        }
+    }
+    RA_HD int lightest_run(int n) const {  // of n consecutive ranges
+        int least = sum;
+        for (int k = 0; k < C; ++k) {
+            int x = 0;
+            for (int j = 0; j < C; ++j) x += j < n % C ? w[(k + j) % C] : 0;
+            least = x < least ? x : least;
+        }
+        return n / C * sum + (n % C ? least : 0);
+    }
+    RA_HD int weight_before(int k, int turns) const {  // of the first k classes, and of so many whole turns of the classes
+        int x = turns * sum;
+        for (int j = 0; j < C; ++j) x += j < k ? w[j] : 0;
+        return x;
+    }
+    RA_HD double tiles_per_weight() const { return (double)total / (double)weight_before(n_ranges % C, n_ranges / C); }
+    // first tile of range r, 0 <= r <= n_ranges: monotone, as the rounding of the product is (in double: a batch has up to
+    // 2^30 tiles, and a float's rounding could move the ends by several)
+    RA_HD int begin(int r, double per_weight) const {
+        const int t = (int)((double)weight_before(r % C, r / C) * per_weight);
+        return r == n_ranges || t > total ? total : t;
+    }
+    // pieces of a sequence of U tiles that is cut by itself
+    RA_HD int cuts(int U) const { return U > 0 ? (U + len - 1) / len : 0; }
+    // A launch that does not fill the chip anyway, its ranges as short as they get (n_apart: the sum of cuts()): every
+    // sequence by itself, so that no workgroup starts twice.
+    RA_HD bool apart(int n_apart, int slots, int min_tiles) const { return len == min_tiles && n_apart <= slots && n_apart > 0; }
+};
+
+}  // namespace ra

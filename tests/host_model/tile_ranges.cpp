@@ -1,0 +1,97 @@
+// The cut of a question's key tiles into ranges (tile_ranges.hpp), on the CPU: random batches over the chip's slot counts,
+// part limits and weights, among them one long dialogue between two short ones.  Checked for every batch:
+//   * the ranges tile [0, total), none is empty, there are at most `slots` of them;
+//   * at most max_parts ranges meet one sequence: the partial results of a row have room for that many and no more;
+//   * sequences cut by themselves have at most max_parts pieces.
+//
+// usage: tile_ranges [seed] [cases]     exit status 0 = every check passed
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <vector>
+
+#include "tile_ranges.hpp"
+
+using namespace ra;
+
+static int bad = 0, weighted = 0;
+static long long n_checked = 0;
+
+template <int C>
+static void check(const std::vector<int>& U, int slots, int min_tiles, int max_parts, bool full, const RangeWeights<C>& weights) {
+    int total = 0, most = 0, n_apart = 0;
+    for (int u : U) {
+        total += u;
+        most = u > most ? u : most;
+    }
+    if (slots > kMaxRanges) slots = kMaxRanges;
+    const TileCut<C> cut(total, most, slots, min_tiles, max_parts, full, weights);
+    ++n_checked;
+    auto report = [&](const char* what, int b, int n) {
+        if (++bad <= 10)
+            std::fprintf(stderr, "  %s: sequence %d (%d tiles) %d, of %d tiles, %d slots, max_parts %d, %d classes, full %d\n", what, b,
+                         b < 0 ? 0 : U[b], n, total, slots, max_parts, C, (int)full);
+    };
+    for (int u : U) n_apart += cut.cuts(u);
+    if (cut.apart(n_apart, slots, min_tiles)) {
+        for (size_t b = 0; b < U.size(); ++b)
+            if (cut.cuts(U[b]) > max_parts) report("pieces of a sequence cut by itself", (int)b, cut.cuts(U[b]));
+        return;
+    }
+    const double per_weight = cut.tiles_per_weight();
+    if (cut.n_ranges > slots || cut.begin(0, per_weight) != 0 || cut.begin(cut.n_ranges, per_weight) != total)
+        report("ranges do not tile the batch", -1, cut.n_ranges);
+    bool unequal = false;
+    for (int k = 0; k < C; ++k) unequal |= cut.w[k] != cut.w[0];
+    weighted += unequal;
+    if (total == 0) return;
+    std::vector<int> begin;
+    for (int r = 0; r <= cut.n_ranges; ++r) begin.push_back(cut.begin(r, per_weight));
+    for (int r = 0; r < cut.n_ranges; ++r)
+        if (begin[r] >= begin[r + 1]) report("empty range", -1, r);
+    int lo = 0;
+    for (size_t b = 0; b < U.size(); lo += U[b++]) {
+        if (U[b] == 0) continue;
+        int parts = 0;
+        for (int r = 0; r < cut.n_ranges; ++r) parts += begin[r] < lo + U[b] && begin[r + 1] > lo;
+        if (parts > max_parts) report("parts of a sequence", (int)b, parts);
+    }
+}
+
+static void check_both(const std::vector<int>& U, int slots, int max_parts, bool full) {
+    check(U, slots, 8, max_parts, full, attn_range_weights());      // the attention kernel's buffers have max_parts
+    check(U, slots, 8, kMaxRanges + 2, full, score_range_weights());  // the score kernel keeps no partial results
+}
+
+int main(int argc, char** argv) {
+    const unsigned seed = argc > 1 ? (unsigned)std::atoi(argv[1]) : 1u;
+    const int cases = argc > 2 ? std::atoi(argv[2]) : 20000;
+    std::mt19937 rng(seed);
+    auto uni = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+    check_both({100, 1500, 100}, 19, 18, true);
+    check_both({21, 320, 21}, 19, 18, true);
+    check_both({90, 44, 2239, 3, 146}, 19, 18, true);
+    check_both({30, 392, 30}, 17, 16, true);
+    // one long dialogue between two short ones, every slot count and part limit near each other
+    for (int slots = 3; slots <= 40; ++slots)
+        for (int max_parts = 3; max_parts <= 18; ++max_parts)
+            for (int k = 0; k < 40; ++k) {
+                const int most = uni(8 * max_parts, 200 * max_parts), side = uni(0, most / 4);
+                check_both({side, most, uni(0, 1) ? side : uni(0, most / 4)}, slots, max_parts, true);
+            }
+    for (int c = 0; c < cases; ++c) {
+        const int B = uni(1, kInlineBatch), style = uni(0, 4), slots = uni(1, style == 3 ? 1500 : 64);
+        std::vector<int> U(B);
+        for (int& u : U) {
+            u = uni(0, 60);
+            if (style == 1) u = uni(0, 2) ? 0 : uni(1, 900);
+            if (style == 2) u = 1;
+            if (style == 3) u = uni(0, 30000);
+            if (style == 4) u = uni(1, 1 << uni(1, 24));
+        }
+        if (style == 0) U[uni(0, B - 1)] = uni(1, 5000);
+        check_both(U, slots, uni(3, 18), uni(0, 3) > 0);
+    }
+    std::printf("%s: %lld cuts (%d with unequal ranges), seed %u, %d failed checks\n", bad ? "FAILED" : "ok", n_checked, weighted, seed, bad);
+    return bad ? 1 : 0;
+}

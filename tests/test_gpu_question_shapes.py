@@ -61,3 +61,24 @@ def test_question(batch, q_len, Hq, Hkv):
         assert ora.row_error(out[b], ro) < STREAM_TOL, b
         assert np.allclose(lse[b], rl, rtol=0, atol=2e-5 * max(1.0, np.abs(rl).max())), b
     eng.close()
+
+
+def test_one_long_dialogue_between_two_short_ones():
+    """21, 320 and 21 key tiles in 19 ranges (26 items a range on 256 compute units): cut by the weights of the two classes of
+    workgroups the long dialogue would meet 19 ranges, and a row's partial results have room for 18."""
+    lens = [[17 * 32], [256] * 39 + [128], [17 * 32]]
+    w = make_workload("cfg3", B=3, Hq=32, Hkv=2, q_len=100, cur_len=100, n_relevant=1, lens=lens)
+    eng = Engine(w)
+    v0, v1 = device_view(w, 0), device_view(w, 1)
+    q0, q1, ck0, cv0, ck1, cv1 = (to_device(x, "bf16") for x in (w.q(0), w.q(1), w.cur_k(0), w.cur_v(0), w.cur_k(1), w.cur_v(1)))
+    out, lse = ra.ra_round_sparse_attn_prefill(eng.ctx, q1, v1, None, None, ck1, cv1, scale=w.scale)
+    again, lse2 = ra.ra_round_sparse_attn_prefill(eng.ctx, q1, v1, None, None, ck1, cv1, scale=w.scale)
+    out2, _, _, S2 = ra.ra_watershed_attn_prefill(eng.ctx, q0, v0, ck0, cv0, scale=w.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again) and torch.equal(lse, lse2)
+    for b in range(w.B):
+        rounds = list(range(w.n_rounds(b)))
+        for layer, o in ((1, out), (0, out2)):
+            assert ora.row_error(o[b].cpu().numpy(), pipeline.attention_for_sequence(w, b, layer, rounds)[0]) < STREAM_TOL, (layer, b)
+        assert np.abs(S2[b, :len(rounds)].cpu().numpy() - pipeline.scores_for_sequence(w, b)[1]).max() < SCORE_TOL, b
+    eng.close()
