@@ -367,12 +367,13 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* part_acc, con
         num.x *= f_old, num.y *= f_old, num.z *= f_old, num.w *= f_old;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float f = p0 + j < n ? fast_exp2((m[j] - m_new) * c) : 0.f;
+            const bool real = p0 + j < n;  // past the last piece its repeat counts as zeros: infinity times a weight of zero is NaN
+            const float f = real ? fast_exp2((m[j] - m_new) * c) : 0.f;
             den = __builtin_fmaf(l[j], f, den);
-            num.x = __builtin_fmaf(v[j].x, f, num.x);
-            num.y = __builtin_fmaf(v[j].y, f, num.y);
-            num.z = __builtin_fmaf(v[j].z, f, num.z);
-            num.w = __builtin_fmaf(v[j].w, f, num.w);
+            num.x = __builtin_fmaf(real ? v[j].x : 0.f, f, num.x);
+            num.y = __builtin_fmaf(real ? v[j].y : 0.f, f, num.y);
+            num.z = __builtin_fmaf(real ? v[j].z : 0.f, f, num.z);
+            num.w = __builtin_fmaf(real ? v[j].w : 0.f, f, num.w);
         }
         M = m_new;
     }
