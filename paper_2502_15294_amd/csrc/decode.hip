@@ -377,8 +377,9 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* part_acc, con
         }
         M = m_new;
     }
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    *reinterpret_cast<float4*>(out + (size_t)row * D + c4 * 4) = make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (den > 0.f) o = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);  // quotients: a reciprocal would round twice
+    *reinterpret_cast<float4*>(out + (size_t)row * D + c4 * 4) = o;
     if (lse && c4 == 0) lse[row] = den > 0.f ? __builtin_fmaf(M, scale, __builtin_logf(den)) : -__builtin_inff();
 }
 

@@ -55,3 +55,19 @@ def test_an_infinite_value_of_a_question_comes_out_infinite(pieces):
     assert torch.isposinf(out[..., 7]).all()
     assert torch.isfinite(ref).all() and torch.equal(out[..., others], ref[..., others]) and torch.equal(lse, ref_lse)
     eng.close()
+
+
+@pytest.mark.parametrize("pieces", PIECES)
+@pytest.mark.parametrize("d", [64, 128])
+def test_the_merged_output_is_the_correctly_rounded_quotient(d, pieces):
+    """With a query of zeros every weight is one, and sums of small whole numbers are exact: what is left to round is the
+    division by the sum of the weights."""
+    w, eng, v, q = _decode_case("f32", d, pieces, last=77)
+    n, tiles = 128 * (pieces - 1) + 77, 8 * pieces - 3
+    values = v.tensors[1].view(-1)[:w.Hkv * tiles * 16 * d].view(w.Hkv, tiles, d, 16)
+    values.copy_(torch.randint(-50, 200, values.shape, generator=torch.Generator().manual_seed(pieces)))
+    out, _ = ra.ra_round_sparse_attn_decode(eng.ctx, torch.zeros_like(q), v, scale=w.scale)
+    total = values.permute(0, 1, 3, 2).reshape(w.Hkv, -1, d)[:, :n].double().sum(1).float()
+    want = (total.cpu().numpy() / np.float32(n)).repeat(w.Hq // w.Hkv, axis=0)
+    assert np.array_equal(out[0].cpu().numpy(), want)
+    eng.close()
