@@ -377,9 +377,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* part_acc, con
         }
         M = m_new;
     }
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (den > 0.f) o = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);  // quotients: a reciprocal would round twice
-    *reinterpret_cast<float4*>(out + (size_t)row * D + c4 * 4) = o;
+    typedef float dword4_t __attribute__((ext_vector_type(4), aligned(4)));  // the caller's buffer is floats, no more aligned than that
+    dword4_t o = {0.f, 0.f, 0.f, 0.f};
+    if (den > 0.f) o = dword4_t{num.x / den, num.y / den, num.z / den, num.w / den};  // quotients: a reciprocal would round twice
+    *reinterpret_cast<dword4_t*>(out + (size_t)row * D + c4 * 4) = o;
     if (lse && c4 == 0) lse[row] = den > 0.f ? __builtin_fmaf(M, scale, __builtin_logf(den)) : -__builtin_inff();
 }
 

@@ -35,6 +35,20 @@ def test_an_infinite_value_of_the_last_piece_comes_out_infinite(dtype, d, pieces
     eng.close()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_the_output_may_lie_anywhere(d):
+    """A buffer of floats that starts 4, 8 or 12 bytes past a 16-byte boundary."""
+    w, eng, v, q = _decode_case("f32", d, 3)
+    ref, ref_lse = ra.ra_round_sparse_attn_decode(eng.ctx, q, v, scale=w.scale)
+    for n in (1, 2, 3):
+        buf = torch.full((ref.numel() + 8,), 5.0, device="cuda")
+        out, lse = ra.ra_round_sparse_attn_decode(eng.ctx, q, v, scale=w.scale, out=buf[n:n + ref.numel()].view(ref.shape))
+        torch.cuda.synchronize()
+        assert out.data_ptr() % 16 == 4 * n and torch.equal(out, ref) and torch.equal(lse, ref_lse)
+        assert (buf[:n] == 5).all() and (buf[n + ref.numel():] == 5).all()
+    eng.close()
+
+
 @pytest.mark.parametrize("pieces", PIECES)
 def test_an_infinite_value_of_a_question_comes_out_infinite(pieces):
     """A dialogue of one round and a question of 20 tokens: 8 key tiles a piece (with room declared for more tokens, or the
