@@ -52,6 +52,7 @@ struct AttnArgs {
     float* rec_ml;    // [records][inner][16][2]   running max of the raw logits, sum of 2^((logit - max) * c)
     int* seq_rec;     // [B][2] first record and number of records of every sequence (written by the kernel)
     int max_ranges;   // most ranges the batch's key tiles are cut into
+    int shape_units;  // shortest range the launch shape and the records have room for (mfma_decode_shape)
     int range_skew;   // in 1/1000: how much more than half of the tiles the first half of the ranges gets (see RangeCut)
     int num_cu;       // compute units of the device (many-row kernel)
     int plan_inline;  // many-row kernel: it plans itself, no planning kernel ran
@@ -98,11 +99,11 @@ struct MfmaDecodeShape {
     int n_rowblocks, inner, grid, max_ranges, records;
     size_t rec_bytes, ml_bytes;
 };
-inline MfmaDecodeShape mfma_decode_shape(int num_cu, int B, int Hkv, int D, int rows_total, long long max_tiles) {
+inline MfmaDecodeShape mfma_decode_shape(int num_cu, int B, int Hkv, int D, int rows_total, long long max_tiles, int shape_units) {
     MfmaDecodeShape s;
     s.n_rowblocks = (rows_total + 15) / 16;
     s.inner = Hkv * s.n_rowblocks;
-    long long want = max_tiles / kMfmaSpreadUnits;  // ranges the batch can have at most
+    long long want = max_tiles / shape_units;    // ranges the batch can have at most
     if (want < 1) want = 1;
     long long grid = (want * s.inner + 3) / 4;   // four waves per workgroup, at least one work item per wave
     // One workgroup per compute unit, i.e. one wave per SIMD.  With two, the hardware serves the older wave of a
@@ -138,6 +139,16 @@ inline MfmaDecodeWorkspace mfma_decode_workspace(const MfmaDecodeShape& s, int B
     w.ml_off = w.rec_off + s.rec_bytes;
     w.total = w.ml_off + s.ml_bytes;
     return w;
+}
+// The launch shape and scratch that fit into `bytes`: ranges as short as kMfmaSpreadUnits if there is room for as many,
+// otherwise of kMfmaMinUnits (half the records), whether those fit or not.  Returns the shortest range of the shape.
+inline int mfma_decode_fit(int num_cu, int B, int R_max, int Hkv, int D, int rows_total, long long max_tiles, size_t bytes,
+                           MfmaDecodeShape& s, MfmaDecodeWorkspace& w) {
+    for (int units = kMfmaSpreadUnits;; units = kMfmaMinUnits) {
+        s = mfma_decode_shape(num_cu, B, Hkv, D, rows_total, max_tiles, units);
+        w = mfma_decode_workspace(s, B, R_max);
+        if (units == kMfmaMinUnits || w.total <= bytes) return units;
+    }
 }
 // Most pieces one sequence can be cut into by the many-row kernel (row length of its piece buffers).
 inline int mfma_max_pieces(int64_t max_tokens, int min_units, int cap) {

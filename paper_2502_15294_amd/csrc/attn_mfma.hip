@@ -689,7 +689,7 @@ int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) 
     if (a.G > 16) return fail(RA_ERR_UNSUPPORTED, "attention: Hq / Hkv = %d exceeds 16", a.G);
     if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "attention: batch %d exceeds %d", B, kMaxBatch);
     const MfmaDecodeShape s =
-        mfma_decode_shape(num_cu, B, Hkv, D, rows_total, mfma_max_tiles(B, a.max_tokens, a.view.R_max, a.cur_cap));
+        mfma_decode_shape(num_cu, B, Hkv, D, rows_total, mfma_max_tiles(B, a.max_tokens, a.view.R_max, a.cur_cap), a.shape_units);
     if (a.max_ranges != s.max_ranges) return fail(RA_ERR_INVALID_ARG, "attention: launch shape mismatch");
     if (D == 128) launch_attn_mfma_d<128>(a, paged, s, st);
     else launch_attn_mfma_d<64>(a, paged, s, st);
@@ -699,7 +699,7 @@ int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) 
 // Second step of the matrix-core kernel above: merges the records of the sequences that were cut.
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st) {
     const MfmaDecodeShape s = mfma_decode_shape(num_cu, a.view.B, a.view.Hkv, a.view.d, a.q_len * a.G,
-                                                mfma_max_tiles(a.view.B, a.max_tokens, a.view.R_max, a.cur_cap));
+                                                mfma_max_tiles(a.view.B, a.max_tokens, a.view.R_max, a.cur_cap), a.shape_units);
     if (s.max_ranges <= 1) return;  // a single range never cuts a sequence
     const dim3 g((unsigned)(a.view.B * s.inner)), blk(256);
     if (a.view.d == 128) hipLaunchKernelGGL((merge_records_kernel<128>), g, blk, 0, st, a, s.n_rowblocks);

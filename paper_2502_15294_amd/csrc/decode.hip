@@ -480,9 +480,17 @@ static int decode_impl(ra_ctx* ctx, const Workspace* scratch, void* stream, cons
     const auto aligned16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
     const bool try64 = layer->dtype == RA_BF16 && D == 64 && B <= kMaxBatch && max_tiles < ((long long)1 << 30) &&
                        aligned16(q) && aligned16(layer->k) && aligned16(layer->v) && aligned16(cur_k) && aligned16(out);
+    // one entry per 32-token tile of a sequence's table: history rounds (each rounded up), then the current round
+    const int64_t n_tiles64 = layer->max_tokens / 32 + layer->R_max + (has_cur ? cur_cap / 32 + 1 : 0);
+    RA_REQUIRE(!with_scores || n_tiles64 <= (int64_t)1 << 24, RA_ERR_UNSUPPORTED, "watershed decode: max_tokens too large");
+    const int n_tiles_max = (int)n_tiles64;
+    const size_t tile_bytes = with_scores ? align_up(rows * n_tiles_max * sizeof(float), 256) : 0;
+    const size_t p_bytes = with_scores ? scores_finish_part_bytes(1, B, Hq, layer->R_max, n_tiles_max) : 0;
+    const size_t score_bytes = tile_bytes + p_bytes;
+    int shape_units = 0;
     if (mfma || try64) {
-        shape = mfma_decode_shape(ctx->num_cu, B, layer->Hkv, D, G, max_tiles);
-        mw = mfma_decode_workspace(shape, B, layer->R_max);
+        shape_units = mfma_decode_fit(ctx->num_cu, B, layer->R_max, layer->Hkv, D, G, max_tiles,
+                                      ws.bytes > score_bytes ? ws.bytes - score_bytes : 0, shape, mw);
         plan_off = mw.plan_off;
         scratch_total = mw.total;
         if (try64) mfma = ws.base != nullptr && ws.bytes >= scratch_total;
@@ -493,15 +501,9 @@ static int decode_impl(ra_ctx* ctx, const Workspace* scratch, void* stream, cons
         plan_off = w.plan_off;
         scratch_total = w.total;
     }
-    // one entry per 32-token tile of a sequence's table: history rounds (each rounded up), then the current round
-    const int64_t n_tiles64 = layer->max_tokens / 32 + layer->R_max + (has_cur ? cur_cap / 32 + 1 : 0);
-    RA_REQUIRE(!with_scores || n_tiles64 <= (int64_t)1 << 24, RA_ERR_UNSUPPORTED, "watershed decode: max_tokens too large");
-    const int n_tiles_max = (int)n_tiles64;
-    const size_t tile_bytes = with_scores ? align_up(rows * n_tiles_max * sizeof(float), 256) : 0;
-    const size_t p_bytes = with_scores ? scores_finish_part_bytes(1, B, Hq, layer->R_max, n_tiles_max) : 0;
-    RA_REQUIRE(ws.base != nullptr && ws.bytes >= scratch_total + tile_bytes + p_bytes, RA_ERR_WORKSPACE,
+    RA_REQUIRE(ws.base != nullptr && ws.bytes >= scratch_total + score_bytes, RA_ERR_WORKSPACE,
                "decode: %s has %zu bytes, this call needs %zu", scratch ? "the built-in scratch" : "the workspace", ws.bytes,
-               scratch_total + tile_bytes + p_bytes);
+               scratch_total + score_bytes);
 
     AttnArgs a = {};
     a.view = to_dev(layer);
@@ -534,6 +536,7 @@ static int decode_impl(ra_ctx* ctx, const Workspace* scratch, void* stream, cons
     a.rec_ml = mfma ? reinterpret_cast<float*>(ws.base + mw.ml_off) : nullptr;
     a.seq_rec = reinterpret_cast<int*>(ws.base + kWsSeqRecOff);
     a.max_ranges = shape.max_ranges;
+    a.shape_units = shape_units;
     a.range_skew = kRangeSkew;
 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);

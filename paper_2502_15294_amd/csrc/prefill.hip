@@ -53,14 +53,14 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     MfmaDecodeShape shape = {};
     MfmaDecodeWorkspace mw = {};
     AttnWorkspace w = {};
-    int S = 1;
+    int S = 1, shape_units = 0;
     bool plan_inline = few_rows && attn_mfma_plans_inline(B, layer->R_max);
     size_t plan_off, scratch_total;
     if (few_rows) {
         const long long max_tiles = mfma_max_tiles(B, layer->max_tokens, layer->R_max, cur_len);
         RA_REQUIRE(max_tiles < ((long long)1 << 30), RA_ERR_UNSUPPORTED, "prefill: max_tokens too large for this batch");
-        shape = mfma_decode_shape(ctx->num_cu, B, layer->Hkv, D, q_len * G, max_tiles);
-        mw = mfma_decode_workspace(shape, B, layer->R_max);
+        shape_units = mfma_decode_fit(ctx->num_cu, B, layer->R_max, layer->Hkv, D, q_len * G, max_tiles,
+                                      ctx->ws.bytes > score_bytes ? ctx->ws.bytes - score_bytes : 0, shape, mw);
         plan_off = mw.plan_off;
         scratch_total = mw.total;
     } else {
@@ -114,6 +114,7 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     a.rec_ml = few_rows ? reinterpret_cast<float*>(ctx->ws.base + mw.ml_off) : nullptr;
     a.seq_rec = reinterpret_cast<int*>(ctx->ws.base + kWsSeqRecOff);
     a.max_ranges = shape.max_ranges;
+    a.shape_units = shape_units;
     a.range_skew = kRangeSkew;
     a.num_cu = ctx->num_cu;
     a.p_half = with_scores ? 0 : ctx->prefill_p_half;  // the watershed call's scores decide the selection: full precision
