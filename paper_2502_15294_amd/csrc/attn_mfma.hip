@@ -75,6 +75,15 @@ __device__ __forceinline__ int wave_exclusive_scan(int v, int lane, int& total) 
     return incl - v;
 }
 
+// Of two pairs of bf16 numbers >= 0: `part`, but where `whole` is not zero no less than the smallest normal number (they
+// order like their bits).
+__device__ __forceinline__ uint32_t at_least_smallest(uint32_t part, uint32_t whole) {
+    typedef unsigned short pair_t __attribute__((ext_vector_type(2)));
+    const pair_t smallest = {0x0080, 0x0080};
+    const pair_t least = __builtin_elementwise_min(__builtin_bit_cast(pair_t, whole), smallest);
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(pair_t, part), least));
+}
+
 // Merge of the records (a record: the accumulators of the 16 rows of a block, row-major [16][D], and (max, sum)
 // per row) of every (sequence, KV head, row block) that was cut; grid (B * inner), block 256.
 // Thread = (group, row, four channels): the rows of the block (at most eight per pass) times D / 4 channel quads fill
@@ -570,8 +579,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 }
                 // P as a sum of bf16 numbers by truncation, and O^T += V^T . (each of them).  With 64 channels an infinite
                 // value comes out infinite, as it does from the generic kernel: no part of a weight that is not zero is
-                // zero (each remainder carries 2^-23 of the part's weight more, which the sum of the weights is given too), and
-                // a half tile past the segment's end, which holds the last block once more, counts as zeros.
+                // zero (a remainder that is takes the smallest normal number, 2^-126), and a half tile past the segment's
+                // end, which holds the last block once more, counts as zeros.
                 uint4 ph[kParts];
 #pragma unroll
                 for (int i = 0; i < kParts; ++i) {
@@ -579,10 +588,15 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                     ph[i].y = pack_trunc(p[2], p[3]);
                     ph[i].z = pack_trunc(p[4], p[5]);
                     ph[i].w = pack_trunc(p[6], p[7]);
+                    if (D == 64 && i > 0) {
+                        ph[i].x = at_least_smallest(ph[i].x, ph[0].x);
+                        ph[i].y = at_least_smallest(ph[i].y, ph[0].y);
+                        ph[i].z = at_least_smallest(ph[i].z, ph[0].z);
+                        ph[i].w = at_least_smallest(ph[i].w, ph[0].w);
+                    }
                     if (i + 1 < kParts)
 #pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            p[j] = D == 64 ? __builtin_fmaf(p[j], 1.f + 0x1p-23f, -trunc_bf16(p[j])) : p[j] - trunc_bf16(p[j]);
+                        for (int j = 0; j < 8; ++j) p[j] -= trunc_bf16(p[j]);
                 }
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
@@ -636,7 +650,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             else stream(std::true_type());
 
             // ---- the four lane groups hold partial sums of the same rows -------------------------------------
-            l = xrow_sum4(l) * (D == 64 ? 1.f + 0x1p-23f : 1.f);
+            l = xrow_sum4(l);
             if (parts.n_parts == 1) {
                 if (row_ok) {
                     const float inv = l > 0.f ? 1.f / l : 0.f;

@@ -106,3 +106,28 @@ def test_head64_infinite_value_comes_out_infinite(last_len):
         others = [c for c in range(64) if c != 7]
         assert torch.isfinite(ref).all() and torch.equal(out[..., others], ref[..., others])
     eng.close()
+
+
+@pytest.mark.parametrize("bits", [20, 40, 60, 80, 90, 100, 110, 120, 125])
+def test_head64_infinite_value_with_a_tiny_weight(bits):
+    """Two tokens, one 2^-bits of the other and with an infinite value: infinite as long as the weight is not zero, from
+    the matrix cores as from the generic kernel."""
+    w = make_workload("cfg2", d=64, n_relevant=0, B=1, lens=[[2]], cur_len=0)
+    eng = Engine(w)
+    v = device_view(w, 1)
+    q = torch.zeros((1, w.Hq, 64), dtype=torch.bfloat16, device="cuda")
+    q[..., 0] = 1
+    keys = v.tensors[0].view(-1)[:w.Hkv * 2 * 64].view(w.Hkv, 2, 64)
+    keys.zero_()
+    keys[:, 1, 0] = -bits  # exact in bf16
+    values = v.tensors[1].view(-1)[:w.Hkv * 64 * 16].view(w.Hkv, 64, 16)
+    values[:, 7, 1] = float("inf")
+    scale = float(np.log(2.0))
+    out, lse = ra.ra_round_sparse_attn_decode(eng.ctx, q, v, scale=scale)
+    generic, _ = ra.ra_round_sparse_attn_decode(eng.ctx, _offset(q, 4), v, scale=scale)
+    torch.cuda.synchronize()
+    others = [c for c in range(64) if c != 7]
+    assert torch.isposinf(generic[..., 7]).all() and torch.isposinf(out[..., 7]).all()
+    assert (out[..., others] - generic[..., others]).abs().max() < OUT_TOL * generic[..., others].abs().max()
+    assert lse.abs().max() < 2.0 ** -bits + 1e-7
+    eng.close()
