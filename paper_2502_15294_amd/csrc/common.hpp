@@ -51,17 +51,21 @@ struct KernelTimer {
 };
 }  // namespace ra
 
-// Launch of a streaming kernel (the one ra_profile_last_ms reports).
-#define RA_LAUNCH_TIMED(kernel, grid, block, smem, st, ...)                                                      \
+// Launch of a streaming kernel (the one ra_profile_last_ms reports).  A pass of several launches takes its start from the
+// first and its end from the last of them.
+#define RA_LAUNCH_TIMED_PART(first, last, kernel, grid, block, smem, st, ...)                                    \
     do {                                                                                                         \
         if (::ra::g_timed_ctx) {                                                                                 \
-            hipExtLaunchKernelGGL(kernel, grid, block, (std::uint32_t)(smem), st, ::ra::g_timed_ctx->ev_start,    \
-                                  ::ra::g_timed_ctx->ev_stop, 0, __VA_ARGS__);                                   \
+            hipExtLaunchKernelGGL(kernel, grid, block, (std::uint32_t)(smem), st,                                \
+                                  (first) ? ::ra::g_timed_ctx->ev_start : nullptr,                               \
+                                  (last) ? ::ra::g_timed_ctx->ev_stop : nullptr, 0, __VA_ARGS__);                \
             ::ra::g_timed_ctx->timed = true;                                                                     \
         } else {                                                                                                 \
             hipLaunchKernelGGL(kernel, grid, block, smem, st, __VA_ARGS__);                                      \
         }                                                                                                        \
     } while (0)
+#define RA_LAUNCH_TIMED(kernel, grid, block, smem, st, ...) \
+    RA_LAUNCH_TIMED_PART(true, true, kernel, grid, block, smem, st, __VA_ARGS__)
 
 namespace ra {
 

@@ -382,13 +382,12 @@ static void launch_scores_mfma_tab(ScoreArgs a, bool paged, size_t smem, hipStre
     constexpr int kGridY = 65535;  // chunks of one launch
     for (a.chunk0 = 0; a.chunk0 < a.n_chunks_max; a.chunk0 += kGridY) {
         const dim3 grid(a.view.Hkv, std::min(kGridY, a.n_chunks_max - a.chunk0), a.view.B);
-        if (a.view.d == 128) {
-            if (paged) RA_LAUNCH_TIMED((scores_mfma_kernel<true, TAB>), grid, dim3(256), smem, st, a);
-            else RA_LAUNCH_TIMED((scores_mfma_kernel<false, TAB>), grid, dim3(256), smem, st, a);
-        } else {
-            if (paged) RA_LAUNCH_TIMED((scores_head64_kernel<true, TAB>), grid, dim3(256), smem, st, a);
-            else RA_LAUNCH_TIMED((scores_head64_kernel<false, TAB>), grid, dim3(256), smem, st, a);
-        }
+        const bool first = a.chunk0 == 0, last = a.chunk0 + kGridY >= a.n_chunks_max;
+#define RA_CHUNK_CASE(D_, P_, K_) \
+        if (a.view.d == D_ && paged == P_) RA_LAUNCH_TIMED_PART(first, last, (K_<P_, TAB>), grid, dim3(256), smem, st, a);
+        RA_CHUNK_CASE(128, false, scores_mfma_kernel) RA_CHUNK_CASE(128, true, scores_mfma_kernel)
+        RA_CHUNK_CASE(64, false, scores_head64_kernel) RA_CHUNK_CASE(64, true, scores_head64_kernel)
+#undef RA_CHUNK_CASE
     }
 }
 

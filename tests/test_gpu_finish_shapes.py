@@ -69,6 +69,28 @@ def test_scores_with_a_capacity_whose_rows_do_not_fit_lds():
     eng.close()
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_a_score_pass_of_two_launches(d):
+    """Room declared for more chunks than one launch takes (65 535): the same scores, and the measured time is that of the
+    whole pass (nearly all of it the first launch, whose workgroups find their chunk past the last one)."""
+    w = make_workload("cfg2", B=1, d=d, lens=[[300, 7, 500]], n_relevant=1)
+    eng = Engine(w, extra_tokens=66000 * 256)
+    view = device_view(w, 0)
+    k, v, off, ln, nr, bt, off_v = view.tensors
+    q = to_device(w.q(0), w.dtype)
+    want = ra.ra_round_scores(eng.ctx, q, view, scale=w.scale)
+    ms = []
+    ra.ra_profile_kernels(eng.ctx, True)
+    for chunks in (65000, 66000):
+        roomy = ra.KVView(k, v, off, ln, nr, view.Hkv, view.d, chunks * 256, seg_off_v=off_v)
+        for _ in range(3):
+            got = ra.ra_round_scores(eng.ctx, q, roomy, scale=w.scale)
+        ms.append(ra.ra_profile_last_ms(eng.ctx))
+        assert all((x - y).abs().max() < 1e-6 for x, y in zip(got, want))
+    assert ms[1] > 0.5 * ms[0] > 0, ms
+    eng.close()
+
+
 @pytest.mark.parametrize("R", [1, 2, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 257, 511, 1024])
 @pytest.mark.parametrize("kind", ["spread", "ties", "equal"])
 def test_selection_sizes(R, kind):
