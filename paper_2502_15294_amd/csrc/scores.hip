@@ -203,9 +203,12 @@ __device__ __forceinline__ float sum_segments(float v) {
     }
     return v;
 }
-// log-sum-exp of x[lo .. hi).  A round of up to four values (1024 tokens) is read in one go.
+// log-sum-exp of x[lo .. hi).  A round of up to four values (1024 tokens) is read in one go; with ONE_FIRST, for dialogues of
+// so many rounds that most are a single value, that one is read first.
+template <bool ONE_FIRST>
 __device__ __forceinline__ float lse_range(const float* x, int lo, int hi) {
     if (hi <= lo) return -__builtin_inff();
+    if (ONE_FIRST && hi - lo == 1) return x[lo];
     float v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = x[min(lo + j, hi - 1)];
@@ -230,6 +233,20 @@ __device__ __forceinline__ float lse_range(const float* x, int lo, int hi) {
 // one sequence of 12 rounds and 32 heads and 16.7 for 64 of 50 rounds and 64 heads (with the selection, which had 2 and 6
 // of them); now 4.4 and 12.8, and the head kernel of a 128-token question 13.6 -> 7.0 microseconds.
 
+// f(k) for the rounds per lane that a view of R_max rounds has, k < KPL, four at a time: a group past R_max is skipped by a
+// scalar branch, which also keeps the compiler from fetching all sixteen ahead.  (With every one of sixteen unrolled, and
+// sixteen waves a workgroup, the one-token and head kernels spilled 70 to 176 registers: 300 rounds, the head kernel 53.1
+// microseconds for 8 dialogues of one token and 68.6 for 4 of 128 tokens, now 7.5 and 20.8.)
+template <int KPL, typename F>
+__device__ __forceinline__ void for_rounds(int R_max, F f) {
+#pragma unroll
+    for (int k0 = 0; k0 < KPL; k0 += 4)
+        if (k0 == 0 || 64 * k0 < R_max) {
+#pragma unroll
+            for (int k = k0; k < (KPL < 4 ? KPL : k0 + 4); ++k) f(k);
+        }
+}
+
 // Where the values of the rounds r = (lane mod SEG) + SEG k lie in a row: [lo[k], hi[k]), empty for r >= R.  `cum` is LDS
 // for the prefix sum over more than 64 rounds.  Returns the values of all history rounds.  Called by all threads.
 template <int SEG, int KPL>
@@ -252,11 +269,12 @@ __device__ __forceinline__ int round_places(const FinishArgs& a, int b, int& R, 
         }
         exclusive_scan_units(cum, R);
 #pragma unroll
-        for (int k = 0; k < KPL; ++k) {
+        for (int k = 0; k < KPL; ++k) lo[k] = hi[k] = 0;
+        for_rounds<KPL>(a.R_max, [&](int k) {
             const int r = j + 64 * k;
             lo[k] = r < R ? cum[r] : 0;
             hi[k] = r < R ? cum[r + 1] : 0;
-        }
+        });
         return R > 0 ? cum[R] : 0;
     }
 }
@@ -281,39 +299,39 @@ __device__ __forceinline__ void stage_floats(const float* src, int n, float* str
 
 // Probability mass of the rounds (lane mod SEG) + SEG k for one query token and head from its row of log-sum-exps:
 // softmax over the history rounds and, if has_cur, the current round's values behind them.  Zeros where the token sees
-// no key.
+// no key; groups of rounds past R_max are left as they are.
 template <int SEG, int KPL>
-__device__ __forceinline__ void round_masses(const float* row, const int (&lo)[KPL], const int (&hi)[KPL], bool has_cur,
-                                             int cur_lo, int cur_hi, float (&e)[KPL]) {
+__device__ __forceinline__ void round_masses(int R_max, const float* row, const int (&lo)[KPL], const int (&hi)[KPL],
+                                             bool has_cur, int cur_lo, int cur_hi, float (&e)[KPL]) {
     float mx = -__builtin_inff();
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) {
-        e[k] = lse_range(row, lo[k], hi[k]);
+    for_rounds<KPL>(R_max, [&](int k) {
+        e[k] = lse_range<(KPL > 4)>(row, lo[k], hi[k]);
         mx = fmaxf(mx, e[k]);
-    }
-    const float lc = has_cur ? lse_range(row, cur_lo, cur_hi) : -__builtin_inff();
+    });
+    const float lc = has_cur ? lse_range<(KPL > 4)>(row, cur_lo, cur_hi) : -__builtin_inff();
     mx = fmaxf(wave_max<SEG>(mx), lc);
     const bool none = mx == -__builtin_inff();
     float sum = 0.f;
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) {
+    for_rounds<KPL>(R_max, [&](int k) {
         e[k] = none ? 0.f : __expf(e[k] - mx);
         sum += e[k];
-    }
+    });
     const float z = wave_sum<SEG>(sum) + (none ? 1.f : __expf(lc - mx));
     const float inv = 1.f / z;
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) e[k] *= inv;
+    for_rounds<KPL>(R_max, [&](int k) { e[k] *= inv; });
 }
 
 // One query token per sequence: grid (B), 4 to 16 waves.  A wave takes groups of P = 64 / SEG consecutive heads: group w,
 // w + W, ..., with the rows of HB groups asked for together.  P goes to p_out [B][Hq][R_max] if wanted; the head mean
 // is accumulated per wave in registers and reduced over the waves through LDS in a fixed order.
 constexpr int kFinishWaves = 8;              // of the kernels that finish a head per workgroup
+// Most waves of the kernels that finish a sequence per workgroup.  With sixteen a wave has 128 registers, too few for sixteen
+// rounds per lane.
+__host__ __device__ constexpr int most_head_waves(int KPL) { return KPL > 4 ? 8 : kSelectWaves; }
 constexpr size_t kFinishLdsMax = 96 * 1024;  // dynamic LDS of a finishing kernel (the selection's 13 KB come on top)
 
 template <int SEG, int KPL, int HB, bool STAGED>
-__global__ __launch_bounds__(1024) void scores_finish_kernel(FinishArgs a) {
+__global__ __launch_bounds__(most_head_waves(KPL) * 64) void scores_finish_kernel(FinishArgs a) {
     constexpr int P = 64 / SEG;
     extern __shared__ __align__(16) char smem[];
     int* cum = reinterpret_cast<int*>(smem);                       // [R_max + 2] chunk prefix of the history rounds
@@ -330,11 +348,10 @@ __global__ __launch_bounds__(1024) void scores_finish_kernel(FinishArgs a) {
 #pragma unroll
         for (int j = 0; j < HB; ++j) {
             const int hj = h0 + j * W * P, h = hj + seg;
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
+            for_rounds<KPL>(a.R_max, [&](int k) {
                 const int r = rl + SEG * k;
                 av[j][k] = a.acc && h < a.Hq && r < a.R_max ? a.acc[((size_t)b * a.Hq + h) * a.R_max + r] : 0.f;
-            }
+            });
             if constexpr (STAGED)
                 if (hj < a.Hq) stage_floats(part_b + (size_t)hj * n, min(P, a.Hq - hj) * n, strip + j * P * n);
         }
@@ -359,11 +376,10 @@ __global__ __launch_bounds__(1024) void scores_finish_kernel(FinishArgs a) {
             const int hs_in = mine ? seg : 0;
             float qatt[KPL];
             if (!overflow)
-                round_masses<SEG>(STAGED ? strip + (j * P + hs_in) * n : part_b + (size_t)(hj + hs_in) * n, lo, hi, a.has_cur,
+                round_masses<SEG>(a.R_max, STAGED ? strip + (j * P + hs_in) * n : part_b + (size_t)(hj + hs_in) * n, lo, hi, a.has_cur,
                                   hist_chunks, hist_chunks + cur_chunks, qatt);
             float tot = 0.f;
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
+            for_rounds<KPL>(a.R_max, [&](int k) {
                 const int r = rl + SEG * k;
                 if (overflow) qatt[k] = 0.f;
                 if (a.acc && !overflow && r < R && mine) {
@@ -371,17 +387,16 @@ __global__ __launch_bounds__(1024) void scores_finish_kernel(FinishArgs a) {
                     a.acc[((size_t)b * a.Hq + h) * a.R_max + r] = qatt[k];
                 }
                 tot += qatt[k];
-            }
+            });
             tot = wave_sum<SEG>(tot);
             const float inv = tot > 0.f ? 1.f / tot : 0.f;
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
+            for_rounds<KPL>(a.R_max, [&](int k) {
                 const int r = rl + SEG * k;
                 // a max_tokens that understates the cache would leave chunks unscored: make that loud
                 const float val = overflow ? __builtin_nanf("") : (r < R ? qatt[k] * inv : 0.f);
                 hsum[k] += mine ? val : 0.f;
                 if (a.p_out && mine && r < a.R_max) a.p_out[((size_t)b * a.Hq + h) * a.R_max + r] = val;
-            }
+            });
         }
     }
 #pragma unroll
@@ -453,10 +468,9 @@ __global__ __launch_bounds__(kFinishWaves * 64) void scores_finish_rows_kernel(F
             const bool mine = ij + seg < a.q_len;  // a segment past the last token repeats the group's first one, unused
             const int in = mine ? seg : 0;
             float e[KPL];
-            round_masses<SEG>(STAGED ? strip + (j * P + in) * n : part_h + (size_t)(ij + in) * n, lo, hi, a.has_cur,
+            round_masses<SEG>(a.R_max, STAGED ? strip + (j * P + in) * n : part_h + (size_t)(ij + in) * n, lo, hi, a.has_cur,
                               hist_chunks, all_chunks, e);
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) qatt[k] += mine ? e[k] : 0.f;
+            for_rounds<KPL>(a.R_max, [&](int k) { qatt[k] += mine ? e[k] : 0.f; });
         }
     }
 #pragma unroll
@@ -559,7 +573,7 @@ struct HeadsSelect {
 };
 constexpr int kMaxSplits = 8;  // most partial masses per head (scores_finish_splits)
 template <int SEG, int KPL, int HB>
-__global__ __launch_bounds__(1024) void scores_heads_kernel(const float* p_part, int Z, int R_max, int Hq, float* p_out,
+__global__ __launch_bounds__(most_head_waves(KPL) * 64) void scores_heads_kernel(const float* p_part, int Z, int R_max, int Hq, float* p_out,
                                                             float* s_out, float* acc, HeadsSelect hsel) {
     constexpr int P = 64 / SEG;
     extern __shared__ __align__(16) char smem[];
@@ -573,25 +587,36 @@ __global__ __launch_bounds__(1024) void scores_heads_kernel(const float* p_part,
     for (int h0 = wave * P; h0 < Hq; h0 += HB * W * P) {
         float tot[HB][KPL];
 #pragma unroll
-        for (int j = 0; j < HB; ++j)
+        for (int j = 0; j < HB; ++j) {
+            const int h = h0 + j * W * P + seg;
+            const float* ph = p_part + ((size_t)b * Hq + (h < Hq ? h : 0)) * Z * R_max;
+            if constexpr (KPL <= 4) {  // every part of every round asked for at once
 #pragma unroll
-            for (int k = 0; k < KPL; ++k) {
-                const int h = h0 + j * W * P + seg, r = rl + SEG * k;
-                const bool ok = h < Hq && r < R_max;
-                const float* ph = p_part + ((size_t)b * Hq + (ok ? h : 0)) * Z * R_max + (ok ? r : 0);
-                float v[kMaxSplits];
+                for (int k = 0; k < KPL; ++k) {
+                    const int r = rl + SEG * k;
+                    const bool ok = h < Hq && r < R_max;
+                    float v[kMaxSplits];
 #pragma unroll
-                for (int z = 0; z < kMaxSplits; ++z) v[z] = ok && z < Z ? ph[(size_t)z * R_max] : 0.f;
-                tot[j][k] = 0.f;
+                    for (int z = 0; z < kMaxSplits; ++z) v[z] = ok && z < Z ? ph[(size_t)z * R_max + r] : 0.f;
+                    tot[j][k] = 0.f;
 #pragma unroll
-                for (int z = 0; z < kMaxSplits; ++z) tot[j][k] += v[z];
+                    for (int z = 0; z < kMaxSplits; ++z) tot[j][k] += v[z];
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < KPL; ++k) tot[j][k] = 0.f;
+                for (int z = 0; z < Z; ++z)
+                    for_rounds<KPL>(R_max, [&](int k) {
+                        const int r = rl + SEG * k;
+                        tot[j][k] += h < Hq && r < R_max ? ph[(size_t)z * R_max + r] : 0.f;
+                    });
             }
+        }
 #pragma unroll
         for (int j = 0; j < HB; ++j) {
             const int h = h0 + j * W * P + seg;
             float all = 0.f;
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
+            for_rounds<KPL>(R_max, [&](int k) {
                 const int r = rl + SEG * k;
                 if (acc && h < Hq && r < R_max && tot[j][k] == tot[j][k]) {  // (an undersized pass leaves the running masses alone)
                     float* slot = acc + ((size_t)b * Hq + h) * R_max + r;
@@ -599,16 +624,15 @@ __global__ __launch_bounds__(1024) void scores_heads_kernel(const float* p_part,
                     *slot = tot[j][k];
                 }
                 all += tot[j][k];
-            }
+            });
             all = wave_sum<SEG>(all);
             const float inv = all > 0.f ? 1.f / all : (all == all ? 0.f : all);  // (NaN marks an undersized pass)
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
+            for_rounds<KPL>(R_max, [&](int k) {
                 const int r = rl + SEG * k;
                 const float p = tot[j][k] * inv;
                 if (p_out && h < Hq && r < R_max) p_out[((size_t)b * Hq + h) * R_max + r] = p;
                 mine[k] += p;  // (zero for a segment past the last head)
-            }
+            });
         }
     }
 #pragma unroll
@@ -677,9 +701,9 @@ int scores_finish_splits(int q_len, int B, int Hq) {
         else LAUNCH(64, kMaxRounds / 64);                         \
     } while (0)
 
-// Waves of a workgroup that finishes `groups` groups of heads of one sequence: 4 to 16, and as the LDS allows.
-static int head_waves(int groups, int R_max) {
-    int W = groups < 4 ? 4 : (groups > kSelectWaves ? kSelectWaves : groups);
+// Waves of a workgroup that finishes `groups` groups of heads of one sequence: 4 to `most`, and as the LDS allows.
+static int head_waves(int groups, int most, int R_max) {
+    int W = groups < 4 ? 4 : (groups > most ? most : groups);
     while (W > 4 && (size_t)(W + 1) * (R_max + 2) * sizeof(float) > kFinishLdsMax) --W;
     return W;
 }
@@ -705,7 +729,7 @@ static void launch_heads(const FinishArgs& f, int B, const float* p_part, int Z,
     hsel.n_rounds = f.n_rounds;
     hsel.sel_idx = f.sel_idx;
     hsel.n_sel = f.n_sel;
-    const int W = head_waves((f.Hq * SEG + 63) / 64, f.R_max);
+    const int W = head_waves((f.Hq * SEG + 63) / 64, most_head_waves(KPL), f.R_max);
     hipLaunchKernelGGL((scores_heads_kernel<SEG, KPL, HB>), dim3(B), dim3(W * 64), (size_t)W * f.R_max * sizeof(float), st,
                        p_part, Z, f.R_max, f.Hq, f.p_out, f.s_out, f.acc, hsel);
 }
@@ -736,7 +760,7 @@ void launch_scores_finish_rows(const FinishArgs& f, int B, float* p_part, int Z,
 // fetched together as it has and as their rows fit into LDS; rows that do not fit even so are read from memory.
 template <int SEG, int KPL, int HB>
 static void launch_single(const FinishArgs& f, int B, hipStream_t st) {
-    const int groups = (f.Hq * SEG + 63) / 64, W = head_waves(groups, f.R_max);
+    const int groups = (f.Hq * SEG + 63) / 64, W = head_waves(groups, most_head_waves(KPL), f.R_max);
     const size_t base = (size_t)(f.R_max + 2) * sizeof(int) + (size_t)W * f.R_max * sizeof(float);
     const size_t staged = base + (size_t)W * HB * (64 / SEG) * f.n_chunks_max * sizeof(float);
     if (HB > 1 && (groups <= W * (HB / 2) || staged > kFinishLdsMax))

@@ -21,7 +21,8 @@ def _lens(R, seed):
 
 
 CASES = [(R, Hq, Hkv, q_len) for R in (1, 15, 16, 17, 32, 33, 64, 65, 256, 257)
-         for Hq, Hkv, q_len in ((3, 1, 1), (24, 8, 1), (18, 2, 5))] + [(50, 64, 8, 1), (50, 64, 8, 7), (40, 32, 8, 70)]
+         for Hq, Hkv, q_len in ((3, 1, 1), (24, 8, 1), (18, 2, 5))] + [
+    (R, Hq, Hkv, q_len) for R in (512, 513, 1024) for Hq, Hkv, q_len in ((3, 1, 1), (32, 8, 1), (18, 2, 5))] + [(50, 64, 8, 1), (50, 64, 8, 7), (40, 32, 8, 70)]
 
 
 @pytest.mark.parametrize("R,Hq,Hkv,q_len", CASES)
