@@ -280,8 +280,10 @@ __device__ __forceinline__ void wait_for_loads_so_far() { __builtin_amdgcn_s_wai
 //   n_b = clamp(ceil(U_b / T), 1, S)   pieces of about equal size whatever the selection sizes are.
 // T is the smallest piece (>= min_units) for which the batch has no more than `slots` pieces: one piece more than the
 // launch has workgroups for would run after all the others, alone on its compute unit and as long as they took
-// together (T = ceil(sum U_b / slots) leaves up to B - 1 such pieces: the score kernel of a 128-token question over four
-// dialogues of unequal length 224 -> 197 microseconds).  Batches above 64 sequences, which are hardly cut, take that T.
+// together (T = ceil(sum U_b / slots) leaves up to B - 1 such pieces: score kernel of a 128-token question over 4 dialogues
+// of 300 rounds 209 -> 171 microseconds, 16 of 100 rounds 240 -> 227, 24 of 50 rounds 247 -> 205).  With fewer than two
+// slots a sequence the smallest such T is the length of a whole sequence, and T = ceil(sum U_b / slots) is taken (32
+// dialogues of 40 rounds, 48 slots: 302 -> 222; 64 of 20 rounds, 96 slots: 159 -> 133), as above 64 sequences.
 // sU[b] = U_b, sps = exclusive prefix of n_b (sps[B] = number of pieces).  Must be called by all threads of the
 // workgroup.
 __device__ inline int build_schedule(const char* plan, int cap, int B, int S, int min_units, int slots, int* sU, int* sps) {
@@ -298,7 +300,7 @@ __device__ inline int build_schedule(const char* plan, int cap, int B, int S, in
     };
     int T = (int)(((unsigned)total + (unsigned)slots - 1) / (unsigned)slots);
     if (T < min_units) T = min_units;
-    if (B > 1 && B <= 64 && slots > B) {
+    if (B > 1 && B <= 64 && slots >= 2 * B) {
         // every thread tries one T between that and the one that fits for certain; the smallest that fits is taken
         const int most = (int)(((unsigned)total + (unsigned)(slots - B) - 1) / (unsigned)(slots - B));
         const int mine = T + (int)((unsigned)max(most - T, 0) * threadIdx.x / (blockDim.x - 1));
