@@ -84,6 +84,8 @@ int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st);
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st);  // ... and its second step
 // Same operands, many query rows per KV head: the waves own different rows and share key tiles through LDS.
 int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st);
+// ... which needs no planning kernel before it then (AttnArgs::plan_inline); the shape, min_units and S must be set
+bool attn_prefill_plans_inline(const AttnArgs& a, bool tile_lse, int num_cu);
 // Small batches: the first kernel resolves the selection itself (every workgroup reads the whole batch's segment
 // lists in one memory round trip and keeps them in LDS), so that no planning kernel runs before it.
 inline size_t attn_mfma_inline_bytes(int B, int R_max) {

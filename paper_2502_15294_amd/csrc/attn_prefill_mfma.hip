@@ -63,7 +63,8 @@ constexpr int kTileP = 32;                      // tokens per key tile
 constexpr int kNTP = 2;                         // 16-row tiles per wave
 constexpr int kRowsPerItem = 4 * kNTP * 16;     // 128
 constexpr int kTileBytes = 16384;               // 8 K fragments of 1 KB + 16 V fragments of 512 B
-constexpr int kPiecesPerWorkgroupP = 4;            // large batches, planned by a kernel of their own
+constexpr int kPiecesPerWorkgroupP = 4;         // large batches, planned by a kernel of their own
+constexpr int kWorkgroupsPerCuP = 2;
 
 // A wave's quarter of a key/value tile on its way from global memory to LDS.
 struct Share {
@@ -76,7 +77,7 @@ struct Share {
 // its loop the kernel takes 412 instead of 400 microseconds for the 512 rows of a 128-token question at the watershed
 // layer, which need none, paged 502 instead of 483; without the scores 147 and 145.)
 template <bool PAGED, bool TILE_LSE, bool P_HALF, bool INLINE_PLAN, bool RAGGED>
-__global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, int n_rowblocks) {
+__global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kernel(AttnArgs a, int n_rowblocks) {
     extern __shared__ __align__(16) char smem[];
     __shared__ int sU[INLINE_PLAN ? kInlineBatch : kMaxBatch], sps[INLINE_PLAN ? 1 : kMaxBatch + 1];
     __shared__ typename std::conditional<INLINE_PLAN, TileRanges, int>::type ranges;
@@ -102,8 +103,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
         lists.load(reinterpret_cast<char*>(ccum) + (TILE_LSE ? align16((cap + 1) * (int)sizeof(int)) : 0), vw, a.sel_idx, a.n_sel,
                    [&](int) { return a.cur_k ? a.cur_len_host : 0; });
         lists.count_tiles(vw.B, sU);
-        P = cut_tiles<2>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, a.S,
-                         gridDim.x >= 2u * (unsigned)a.num_cu, attn_range_weights());
+        P = cut_tiles<kWorkgroupsPerCuP>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, a.S,
+                                         gridDim.x >= kWorkgroupsPerCuP * (unsigned)a.num_cu, attn_range_weights());
         if (blockIdx.x == 0) {
             if (tid < vw.B) a.n_parts[tid] = ranges.parts[tid];
             // a sequence with an empty key set lies in no range: its rows are written here
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
         const int rowblock = uniform(rest / Hkv), g = rest - rowblock * Hkv;
         int b, s, S_eff, u_lo, u_hi;
         if constexpr (INLINE_PLAN) {
-            const int r = range_at<2>(piece, P);
+            const int r = range_at<kWorkgroupsPerCuP>(piece, P);
             const int t_lo = max(uniform(ranges.bound[r]), reached), t_hi = uniform(ranges.bound[r + 1]);
             if (t_lo >= t_hi) {  // (an empty range)
                 item += gridDim.x;
@@ -557,22 +558,37 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(AttnArgs a, i
 }
 
 
+// Dynamic LDS of a launch.
+static size_t attn_prefill_lds(int B, int R_max, bool tile_lse, bool plan_inline) {
+    return align_up(SlotTable::bytes(R_max + 1), 16) + 2 * kTileBytes + (tile_lse ? align_up((size_t)(R_max + 2) * sizeof(int), 16) : 0) +
+           (plan_inline ? BatchLists::bytes(B, R_max) : 0);
+}
+// Workgroups of a launch: as many as the chip holds, if there are as many pieces.
+static long long attn_prefill_grid(const AttnArgs& a, int num_cu, int inner) {
+    const int B = a.view.B;
+    const long long max_tiles = (long long)B * (a.max_tokens / kTileP + a.view.R_max + 1 + a.cur_cap / kTileP + 1);
+    long long max_pieces = (long long)B + max_tiles / a.min_units;
+    if (max_pieces > (long long)B * a.S) max_pieces = (long long)B * a.S;
+    long long grid = (long long)kWorkgroupsPerCuP * num_cu;
+    if (grid > max_pieces * inner) grid = max_pieces * inner;
+    return grid < 1 ? 1 : grid;
+}
+static int attn_prefill_rowblocks(const AttnArgs& a) { return (a.q_len * a.G + kRowsPerItem - 1) / kRowsPerItem; }
+bool attn_prefill_plans_inline(const AttnArgs& a, bool tile_lse, int num_cu) {
+    const int B = a.view.B, R_max = a.view.R_max;
+    return prefill_plans_inline(B, R_max, attn_prefill_lds(B, R_max, tile_lse, true),
+                                attn_prefill_grid(a, num_cu, a.view.Hkv * attn_prefill_rowblocks(a)), num_cu);
+}
+
 int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) {
     const int rows_total = a.q_len * a.G;
     const int B = a.view.B, Hkv = a.view.Hkv;
     if (a.G > 16) return fail(RA_ERR_UNSUPPORTED, "prefill: Hq / Hkv = %d exceeds 16", a.G);
     if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "prefill: batch %d exceeds %d", B, kMaxBatch);
-    const int n_rowblocks = (rows_total + kRowsPerItem - 1) / kRowsPerItem;
+    const int n_rowblocks = attn_prefill_rowblocks(a);
     const bool plan_inline = a.plan_inline != 0;
-    const size_t smem = align_up(SlotTable::bytes(a.view.R_max + 1), 16) + 2 * kTileBytes +
-                        (a.tile_lse ? align_up((size_t)(a.view.R_max + 2) * sizeof(int), 16) : 0) +
-                        (plan_inline ? BatchLists::bytes(B, a.view.R_max) : 0);
-    const long long max_tiles = (long long)B * (a.max_tokens / kTileP + a.view.R_max + 1 + a.cur_cap / kTileP + 1);
-    long long max_pieces = (long long)B + max_tiles / a.min_units;
-    if (max_pieces > (long long)B * a.S) max_pieces = (long long)B * a.S;
-    long long grid = (long long)2 * num_cu;
-    if (grid > max_pieces * Hkv * n_rowblocks) grid = max_pieces * Hkv * n_rowblocks;
-    if (grid < 1) grid = 1;
+    const size_t smem = attn_prefill_lds(B, a.view.R_max, a.tile_lse != nullptr, plan_inline);
+    const long long grid = attn_prefill_grid(a, num_cu, Hkv * n_rowblocks);
     const bool lse = a.tile_lse != nullptr, half = a.p_half != 0;
     const int row_tiles = (rows_total + 15) / 16;
     const bool ragged = row_tiles != n_rowblocks * 4 * kNTP;

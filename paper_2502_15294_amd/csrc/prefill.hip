@@ -50,32 +50,38 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     const size_t tile_bytes = with_scores ? align_up(rows * n_tiles_max * sizeof(float), 256) : 0;
     const size_t p_bytes = with_scores ? scores_finish_part_bytes(q_len, B, Hq, layer->R_max, n_tiles_max) : 0;
     const size_t score_bytes = tile_bytes + p_bytes;
+    AttnArgs a = {};
+    a.view = to_dev(layer);
+    a.cur_len_host = cur_len;
+    a.cur_cap = cur_len;
+    a.max_tokens = layer->max_tokens;
+    a.q_len = q_len;
+    a.Hq = Hq;
+    a.G = G;
+    a.S = 1;
+    a.min_units = few_rows ? kMfmaMinUnits : attn_min_units();
+    a.num_cu = ctx->num_cu;
     MfmaDecodeShape shape = {};
     MfmaDecodeWorkspace mw = {};
     AttnWorkspace w = {};
-    int S = 1, shape_units = 0;
     bool plan_inline = few_rows && attn_mfma_plans_inline(B, layer->R_max);
     size_t plan_off, scratch_total;
     if (few_rows) {
         const long long max_tiles = mfma_max_tiles(B, layer->max_tokens, layer->R_max, cur_len);
         RA_REQUIRE(max_tiles < ((long long)1 << 30), RA_ERR_UNSUPPORTED, "prefill: max_tokens too large for this batch");
-        shape_units = mfma_decode_fit(ctx->num_cu, B, layer->R_max, layer->Hkv, D, q_len * G, max_tiles,
-                                      ctx->ws.bytes > score_bytes ? ctx->ws.bytes - score_bytes : 0, shape, mw);
+        a.shape_units = mfma_decode_fit(ctx->num_cu, B, layer->R_max, layer->Hkv, D, q_len * G, max_tiles,
+                                        ctx->ws.bytes > score_bytes ? ctx->ws.bytes - score_bytes : 0, shape, mw);
         plan_off = mw.plan_off;
         scratch_total = mw.total;
     } else {
-        S = mfma_max_pieces(layer->max_tokens + cur_len, attn_min_units(), 8);
-        w = attn_workspace(rows, S, D, B, layer->R_max);
         // Small batches: the kernel plans itself and cuts the batch into ranges, whose ends a sequence shares with its
         // neighbours (two parts more).  A workspace that only fits the other schedule gets that one.
-        if (prefill_plans_inline(B, layer->R_max)) {
-            const int S_ranges = mfma_max_pieces(layer->max_tokens + cur_len, attn_min_units(), 16) + 2;
-            const AttnWorkspace w_ranges = attn_workspace(rows, S_ranges, D, B, layer->R_max);
-            plan_inline = ctx->ws.bytes >= w_ranges.total + score_bytes;
-            if (plan_inline) {
-                S = S_ranges;
-                w = w_ranges;
-            }
+        a.S = mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2;
+        w = attn_workspace(rows, a.S, D, B, layer->R_max);
+        plan_inline = attn_prefill_plans_inline(a, with_scores, ctx->num_cu) && ctx->ws.bytes >= w.total + score_bytes;
+        if (!plan_inline) {
+            a.S = mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 8);
+            w = attn_workspace(rows, a.S, D, B, layer->R_max);
         }
         plan_off = w.plan_off;
         scratch_total = w.total;
@@ -83,22 +89,12 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     RA_REQUIRE(ctx->ws.base != nullptr && ctx->ws.bytes >= scratch_total + score_bytes, RA_ERR_WORKSPACE,
                "prefill: workspace has %zu bytes, this call needs %zu", ctx->ws.bytes, scratch_total + score_bytes);
 
-    AttnArgs a = {};
-    a.view = to_dev(layer);
     a.q = q;
     a.sel_idx = sel_idx;
     a.n_sel = n_sel;
     a.cur_k = cur_len ? cur_k : nullptr;
     a.cur_v = cur_len ? cur_v : nullptr;
     a.cur_len_dev = nullptr;
-    a.cur_len_host = cur_len;
-    a.cur_cap = cur_len;
-    a.max_tokens = layer->max_tokens;
-    a.q_len = q_len;
-    a.Hq = Hq;
-    a.G = G;
-    a.S = S;
-    a.min_units = few_rows ? kMfmaMinUnits : attn_min_units();
     a.c = scale * kLog2e;
     a.scale = scale;
     a.part_acc = few_rows ? nullptr : reinterpret_cast<float*>(ctx->ws.base + w.acc_off);
@@ -114,9 +110,7 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     a.rec_ml = few_rows ? reinterpret_cast<float*>(ctx->ws.base + mw.ml_off) : nullptr;
     a.seq_rec = reinterpret_cast<int*>(ctx->ws.base + kWsSeqRecOff);
     a.max_ranges = shape.max_ranges;
-    a.shape_units = shape_units;
     a.range_skew = kRangeSkew;
-    a.num_cu = ctx->num_cu;
     a.p_half = with_scores ? 0 : ctx->prefill_p_half;  // the watershed call's scores decide the selection: full precision
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     a.plan_inline = plan_inline;
@@ -128,7 +122,7 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
             return rc;
     }
     if (few_rows) launch_merge_records(a, ctx->num_cu, st);
-    else if (S > 1) launch_combine(a, D, rows, st);
+    else if (a.S > 1) launch_combine(a, D, rows, st);
     if (with_scores) {
         // Eq. 1 over history rounds and, for several query tokens, the visible part of the question itself
         // (with one query token the current round cancels in the normalisation over history rounds).

@@ -404,15 +404,16 @@ int launch_scores_prefill_mfma(const ScoreArgs& a, bool paged, int num_cu, hipSt
     if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "round_scores: batch %d exceeds %d", B, kMaxBatch);
     const int rows_total = a.q_len * G;
     const int n_rowblocks = (rows_total + kRowsPerItemS - 1) / kRowsPerItemS;
-    const bool plan_inline = prefill_plans_inline(B, a.view.R_max);
-    const size_t smem = align_up(SlotTable::bytes(a.view.R_max + 1), 16) + 2 * kKTileBytes +
-                        align_up((size_t)(a.view.R_max + 2) * sizeof(int), 16) +
-                        (plan_inline ? BatchLists::bytes(B, a.view.R_max) : 0);
+    const size_t table_lds = align_up(SlotTable::bytes(a.view.R_max + 1), 16) + 2 * kKTileBytes +
+                             align_up((size_t)(a.view.R_max + 2) * sizeof(int), 16);
+    const size_t inline_lds = table_lds + BatchLists::bytes(B, a.view.R_max);
     long long max_pieces = (long long)B + (long long)B * a.n_chunks_max * kTilesPerChunk / a.min_units;
     if (max_pieces > (long long)B * a.S) max_pieces = (long long)B * a.S;
     long long grid = (long long)kWorkgroupsPerCuS * num_cu;
     if (grid > max_pieces * Hkv * n_rowblocks) grid = max_pieces * Hkv * n_rowblocks;
     if (grid < 1) grid = 1;
+    const bool plan_inline = prefill_plans_inline(B, a.view.R_max, inline_lds, grid, num_cu);
+    const size_t smem = plan_inline ? inline_lds : table_lds;
     if (!plan_inline) launch_scores_plan(a, st);
     const int row_tiles = (rows_total + 15) / 16;
     const bool ragged = row_tiles != n_rowblocks * 4 * kNTS;

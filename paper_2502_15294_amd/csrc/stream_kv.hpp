@@ -331,7 +331,11 @@ __device__ __forceinline__ int find_slot(const T* cum, int n, T u) {
 // The segment lists of the whole batch in LDS, read in one memory round trip: a kernel that has them needs no planning
 // kernel before it and no second trip for the tables that one would have written.
 constexpr int kInlineRounds = 1024;  // most sequences times R_max
-inline bool prefill_plans_inline(int B, int R_max) { return B <= kInlineBatch && (long long)B * R_max <= kInlineRounds; }
+// A launch that plans itself must still hold as many workgroups on a compute unit as it has for one: the lists, 24 bytes per
+// (sequence, round), come on top of the table's.  (128-token question, one dialogue of 619 rounds: the score kernel, three
+// to a unit, 78.9 microseconds behind the planning kernel and 109.4 with its own plan, of which two fit; 618 rounds, of
+// which three do, 84.3.  917 rounds: the attention kernel 93.5 and 114.2, two to a unit and one; 914: 74.6.)
+constexpr size_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;
 __device__ constexpr int align16(int x) { return (x + 15) & ~15; }
 struct BatchLists {
     long long *ok, *ov;  // [B][R_max] starts of the rounds' keys / values, by round index
@@ -433,6 +437,11 @@ struct TileRanges {
     int seq[kInlineBatch];       // first tile of every sequence
     int part0[kInlineBatch], parts[kInlineBatch];  // first range that meets a sequence, number of them
 };
+// lds: dynamic LDS of the launch that plans itself; grid: its workgroups.
+inline bool prefill_plans_inline(int B, int R_max, size_t lds, long long grid, int num_cu) {
+    const size_t all = align_up(lds + sizeof(TileRanges) + (kInlineBatch + 4) * sizeof(int), kLdsGranule);
+    return B <= kInlineBatch && (long long)B * R_max <= kInlineRounds && (grid + num_cu - 1) / num_cu * all <= kLdsPerUnit;
+}
 // Fills `tr` from the sequences' tiles sU; returns the number of ranges.  All threads call it; no barrier behind the counts
 // needed before it, one at its end.
 template <int C>
