@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
                    [&](int) { return a.cur_k ? a.cur_len_host : 0; });
         lists.count_tiles(vw.B, sU);
         P = cut_tiles<kWorkgroupsPerCuP>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, a.S,
-                                         gridDim.x >= kWorkgroupsPerCuP * (unsigned)a.num_cu, attn_range_weights());
+                                         !PAGED && !P_HALF && gridDim.x >= kWorkgroupsPerCuP * (unsigned)a.num_cu, attn_range_weights());
         if (blockIdx.x == 0) {
             if (tid < vw.B) a.n_parts[tid] = ranges.parts[tid];
             // a sequence with an empty key set lies in no range: its rows are written here

@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                    [&](int) { return a.cur_k ? a.cur_len : 0; });
         lists.count_tiles(vw.B, sU);
         P = cut_tiles<kWorkgroupsPerCuS>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, kMaxRanges + 2,
-                                         gridDim.x >= kWorkgroupsPerCuS * (unsigned)a.num_cu, score_range_weights());
+                                         !PAGED && gridDim.x >= kWorkgroupsPerCuS * (unsigned)a.num_cu, score_range_weights());
     } else {
         const int slots = max((int)gridDim.x * kPiecesPerWorkgroupS / inner, 1);
         P = build_schedule(a.plan, cap, vw.B, a.S, a.min_units, slots, sU, sps);

@@ -10,6 +10,13 @@
 // (128-token question over four dialogues of 32 000 tokens: the classes of the score kernel ended after 118, 140 and
 // 187 microseconds, of the attention kernel after 121 and 154).  A launch that fills the chip C deep therefore deals the
 // ranges out to C classes in turn (class k = the k-th workgroup to land on a unit) and sizes them by `weight`.
+// That holds if every class has as many ranges as the others: with one range more in the first class its last workgroups
+// land second on their units and are the longest of all (200 tokens, 9 ranges of the attention kernel: 118.7 microseconds
+// by weight, 109.0 equal; the score kernel with 5, 8, 19 ranges: 305, 204, 163 and 285, 182, 150; with 48 ranges 156 and
+// 169, attention kernel with 2 ranges of 1000 tokens 249 and 277, at the watershed layer with 16 399 and 414).  Launches
+// over paged blocks, which wait for their table entries, and of the fp16 mode are not served that way: attention kernel
+// 179 microseconds by weight and 171 equal paged, 485 and 469 at the watershed layer, 132 and 127 in the fp16 mode; score
+// kernel, paged, 192 and 190.
 //
 // Plain arithmetic usable on host and device; tests/host_model/tile_ranges.cpp runs it on the CPU.
 #pragma once
@@ -45,7 +52,7 @@ template <int C>
 struct TileCut {
     int total, len, n_ranges, w[C], sum;  // sum: weight of a turn of the classes
 
-    // most: tiles of the longest sequence; full: the launch fills the chip if it has as many ranges as it may have
+    // most: tiles of the longest sequence; full: by weight, if there are as many ranges as the launch may have
     RA_HD TileCut(int total_, int most, int slots, int min_tiles, int max_parts, bool full, const RangeWeights<C>& weights) {
         total = total_;
         len = (total + slots - 1) / slots;
@@ -58,7 +65,7 @@ struct TileCut {
         for (int k = 0; k < C; ++k) sum += w[k] = weights.w[k];
         const bool fits = n_ranges <= max_parts ||
                           (long long)lightest_run(max_parts - 1) * total >= (long long)most * weight_before(n_ranges % C, n_ranges / C);
-        if (!(full && n_ranges == slots && fits)) {
+        if (!(full && n_ranges == slots && n_ranges % C == 0 && fits)) {
             for (int k = 0; k < C; ++k) w[k] = 1000;
             sum = 1000 * C;
         }

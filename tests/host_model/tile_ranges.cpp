@@ -43,6 +43,7 @@ static void check(const std::vector<int>& U, int slots, int min_tiles, int max_p
         report("ranges do not tile the batch", -1, cut.n_ranges);
     bool unequal = false;
     for (int k = 0; k < C; ++k) unequal |= cut.w[k] != cut.w[0];
+    if (unequal && (!full || cut.n_ranges != slots || cut.n_ranges % C)) report("unequal ranges where the classes are not even", -1, cut.n_ranges);
     weighted += unequal;
     if (total == 0) return;
     std::vector<int> begin;
