@@ -56,6 +56,7 @@ struct AttnArgs {
     int range_skew;   // in 1/1000: how much more than half of the tiles the first half of the ranges gets (see RangeCut)
     int num_cu;       // compute units of the device (many-row kernel)
     int plan_inline;  // many-row kernel: it plans itself, no planning kernel ran
+    int slots;        // ... and cuts the batch into at most so many ranges
     int p_half;       // many-row kernel: probabilities as one fp16 operand instead of two bf16 (ra_set_prefill_precision)
 };
 
@@ -83,7 +84,7 @@ int attn_min_units();  // smallest piece of a sequence's key set, in 32-token ti
 int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st);
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st);  // ... and its second step
 // Same operands, many query rows per KV head: the waves own different rows and share key tiles through LDS.
-int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st);
+int launch_attn_prefill_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st);
 // ... which needs no planning kernel before it then (AttnArgs::plan_inline); the shape, min_units and S must be set
 bool attn_prefill_plans_inline(const AttnArgs& a, bool tile_lse, int num_cu);
 // Small batches: the first kernel resolves the selection itself (every workgroup reads the whole batch's segment

@@ -103,8 +103,10 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
         lists.load(reinterpret_cast<char*>(ccum) + (TILE_LSE ? align16((cap + 1) * (int)sizeof(int)) : 0), vw, a.sel_idx, a.n_sel,
                    [&](int) { return a.cur_k ? a.cur_len_host : 0; });
         lists.count_tiles(vw.B, sU);
-        P = cut_tiles<kWorkgroupsPerCuP>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, a.S,
-                                         !PAGED && !P_HALF && gridDim.x >= kWorkgroupsPerCuP * (unsigned)a.num_cu, attn_range_weights());
+        P = cut_tiles<kWorkgroupsPerCuP>(ranges, sU, vw.B, a.slots, a.min_units, a.S,
+                                         !PAGED && !P_HALF && gridDim.x >= kWorkgroupsPerCuP * (unsigned)a.num_cu &&
+                                             a.slots * inner <= (int)gridDim.x,
+                                         attn_range_weights());
         if (blockIdx.x == 0) {
             if (tid < vw.B) a.n_parts[tid] = ranges.parts[tid];
             // a sequence with an empty key set lies in no range: its rows are written here
@@ -580,7 +582,7 @@ bool attn_prefill_plans_inline(const AttnArgs& a, bool tile_lse, int num_cu) {
                                 attn_prefill_grid(a, num_cu, a.view.Hkv * attn_prefill_rowblocks(a)), num_cu);
 }
 
-int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) {
+int launch_attn_prefill_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st) {
     const int rows_total = a.q_len * a.G;
     const int B = a.view.B, Hkv = a.view.Hkv;
     if (a.G > 16) return fail(RA_ERR_UNSUPPORTED, "prefill: Hq / Hkv = %d exceeds 16", a.G);
@@ -589,6 +591,7 @@ int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, int num_cu, hipStrea
     const bool plan_inline = a.plan_inline != 0;
     const size_t smem = attn_prefill_lds(B, a.view.R_max, a.tile_lse != nullptr, plan_inline);
     const long long grid = attn_prefill_grid(a, num_cu, Hkv * n_rowblocks);
+    a.slots = question_slots(Hkv * n_rowblocks, grid, num_cu, true);
     const bool lse = a.tile_lse != nullptr, half = a.p_half != 0;
     const int row_tiles = (rows_total + 15) / 16;
     const bool ragged = row_tiles != n_rowblocks * 4 * kNTP;

@@ -22,6 +22,7 @@ struct ScoreArgs {
     // many-row kernel only: room for its segment tables and the bounds of its schedule
     const char* plan;   // [B][plan_stride(R_max + 1)]
     int num_cu = 0;     // compute units of the device
+    int slots = 0;      // most ranges a launch that plans itself cuts the batch into
     int S, min_units;   // a sequence is cut into at most S pieces of at least min_units key tiles
 };
 
@@ -68,7 +69,7 @@ __device__ __forceinline__ int cur_visible(int cur_len, int q_len, int i) {
 }
 
 // bf16, d = 128, Hq/Hkv <= 16: matrix-core streaming kernels, for up to 16 query rows per KV head and for more.
-int launch_scores_prefill_mfma(const ScoreArgs& a, bool paged, int num_cu, hipStream_t st);
+int launch_scores_prefill_mfma(ScoreArgs a, bool paged, int num_cu, hipStream_t st);
 int launch_scores_mfma(const ScoreArgs& a, bool paged, int num_cu, hipStream_t st);
 
 }  // namespace ra

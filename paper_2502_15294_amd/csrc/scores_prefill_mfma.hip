@@ -107,8 +107,10 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
         lists.load(reinterpret_cast<char*>(tcum) + align16((cap + 1) * (int)sizeof(int)), vw, nullptr, nullptr,
                    [&](int) { return a.cur_k ? a.cur_len : 0; });
         lists.count_tiles(vw.B, sU);
-        P = cut_tiles<kWorkgroupsPerCuS>(ranges, sU, vw.B, max((int)gridDim.x / inner, 1), a.min_units, kMaxRanges + 2,
-                                         !PAGED && gridDim.x >= kWorkgroupsPerCuS * (unsigned)a.num_cu, score_range_weights());
+        P = cut_tiles<kWorkgroupsPerCuS>(ranges, sU, vw.B, a.slots, a.min_units, kMaxRanges + 2,
+                                         !PAGED && gridDim.x >= kWorkgroupsPerCuS * (unsigned)a.num_cu &&
+                                             a.slots * inner <= (int)gridDim.x,
+                                         score_range_weights());
     } else {
         const int slots = max((int)gridDim.x * kPiecesPerWorkgroupS / inner, 1);
         P = build_schedule(a.plan, cap, vw.B, a.S, a.min_units, slots, sU, sps);
@@ -397,7 +399,7 @@ static void launch_scores_plan(const ScoreArgs& a, hipStream_t st) {
                        const_cast<char*>(a.plan));
 }
 
-int launch_scores_prefill_mfma(const ScoreArgs& a, bool paged, int num_cu, hipStream_t st) {
+int launch_scores_prefill_mfma(ScoreArgs a, bool paged, int num_cu, hipStream_t st) {
     const int G = a.Hq / a.view.Hkv;
     if (G > 16) return fail(RA_ERR_UNSUPPORTED, "round_scores: Hq / Hkv = %d exceeds 16", G);
     const int B = a.view.B, Hkv = a.view.Hkv;
@@ -412,6 +414,7 @@ int launch_scores_prefill_mfma(const ScoreArgs& a, bool paged, int num_cu, hipSt
     long long grid = (long long)kWorkgroupsPerCuS * num_cu;
     if (grid > max_pieces * Hkv * n_rowblocks) grid = max_pieces * Hkv * n_rowblocks;
     if (grid < 1) grid = 1;
+    a.slots = question_slots(Hkv * n_rowblocks, grid, num_cu, false);
     const bool plan_inline = prefill_plans_inline(B, a.view.R_max, inline_lds, grid, num_cu);
     const size_t smem = plan_inline ? inline_lds : table_lds;
     if (!plan_inline) launch_scores_plan(a, st);

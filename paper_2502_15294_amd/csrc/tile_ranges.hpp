@@ -41,6 +41,24 @@ struct RangeWeights {
 RA_HD constexpr RangeWeights<3> score_range_weights() { return {{1370, 1080, 550}}; }
 RA_HD constexpr RangeWeights<2> attn_range_weights() { return {{1180, 820}}; }
 
+// Most ranges of a launch of `grid` workgroups, `inner` of which stream each range (its KV heads and blocks of query rows).
+// A range's workgroups lie on consecutive units, and the launch lasts as long as the unit with the most of them.  As many
+// ranges as run at the same time, if that leaves no more than an eighth of the units' time unused; otherwise the fewest
+// more for which it does, by workgroups that stream several ranges one after the other.  With `partials`, whose number
+// grows with the ranges, only if that takes a sixth off.  (Attention kernel, 600 tokens of 64 heads, inner 304: 1 range 450
+// microseconds, 3 335; 1500 tokens, inner 376: 1 range 336, 2 291; 2500, inner 632: 1 range 649, 2 542; 200 of 64 heads,
+// inner 104: 4 ranges 211, 7 212.  Score kernel, 2500 tokens, inner 320: 2 ranges 426, 3 381.)
+inline int question_slots(int inner, long long grid, int num_cu, bool partials) {
+    const int at_once = (int)(grid / inner) < 1 ? 1 : (int)(grid / inner);
+    if (grid < num_cu) return at_once;
+    auto busiest = [&](int s) { return ((long long)s * inner + num_cu - 1) / num_cu; };  // workgroups' worth of ranges on a unit
+    for (int s = at_once; s <= 4 * at_once + 4; ++s) {
+        if (busiest(s) * num_cu * 8 > (long long)s * inner * 9) continue;
+        return partials && busiest(s) * at_once * 6 > busiest(at_once) * s * 5 ? at_once : s;
+    }
+    return at_once;
+}
+
 // At most `slots` ranges of about `len` tiles, at least min_tiles, such that at most max_parts (> 2) of them meet one
 // sequence: the partial results of a row have room for that many.  A sequence that meets max_parts + 1 ranges holds the
 // max_parts - 1 between its first and its last one whole, and at least a tile of each of those two.

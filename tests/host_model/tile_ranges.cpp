@@ -3,6 +3,7 @@
 //   * the ranges tile [0, total), none is empty, there are at most `slots` of them;
 //   * at most max_parts ranges meet one sequence: the partial results of a row have room for that many and no more;
 //   * sequences cut by themselves have at most max_parts pieces.
+// And the number of ranges that launches of many query rows are given.
 //
 // usage: tile_ranges [seed] [cases]     exit status 0 = every check passed
 #include <cstdio>
@@ -93,6 +94,14 @@ int main(int argc, char** argv) {
         if (style == 0) U[uni(0, B - 1)] = uni(1, 5000);
         check_both(U, slots, uni(3, 18), uni(0, 3) > 0);
     }
+    // ranges handed to a launch that fills the chip: one at least, all at the same time, or a whole number of rounds to within
+    // an eighth
+    for (int deep = 2; deep <= 3; ++deep)
+        for (int inner = 1; inner <= 3000; ++inner) {
+            const int cu = 256, s = question_slots(inner, deep * cu, cu, deep == 2), at_once = deep * cu / inner > 1 ? deep * cu / inner : 1;
+            const long long busiest = ((long long)s * inner + cu - 1) / cu;
+            if (s < at_once || (s > at_once && busiest * cu * 8 > 9ll * s * inner)) ++bad;
+        }
     std::printf("%s: %lld cuts (%d with unequal ranges), seed %u, %d failed checks\n", bad ? "FAILED" : "ok", n_checked, weighted, seed, bad);
     return bad ? 1 : 0;
 }

@@ -85,3 +85,26 @@ def test_one_long_dialogue_between_two_short_ones():
             assert ora.row_error(o[b].cpu().numpy(), pipeline.attention_for_sequence(w, b, layer, rounds)[0]) < STREAM_TOL, (layer, b)
         assert np.abs(S2[b, :len(rounds)].cpu().numpy() - pipeline.scores_for_sequence(w, b)[1]).max() < SCORE_TOL, b
     eng.close()
+
+
+@pytest.mark.parametrize("q_len,Hq,Hkv", [(88, 256, 16), (112, 512, 32)])
+def test_more_rows_than_the_chip_takes_ranges_of(q_len, Hq, Hkv):
+    """Workgroups that stream several ranges one after the other, some of which cross from one dialogue into the next: 176
+    items a range in the attention kernel (two ranges at a time on 256 units, four handed out), 224 in the score kernel."""
+    w = make_workload("cfg3", B=3, Hq=Hq, Hkv=Hkv, q_len=q_len, cur_len=q_len + 3, n_relevant=1, lens=[[400, 33], [5, 500, 64], [100]])
+    eng = Engine(w)
+    v0, v1 = device_view(w, 0), device_view(w, 1)
+    q0, q1, ck0, cv0, ck1, cv1 = (to_device(x, "bf16") for x in (w.q(0), w.q(1), w.cur_k(0), w.cur_v(0), w.cur_k(1), w.cur_v(1)))
+    P, S = ra.ra_round_scores(eng.ctx, q0, v0, ck0, scale=w.scale)
+    out, _ = ra.ra_round_sparse_attn_prefill(eng.ctx, q1, v1, None, None, ck1, cv1, scale=w.scale)
+    out2, _, _, S2 = ra.ra_watershed_attn_prefill(eng.ctx, q0, v0, ck0, cv0, scale=w.scale)
+    torch.cuda.synchronize()
+    for b in range(w.B):
+        rounds = list(range(w.n_rounds(b)))
+        rP, rS = pipeline.scores_for_sequence(w, b)
+        assert np.abs(P[b, :, :len(rounds)].cpu().numpy() - rP).max() < SCORE_TOL
+        assert np.abs(S[b, :len(rounds)].cpu().numpy() - rS).max() < SCORE_TOL
+        assert np.abs(S2[b, :len(rounds)].cpu().numpy() - rS).max() < SCORE_TOL
+        for layer, o in ((1, out), (0, out2)):
+            assert ora.row_error(o[b].cpu().numpy(), pipeline.attention_for_sequence(w, b, layer, rounds)[0]) < STREAM_TOL, (layer, b)
+    eng.close()
