@@ -309,8 +309,22 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
 
     // While every range of two tiles still gets a wave of its own the ranges are that short: one round trip to memory
     // instead of two (one dialogue's step, 45 tiles: 14.2 -> 11.4 microseconds, the merge 4.0 -> 5.0).  With more work
-    // than that the shorter ranges only add records (8 dialogues, 480 tiles: 18.7 -> 19.6).
-    const bool spread = (unsigned)total <= kMfmaSpreadUnits * (gridDim.x * 4u / (unsigned)inner);
+    // than that the shorter ranges only add records (8 dialogues, 480 tiles: 18.7 -> 19.6).  And the records of one
+    // sequence, which a workgroup of the merge walks, must not cost more than that: records times rows.  (Whole call, ranges
+    // of four and of two tiles: 64 tiles of 4 rows 17.6 and 17.0 microseconds, 96 18.2 and 18.5; 32 tiles of 8 rows 16.8
+    // and 16.4, 48 17.8 and 18.5, 128 24.0 and 28.0; of 16 rows 16 tiles 17.4 and 17.2, 128 31.7 and 44.3; 64 channels,
+    // 96 tiles of 4 rows 14.8 and 14.4, 128 15.5 and 15.6.)
+    bool spread = (unsigned)total <= kMfmaSpreadUnits * (gridDim.x * 4u / (unsigned)inner);
+    const int merge_rows = min(rows_total, 16), merge_limit = D == 128 ? 256 : 384;
+    if (spread && total * merge_rows > merge_limit) {
+        float most = 0.f;  // tiles of the longest sequence (exact: fewer than 2^24)
+        for (int b = lane; b < B; b += 64) most = vmax(most, (float)sU[b]);
+        most = vmax(most, dpp_mov<0xB1>(most));
+        most = vmax(most, dpp_mov<0x4E>(most));
+        most = vmax(most, dpp_mov<0x141>(most));
+        most = xrow_max4(vmax(most, dpp_mov<0x140>(most)));
+        spread = uni((int)most) * merge_rows <= merge_limit;
+    }
     const RangeCut cut = range_cut((unsigned)total, spread ? kMfmaSpreadUnits : a.min_units, a.max_ranges, a.range_skew);
     const int n_items = (int)cut.n_ranges * inner;
     const bool long_ranges = cut.total > (kMfmaMinUnits + 1) * cut.n_ranges;
