@@ -165,7 +165,8 @@ __global__ __launch_bounds__(256) void merge_records_kernel(AttnArgs a, int n_ro
 // TILE_LSE: also one log-sum-exp per (query row, key tile), the raw material of the round scores at the watershed
 // layer; staged per wave in LDS and written out in runs of up to 64 tiles per row.
 // INLINE_PLAN: the workgroup resolves the batch's selections itself instead of reading the planning kernel's tables.
-template <int D, bool PAGED, bool TILE_LSE, bool INLINE_PLAN>
+// MAYBE_LONG (launches that plan inline): the ranges can be long enough for non-temporal value loads.
+template <int D, bool PAGED, bool TILE_LSE, bool INLINE_PLAN, bool MAYBE_LONG>
 __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_rowblocks) {
     constexpr int KK = D / 32, DT = D / 16, kParts = D == 64 ? 3 : 2;  // contraction steps of Q.K^T, 16-channel tiles of the output,
                                                                         // bf16 numbers a probability is carried as
@@ -660,8 +661,14 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             // by latency and the hint costs (39 MB of keys and values: 16.2 -> 17.1 microseconds; 59 MB, four tiles a
             // range: 18.9 and 19.1), longer ones are bandwidth (118 MB: 30.4 -> 28.0; 0.7 GB: 135 -> 125; 2.4 GB: 419 ->
             // 378).  Whole loops, not a choice at each load: the loads of a tile would sit in separate branches.
-            if (INLINE_PLAN && !long_ranges) stream(std::false_type());
-            else stream(std::true_type());
+            // A launch whose host-known bound on the tiles rules long ranges out carries the first loop alone (one dialogue of 40
+            // rounds, a third kept, whole call: 19.0 -> 18.7 microseconds).
+            if constexpr (INLINE_PLAN && !MAYBE_LONG) {
+                stream(std::false_type());
+            } else {
+                if (INLINE_PLAN && !long_ranges) stream(std::false_type());
+                else stream(std::true_type());
+            }
 
             // ---- the four lane groups hold partial sums of the same rows -------------------------------------
             l = xrow_sum4(l);
@@ -697,17 +704,19 @@ static void launch_attn_mfma_d(const AttnArgs& a, bool paged, const MfmaDecodeSh
     const size_t smem = (tile_lse ? (size_t)4 * 16 * kLsePitch * sizeof(float) : 0) +
                         (inline_plan ? attn_mfma_inline_bytes(B, a.view.R_max) : 0);
     const dim3 g((unsigned)s.grid), blk(256);
-#define RA_ATTN_CASE(P_, L_, I_)                                                                          \
-    if (paged == P_ && tile_lse == L_ && inline_plan == I_) {                                             \
-        RA_LAUNCH_TIMED((attn_mfma_kernel<D, P_, L_, I_>), g, blk, smem, st, a, s.n_rowblocks);           \
+    const long long max_tiles = mfma_max_tiles(B, a.max_tokens, a.view.R_max, a.cur_cap);
+    const bool maybe_long = inline_plan && max_tiles > (kMfmaMinUnits + 1ll) * s.max_ranges;
+#define RA_ATTN_CASE(P_, L_, I_, M_)                                                                      \
+    if (paged == P_ && tile_lse == L_ && inline_plan == I_ && maybe_long == M_) {                         \
+        RA_LAUNCH_TIMED((attn_mfma_kernel<D, P_, L_, I_, M_>), g, blk, smem, st, a, s.n_rowblocks);       \
         return;                                                                                           \
     }
-    RA_ATTN_CASE(false, false, false) RA_ATTN_CASE(false, false, true) RA_ATTN_CASE(true, false, false)
-    RA_ATTN_CASE(true, false, true)
+#define RA_ATTN_CASES(P_, L_) RA_ATTN_CASE(P_, L_, false, false) RA_ATTN_CASE(P_, L_, true, false) RA_ATTN_CASE(P_, L_, true, true)
+    RA_ATTN_CASES(false, false) RA_ATTN_CASES(true, false)
     if constexpr (D == 128) {  // scores from the attention pass: 128 channels only
-        RA_ATTN_CASE(false, true, false) RA_ATTN_CASE(false, true, true) RA_ATTN_CASE(true, true, false)
-        RA_ATTN_CASE(true, true, true)
+        RA_ATTN_CASES(false, true) RA_ATTN_CASES(true, true)
     }
+#undef RA_ATTN_CASES
 #undef RA_ATTN_CASE
 }
 
