@@ -596,6 +596,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 // value comes out infinite, as it does from the generic kernel: no part of a weight that is not zero is
                 // zero (a remainder that is takes the smallest normal number, 2^-126), and a half tile past the segment's
                 // end, which holds the last block once more, counts as zeros.
+                // (the compiler's iterative-ilp schedule, which the tests compare with, crashes on 64 channels without the fence)
+                if (D == 64) __builtin_amdgcn_sched_barrier(0);
                 uint4 ph[kParts];
 #pragma unroll
                 for (int i = 0; i < kParts; ++i) {
