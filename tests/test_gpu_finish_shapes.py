@@ -53,20 +53,30 @@ def test_scores_and_selection(R, Hq, Hkv, q_len):
     eng.close()
 
 
-def test_scores_with_a_capacity_whose_rows_do_not_fit_lds():
-    """32 heads of 300 rounds with room declared for 40 000 tokens: the rows are read from memory instead."""
-    w = make_workload("cfg2", B=1, lens=[[9] * 300], n_relevant=2)
-    eng = Engine(w, extra_tokens=40000)
+@pytest.mark.parametrize("q_len,chunks", [(1, 3000), (5, 500)])
+def test_scores_with_a_capacity_whose_rows_do_not_fit_lds(q_len, chunks):
+    """Four heads of 16 rounds with room declared for so many chunks that a workgroup's rows do not fit the finishing kernels'
+    LDS: they are read from memory instead."""
+    R, Hq, heads_per_wave = 16, 4, 4
+    waves, limit = (4, 96 * 1024) if q_len == 1 else (8, 48 * 1024)  # one token per sequence; several, two workgroups a unit
+    assert (R + 2) * 4 + waves * R * 4 + waves * heads_per_wave * chunks * 4 > limit
+    assert q_len > 1 or Hq * chunks < 16384  # the one-token kernel, not the one that takes a head per workgroup
+    cur_len = 9 if q_len > 1 else 0
+    w = make_workload("cfg2", B=2, Hq=Hq, Hkv=1, q_len=q_len, cur_len=cur_len, lens=[[9, 600] * 8, [300] * 13], n_relevant=2)
+    room = (chunks - R - (1 if cur_len else 0)) * 256
+    eng = Engine(w, extra_tokens=room)
     view = device_view(w, 0)
     k, v, off, ln, nr, bt, off_v = view.tensors
-    roomy = ra.KVView(k, v, off, ln, nr, view.Hkv, view.d, 40000, seg_off_v=off_v)
+    roomy = ra.KVView(k, v, off, ln, nr, view.Hkv, view.d, room, seg_off_v=off_v)
     q = to_device(w.q(0), w.dtype)
-    a = ra.ra_round_scores_select(eng.ctx, q, view, scale=w.scale)
-    b = ra.ra_round_scores_select(eng.ctx, q, roomy, scale=w.scale)
+    ck = to_device(w.cur_k(0), w.dtype) if cur_len else None
+    a = ra.ra_round_scores_select(eng.ctx, q, view, cur_k=ck, scale=w.scale)
+    b = ra.ra_round_scores_select(eng.ctx, q, roomy, cur_k=ck, scale=w.scale)
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(a, b))
-    rP, _ = pipeline.scores_for_sequence(w, 0)
-    assert np.abs(a[0][0].cpu().numpy() - rP).max() < SCORE_TOL
+    for i in range(w.B):
+        rP, _ = pipeline.scores_for_sequence(w, i)
+        assert np.abs(a[0][i, :, :w.n_rounds(i)].cpu().numpy() - rP).max() < SCORE_TOL
     eng.close()
 
 

@@ -1,6 +1,6 @@
 """Questions at the sizes where their kernels change shape: row counts around the 16-row tiles and row blocks, batches that
-the launch plans itself and ones planned by a kernel of their own, launches that fill the chip (ranges that cross from
-one dialogue into the next) and ones that do not, dialogues without any key."""
+the launch plans itself and ones planned by a kernel of their own, dialogues cut by themselves and ranges that cross from
+one into the next, equal and by weight, dialogues without any key."""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +16,7 @@ STREAM_TOL, SCORE_TOL = 5e-5, 1e-5  # the bars of the other parity tests: P carr
 
 ROWS = [(9, 32, 8), (8, 64, 8), (16, 64, 8), (17, 64, 8), (48, 32, 8), (65, 32, 8), (50, 24, 8), (30, 32, 2)]
 BATCHES = {
-    "long": dict(lens=[[900, 3, 700, 250], [17, 640, 33], [1000, 900, 800, 31, 5]]),      # fills the chip at 16 items a range
+    "long": dict(lens=[[900, 3, 700, 250], [17, 640, 33], [1000, 900, 800, 31, 5]]),      # about 170 tiles: equal ranges, or cut apart
     "short_paged": dict(lens=[[5, 16, 17, 0, 33], [64, 3], [0, 0]], block_size=16),
     "lists_of_1024": dict(B=64, R=16, length=("uniform", 0, 12)),                         # the most that is planned inline
     "planned_apart": dict(B=30, R=40, length=("uniform", 0, 9), block_size=16),
@@ -66,24 +66,30 @@ def test_question(batch, q_len, Hq, Hkv):
     eng.close()
 
 
-def test_one_long_dialogue_between_two_short_ones():
-    """21, 320 and 21 key tiles in 19 ranges (26 items a range on 256 compute units): cut by the weights of the two classes of
-    workgroups the long dialogue would meet 19 ranges, and a row's partial results have room for 18."""
-    lens = [[17 * 32], [256] * 39 + [128], [17 * 32]]
-    w = make_workload("cfg3", B=3, Hq=32, Hkv=2, q_len=100, cur_len=100, n_relevant=1, lens=lens)
+@pytest.mark.parametrize("q_len,Hkv,tiles", [(100, 2, (17, 316, 17)), (128, 8, (60, 330, 60))])
+def test_one_long_dialogue_between_two_short_ones(q_len, Hkv, tiles):
+    """More than eight key tiles for every range that 256 compute units take.  100 tokens, 2 KV heads: 19 ranges, 26 items each;
+    cut by the weights of the two classes of workgroups the long dialogue would meet 19 of them, and a row's partial
+    results have room for 18.  128 tokens, 8 KV heads: 16 ranges in the attention kernel and 48 in the score kernel, by
+    weight."""
+    lens = [[32 * n] if n < 100 else [256] * (n // 8) + [32 * (n % 8)] * (n % 8 > 0) for n in tiles]
+    w = make_workload("cfg3", B=3, Hq=32, Hkv=Hkv, q_len=q_len, cur_len=q_len, n_relevant=1, lens=lens)
     eng = Engine(w)
     v0, v1 = device_view(w, 0), device_view(w, 1)
     q0, q1, ck0, cv0, ck1, cv1 = (to_device(x, "bf16") for x in (w.q(0), w.q(1), w.cur_k(0), w.cur_v(0), w.cur_k(1), w.cur_v(1)))
     out, lse = ra.ra_round_sparse_attn_prefill(eng.ctx, q1, v1, None, None, ck1, cv1, scale=w.scale)
     again, lse2 = ra.ra_round_sparse_attn_prefill(eng.ctx, q1, v1, None, None, ck1, cv1, scale=w.scale)
     out2, _, _, S2 = ra.ra_watershed_attn_prefill(eng.ctx, q0, v0, ck0, cv0, scale=w.scale)
+    _, S = ra.ra_round_scores(eng.ctx, q0, v0, ck0, scale=w.scale)
     torch.cuda.synchronize()
     assert torch.equal(out, again) and torch.equal(lse, lse2)
     for b in range(w.B):
         rounds = list(range(w.n_rounds(b)))
         for layer, o in ((1, out), (0, out2)):
             assert ora.row_error(o[b].cpu().numpy(), pipeline.attention_for_sequence(w, b, layer, rounds)[0]) < STREAM_TOL, (layer, b)
-        assert np.abs(S2[b, :len(rounds)].cpu().numpy() - pipeline.scores_for_sequence(w, b)[1]).max() < SCORE_TOL, b
+        rS = pipeline.scores_for_sequence(w, b)[1]
+        for got in (S, S2):
+            assert np.abs(got[b, :len(rounds)].cpu().numpy() - rS).max() < SCORE_TOL, b
     eng.close()
 
 
