@@ -238,6 +238,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
         const char *tile_k = nullptr, *tile_v = nullptr;
         long long seg_tab = 0;                          // paged history: first block-table slot
         unsigned kstride = 256;                         // bytes from one token's keys to the next
+        BlockWindow blocks;
+        if constexpr (PAGED) blocks.open(vw, b);
         // Direct loads: 16 bytes per lane, lane L's piece landing at (destination + 16 L).  Keys: the tile's LDS
         // image is row-major, 256 bytes per row, row rho = 16 h + r being row r of the operand of half h, i.e. token
         // 8 (r / 4) + 4 h + r % 4 of the tile (which makes a lane's eight probabilities eight consecutive tokens),
@@ -293,10 +295,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
             const unsigned kd = buf_lds + 8 * wave * 256, vd = buf_lds + 8192 + 2 * wave * 1024;
             if (!seg_cur && PAGED) {
                 const int blk0 = tok0 >> 4, blk1 = min(blk0 + 1, (seg_len - 1) >> 4);
-                const long long last = vw.max_blocks - 1;
-                const long long s0 = min(max(seg_tab + blk0, 0ll), last), s1 = min(max(seg_tab + blk1, 0ll), last);
-                const int p0 = max(uni(vw.block_table[(size_t)b * vw.max_blocks + s0]), 0);
-                const int p1 = max(uni(vw.block_table[(size_t)b * vw.max_blocks + s1]), 0);
+                const int p0 = blocks.block(seg_tab + blk0), p1 = blocks.block(seg_tab + blk1);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const bool upper = k_tok[j] >> 4;

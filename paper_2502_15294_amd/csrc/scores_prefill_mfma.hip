@@ -211,6 +211,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
         const char *seg_k = nullptr, *tile_k = nullptr;  // contiguous history / current round
         long long seg_tab = 0;                           // paged history: first block-table slot
         unsigned kstride = 256;                          // bytes from one token's keys to the next
+        BlockWindow blocks;
+        if constexpr (PAGED) blocks.open(vw, b);
         // This wave fills rows 8 wave .. + 7 of the tile's LDS image (row = token of the tile, 256 bytes) with two
         // loads of four whole rows each, 16 lanes per row; lane L's 16 bytes land at position L % 16 of its row,
         // where chunk (L % 16 - row) mod 16 belongs.
@@ -245,8 +247,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
             if (!seg_cur && PAGED) {
                 const int tok0 = seg_len - rows_left;
                 const int blk = min((tok0 >> 4) + (wave >> 1), (seg_len - 1) >> 4);
-                const long long si = min(max(seg_tab + blk, 0ll), (long long)vw.max_blocks - 1);
-                const int pb = max(uni(vw.block_table[(size_t)b * vw.max_blocks + si]), 0);
+                const int pb = blocks.block(seg_tab + blk);
                 const char* kb = reinterpret_cast<const char*>(uni64(reinterpret_cast<long long>(kbase + ((size_t)pb * Hkv + g) * 4096)));
                 const int last_row = seg_len - 1 - blk * 16;
                 const int r0 = min(8 * (wave & 1) + q4, last_row), r1 = min(8 * (wave & 1) + 4 + q4, last_row);
