@@ -4,7 +4,7 @@ Every function below has the name of the C entry point it forwards to (see
 include/round_attention.h) and does nothing but turn torch tensors into device pointers,
 fill the C structs and check the returned status.  PyTorch supplies device memory and
 streams; all computation happens in the library's kernels.  There is no fallback: if the
-shared library has not been built, importing `lib()` users fail with an ImportError.
+shared library or the extension module has not been built, their users fail with an ImportError.
 """
 from __future__ import annotations
 
@@ -140,6 +140,26 @@ def lib() -> C.CDLL:
     return _lib
 
 
+# The compute calls go through a small extension module (csrc/binding.cpp), because small steps are bound by what the host
+# does per call: a step of one fp32 sequence of 8 short rounds, two calls and six new outputs, 24.7 microseconds through
+# ctypes and torch.empty, 19.9 this way.
+_native = None
+
+
+def _load_native():
+    global _native
+    L = lib()
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise ImportError(f"{_HERE}/_binding.so cannot be loaded ({e}): build it with `python -m paper_2502_15294_amd.build`") from e
+    _binding.setup(_check, *[C.cast(getattr(L, name), C.c_void_p).value for name in (
+        "ra_round_scores", "ra_round_scores_select", "ra_round_scores_accumulate", "ra_selection_coverage",
+        "ra_round_sparse_attn_decode", "ra_watershed_attn_decode", "ra_round_sparse_attn_prefill", "ra_watershed_attn_prefill")])
+    _native = _binding
+    return _native
+
+
 def _check(rc: int) -> None:
     if rc != 0:
         raise RaError(rc, lib().ra_last_error().decode())
@@ -244,17 +264,7 @@ def ra_profile_last_ms(ctx) -> float:
 def ra_round_scores(ctx, q: torch.Tensor, view: KVView, cur_k: Optional[torch.Tensor] = None,
                     scale: Optional[float] = None, scores_head: Optional[torch.Tensor] = None,
                     scores: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
-    B, q_len, Hq, d = q.shape
-    if scale is None:
-        scale = d ** -0.5
-    if scores_head is None:
-        scores_head = torch.empty((B, Hq, view.R_max), dtype=torch.float32, device=q.device)
-    if scores is None:
-        scores = torch.empty((B, view.R_max), dtype=torch.float32, device=q.device)
-    cur_len = 0 if cur_k is None else cur_k.shape[1]
-    _check(lib().ra_round_scores(ctx, _stream(stream), _ptr(q), q_len, Hq, C.byref(view.c), _ptr(cur_k), cur_len,
-                                 scale, _ptr(scores_head), _ptr(scores)))
-    return scores_head, scores
+    return (_native or _load_native()).scores(ctx, _stream(stream), q, view, cur_k, scale, scores_head, scores)
 
 
 def ra_round_scores_select(ctx, q: torch.Tensor, view: KVView, params: Optional["ra_select_params"] = None,
@@ -263,24 +273,10 @@ def ra_round_scores_select(ctx, q: torch.Tensor, view: KVView, params: Optional[
                            sel_idx: Optional[torch.Tensor] = None, n_sel: Optional[torch.Tensor] = None, stream=None
                            ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor, torch.Tensor]:
     """Returns (scores_head, scores, sel_idx, n_sel)."""
-    B, q_len, Hq, d = q.shape
-    if scale is None:
-        scale = d ** -0.5
     if params is None:
         params = make_select_params()
-    if scores_head is None:
-        scores_head = torch.empty((B, Hq, view.R_max), dtype=torch.float32, device=q.device)
-    if scores is None:
-        scores = torch.empty((B, view.R_max), dtype=torch.float32, device=q.device)
-    if sel_idx is None:
-        sel_idx = torch.empty((B, view.R_max), dtype=torch.int32, device=q.device)
-    if n_sel is None:
-        n_sel = torch.empty((B,), dtype=torch.int32, device=q.device)
-    cur_len = 0 if cur_k is None else cur_k.shape[1]
-    _check(lib().ra_round_scores_select(ctx, _stream(stream), _ptr(q), q_len, Hq, C.byref(view.c), _ptr(cur_k), cur_len,
-                                        scale, C.byref(params), _ptr(scores_head), _ptr(scores), _ptr(sel_idx),
-                                        _ptr(n_sel)))
-    return scores_head, scores, sel_idx, n_sel
+    return (_native or _load_native()).scores_select(ctx, _stream(stream), q, view, params, cur_k, scale, scores_head, scores,
+                                                     sel_idx, n_sel)
 
 
 def ra_round_scores_accumulate(ctx, q: torch.Tensor, view: KVView, acc: torch.Tensor,
@@ -288,18 +284,7 @@ def ra_round_scores_accumulate(ctx, q: torch.Tensor, view: KVView, acc: torch.Te
                                scores_head: Optional[torch.Tensor] = None, scores: Optional[torch.Tensor] = None,
                                stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """acc: float32 [B, Hq, R_max], updated in place; returns the normalised running totals."""
-    B, q_len, Hq, d = q.shape
-    assert acc.dtype == torch.float32 and tuple(acc.shape) == (B, Hq, view.R_max)
-    if scale is None:
-        scale = d ** -0.5
-    if scores_head is None:
-        scores_head = torch.empty((B, Hq, view.R_max), dtype=torch.float32, device=q.device)
-    if scores is None:
-        scores = torch.empty((B, view.R_max), dtype=torch.float32, device=q.device)
-    cur_len = 0 if cur_k is None else cur_k.shape[1]
-    _check(lib().ra_round_scores_accumulate(ctx, _stream(stream), _ptr(q), q_len, Hq, C.byref(view.c), _ptr(cur_k),
-                                            cur_len, scale, _ptr(acc), _ptr(scores_head), _ptr(scores)))
-    return scores_head, scores
+    return (_native or _load_native()).scores_accumulate(ctx, _stream(stream), q, view, acc, cur_k, scale, scores_head, scores)
 
 
 def ra_layer_divergence(ctx, p: torch.Tensor, n_rounds: torch.Tensor, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
@@ -315,11 +300,7 @@ def ra_layer_divergence(ctx, p: torch.Tensor, n_rounds: torch.Tensor, stream=Non
 
 def ra_selection_coverage(ctx, scores: torch.Tensor, sel_idx: torch.Tensor, n_sel: torch.Tensor, stream=None
                           ) -> torch.Tensor:
-    B, R_max = scores.shape
-    cov = torch.empty((B,), dtype=torch.float32, device=scores.device)
-    _check(lib().ra_selection_coverage(ctx, _stream(stream), _ptr(scores), _ptr(sel_idx), _ptr(n_sel), B, R_max,
-                                       _ptr(cov)))
-    return cov
+    return (_native or _load_native()).coverage(ctx, _stream(stream), scores, sel_idx, n_sel)
 
 
 def make_select_params(strategy: int = RA_SEL_ADAPTIVE, lam: float = 1.0, fraction: float = 0.10,
@@ -350,18 +331,8 @@ def ra_round_sparse_attn_decode(ctx, q: torch.Tensor, view: KVView, sel_idx: Opt
                                 cur_v: Optional[torch.Tensor] = None, cur_len: Optional[torch.Tensor] = None,
                                 scale: Optional[float] = None, out: Optional[torch.Tensor] = None,
                                 lse: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
-    B, Hq, d = q.shape
-    if scale is None:
-        scale = d ** -0.5
-    if out is None:
-        out = torch.empty((B, Hq, d), dtype=torch.float32, device=q.device)
-    if lse is None:
-        lse = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    cur_cap = 0 if cur_k is None else cur_k.shape[1]
-    _check(lib().ra_round_sparse_attn_decode(ctx, _stream(stream), _ptr(q), Hq, C.byref(view.c), _ptr(sel_idx),
-                                             _ptr(n_sel), _ptr(cur_k), _ptr(cur_v), _ptr(cur_len), cur_cap, scale,
-                                             _ptr(out), _ptr(lse)))
-    return out, lse
+    return (_native or _load_native()).decode(ctx, _stream(stream), q, view, sel_idx, n_sel, cur_k, cur_v, cur_len, scale, out,
+                                              lse)
 
 
 def ra_round_sparse_attn_decode_noalloc(ctx, q: torch.Tensor, view: KVView, out: torch.Tensor, lse: Optional[torch.Tensor],
@@ -386,22 +357,8 @@ def ra_watershed_attn_decode(ctx, q: torch.Tensor, view: KVView, cur_k: Optional
                              scores: Optional[torch.Tensor] = None, stream=None
                              ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor, torch.Tensor]:
     """Returns (out, lse, scores_head, scores)."""
-    B, Hq, d = q.shape
-    if scale is None:
-        scale = d ** -0.5
-    if out is None:
-        out = torch.empty((B, Hq, d), dtype=torch.float32, device=q.device)
-    if lse is None:
-        lse = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    if scores_head is None:
-        scores_head = torch.empty((B, Hq, view.R_max), dtype=torch.float32, device=q.device)
-    if scores is None:
-        scores = torch.empty((B, view.R_max), dtype=torch.float32, device=q.device)
-    cur_cap = 0 if cur_k is None else cur_k.shape[1]
-    _check(lib().ra_watershed_attn_decode(ctx, _stream(stream), _ptr(q), Hq, C.byref(view.c), _ptr(cur_k), _ptr(cur_v),
-                                          _ptr(cur_len), cur_cap, scale, _ptr(out), _ptr(lse), _ptr(scores_head),
-                                          _ptr(scores)))
-    return out, lse, scores_head, scores
+    return (_native or _load_native()).watershed_decode(ctx, _stream(stream), q, view, cur_k, cur_v, cur_len, scale, out, lse,
+                                                        scores_head, scores)
 
 
 def ra_round_sparse_attn_prefill(ctx, q: torch.Tensor, view: KVView, sel_idx: Optional[torch.Tensor] = None,
@@ -409,18 +366,7 @@ def ra_round_sparse_attn_prefill(ctx, q: torch.Tensor, view: KVView, sel_idx: Op
                                  cur_v: Optional[torch.Tensor] = None, scale: Optional[float] = None,
                                  out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None, stream=None
                                  ) -> Tuple[torch.Tensor, torch.Tensor]:
-    B, q_len, Hq, d = q.shape
-    if scale is None:
-        scale = d ** -0.5
-    if out is None:
-        out = torch.empty((B, q_len, Hq, d), dtype=torch.float32, device=q.device)
-    if lse is None:
-        lse = torch.empty((B, q_len, Hq), dtype=torch.float32, device=q.device)
-    cur_len = 0 if cur_k is None else cur_k.shape[1]
-    _check(lib().ra_round_sparse_attn_prefill(ctx, _stream(stream), _ptr(q), q_len, Hq, C.byref(view.c),
-                                              _ptr(sel_idx), _ptr(n_sel), _ptr(cur_k), _ptr(cur_v), cur_len, scale,
-                                              _ptr(out), _ptr(lse)))
-    return out, lse
+    return (_native or _load_native()).prefill(ctx, _stream(stream), q, view, sel_idx, n_sel, cur_k, cur_v, scale, out, lse)
 
 
 def ra_watershed_attn_prefill(ctx, q: torch.Tensor, view: KVView, cur_k: Optional[torch.Tensor] = None,
@@ -429,22 +375,8 @@ def ra_watershed_attn_prefill(ctx, q: torch.Tensor, view: KVView, cur_k: Optiona
                               scores_head: Optional[torch.Tensor] = None, scores: Optional[torch.Tensor] = None,
                               stream=None) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor, torch.Tensor]:
     """Returns (out, lse, scores_head, scores)."""
-    B, q_len, Hq, d = q.shape
-    if scale is None:
-        scale = d ** -0.5
-    if out is None:
-        out = torch.empty((B, q_len, Hq, d), dtype=torch.float32, device=q.device)
-    if lse is None:
-        lse = torch.empty((B, q_len, Hq), dtype=torch.float32, device=q.device)
-    if scores_head is None:
-        scores_head = torch.empty((B, Hq, view.R_max), dtype=torch.float32, device=q.device)
-    if scores is None:
-        scores = torch.empty((B, view.R_max), dtype=torch.float32, device=q.device)
-    cur_len = 0 if cur_k is None else cur_k.shape[1]
-    _check(lib().ra_watershed_attn_prefill(ctx, _stream(stream), _ptr(q), q_len, Hq, C.byref(view.c), _ptr(cur_k),
-                                           _ptr(cur_v), cur_len, scale, _ptr(out), _ptr(lse), _ptr(scores_head),
-                                           _ptr(scores)))
-    return out, lse, scores_head, scores
+    return (_native or _load_native()).watershed_prefill(ctx, _stream(stream), q, view, cur_k, cur_v, scale, out, lse,
+                                                         scores_head, scores)
 
 
 # ---- round-indexed KV store ----------------------------------------------------------------------

@@ -17,6 +17,8 @@ LIB = os.path.join(HERE, "libround_attention.so")
 EXAMPLE_SRC = os.path.join(HERE, "examples", "decode_step.c")
 EXAMPLE = os.path.join(HERE, "ra_decode_step")  # plain C program driving the library through the C boundary alone
 SOURCES = ["context.hip", "decode.hip", "attn_mfma.hip", "attn_prefill_mfma.hip", "scores.hip", "scores_mfma.hip", "scores_prefill_mfma.hip", "select.hip", "prefill.hip", "kv_store.hip", "monitor.hip"]
+BINDING_SRC = os.path.join(CSRC, "binding.cpp")
+BINDING = os.path.join(HERE, "_binding.so")  # the compute calls' Python side (host code only)
 # packed-fp32 instruction selection is switched off for every device translation unit
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -43,17 +45,38 @@ def build(force: bool = True, jobs: int = 6) -> str:
     """Compile every translation unit and link the shared library.  Always recompiles when
     `force` is set; otherwise only when a source or header is newer than the library."""
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(ROOT, "include", "round_attention.h")]
-    if not force and os.path.exists(LIB) and all(os.path.getmtime(d) <= os.path.getmtime(LIB) for d in deps):
+    if not force and all(os.path.exists(out) and all(os.path.getmtime(d) <= os.path.getmtime(out) for d in deps)
+                         for out in (LIB, BINDING)):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        binding = ex.submit(build_binding)
         objs = list(ex.map(_compile, SOURCES))
+        binding.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr[-4000:]}")
     build_example()
     return LIB
+
+
+def build_binding() -> str:
+    """The extension module, compiled against torch's headers by the host C++ compiler."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    include = [arg for d in [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+               for arg in ("-I", d)]
+    libs = [arg for d in cpp_extension.library_paths() for arg in ("-L", d)]
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *include, BINDING_SRC, "-o", BINDING, *libs,
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"extension module failed to build:\n{r.stderr[-4000:]}")
+    return BINDING
 
 
 def build_example() -> str:

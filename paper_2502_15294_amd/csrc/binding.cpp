@@ -1,0 +1,366 @@
+// The compute entry points as Python calls them: torch tensors to device pointers, outputs that the caller did not pass
+// allocated, the status checked.  No computation.
+//
+// A step of a small model is bound by the host: two calls whose four kernels take less time than it takes to issue them.
+// Through ctypes the step's two calls cost 23.7 microseconds (one sequence, 4 heads, 8 rounds): 11.0 in the library,
+// nearly all of it the launches, 8.6 for the six output tensors (torch.empty from Python takes 1.4 each) and 4 of argument
+// marshalling.  Here an output costs what the allocator costs and the arguments are read directly: 24.7 -> 19.9 microseconds
+// a pass on one GPU.
+//
+// The library is not linked: its functions arrive as addresses (setup), from whichever build of it was loaded.
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <ATen/ATen.h>
+#include <cmath>
+#include <cstring>
+
+#include "round_attention.h"
+
+namespace {
+
+struct Functions {
+    decltype(&ra_round_scores) scores;
+    decltype(&ra_round_scores_select) scores_select;
+    decltype(&ra_round_scores_accumulate) scores_accumulate;
+    decltype(&ra_selection_coverage) coverage;
+    decltype(&ra_round_sparse_attn_decode) decode;
+    decltype(&ra_watershed_attn_decode) watershed_decode;
+    decltype(&ra_round_sparse_attn_prefill) prefill;
+    decltype(&ra_watershed_attn_prefill) watershed_prefill;
+} fn;
+PyObject* on_error = nullptr;  // called with a status that is not RA_OK; raises
+PyObject* name_c = nullptr;    // "c"
+
+// A Python error is set: leave the entry point.
+struct PythonError {};
+
+template <typename T>
+T* address_of(PyObject* o, const char* what) {  // a ctypes object's memory; None is a null pointer
+    if (o == Py_None) return nullptr;
+    Py_buffer buf;
+    if (PyObject_GetBuffer(o, &buf, PyBUF_SIMPLE) != 0) throw PythonError();
+    T* p = static_cast<T*>(buf.buf);
+    const bool fits = buf.len >= (Py_ssize_t)sizeof(T);
+    PyBuffer_Release(&buf);  // the object itself is kept by the caller's reference
+    if (!fits) {
+        PyErr_Format(PyExc_TypeError, "%s: not the structure that the library takes", what);
+        throw PythonError();
+    }
+    return p;
+}
+
+ra_ctx* context(PyObject* o) {
+    if (PyLong_Check(o)) {
+        void* p = PyLong_AsVoidPtr(o);
+        if (PyErr_Occurred()) throw PythonError();
+        return static_cast<ra_ctx*>(p);
+    }
+    void** p = address_of<void*>(o, "ctx");
+    return p ? static_cast<ra_ctx*>(*p) : nullptr;
+}
+
+void* stream_handle(PyObject* o) {
+    if (o == Py_None) return nullptr;
+    void* p = PyLong_AsVoidPtr(o);
+    if (PyErr_Occurred()) throw PythonError();
+    return p;
+}
+
+// The C view of a KVView; holds a reference to the structure while the call lasts.
+struct View {
+    PyObject* c;
+    const ra_kv_view* p;
+    explicit View(PyObject* view) : c(PyObject_GetAttr(view, name_c)), p(nullptr) {
+        if (!c) throw PythonError();
+        try {
+            p = address_of<ra_kv_view>(c, "view");
+            if (!p) {
+                PyErr_SetString(PyExc_TypeError, "view: not a KVView");
+                throw PythonError();
+            }
+        } catch (...) {
+            Py_DECREF(c);
+            throw;
+        }
+    }
+    View(const View&) = delete;
+    View& operator=(const View&) = delete;
+    ~View() { Py_DECREF(c); }
+    const ra_kv_view* operator->() const { return p; }
+};
+
+const at::Tensor* tensor_or_null(PyObject* o) {
+    if (o == Py_None) return nullptr;
+    if (!THPVariable_Check(o)) {
+        PyErr_Format(PyExc_TypeError, "expected a torch.Tensor, not %s", Py_TYPE(o)->tp_name);
+        throw PythonError();
+    }
+    return &THPVariable_Unpack(o);
+}
+const at::Tensor& tensor(PyObject* o) {
+    const at::Tensor* t = tensor_or_null(o);
+    if (!t) {
+        PyErr_SetString(PyExc_AttributeError, "expected a torch.Tensor, not None");
+        throw PythonError();
+    }
+    return *t;
+}
+void* data(const at::Tensor& t) {
+    if (!t.is_contiguous()) {
+        PyErr_SetString(PyExc_AssertionError, "tensors handed to the library must be contiguous");
+        throw PythonError();
+    }
+    return t.data_ptr();
+}
+template <typename T = void>
+T* data(PyObject* o) {
+    const at::Tensor* t = tensor_or_null(o);
+    return t ? static_cast<T*>(data(*t)) : nullptr;
+}
+void want_dims(const at::Tensor& t, int64_t dims) {
+    if (t.dim() == dims) return;
+    PyErr_Format(PyExc_ValueError, "a tensor of %d dimensions is needed here, this one has %d", (int)dims, (int)t.dim());
+    throw PythonError();
+}
+int second_size(PyObject* o) {  // tokens of the current round; 0 without one
+    const at::Tensor* t = tensor_or_null(o);
+    return t ? (int)t->size(1) : 0;
+}
+float scale_of(PyObject* o, int64_t d) {
+    if (o == Py_None) return (float)std::pow((double)d, -0.5);
+    const double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred()) throw PythonError();
+    return (float)v;
+}
+
+// An output: the caller's tensor, or a new one.
+struct Output {
+    PyObject* o;
+    Output(PyObject* given, at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) : o(given) {
+        if (given != Py_None) Py_INCREF(given);
+        else o = THPVariable_Wrap(at::empty(shape, at::TensorOptions().dtype(type).device(like.device())));
+        if (!o) throw PythonError();
+    }
+    Output(const Output&) = delete;
+    Output& operator=(const Output&) = delete;
+    ~Output() { Py_XDECREF(o); }
+    template <typename T>
+    T* ptr() const { return data<T>(o); }
+};
+
+template <typename... Outputs>
+PyObject* results(const Outputs&... outs) {
+    return PyTuple_Pack((Py_ssize_t)sizeof...(Outputs), outs.o...);
+}
+
+// The library call with the interpreter released, as ctypes does it; a status that is not RA_OK is raised.
+template <typename Call>
+void checked(Call call) {
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = call();
+    Py_END_ALLOW_THREADS
+    if (rc == RA_OK) return;
+    PyObject* r = PyObject_CallFunction(on_error, "i", rc);
+    if (r) {
+        Py_DECREF(r);
+        PyErr_SetString(PyExc_SystemError, "the status handler did not raise");
+    }
+    throw PythonError();
+}
+
+constexpr at::ScalarType kF32 = at::kFloat, kI32 = at::kInt;
+
+// (ctx, stream, q, view, cur_k, scale, scores_head, scores)
+PyObject* scores(PyObject* const* a) {
+    const at::Tensor& q = tensor(a[2]);
+    want_dims(q, 4);
+    const View view(a[3]);
+    const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), R = view->R_max;
+    const Output ph(a[6], {B, Hq, R}, kF32, q), p(a[7], {B, R}, kF32, q);
+    ra_ctx* ctx = context(a[0]);
+    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[4]);
+    float *php = ph.ptr<float>(), *pp = p.ptr<float>();
+    const int cur = second_size(a[4]);
+    const float scale = scale_of(a[5], q.size(3));
+    checked([&] { return fn.scores(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, php, pp); });
+    return results(ph, p);
+}
+
+// (ctx, stream, q, view, params, cur_k, scale, scores_head, scores, sel_idx, n_sel)
+PyObject* scores_select(PyObject* const* a) {
+    const at::Tensor& q = tensor(a[2]);
+    want_dims(q, 4);
+    const View view(a[3]);
+    const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), R = view->R_max;
+    const Output ph(a[7], {B, Hq, R}, kF32, q), p(a[8], {B, R}, kF32, q), sel(a[9], {B, R}, kI32, q), n(a[10], {B}, kI32, q);
+    ra_ctx* ctx = context(a[0]);
+    const ra_select_params* params = address_of<ra_select_params>(a[4], "params");
+    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[5]);
+    float *php = ph.ptr<float>(), *pp = p.ptr<float>();
+    int32_t *sp = sel.ptr<int32_t>(), *np = n.ptr<int32_t>();
+    const int cur = second_size(a[5]);
+    const float scale = scale_of(a[6], q.size(3));
+    checked([&] { return fn.scores_select(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, params, php, pp, sp, np); });
+    return results(ph, p, sel, n);
+}
+
+// (ctx, stream, q, view, acc, cur_k, scale, scores_head, scores)
+PyObject* scores_accumulate(PyObject* const* a) {
+    const at::Tensor& q = tensor(a[2]);
+    want_dims(q, 4);
+    const View view(a[3]);
+    const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), R = view->R_max;
+    const at::Tensor& acc = tensor(a[4]);
+    if (acc.scalar_type() != kF32 || acc.sizes() != at::IntArrayRef({B, Hq, R})) {
+        PyErr_SetString(PyExc_AssertionError, "acc must be float32 [B, Hq, R_max]");
+        throw PythonError();
+    }
+    const Output ph(a[7], {B, Hq, R}, kF32, q), p(a[8], {B, R}, kF32, q);
+    ra_ctx* ctx = context(a[0]);
+    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[5]);
+    float *ap = static_cast<float*>(data(acc)), *php = ph.ptr<float>(), *pp = p.ptr<float>();
+    const int cur = second_size(a[5]);
+    const float scale = scale_of(a[6], q.size(3));
+    checked([&] { return fn.scores_accumulate(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, ap, php, pp); });
+    return results(ph, p);
+}
+
+// (ctx, stream, scores, sel_idx, n_sel)
+PyObject* coverage(PyObject* const* a) {
+    const at::Tensor& s = tensor(a[2]);
+    want_dims(s, 2);
+    const int64_t B = s.size(0), R = s.size(1);
+    Output cov(Py_None, {B}, kF32, s);
+    ra_ctx* ctx = context(a[0]);
+    void* st = stream_handle(a[1]);
+    const float* sp = static_cast<float*>(data(s));
+    const int32_t *sel = data<int32_t>(a[3]), *n = data<int32_t>(a[4]);
+    float* cp = cov.ptr<float>();
+    checked([&] { return fn.coverage(ctx, st, sp, sel, n, (int)B, (int)R, cp); });
+    PyObject* r = cov.o;
+    cov.o = nullptr;
+    return r;
+}
+
+// (ctx, stream, q, view, sel_idx, n_sel, cur_k, cur_v, cur_len, scale, out, lse)
+PyObject* decode(PyObject* const* a) {
+    const at::Tensor& q = tensor(a[2]);
+    want_dims(q, 3);
+    const View view(a[3]);
+    const int64_t B = q.size(0), Hq = q.size(1), d = q.size(2);
+    const Output out(a[10], {B, Hq, d}, kF32, q), lse(a[11], {B, Hq}, kF32, q);
+    ra_ctx* ctx = context(a[0]);
+    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[6]), *cv = data(a[7]);
+    const int32_t *sel = data<int32_t>(a[4]), *n = data<int32_t>(a[5]), *cl = data<int32_t>(a[8]);
+    float *op = out.ptr<float>(), *lp = lse.ptr<float>();
+    const int cap = second_size(a[6]);
+    const float scale = scale_of(a[9], d);
+    checked([&] { return fn.decode(ctx, st, qp, (int)Hq, view.p, sel, n, ck, cv, cl, cap, scale, op, lp); });
+    return results(out, lse);
+}
+
+// (ctx, stream, q, view, cur_k, cur_v, cur_len, scale, out, lse, scores_head, scores)
+PyObject* watershed_decode(PyObject* const* a) {
+    const at::Tensor& q = tensor(a[2]);
+    want_dims(q, 3);
+    const View view(a[3]);
+    const int64_t B = q.size(0), Hq = q.size(1), d = q.size(2), R = view->R_max;
+    const Output out(a[8], {B, Hq, d}, kF32, q), lse(a[9], {B, Hq}, kF32, q);
+    const Output ph(a[10], {B, Hq, R}, kF32, q), p(a[11], {B, R}, kF32, q);
+    ra_ctx* ctx = context(a[0]);
+    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[4]), *cv = data(a[5]);
+    const int32_t* cl = data<int32_t>(a[6]);
+    float *op = out.ptr<float>(), *lp = lse.ptr<float>(), *php = ph.ptr<float>(), *pp = p.ptr<float>();
+    const int cap = second_size(a[4]);
+    const float scale = scale_of(a[7], d);
+    checked([&] { return fn.watershed_decode(ctx, st, qp, (int)Hq, view.p, ck, cv, cl, cap, scale, op, lp, php, pp); });
+    return results(out, lse, ph, p);
+}
+
+// (ctx, stream, q, view, sel_idx, n_sel, cur_k, cur_v, scale, out, lse)
+PyObject* prefill(PyObject* const* a) {
+    const at::Tensor& q = tensor(a[2]);
+    want_dims(q, 4);
+    const View view(a[3]);
+    const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), d = q.size(3);
+    const Output out(a[9], {B, q_len, Hq, d}, kF32, q), lse(a[10], {B, q_len, Hq}, kF32, q);
+    ra_ctx* ctx = context(a[0]);
+    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[6]), *cv = data(a[7]);
+    const int32_t *sel = data<int32_t>(a[4]), *n = data<int32_t>(a[5]);
+    float *op = out.ptr<float>(), *lp = lse.ptr<float>();
+    const int cur = second_size(a[6]);
+    const float scale = scale_of(a[8], d);
+    checked([&] { return fn.prefill(ctx, st, qp, (int)q_len, (int)Hq, view.p, sel, n, ck, cv, cur, scale, op, lp); });
+    return results(out, lse);
+}
+
+// (ctx, stream, q, view, cur_k, cur_v, scale, out, lse, scores_head, scores)
+PyObject* watershed_prefill(PyObject* const* a) {
+    const at::Tensor& q = tensor(a[2]);
+    want_dims(q, 4);
+    const View view(a[3]);
+    const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), d = q.size(3), R = view->R_max;
+    const Output out(a[7], {B, q_len, Hq, d}, kF32, q), lse(a[8], {B, q_len, Hq}, kF32, q);
+    const Output ph(a[9], {B, Hq, R}, kF32, q), p(a[10], {B, R}, kF32, q);
+    ra_ctx* ctx = context(a[0]);
+    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[4]), *cv = data(a[5]);
+    float *op = out.ptr<float>(), *lp = lse.ptr<float>(), *php = ph.ptr<float>(), *pp = p.ptr<float>();
+    const int cur = second_size(a[4]);
+    const float scale = scale_of(a[6], d);
+    checked([&] { return fn.watershed_prefill(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cv, cur, scale, op, lp, php, pp); });
+    return results(out, lse, ph, p);
+}
+
+// The Python function: argument count, C++ exceptions (an allocation that fails among them) turned into Python's.
+template <PyObject* (*F)(PyObject* const*), Py_ssize_t N>
+PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+    HANDLE_TH_ERRORS
+    if (nargs != N) {
+        PyErr_Format(PyExc_TypeError, "%zd arguments expected, %zd given", N, nargs);
+        return nullptr;
+    }
+    try {
+        return F(args);
+    } catch (const PythonError&) {
+        return nullptr;
+    }
+    END_HANDLE_TH_ERRORS
+}
+
+// setup(status handler, addresses in the order of Functions)
+PyObject* setup(PyObject* const* a) {
+    void* p[sizeof(Functions) / sizeof(void*)];
+    for (size_t i = 0; i < sizeof(p) / sizeof(p[0]); ++i) {
+        p[i] = PyLong_AsVoidPtr(a[1 + i]);
+        if (PyErr_Occurred()) throw PythonError();
+    }
+    std::memcpy(&fn, p, sizeof(fn));
+    Py_INCREF(a[0]);
+    Py_XDECREF(on_error);
+    on_error = a[0];
+    Py_RETURN_NONE;
+}
+
+#define RA_METHOD(NAME, N) {#NAME, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(entry<NAME, N>)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {
+    RA_METHOD(setup, 9),
+    RA_METHOD(scores, 8),
+    RA_METHOD(scores_select, 11),
+    RA_METHOD(scores_accumulate, 9),
+    RA_METHOD(coverage, 5),
+    RA_METHOD(decode, 12),
+    RA_METHOD(watershed_decode, 12),
+    RA_METHOD(prefill, 11),
+    RA_METHOD(watershed_prefill, 11),
+    {nullptr, nullptr, 0, nullptr},
+};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__binding() {
+    name_c = PyUnicode_InternFromString("c");
+    return name_c ? PyModule_Create(&module) : nullptr;
+}
