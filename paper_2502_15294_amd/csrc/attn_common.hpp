@@ -98,6 +98,7 @@ inline bool attn_mfma_plans_inline(int B, int R_max) {
 // Launch shape and scratch of that kernel.  `max_tiles` bounds the 32-token key tiles of the whole batch.
 constexpr int kMfmaMinUnits = 4;     // shortest range in key tiles (two tiles are in flight per wave; ranges of 2 and of 8 measured no better)
 constexpr int kMfmaSpreadUnits = 2;  // ... and while the launch has waves to spare for all of them
+constexpr int kMfmaSpreadLongest = 384;  // ... and no sequence has more tiles than this
 struct MfmaDecodeShape {
     int n_rowblocks, inner, grid, max_ranges, records;
     size_t rec_bytes, ml_bytes;

@@ -73,80 +73,73 @@ __device__ __forceinline__ uint32_t at_least_smallest(uint32_t part, uint32_t wh
 }
 
 // Merge of the records (a record: the accumulators of the 16 rows of a block, row-major [16][D], and (max, sum)
-// per row) of every (sequence, KV head, row block) that was cut; grid (B * inner), block 256.
-// Thread = (group, row, four channels): the rows of the block (at most eight per pass) times D / 4 channel quads fill
-// 16 .. 256 threads, and when they fill fewer the remaining threads form further groups that take every NG-th
-// record; the groups are then merged through LDS.  Four records per thread are in flight at a time.
-template <int D>
+// per row) of every (sequence, KV head, row block) that was cut; grid (B * inner, rows of a block / ROWS), block 256.
+// Thread = (group, row, four channels): the ROWS rows of the workgroup times D / 4 channel quads, and the remaining threads
+// form further groups that take every NG-th record; the groups are then merged through LDS.  A thread has FLIGHT records in
+// flight, so the kernel is bound by its dependent round trips: records / (NG * FLIGHT) of them.
+template <int D, int ROWS, int FLIGHT>
 __global__ __launch_bounds__(256) void merge_records_kernel(AttnArgs a, int n_rowblocks) {
-    __shared__ float sh_num[1024 / D][8][D];  // [group][row][channel]
-    __shared__ float sh_ml[1024 / D][8][2];
+    constexpr int kQuads = D / 4, kGroup = kQuads * ROWS, NG = 256 / kGroup;
+    static_assert(NG >= 1 && NG * kGroup == 256, "threads of a workgroup");
+    __shared__ float sh_num[NG][ROWS][D];
+    __shared__ float sh_ml[NG][ROWS][2];
     const int Hkv = a.view.Hkv, inner = Hkv * n_rowblocks;
     const int b = blockIdx.x / inner, gi = blockIdx.x - b * inner;
     const int g = gi % Hkv, rowblock = gi / Hkv;
     const int rec0 = a.seq_rec[2 * b], n_parts = a.seq_rec[2 * b + 1];
     if (n_parts <= 1) return;  // written directly by the streaming kernel (or no key at all)
-    const int rows_here = min(16, a.q_len * a.G - rowblock * 16);
-    const int t = threadIdx.x;
-    for (int row0 = 0; row0 < rows_here; row0 += 8) {
-        const int R = min(8, rows_here - row0);
-        const int rp_log2 = R <= 1 ? 0 : (R <= 2 ? 1 : (R <= 4 ? 2 : 3));
-        constexpr int kQuadsLog2 = D == 128 ? 5 : 4;  // threads of a row
-        const int group_threads = 1 << (kQuadsLog2 + rp_log2), NG = 256 >> (kQuadsLog2 + rp_log2);
-        const int grp = t >> (kQuadsLog2 + rp_log2), tt = t & (group_threads - 1);
-        const int r = tt >> kQuadsLog2, c4 = tt & (D / 4 - 1);
-        const bool active = r < R;
-        const int row = row0 + (active ? r : 0);
-        float M = kNegBig, den = 0.f;
-        floatx4_t num = floatx4_t{0.f, 0.f, 0.f, 0.f};
-        for (int p0 = grp; p0 < n_parts; p0 += 4 * NG) {
-            floatx4_t v[4];
-            float2 ml[4];
+    const int rows_here = min(16, a.q_len * a.G - rowblock * 16), row0 = blockIdx.y * ROWS;
+    if (row0 >= rows_here) return;
+    const int t = threadIdx.x, grp = t / kGroup, r = t % kGroup / kQuads, c4 = t % kQuads;
+    const int row = min(row0 + r, rows_here - 1);  // past the last row: repeated, not written
+    float M = kNegBig, den = 0.f;
+    floatx4_t num = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    for (int p0 = grp; p0 < n_parts; p0 += FLIGHT * NG) {
+        floatx4_t v[FLIGHT];
+        float2 ml[FLIGHT];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int p = p0 + j * NG;
-                v[j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-                ml[j] = make_float2(kNegBig, 0.f);
-                if (p < n_parts && active) {
-                    const size_t rrow = ((size_t)(rec0 + p) * inner + gi) * 16 + row;
-                    v[j] = *reinterpret_cast<const floatx4_t*>(a.rec_acc + rrow * D + c4 * 4);
-                    ml[j] = *reinterpret_cast<const float2*>(a.rec_ml + rrow * 2);
-                }
+        for (int j = 0; j < FLIGHT; ++j) {
+            const int p = p0 + j * NG;
+            v[j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+            ml[j] = make_float2(kNegBig, 0.f);
+            if (p < n_parts) {
+                const size_t rrow = ((size_t)(rec0 + p) * inner + gi) * 16 + row;
+                v[j] = *reinterpret_cast<const floatx4_t*>(a.rec_acc + rrow * D + c4 * 4);
+                ml[j] = *reinterpret_cast<const float2*>(a.rec_ml + rrow * 2);
             }
+        }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float m_new = fmaxf(M, ml[j].x);
-                const float f_old = fast_exp2((M - m_new) * a.c), f_new = fast_exp2((ml[j].x - m_new) * a.c);
-                den = __builtin_fmaf(ml[j].y, f_new, den * f_old);
-                num = v[j] * f_new + num * f_old;
-                M = m_new;
-            }
+        for (int j = 0; j < FLIGHT; ++j) {
+            const float m_new = fmaxf(M, ml[j].x);
+            const float f_old = fast_exp2((M - m_new) * a.c), f_new = fast_exp2((ml[j].x - m_new) * a.c);
+            den = __builtin_fmaf(ml[j].y, f_new, den * f_old);
+            num = v[j] * f_new + num * f_old;
+            M = m_new;
         }
-        if (active) {
-            *reinterpret_cast<floatx4_t*>(&sh_num[grp][r][c4 * 4]) = num;
-            if (c4 == 0) {
-                sh_ml[grp][r][0] = M;
-                sh_ml[grp][r][1] = den;
-            }
+    }
+    *reinterpret_cast<floatx4_t*>(&sh_num[grp][r][c4 * 4]) = num;
+    if (c4 == 0) {
+        sh_ml[grp][r][0] = M;
+        sh_ml[grp][r][1] = den;
+    }
+    __syncthreads();
+    if (grp == 0 && row0 + r < rows_here) {
+        float Mx = kNegBig;
+#pragma unroll
+        for (int k = 0; k < NG; ++k) Mx = fmaxf(Mx, sh_ml[k][r][0]);
+        float d = 0.f;
+        floatx4_t o = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < NG; ++k) {
+            const float f = fast_exp2((sh_ml[k][r][0] - Mx) * a.c);
+            d = __builtin_fmaf(sh_ml[k][r][1], f, d);
+            o += *reinterpret_cast<const floatx4_t*>(&sh_num[k][r][c4 * 4]) * f;
         }
-        __syncthreads();
-        if (grp == 0 && active) {
-            float Mx = kNegBig;
-            for (int k = 0; k < NG; ++k) Mx = fmaxf(Mx, sh_ml[k][r][0]);
-            float d = 0.f;
-            floatx4_t o = floatx4_t{0.f, 0.f, 0.f, 0.f};
-            for (int k = 0; k < NG; ++k) {
-                const float f = fast_exp2((sh_ml[k][r][0] - Mx) * a.c);
-                d = __builtin_fmaf(sh_ml[k][r][1], f, d);
-                o += *reinterpret_cast<const floatx4_t*>(&sh_num[k][r][c4 * 4]) * f;
-            }
-            const int rw = rowblock * 16 + row, qi = rw / a.G;
-            const size_t rid = ((size_t)b * a.q_len + qi) * a.Hq + (size_t)g * a.G + (rw - qi * a.G);
-            const float inv = d > 0.f ? 1.f / d : 0.f;
-            *reinterpret_cast<floatx4_t*>(a.out + rid * D + c4 * 4) = o * inv;
-            if (a.lse && c4 == 0) a.lse[rid] = d > 0.f ? __builtin_fmaf(Mx, a.scale, __builtin_logf(d)) : -__builtin_inff();
-        }
-        __syncthreads();  // the next pass reuses the buffers
+        const int rw = rowblock * 16 + row, qi = rw / a.G;
+        const size_t rid = ((size_t)b * a.q_len + qi) * a.Hq + (size_t)g * a.G + (rw - qi * a.G);
+        const float inv = d > 0.f ? 1.f / d : 0.f;
+        *reinterpret_cast<floatx4_t*>(a.out + rid * D + c4 * 4) = o * inv;
+        if (a.lse && c4 == 0) a.lse[rid] = d > 0.f ? __builtin_fmaf(Mx, a.scale, __builtin_logf(d)) : -__builtin_inff();
     }
 }
 
@@ -309,22 +302,20 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     }
 
     // While every range of two tiles still gets a wave of its own the ranges are that short: one round trip to memory
-    // instead of two (one dialogue's step, 45 tiles: 14.2 -> 11.4 microseconds, the merge 4.0 -> 5.0).  With more work
-    // than that the shorter ranges only add records (8 dialogues, 480 tiles: 18.7 -> 19.6).  And the records of one
-    // sequence, which a workgroup of the merge walks, must not cost more than that: records times rows.  (Whole call, ranges
-    // of four and of two tiles: 64 tiles of 4 rows 17.6 and 17.0 microseconds, 96 18.2 and 18.5; 32 tiles of 8 rows 16.8
-    // and 16.4, 48 17.8 and 18.5, 128 24.0 and 28.0; of 16 rows 16 tiles 17.4 and 17.2, 128 31.7 and 44.3; 64 channels,
-    // 96 tiles of 4 rows 14.8 and 14.4, 128 15.5 and 15.6.)
+    // instead of two (one dialogue's step, 45 tiles: 14.2 -> 11.4 microseconds).  With more work than that the shorter ranges
+    // only add records (8 dialogues, 480 tiles: 18.7 -> 19.6).  And the records of one sequence must not cost the merge more
+    // than that.  (Whole call, ranges of four and of two tiles: 65 tiles of 8 rows 15.6 and 13.1 microseconds, 193 16.5 and
+    // 15.5, 241 16.6 and 16.4; of 16 rows 65 tiles 15.5 and 12.8, 241 16.3 and 14.7, 481 17.5 and 17.0, twice 481 18.2 and
+    // 18.9, 801 19.6 and 20.9; 64 channels, 97 tiles of 4 rows 12.9 and 11.4.)
     bool spread = (unsigned)total <= kMfmaSpreadUnits * (gridDim.x * 4u / (unsigned)inner);
-    const int merge_rows = min(rows_total, 16), merge_limit = D == 128 ? 256 : 384;
-    if (spread && total * merge_rows > merge_limit) {
+    if (spread && total > kMfmaSpreadLongest) {
         float most = 0.f;  // tiles of the longest sequence (exact: fewer than 2^24)
         for (int b = lane; b < B; b += 64) most = vmax(most, (float)sU[b]);
         most = vmax(most, dpp_mov<0xB1>(most));
         most = vmax(most, dpp_mov<0x4E>(most));
         most = vmax(most, dpp_mov<0x141>(most));
         most = xrow_max4(vmax(most, dpp_mov<0x140>(most)));
-        spread = uni((int)most) * merge_rows <= merge_limit;
+        spread = uni((int)most) <= kMfmaSpreadLongest;
     }
     const RangeCut cut = range_cut((unsigned)total, spread ? kMfmaSpreadUnits : a.min_units, a.max_ranges, a.range_skew);
     const int n_items = (int)cut.n_ranges * inner;
@@ -735,14 +726,35 @@ int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) 
     return RA_OK;
 }
 
+// A workgroup for every row while they are at most four to a compute unit: few sequences are cut into many records each, and
+// one workgroup walking them for eight rows took most of the call (whole decode call, in microseconds: one dialogue of 100
+// rounds of 600 tokens, 30 % kept, 2 KV heads of 16 rows 87.5 -> 19.1, of 200 rounds, 8 KV heads of 4 rows 49.3 -> 35.0;
+// four of 20 rounds 25.9 -> 20.6).  More rows than that have few records each, and a workgroup per row is mostly
+// its own start: 64 dialogues, 512 blocks of 8 rows, 30.5 with a workgroup for 8 rows, 34.3 with one per row; 80 blocks of 16
+// rows 37.3 and 38.0; 128 blocks of 8 rows 79.1 and 78.8.
+constexpr unsigned kMergeByRow = 1024;
 // Second step of the matrix-core kernel above: merges the records of the sequences that were cut.
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st) {
     const MfmaDecodeShape s = mfma_decode_shape(num_cu, a.view.B, a.view.Hkv, a.view.d, a.q_len * a.G,
                                                 mfma_max_tiles(a.view.B, a.max_tokens, a.view.R_max, a.cur_cap), a.shape_units);
     if (s.max_ranges <= 1) return;  // a single range never cuts a sequence
-    const dim3 g((unsigned)(a.view.B * s.inner)), blk(256);
-    if (a.view.d == 128) hipLaunchKernelGGL((merge_records_kernel<128>), g, blk, 0, st, a, s.n_rowblocks);
-    else hipLaunchKernelGGL((merge_records_kernel<64>), g, blk, 0, st, a, s.n_rowblocks);
+    const int rows = a.q_len * a.G < 16 ? a.q_len * a.G : 16;
+    const unsigned units = (unsigned)(a.view.B * s.inner);
+    auto launch = [&](auto rows_per_workgroup, auto flight) {
+        constexpr int ROWS = decltype(rows_per_workgroup)::value, FLIGHT = decltype(flight)::value;
+        const dim3 g(units, (rows + ROWS - 1) / ROWS), blk(256);
+        if (a.view.d == 128) hipLaunchKernelGGL((merge_records_kernel<128, ROWS, FLIGHT>), g, blk, 0, st, a, s.n_rowblocks);
+        else hipLaunchKernelGGL((merge_records_kernel<64, ROWS, FLIGHT>), g, blk, 0, st, a, s.n_rowblocks);
+    };
+    typedef std::integral_constant<int, 1> one;
+    typedef std::integral_constant<int, 2> two;
+    typedef std::integral_constant<int, 4> four;
+    typedef std::integral_constant<int, 8> eight;
+    if (units * rows <= kMergeByRow) launch(one(), eight());
+    else if (rows <= 1) launch(one(), four());
+    else if (rows <= 2) launch(two(), four());
+    else if (rows <= 4) launch(four(), four());
+    else launch(eight(), four());
 }
 
 }  // namespace ra
