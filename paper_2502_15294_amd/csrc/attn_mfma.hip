@@ -317,13 +317,38 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
         most = xrow_max4(vmax(most, dpp_mov<0x140>(most)));
         spread = uni((int)most) <= kMfmaSpreadLongest;
     }
-    const RangeCut cut = range_cut((unsigned)total, spread ? kMfmaSpreadUnits : a.min_units, a.max_ranges, a.range_skew);
-    const int n_items = (int)cut.n_ranges * inner;
-    const bool long_ranges = cut.total > (kMfmaMinUnits + 1) * cut.n_ranges;
+    const int min_units = spread ? kMfmaSpreadUnits : a.min_units;
+    const RangeCut cut = range_cut((unsigned)total, min_units, a.max_ranges, a.range_skew);
+    int n_ranges = (int)cut.n_ranges;
+    // Few sequences are cut each by itself (lane b: sequence b, its first range and its pieces) if that takes no more ranges
+    // than there may be, of no more than a tile more.  (Whole decode call: 8 dialogues of 20 rounds, 30 % kept, 30.6 -> 29.8
+    // microseconds, 3 of 33 rounds 22.4 -> 22.0; 5 of 20 rounds, paged, 23.7 -> 22.4; 16 of 24 rounds, 64 channels, 34.7 ->
+    // 33.5, 2 KV heads 26.0 -> 24.2.)  With more sequences the pieces come out uneven, and the launch waits for the longest:
+    // 16 dialogues, 128 ranges, 121.6 -> 122.7; 24, 256 ranges, 56.8 -> 58.0; 40 of a few tiles 16.0 -> 17.5.
+    bool by_sequence = false;
+    int my_first = 0;
+    SeqCut my_cut = {0, 0, 0};
+    if (INLINE_PLAN && B * kSeqCutRanges <= a.max_ranges) {
+        const int U = lane < B ? sU[lane] : 0, len = seq_cut_len((unsigned)total, min_units, a.max_ranges);
+#pragma unroll
+        for (int i = 0; i < kSeqCutTries; ++i) {
+            if (by_sequence) break;
+            my_cut = seq_cut(U, len + i);
+            const int incl = wave_inclusive_sum(my_cut.n), n = __builtin_amdgcn_readlane(incl, 63);
+            if (n <= a.max_ranges) {
+                by_sequence = true;
+                my_first = incl - my_cut.n;
+                n_ranges = n;
+            }
+        }
+    }
+    const int n_items = n_ranges * inner;
+    const bool long_ranges = total > (kMfmaMinUnits + 1) * n_ranges;
     if (blockIdx.x == 0)  // for the merge kernel: first record and number of records of every sequence
         for (int b = tid; b < B; b += 256) {
             SeqParts sp = {0, 0};
-            if (sU[b] > 0) sp = seq_parts(cut, sps[b], sps[b + 1]);
+            if (by_sequence) sp = {my_first, my_cut.n};  // (at most 64 sequences: b is the lane)
+            else if (sU[b] > 0) sp = seq_parts(cut, sps[b], sps[b + 1]);
             a.seq_rec[2 * b] = record_index(sp.first_range, b);
             a.seq_rec[2 * b + 1] = sp.n_parts;
         }
@@ -339,11 +364,20 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     for (int item = blockIdx.x * 4 + wave; item < n_items; item += n_waves) {
         const int range = item / inner, gi = item - range * inner;  // the (KV head, row block) items of a range are neighbours
         const int g = gi % Hkv, rowblock = gi / Hkv;
-        int t_lo = (int)range_begin(cut, range);
-        const int t_hi = (int)range_begin(cut, range + 1);
-        int b;  // the sequence that holds tile t_lo: the last one with sps[b] <= t_lo
-        if (B <= 64) b = __popcll(__ballot(lane < B && sps[lane < B ? lane : 0] <= t_lo)) - 1;
-        else b = upper_slot(sps, B, t_lo);
+        int t_lo, t_hi, b;  // its tiles, and the sequence that holds the first of them
+        if (INLINE_PLAN && by_sequence) {
+            b = __popcll(__ballot(lane < B && my_first <= range)) - 1;
+            const SeqCut c = {0, lane_get(my_cut.q, b), lane_get(my_cut.rem, b)};
+            const int j = range - lane_get(my_first, b);
+            t_lo = sps[b] + seq_cut_begin(c, j);
+            t_hi = sps[b] + seq_cut_begin(c, j + 1);
+        } else {
+            t_lo = (int)range_begin(cut, range);
+            t_hi = (int)range_begin(cut, range + 1);
+            // the last one with sps[b] <= t_lo
+            if (B <= 64) b = __popcll(__ballot(lane < B && sps[lane < B ? lane : 0] <= t_lo)) - 1;
+            else b = upper_slot(sps, B, t_lo);
+        }
 
         // ---- the segments of this range: one per sequence it touches --------------------------------------
         for (; t_lo < t_hi; ++b) {
@@ -352,7 +386,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             if (seg_hi <= t_lo) continue;  // a sequence without tiles
             const int u_lo = t_lo - seq_lo, u_hi = seg_hi - seq_lo;  // tiles of the sequence's own table
             t_lo = seg_hi;
-            const SeqParts parts = seq_parts(cut, seq_lo, seq_hi);
+            const bool whole = u_lo == 0 && seg_hi == seq_hi;  // the sequence lies in this range alone
             const int rec = record_index(range, b);
 
             // ---- this wave's query rows ---------------------------------------------------------------
@@ -665,7 +699,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
 
             // ---- the four lane groups hold partial sums of the same rows -------------------------------------
             l = xrow_sum4(l);
-            if (parts.n_parts == 1) {
+            if (whole) {
                 if (row_ok) {
                     const float inv = l > 0.f ? 1.f / l : 0.f;
 #pragma unroll

@@ -87,6 +87,30 @@ RA_HD inline unsigned range_of_tile(const RangeCut& c, unsigned t) {
     return c.n_a + (u < big ? u / (c.q_b + 1) : c.rem_b + (u - big) / c.q_b);
 }
 
+// The other cut, for launches of short ranges: every sequence by itself, into pieces of at most `len` tiles that are equal to
+// within one.  A range that goes on with the next sequence starts twice, queries, segment table and first tile one memory
+// round trip behind the other, and with a few tiles a range that is the longest wave of the launch.  Piece j of sequence b is
+// range first(b) + j, first(b) being the number of pieces of the sequences before b; records as above.
+struct SeqCut {
+    int n, q, rem;  // pieces; the first rem of them have q + 1 tiles, the others q
+};
+RA_HD inline SeqCut seq_cut(int tiles, int len) {
+    SeqCut c;
+    c.n = (int)(((unsigned)tiles + (unsigned)len - 1) / (unsigned)len);
+    c.q = c.n > 0 ? (int)((unsigned)tiles / (unsigned)c.n) : 0;
+    c.rem = tiles - c.q * c.n;
+    return c;
+}
+RA_HD inline int seq_cut_begin(const SeqCut& c, int j) { return j * c.q + (j < c.rem ? j : c.rem); }
+// Piece length to try first: as many pieces as there may be ranges, if every sequence were a whole number of them.  A tile
+// more is tried after it; a range that starts twice costs more than that.
+RA_HD inline int seq_cut_len(unsigned total, int min_units, int max_ranges) {
+    const int len = (int)((total + (unsigned)max_ranges - 1) / (unsigned)max_ranges);
+    return len < min_units ? min_units : len;
+}
+constexpr int kSeqCutTries = 2;
+constexpr int kSeqCutRanges = 12;  // ranges there may be for every sequence of a batch that is cut this way, at least
+
 // Records of a sequence with tiles [t_lo, t_hi), t_hi > t_lo.
 struct SeqParts {
     int first_range, n_parts;

@@ -8,6 +8,7 @@
 //   * the segments handed out cover every key tile of every (KV head, row block) exactly once;
 //   * record indices stay below record_capacity() and no record is written twice;
 //   * a sequence that lies in one range is written directly, exactly once, and leaves no record;
+//   * all of it also for batches whose sequences are cut each by itself (seq_cut);
 //   * for a sequence cut into n parts the merge step (a second kernel, after all waves have exited) finds exactly
 //     the n records first .. first + n - 1 that the streaming kernel announced, and they add up to the sequence.
 //
@@ -30,6 +31,9 @@ struct Launch {
     int B, inner, max_ranges, min_units, n_waves, skew;
     std::vector<int> U;      // tiles per sequence
     std::vector<int> begin;  // prefix, begin[B] = total
+    bool by_sequence = false;  // every sequence cut by itself, as the kernel decides it for few sequences
+    std::vector<SeqCut> cuts;
+    std::vector<int> first;    // first range of every sequence, first[B] = number of ranges
     std::vector<int> rec_val;  // [records][inner] tiles the record stands for (plain memory)
     std::vector<std::atomic<int>> rec_writes, out_writes, tiles_seen;  // [records][inner], [B][inner], [inner]
     std::atomic<int> errors{0};
@@ -41,31 +45,62 @@ static void fail(Launch& L, const char* what, int a, int b) {
     if (L.errors.fetch_add(1) < 5) std::fprintf(stderr, "  model check failed: %s (%d, %d)\n", what, a, b);
 }
 
+static void choose_cut(Launch& L, bool allowed) {
+    const int len = seq_cut_len((unsigned)L.begin[L.B], L.min_units, L.max_ranges);
+    for (int i = 0; i < kSeqCutTries && allowed && !L.by_sequence; ++i) {
+        L.cuts.clear();
+        L.first.assign(1, 0);
+        for (int b = 0; b < L.B; ++b) {
+            L.cuts.push_back(seq_cut(L.U[b], len + i));
+            L.first.push_back(L.first.back() + L.cuts.back().n);
+        }
+        L.by_sequence = L.first.back() <= L.max_ranges;
+        for (int b = 0; b < L.B && L.by_sequence; ++b)
+            for (int j = 0; j < L.cuts[b].n; ++j) {
+                const int n = seq_cut_begin(L.cuts[b], j + 1) - seq_cut_begin(L.cuts[b], j);
+                if (n < 1 || n > len + i) fail(L, "a piece is empty or too long", b, n);
+            }
+    }
+}
+
+static SeqParts parts_of(const Launch& L, const RangeCut& cut, int b) {
+    if (L.by_sequence) return {L.first[b], L.cuts[b].n};
+    return seq_parts(cut, L.begin[b], L.begin[b + 1]);
+}
+
 // What one wavefront does after the kernel's prologue.
 static void wave(Launch& L, int w, unsigned jitter) {
     const unsigned total = (unsigned)L.begin[L.B];
     if (total == 0) return;
     const RangeCut cut = range_cut(total, L.min_units, L.max_ranges, L.skew);
-    int n_items = (int)cut.n_ranges * L.inner;
+    int n_items = (L.by_sequence ? L.first[L.B] : (int)cut.n_ranges) * L.inner;
 #ifdef PLANT_SKIP_LAST_ITEM
     n_items -= 1;  // planted mistake: the last work item is never handed out
 #endif
     std::minstd_rand rng(jitter);
     for (int item = w; item < n_items; item += L.n_waves) {
         const int range = item / L.inner, gi = item - range * L.inner;
-        int t_lo = (int)range_begin(cut, range);
-        const int t_hi = (int)range_begin(cut, range + 1);
-        int b = upper_slot(L.begin.data(), L.B, t_lo);
+        int t_lo, t_hi, b;
+        if (L.by_sequence) {
+            b = -1;
+            for (int k = 0; k < L.B; ++k) b += L.first[k] <= range ? 1 : 0;
+            t_lo = L.begin[b] + seq_cut_begin(L.cuts[b], range - L.first[b]);
+            t_hi = L.begin[b] + seq_cut_begin(L.cuts[b], range - L.first[b] + 1);
+        } else {
+            t_lo = (int)range_begin(cut, range);
+            t_hi = (int)range_begin(cut, range + 1);
+            b = upper_slot(L.begin.data(), L.B, t_lo);
+        }
         for (; t_lo < t_hi; ++b) {
             if (b >= L.B) { fail(L, "walked past the last sequence", range, b); return; }
-            const int seq_lo = L.begin[b], seq_hi = L.begin[b + 1];
+            const int seq_hi = L.begin[b + 1];
             const int seg_hi = t_hi < seq_hi ? t_hi : seq_hi;
             if (seg_hi <= t_lo) continue;
             const int tiles = seg_hi - t_lo;
             t_lo = seg_hi;
             L.tiles_seen[gi].fetch_add(tiles, std::memory_order_relaxed);
             if (rng() & 1) std::this_thread::yield();
-            const SeqParts parts = seq_parts(cut, seq_lo, seq_hi);
+            const SeqParts parts = parts_of(L, cut, b);
             if (range < parts.first_range || range >= parts.first_range + parts.n_parts) fail(L, "range outside the sequence's parts", range, b);
             if (parts.n_parts == 1) {
                 if (tiles != L.U[b]) fail(L, "uncut sequence streamed in part", b, tiles);
@@ -91,7 +126,7 @@ static void merge_step(Launch& L) {
     const RangeCut cut = range_cut(total, L.min_units, L.max_ranges, L.skew);
     for (int b = 0; b < L.B; ++b) {
         if (L.U[b] == 0) continue;
-        const SeqParts parts = seq_parts(cut, L.begin[b], L.begin[b + 1]);  // what block 0 of the kernel announces
+        const SeqParts parts = parts_of(L, cut, b);  // what block 0 of the kernel announces
         if (parts.n_parts <= 1) continue;
         const int rec0 = record_index(parts.first_range, b);
         for (int gi = 0; gi < L.inner; ++gi) {
@@ -110,7 +145,7 @@ int main(int argc, char** argv) {
     const unsigned seed = argc > 1 ? (unsigned)std::atoi(argv[1]) : 1u;
     const int cases = argc > 2 ? std::atoi(argv[2]) : 200;
     std::mt19937 rng(seed);
-    int bad = 0;
+    int bad = 0, by_sequence = 0;
     for (int c = 0; c < cases; ++c) {
         // mostly small batches; every tenth case a batch beyond one wavefront's lanes, up to the library's limit
         const int B = c % 10 == 9 ? 65 + (int)(rng() % 960) : 1 + (int)(rng() % 24);
@@ -134,6 +169,8 @@ int main(int argc, char** argv) {
             }
             L.begin.assign(B + 1, 0);
             for (int b = 0; b < B; ++b) L.begin[b + 1] = L.begin[b] + L.U[b];
+            if (L.begin[B] > 0) choose_cut(L, B <= 64 && c % 4 < 2);
+            by_sequence += L.by_sequence;
             std::vector<std::thread> th;
             for (int w = 0; w < n_waves; ++w) th.emplace_back(wave, std::ref(L), w, (unsigned)rng());
             for (auto& t : th) t.join();
@@ -179,6 +216,7 @@ int main(int argc, char** argv) {
             if (!(r < cut.n_ranges && range_begin(cut, r) <= t && t < range_begin(cut, r + 1))) ++bad;
         }
     }
+    if (cases >= 40 && by_sequence == 0) ++bad;  // the other cut was never met
     std::printf("%s: %d cases x 2 launches, seed %u, %d failed checks\n", bad ? "FAILED" : "ok", cases, seed, bad);
     return bad ? 1 : 0;
 }

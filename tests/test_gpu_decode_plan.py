@@ -67,3 +67,14 @@ def test_one_dialogue_in_many_records(tiles, Hq, Hkv, d):
 def test_many_rows_in_few_records(B, Hq, Hkv):
     w = make_workload("cfg2", B=B, Hq=Hq, Hkv=Hkv, lens=[[290 + 7 * b, 33] for b in range(B)], n_relevant=0, cur_len=9)
     check(w, [[0, 1]] * B, [0, B // 2, B - 1])
+
+
+# dialogues cut each by itself (up to a twelfth as many as there may be ranges) and one more than that, some of them empty
+@pytest.mark.parametrize("B,Hq,Hkv,d", [(2, 16, 2, 128), (10, 32, 8, 128), (11, 32, 8, 128), (21, 32, 8, 64), (22, 32, 8, 64), (42, 16, 2, 128), (43, 16, 2, 128)])
+def test_dialogues_cut_each_by_itself(B, Hq, Hkv, d):
+    rng = np.random.default_rng(B)
+    lens = rng.integers(0, 400, size=(B, 4)).tolist()
+    lens[0] = [0, 0, 0, 1]
+    lens[B // 2] = [0, 0, 0, 0]
+    w = make_workload("cfg2", B=B, Hq=Hq, Hkv=Hkv, d=d, lens=lens, n_relevant=0, cur_len=0)
+    check(w, [[0, 1, 3]] * B, [b for b in (0, 1, B - 1) if b != B // 2])
