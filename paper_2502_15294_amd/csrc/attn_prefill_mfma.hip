@@ -108,7 +108,12 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
                                              a.slots * inner <= (int)gridDim.x,
                                          attn_range_weights());
         if (blockIdx.x == 0) {
-            if (tid < vw.B) a.n_parts[tid] = ranges.parts[tid];
+            const LaneSequence sq = lane_sequence(sU, vw.B);
+            for (int b = wave; b < vw.B; b += 4) {
+                int part0;
+                const int parts = parts_of(ranges, P, sq, b, part0);
+                if (lane == 0) a.n_parts[b] = parts;
+            }
             // a sequence with an empty key set lies in no range: its rows are written here
             for (int b = 0; b < vw.B; ++b) {
                 if (sU[b] != 0) continue;
@@ -134,6 +139,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
     const char* vbase = reinterpret_cast<const char*>(vw.v);
     const char* ck = reinterpret_cast<const char*>(a.cur_k);
     const char* cv = reinterpret_cast<const char*>(a.cur_v);
+
     const int n_items = P * inner;
 
     // One pass per (item, sequence that its range meets); planned apart an item is a piece of one sequence.  A single loop:
@@ -146,16 +152,18 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
         int b, s, S_eff, u_lo, u_hi;
         if constexpr (INLINE_PLAN) {
             const int r = range_at<kWorkgroupsPerCuP>(piece, P);
+            const LaneSequence sq = lane_sequence(sU, vw.B);
             const int t_lo = max(uniform(ranges.bound[r]), reached), t_hi = uniform(ranges.bound[r + 1]);
             if (t_lo >= t_hi) {  // (an empty range)
                 item += gridDim.x;
                 continue;
             }
-            b = sequence_of_tile(ranges, vw.B, t_lo);
-            const int seq_lo = uniform(ranges.seq[b]);
-            const int end = min(t_hi, seq_lo + uniform(sU[b]));
-            s = r - uniform(ranges.part0[b]);
-            S_eff = uniform(ranges.parts[b]);
+            b = sequence_of_tile(sq, vw.B, t_lo);
+            const int seq_lo = __builtin_amdgcn_readlane(sq.tile0, b);
+            const int end = min(t_hi, seq_lo + __builtin_amdgcn_readlane(sq.U, b));
+            int part0;
+            S_eff = parts_of(ranges, P, sq, b, part0);
+            s = r - part0;
             u_lo = t_lo - seq_lo;
             u_hi = end - seq_lo;
             reached = end < t_hi ? end : 0;
@@ -169,6 +177,24 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
         if (reached == 0) item += gridDim.x;
         const int U = sU[b];
 
+        // ---- this wave's query rows: the block's 16-row tiles are dealt out to the waves in turn; asked for before the table is built
+        const int wv = (wave + rowblock + piece) & 3;  // not always the same SIMD gets the odd tile
+        const int my_tiles = !RAGGED ? 2 : (wv < block_tiles(rowblock) ? 1 : 0) + (wv + 4 < block_tiles(rowblock) ? 1 : 0);
+        int qtok[kNTP];
+        bool row_ok[kNTP];
+        size_t rowid[kNTP];
+        uint4 qf[kNTP][4];
+#pragma unroll
+        for (int nt = 0; nt < kNTP; ++nt) {
+            const int row = (rowblock * tiles_per_block + nt * 4 + wv) * 16 + n;
+            row_ok[nt] = nt < my_tiles && row < rows_total;
+            const int rr = row_ok[nt] ? row : 0;
+            qtok[nt] = rr / G;
+            rowid[nt] = ((size_t)b * q_len + qtok[nt]) * a.Hq + (size_t)g * G + (rr - qtok[nt] * G);
+            const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + rowid[nt] * 256);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = qp[kk * 4 + q4];  // rows past the last repeat row 0, unused: no wait here
+        }
         int n_slots, n_hist;
         if (!INLINE_PLAN || !first) __syncthreads();  // the previous pass's readers of the table and the tile buffers are done
         first = false;
@@ -191,31 +217,13 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
             // a piece owns whole chunks: its ends move down to the chunk start at or before them
             auto snap = [&](int u) {
                 if (u <= 0 || u >= U) return u <= 0 ? 0 : U;
-                const int sl = find_slot(tab.cum, n_slots, u);
+                const int sl = find_slot_wave(tab.cum, n_slots, u);
                 return tab.cum[sl] + ((u - tab.cum[sl]) & ~7);
             };
             u_lo = __builtin_amdgcn_readfirstlane(snap(u_lo));
             u_hi = __builtin_amdgcn_readfirstlane(snap(u_hi));
         }
 
-        // ---- this wave's query rows: the block's 16-row tiles are dealt out to the waves in turn -------------------------
-        const int wv = (wave + rowblock + piece) & 3;  // not always the same SIMD gets the odd tile
-        const int my_tiles = !RAGGED ? 2 : (wv < block_tiles(rowblock) ? 1 : 0) + (wv + 4 < block_tiles(rowblock) ? 1 : 0);
-        int qtok[kNTP];
-        bool row_ok[kNTP];
-        size_t rowid[kNTP];
-        uint4 qf[kNTP][4];
-#pragma unroll
-        for (int nt = 0; nt < kNTP; ++nt) {
-            const int row = (rowblock * tiles_per_block + nt * 4 + wv) * 16 + n;
-            row_ok[nt] = nt < my_tiles && row < rows_total;
-            const int rr = row_ok[nt] ? row : 0;
-            qtok[nt] = rr / G;
-            rowid[nt] = ((size_t)b * q_len + qtok[nt]) * a.Hq + (size_t)g * G + (rr - qtok[nt] * G);
-            const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + rowid[nt] * 256);
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = qp[kk * 4 + q4];  // rows past the last repeat row 0, unused: no wait here
-        }
         floatx4_t acc[kNTP][8];
         float m[kNTP], l[kNTP];
         float l_mark[kNTP];  // the running sum as it stood at the start of the current chunk (score output only)
@@ -478,7 +486,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
 
         // ---- walk the key tiles: the whole workgroup in lockstep -----------------------------------------
         if (u_lo < u_hi) {
-            int slot = find_slot(tab.cum, n_slots, u_lo);
+            int slot = find_slot_wave(tab.cum, n_slots, u_lo);
             open_seg(slot, u_lo);
             int c_tok0 = seg_len - rows_left;
             Share sh = load_tile(tiles_lds);

@@ -135,13 +135,14 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
         int b, t_lo, t_hi;  // the pass: tiles [t_lo, t_hi) of sequence b, moved to chunk starts
         if constexpr (INLINE_PLAN) {
             const int r = range_at<kWorkgroupsPerCuS>(piece, P);
+            const LaneSequence sq = lane_sequence(sU, vw.B);
             const int g_lo = max(uni(ranges.bound[r]), reached), g_hi = uni(ranges.bound[r + 1]);
             if (g_lo >= g_hi) {  // (an empty range)
                 item += gridDim.x;
                 continue;
             }
-            b = sequence_of_tile(ranges, vw.B, g_lo);
-            const int seq_lo = uni(ranges.seq[b]), end = min(g_hi, seq_lo + uni(sU[b]));
+            b = sequence_of_tile(sq, vw.B, g_lo);
+            const int seq_lo = __builtin_amdgcn_readlane(sq.tile0, b), end = min(g_hi, seq_lo + __builtin_amdgcn_readlane(sq.U, b));
             t_lo = g_lo - seq_lo;
             t_hi = end - seq_lo;
             reached = end < g_hi ? end : 0;
@@ -154,33 +155,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
         if (reached == 0) item += gridDim.x;
         const int T = sU[b];
 
-        int n_slots, n_hist;
-        if (!INLINE_PLAN || !first) __syncthreads();  // the previous pass's readers of the table and the tile buffers are done
-        first = false;
-        if constexpr (INLINE_PLAN) {
-            n_hist = uni(lists.meta[3 * b + 1]);
-            n_slots = n_hist + (uni(lists.meta[3 * b + 2]) > 0 ? 1 : 0);
-            SlotTable by_tile = tab;  // `cum` of the table is the chunk prefix here
-            by_tile.cum = tcum;
-            lists.table<true>(b, by_tile, tab.cum);
-        } else {
-            const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
-            n_slots = uni(hdr.n_slots);
-            n_hist = uni(hdr.n_hist);
-            __syncthreads();
-            for (int i = tid; i < cap; i += 256) tcum[i] = (int)tab.off_v[i];  // where the planning kernel put it
-            if (tid == 0) tcum[cap] = T;
-            __syncthreads();
-        }
-        auto chunk_of_tile = [&](int t) {  // index of the chunk that holds tile t (the chunk count for t == T)
-            if (t >= T) return uni(tab.cum[n_slots]);
-            const int sl = find_slot(tcum, n_slots, t);
-            return uni(tab.cum[sl] + (t - tcum[sl]) / kTilesPerChunk);
-        };
-        const int u_lo = chunk_of_tile(t_lo), u_hi = chunk_of_tile(t_hi);  // chunks [u_lo, u_hi) of sequence b
-        if (u_lo >= u_hi) continue;
-
-        // ---- this wave's query rows -------------------------------------------------------------------
+        // ---- this wave's query rows, asked for before the table is built -------------------------------
         // The block's 16-row tiles are dealt out to the waves in turn: row nt of this lane is row0 + 64 nt (whatever else is
         // needed of it is recomputed where it is used).
         const int wv = (wave + rowblock + piece) & 3;  // not always the same SIMD gets the odd tile
@@ -203,6 +178,33 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
             m[nt] = kNegBig;
             l[nt] = 0.f;
         }
+
+        int n_slots, n_hist;
+        if (!INLINE_PLAN || !first) __syncthreads();  // the previous pass's readers of the table and the tile buffers are done
+        first = false;
+        if constexpr (INLINE_PLAN) {
+            n_hist = uni(lists.meta[3 * b + 1]);
+            n_slots = n_hist + (uni(lists.meta[3 * b + 2]) > 0 ? 1 : 0);
+            SlotTable by_tile = tab;  // `cum` of the table is the chunk prefix here
+            by_tile.cum = tcum;
+            lists.table<true>(b, by_tile, tab.cum);
+        } else {
+            const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
+            n_slots = uni(hdr.n_slots);
+            n_hist = uni(hdr.n_hist);
+            __syncthreads();
+            for (int i = tid; i < cap; i += 256) tcum[i] = (int)tab.off_v[i];  // where the planning kernel put it
+            if (tid == 0) tcum[cap] = T;
+            __syncthreads();
+        }
+        int slot = 0;
+        auto chunk_of_tile = [&](int t) {  // index of the chunk that holds tile t, of segment `slot` (the chunk count for t == T)
+            if (t >= T) return uni(tab.cum[n_slots]);
+            slot = find_slot_wave(tcum, n_slots, t);
+            return uni(tab.cum[slot] + (t - tcum[slot]) / kTilesPerChunk);
+        };
+        const int u_hi = chunk_of_tile(t_hi), u_lo = chunk_of_tile(t_lo);  // chunks [u_lo, u_hi) of sequence b
+        if (u_lo >= u_hi) continue;
 
         // Uniform state of the loader: the segment it stands in (the table in LDS is read on entry only), and
         // inside it the next tile: the address of its first token's keys (head g) and the tokens left from there.
@@ -350,7 +352,6 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
             done_u = -1;
         };
         // ---- walk the key tiles of chunks [u_lo, u_hi): the whole workgroup in lockstep ------------------------
-        int slot = find_slot(tab.cum, n_slots, u_lo);
         open_seg(slot);
         open_chunk(u_lo);
         int lu = u_lo, lj = 0;  // the tile the loader fetches next: tile lj of chunk lu

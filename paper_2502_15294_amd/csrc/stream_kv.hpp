@@ -11,6 +11,8 @@
 #include "common.hpp"
 #include "tile_ranges.hpp"
 
+#include <type_traits>
+
 namespace ra {
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -360,8 +362,8 @@ __device__ __forceinline__ int find_slot(const T* cum, int n, T u) {
 constexpr int kInlineRounds = 1024;  // most sequences times R_max
 // A launch that plans itself must still hold as many workgroups on a compute unit as it has for one: the lists, 24 bytes per
 // (sequence, round), come on top of the table's.  (128-token question, one dialogue of 619 rounds: the score kernel, three
-// to a unit, 78.9 microseconds behind the planning kernel and 109.4 with its own plan, of which two fit; 618 rounds, of
-// which three do, 84.3.  917 rounds: the attention kernel 93.5 and 114.2, two to a unit and one; 914: 74.6.)
+// to a unit, 78.9 microseconds behind the planning kernel and 109.4 with its own plan while only two of that fitted; 618
+// rounds, of which three did, 84.3.  917 rounds: the attention kernel 93.5 and 114.2, two to a unit and one; 914: 74.6.)
 constexpr size_t kLdsPerUnit = 160 * 1024, kLdsGranule = 1280;
 __device__ constexpr int align16(int x) { return (x + 15) & ~15; }
 struct BatchLists {
@@ -370,30 +372,55 @@ struct BatchLists {
     int* meta;           // [B][3] rounds of the sequence, listed rounds, length of the current round
     int R_max;
     __host__ __device__ static size_t bytes(int B, int R_max) { return ((size_t)B * R_max * 24 + (size_t)B * 12 + 15) & ~(size_t)15; }
-    // sel_idx null: every round; cur_len(b): the current round's tokens.  All threads call it; ends with a barrier.
+    // sel_idx null: every round; cur_len(b): the current round's tokens.  All threads (256) call it; ends with a barrier.
+    // One memory round trip: everything a thread reads is asked for before any of it is used.
     template <typename CurLen>
     __device__ __forceinline__ void load(char* smem, const DevView& vw, const int32_t* sel_idx, const int32_t* n_sel,
                                          CurLen cur_len) {
         R_max = vw.R_max;
-        const int n = vw.B * R_max;
+        listed = sel_idx != nullptr;
+        const int n = vw.B * R_max, tid = threadIdx.x;
         ok = reinterpret_cast<long long*>(smem);
         ov = ok + n;
         len = reinterpret_cast<int*>(ov + n);
         sel = len + n;
         meta = sel + n;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            len[i] = vw.seg_len[i];
-            ok[i] = vw.seg_off[i];
-            ov[i] = vw.seg_off_v[i];
-            if (sel_idx) sel[i] = sel_idx[i];
+        int c_rounds = 0, c_sel = 0;
+        if (tid < vw.B) {
+            c_rounds = vw.n_rounds[tid];
+            if (sel_idx) c_sel = n_sel[tid];
         }
-        for (int b = threadIdx.x; b < vw.B; b += blockDim.x) {
-            const int n_rounds = min(max(vw.n_rounds[b], 0), R_max);
-            meta[3 * b] = n_rounds;
-            meta[3 * b + 1] = sel_idx ? min(max(n_sel[b], 0), R_max) : n_rounds;
-            meta[3 * b + 2] = cur_len(b);
+        auto read = [&](auto per_thread) {
+            constexpr int N = decltype(per_thread)::value;
+            int l[N], s[N];
+            long long k[N], v[N];
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const int i = min(tid + 256 * j, n - 1);
+                l[j] = vw.seg_len[i];
+                k[j] = vw.seg_off[i];
+                v[j] = vw.seg_off_v[i];
+                s[j] = sel_idx ? sel_idx[i] : 0;
+            }
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const int i = tid + 256 * j;
+                if (i < n) {
+                    len[i] = l[j];
+                    ok[i] = k[j];
+                    ov[i] = v[j];
+                    sel[i] = s[j];
+                }
+            }
+        };
+        if (n > 256) read(std::integral_constant<int, kInlineRounds / 256>());
+        else if (n > 0) read(std::integral_constant<int, 1>());
+        if (tid < vw.B) {
+            const int n_rounds = min(max(c_rounds, 0), R_max);
+            meta[3 * tid] = n_rounds;
+            meta[3 * tid + 1] = sel_idx ? min(max(c_sel, 0), R_max) : n_rounds;
+            meta[3 * tid + 2] = cur_len(tid);
         }
-        listed = sel_idx != nullptr;
         __syncthreads();
     }
     // Segment i of sequence b's table, as the planning kernel defines it: the i-th listed round (entries that are not
@@ -458,27 +485,42 @@ struct BatchLists {
     bool listed;
 };
 
-// The cut of the batch's key tiles into ranges (tile_ranges.hpp), in LDS.
+// Largest slot with cum[slot] <= u, for 0 <= u < cum[n]: by all lanes of the wave at once.
+__device__ __forceinline__ int find_slot_wave(const int* cum, int n, int u) {
+    const int lane = threadIdx.x & 63;
+    int c = 0;
+    for (int i = lane; i - lane < n; i += 64) c += __popcll(__ballot(i < n && cum[min(i, n - 1)] <= u));
+    return c - 1;
+}
+// The cut of the batch's key tiles into ranges (tile_ranges.hpp), in LDS: range r is the tiles bound[r] .. bound[r + 1] - 1 of
+// the batch's list.  Which sequence a range begins in and which ranges a sequence meets is found by all lanes at once when a
+// pass needs it (sequences in lanes, find_slot_wave), not looked up in further tables: filling those behind one more barrier,
+// by two searches of a thread per sequence, was half of the 2 microseconds that the cut took of a question's start.
 struct TileRanges {
-    int bound[kMaxRanges + 1];   // range r is the tiles bound[r] .. bound[r + 1] - 1 of the batch's list
-    int seq[kInlineBatch];       // first tile of every sequence
-    int part0[kInlineBatch], parts[kInlineBatch];  // first range that meets a sequence, number of them
+    int bound[kMaxRanges + 1];
 };
 // lds: dynamic LDS of the launch that plans itself; grid: its workgroups.
 inline bool prefill_plans_inline(int B, int R_max, size_t lds, long long grid, int num_cu) {
     const size_t all = align_up(lds + sizeof(TileRanges) + (kInlineBatch + 4) * sizeof(int), kLdsGranule);
     return B <= kInlineBatch && (long long)B * R_max <= kInlineRounds && (grid + num_cu - 1) / num_cu * all <= kLdsPerUnit;
 }
+// Lane b: the tiles of sequence b and the first of them.
+struct LaneSequence {
+    int U, tile0;
+};
+__device__ __forceinline__ LaneSequence lane_sequence(const int* sU, int B) {
+    const int lane = threadIdx.x & 63, U = lane < B ? sU[lane] : 0;
+    return {U, wave_inclusive_sum(U) - U};
+}
 // Fills `tr` from the sequences' tiles sU; returns the number of ranges.  All threads call it; no barrier behind the counts
 // needed before it, one at its end.
 template <int C>
 __device__ __forceinline__ int cut_tiles(TileRanges& tr, const int* sU, int B, int slots, int min_tiles, int max_parts, bool full,
                                          const RangeWeights<C>& weights) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int U = lane < B ? sU[lane] : 0;
-    const int incl = wave_inclusive_sum(U);
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    float top = (float)U;  // (exact: a sequence has fewer than 2^24 tiles)
+    const int tid = threadIdx.x;
+    const LaneSequence sq = lane_sequence(sU, B);
+    const int total = __builtin_amdgcn_readlane(sq.tile0 + sq.U, 63);
+    float top = (float)sq.U;  // (exact: a sequence has fewer than 2^24 tiles)
     top = vmax(top, dpp_mov<0xB1>(top));
     top = vmax(top, dpp_mov<0x4E>(top));
     top = vmax(top, dpp_mov<0x141>(top));
@@ -486,37 +528,34 @@ __device__ __forceinline__ int cut_tiles(TileRanges& tr, const int* sU, int B, i
     const int most = __builtin_amdgcn_readfirstlane((int)top);
     if (slots > kMaxRanges) slots = kMaxRanges;
     const TileCut<C> cut(total, most, slots, min_tiles, max_parts, full, weights);
-    const int P = cut.n_ranges;
-    const int cuts = cut.cuts(U), cuts_incl = wave_inclusive_sum(cuts);
-    const int P_apart = __builtin_amdgcn_readlane(cuts_incl, 63);
-    if (cut.apart(P_apart, slots, min_tiles)) {
-        if (tid < B) {
-            tr.seq[tid] = incl - U;
-            tr.part0[tid] = cuts_incl - cuts;
-            tr.parts[tid] = cuts;
-            for (int j = 0; j < cuts; ++j) tr.bound[cuts_incl - cuts + j] = incl - U + U * j / cuts;
+    int P = cut.n_ranges;
+    if (cut.len == min_tiles) {  // perhaps every sequence by itself
+        const int cuts = cut.cuts(sq.U), cuts_incl = wave_inclusive_sum(cuts);
+        const int P_apart = __builtin_amdgcn_readlane(cuts_incl, 63);
+        if (cut.apart(P_apart, slots, min_tiles)) {
+            if (tid < B)
+                for (int j = 0; j < cuts; ++j) tr.bound[cuts_incl - cuts + j] = sq.tile0 + sq.U * j / cuts;
+            if (tid == 0) tr.bound[P_apart] = total;
+            lds_barrier();
+            return P_apart;
         }
-        if (tid == 0) tr.bound[P_apart] = total;
-        lds_barrier();
-        return P_apart;
     }
     const double per_weight = cut.tiles_per_weight();
     for (int r = tid; r <= P; r += blockDim.x) tr.bound[r] = cut.begin(r, per_weight);
     lds_barrier();
-    if (tid < B) {  // (the first wave)
-        const int lo = incl - U, hi = incl - 1;
-        tr.seq[tid] = lo;
-        const int first = U > 0 ? find_slot(tr.bound, P, lo) : 0;
-        tr.part0[tid] = first;
-        tr.parts[tid] = U > 0 ? find_slot(tr.bound, P, hi) - first + 1 : 0;
-    }
-    lds_barrier();
     return P;
 }
 // The sequence that tile t lies in: the last one that begins at or before it.
-__device__ __forceinline__ int sequence_of_tile(const TileRanges& tr, int B, int t) {
-    const int lane = threadIdx.x & 63;
-    return __popcll(__ballot(lane < B && tr.seq[lane < B ? lane : 0] <= t)) - 1;
+__device__ __forceinline__ int sequence_of_tile(const LaneSequence& sq, int B, int t) {
+    return __popcll(__ballot((int)(threadIdx.x & 63) < B && sq.tile0 <= t)) - 1;
+}
+// Ranges that sequence b meets: the first of them and their number (uniform).
+__device__ __forceinline__ int parts_of(const TileRanges& tr, int P, const LaneSequence& sq, int b, int& first) {
+    const int U = __builtin_amdgcn_readlane(sq.U, b), t0 = __builtin_amdgcn_readlane(sq.tile0, b);
+    first = 0;
+    if (U <= 0) return 0;
+    first = find_slot_wave(tr.bound, P, t0);
+    return find_slot_wave(tr.bound, P, t0 + U - 1) - first + 1;
 }
 // The range that the position-th group of workgroups takes: class 0's ranges first, then class 1's, ...
 template <int C>
