@@ -17,6 +17,8 @@
 #include "scores_common.hpp"
 #include "stream_kv.hpp"
 
+#include <type_traits>
+
 namespace ra {
 
 // Smallest piece a sequence's key set is cut into, in 32-token tiles (pieces of 4 and of 16 tiles measured slower).
@@ -86,12 +88,24 @@ void launch_plan(const AttnArgs& a, int unit_tokens, hipStream_t st) {
 
 // Generic kernel.  A unit is 16 tokens.  Scores: the wave is four rows of 16 lanes, row `grp` takes one
 // token at a time and lane `sub` owns D/16 channels of the key; four DPP adds finish a dot product.
-// Values are stored transposed in 16-token tiles ([D][16]), so for P.V lane `lane` owns channels
-// lane, lane + 64, ... and reads the 16 tokens of each with contiguous loads; the 16 x G probabilities
-// of the unit reach it as scalars (v_readlane), so P.V needs no cross-lane reduction.
+// Values are stored transposed in 16-token tiles ([D][16]).
+// BY TILE: a tile is read as it lies, 1 KB per load instruction: lane `lane` gets tokens 4 (lane % 4) .. + 3 of channels
+// lane / 4, 16 + lane / 4, ..., takes the weights of its four tokens (those of lane row lane % 4) from an LDS strip of its
+// wave's, and its sums over those tokens are added up over four neighbouring lanes at the very end.
+// Otherwise: lane `lane` owns channels lane, lane + 64, ... and reads the 16 tokens of each with contiguous loads; the 16 x G
+// probabilities of the unit reach it as scalars (v_readlane), so P.V needs no cross-lane reduction.  (Reading the 64 bytes of
+// one fp32 channel with four instructions a lane touches 64 lines with each of them, and with 128 channels the tiles of a
+// unit's waves do not stay in the 32 KB of L1 from the first to the last: 480 MB of keys and values, four heads per KV head,
+// 135 -> 102 microseconds by tile, two heads 145 -> 98.)
 // INLINE_PLAN (sequences of up to kGenericInlineRounds rounds): a workgroup builds its sequence's table itself, from one
 // round trip to the lists, and no planning kernel runs before it (3 microseconds and a launch of the smallest steps).
 constexpr int kGenericInlineRounds = 64;
+
+// 128 fp32 channels and up to four heads per KV head.  With eight the sums (64 registers a lane) leave two waves on a SIMD
+// instead of three and the kernel, which keeps one unit in flight, is slower (144 -> 162 microseconds); with 64 channels a
+// channel's 16 tokens of all lanes are half as many lines and mostly still in L1 (71 -> 74, small launches 18.4 -> 22.0).
+template <typename T, int D, int G>
+__host__ __device__ constexpr bool generic_by_tile() { return std::is_same<T, F32>::value && D == 128 && G <= 4; }
 
 template <typename T, int D, int G, bool PAGED, bool INLINE_PLAN>
 __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
@@ -99,8 +113,11 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
     using Ops = RowOps<T, EPL>;
     constexpr int WORDS = Ops::WORDS;
     constexpr int EB = Ops::ELEM_BYTES;
-    constexpr int DPL = D / 64;                 // channels per lane in the P.V phase
-    constexpr int VW = kUnitTokens * EB / 4;    // 32-bit words of one channel's 16 tokens
+    constexpr bool kByTile = generic_by_tile<T, D, G>();  // values as the tile lies
+    constexpr int DPL = kByTile ? D / 16 : D / 64;  // channels per lane in the P.V phase
+    constexpr int TPL = kByTile ? 4 : kUnitTokens;  // tokens per lane and channel there
+    constexpr int VW = kUnitTokens * EB / 4;        // 32-bit words of one channel's 16 tokens
+    __shared__ float4 weights[kByTile ? 4 : 1][kByTile ? G : 1][4];  // [wave][head][token / 4]
 
     extern __shared__ __align__(16) char smem[];
     const int b = blockIdx.z, g = blockIdx.y, s = blockIdx.x;
@@ -162,12 +179,27 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
     const int u_lo = (int)(((long long)U * s) / S_eff);
     const int u_hi = (int)(((long long)U * (s + 1)) / S_eff);
 
+    // Lane `sub`'s share of a row of keys or queries: by tile as 16-byte pieces, one of all lanes 256 contiguous bytes.
+    auto load_share = [&](const char* row) {
+        if constexpr (kByTile) {
+            Frag<WORDS> f;
+#pragma unroll
+            for (int i = 0; i < WORDS / 4; ++i) {
+                const Frag<4> piece = load_frag<4>(row + i * 256 + sub * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f.w[4 * i + e] = piece.w[e];
+            }
+            return f;
+        } else {
+            return load_frag<WORDS>(row + (size_t)sub * EPL * EB);
+        }
+    };
     uint32_t qw[G][WORDS];
     {
         const char* qp = reinterpret_cast<const char*>(a.q) + ((size_t)b * a.Hq + (size_t)g * G) * D * EB;
 #pragma unroll
         for (int h = 0; h < G; ++h) {
-            Frag<WORDS> f = load_frag<WORDS>(qp + ((size_t)h * D + sub * EPL) * EB);
+            const Frag<WORDS> f = load_share(qp + (size_t)h * D * EB);
 #pragma unroll
             for (int e = 0; e < WORDS; ++e) qw[h][e] = f.w[e];
         }
@@ -183,6 +215,8 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
     const char* kbase = reinterpret_cast<const char*>(vw.k);
     const char* vbase = reinterpret_cast<const char*>(vw.v);
 
+    // token of the unit that lane row grp takes in step j
+    auto token = [](int j, int grp) { return kByTile ? grp * 4 + j : j * 4 + grp; };
     for (int u = u_lo + wave, slot = -1; u < u_hi; u += 4) {
         if (slot < 0) slot = find_slot(tab.cum, n_slots, u);
         while (u >= tab.cum[slot + 1]) ++slot;
@@ -210,19 +244,20 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
         Frag<WORDS> kf[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int t = min(j * 4 + grp, ntok - 1);  // rows past the segment's end re-read its last row
-            kf[j] = load_frag<WORDS>(kp + (size_t)t * kstride + (size_t)sub * EPL * EB);
+            const int t = min(token(j, grp), ntok - 1);  // rows past the segment's end re-read its last row
+            kf[j] = load_share(kp + (size_t)t * kstride);
         }
-        // ---- values: 16 tokens of each of this lane's channels ---------------------------------------
-        float vf[DPL][kUnitTokens];
+        // ---- values -----------------------------------------------------------------------------------
+        float vf[DPL][TPL];
         if (is_cur) {  // token-major: strided gather (the current round is short)
 #pragma unroll
             for (int k = 0; k < DPL; ++k)
 #pragma unroll
-                for (int t = 0; t < kUnitTokens; ++t) {
-                    const int tt = min(tok0 + t, len - 1);
+                for (int t = 0; t < TPL; ++t) {
+                    const int tt = min(tok0 + (kByTile ? 4 * (lane & 3) + t : t), len - 1);
+                    const int channel = kByTile ? k * 16 + (lane >> 2) : lane + 64 * k;
                     const char* p = reinterpret_cast<const char*>(a.cur_v) +
-                                    ((((size_t)b * a.cur_cap + tt) * Hkv + g) * D + lane + 64 * k) * EB;
+                                    ((((size_t)b * a.cur_cap + tt) * Hkv + g) * D + channel) * EB;
                     if constexpr (EB == 4) vf[k][t] = *reinterpret_cast<const float*>(p);
                     else vf[k][t] = as_f32((uint32_t)*reinterpret_cast<const unsigned short*>(p) << 16);
                 }
@@ -239,15 +274,21 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
             }
 #pragma unroll
             for (int k = 0; k < DPL; ++k) {
-                Frag<VW> f = load_frag<VW>(vp + (size_t)(lane + 64 * k) * kUnitTokens * EB);
-                if constexpr (EB == 4) {
+                if constexpr (kByTile) {
+                    const Frag<4> f = load_frag<4>(vp + k * 1024 + lane * 16);
 #pragma unroll
-                    for (int t = 0; t < kUnitTokens; ++t) vf[k][t] = as_f32(f.w[t]);
+                    for (int t = 0; t < 4; ++t) vf[k][t] = as_f32(f.w[t]);
                 } else {
+                    Frag<VW> f = load_frag<VW>(vp + (size_t)(lane + 64 * k) * kUnitTokens * EB);
+                    if constexpr (EB == 4) {
 #pragma unroll
-                    for (int t = 0; t < kUnitTokens / 2; ++t) {
-                        vf[k][2 * t] = as_f32(f.w[t] << 16);
-                        vf[k][2 * t + 1] = as_f32(f.w[t] & 0xffff0000u);
+                        for (int t = 0; t < kUnitTokens; ++t) vf[k][t] = as_f32(f.w[t]);
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < kUnitTokens / 2; ++t) {
+                            vf[k][2 * t] = as_f32(f.w[t] << 16);
+                            vf[k][2 * t + 1] = as_f32(f.w[t] & 0xffff0000u);
+                        }
                     }
                 }
             }
@@ -260,7 +301,7 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float d = row16_sum(Ops::dot(kf[j].w, qw[h]));
-                sc[j] = (j * 4 + grp) < ntok ? d : -__builtin_inff();
+                sc[j] = token(j, grp) < ntok ? d : -__builtin_inff();
             }
             float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
             mx = xrow_max4(mx);
@@ -278,17 +319,37 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
 #pragma unroll
             for (int k = 0; k < DPL; ++k) acc[h][k] *= alpha;
         }
-        // ---- P.V: token (j, grp) lives in lane row grp; broadcast its probability as a scalar ---------------
+        if constexpr (kByTile) {
+            // ---- P.V: tokens 4 grp .. + 3 live in lane row grp; lane `lane` needs those of row lane % 4 ------------
+            __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
+            if (sub == 0)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+                for (int h = 0; h < G; ++h) weights[wave][h][grp] = make_float4(p[0][h], p[1][h], p[2][h], p[3][h]);
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int gr = 0; gr < 4; ++gr)
+            for (int h = 0; h < G; ++h) {
+                const float4 w = weights[wave][h][lane & 3];
 #pragma unroll
-                for (int h = 0; h < G; ++h) {
-                    const float pv = as_f32((uint32_t)__builtin_amdgcn_readlane((int)as_u32(p[j][h]), gr * 16));
-#pragma unroll
-                    for (int k = 0; k < DPL; ++k) acc[h][k] = __builtin_fmaf(pv, vf[k][j * 4 + gr], acc[h][k]);
+                for (int k = 0; k < DPL; ++k) {
+                    acc[h][k] = __builtin_fmaf(w.x, vf[k][0], acc[h][k]);
+                    acc[h][k] = __builtin_fmaf(w.y, vf[k][1], acc[h][k]);
+                    acc[h][k] = __builtin_fmaf(w.z, vf[k][2], acc[h][k]);
+                    acc[h][k] = __builtin_fmaf(w.w, vf[k][3], acc[h][k]);
                 }
+            }
+        } else {
+            // ---- P.V: token (j, grp) lives in lane row grp; broadcast its probability as a scalar ---------------
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int gr = 0; gr < 4; ++gr)
+#pragma unroll
+                    for (int h = 0; h < G; ++h) {
+                        const float pv = as_f32((uint32_t)__builtin_amdgcn_readlane((int)as_u32(p[j][h]), gr * 16));
+#pragma unroll
+                        for (int k = 0; k < DPL; ++k) acc[h][k] = __builtin_fmaf(pv, vf[k][j * 4 + gr], acc[h][k]);
+                    }
+        }
     }
 
     // ---- merge: lane rows (sum only; max is already wave-wide), then the four waves through LDS ---------------
@@ -304,7 +365,16 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(AttnArgs a) {
             sl[wave * G + h] = lv;
         }
 #pragma unroll
-        for (int k = 0; k < DPL; ++k) sacc[(wave * G + h) * D + lane + 64 * k] = acc[h][k];
+        for (int k = 0; k < DPL; ++k) {
+            if constexpr (kByTile) {
+                float v = acc[h][k];
+                v += dpp_mov<0xB1>(v);  // over the four lanes of the channel
+                v += dpp_mov<0x4E>(v);
+                if ((lane & 3) == 0) sacc[(wave * G + h) * D + k * 16 + (lane >> 2)] = v;
+            } else {
+                sacc[(wave * G + h) * D + lane + 64 * k] = acc[h][k];
+            }
+        }
     }
     __syncthreads();
     const size_t row0 = (size_t)b * a.Hq + (size_t)g * G;
