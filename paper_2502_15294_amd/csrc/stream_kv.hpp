@@ -34,6 +34,17 @@ __device__ __forceinline__ float row16_sum(float v) {
     v += dpp_mov<0x140>(v);  // row_mirror
     return v;
 }
+// Four sums over the 16 lanes of a row at once: lane i of the row ends with the total of d[i mod 4].  Eleven operations, where
+// four sums that end in every lane take sixteen, and what follows is one value a lane, not four.
+__device__ __forceinline__ float row16_sums(const float (&d)[4]) {
+    const bool odd = threadIdx.x & 1, upper = threadIdx.x & 2;
+    const float a = (odd ? d[1] : d[0]) + dpp_mov<0xB1>(odd ? d[0] : d[1]);  // quad_perm [1,0,3,2]
+    const float b = (odd ? d[3] : d[2]) + dpp_mov<0xB1>(odd ? d[2] : d[3]);
+    float v = (upper ? b : a) + dpp_mov<0x4E>(upper ? a : b);  // quad_perm [2,3,0,1]
+    v += dpp_mov<0x124>(v);                                    // row_ror:4
+    v += dpp_mov<0x128>(v);                                    // row_ror:8
+    return v;
+}
 // Maxima are ordinary float code on purpose.  The compiler inserts the wait states that the hardware leaves to
 // software (a vector instruction that reads the result of a matrix-core product still in flight, a DPP or lane-swap
 // instruction that reads a register just written), and it does so only for instructions it can see: an asm
