@@ -342,6 +342,17 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             }
         }
     }
+    // (in LDS for the items: kept in registers over the streaming loop they cost some, and the compiler's iterative-ilp schedule,
+    // which the tests compare with, crashes on 64 channels)
+    __shared__ int s_cut[INLINE_PLAN ? 64 : 1][3];  // [sequence]: first range, q, rem
+    if (INLINE_PLAN && by_sequence) {
+        if (wave == 0) {
+            s_cut[lane][0] = my_first;
+            s_cut[lane][1] = my_cut.q;
+            s_cut[lane][2] = my_cut.rem;
+        }
+        lds_barrier();
+    }
     const int n_items = n_ranges * inner;
     const bool long_ranges = total > (kMfmaMinUnits + 1) * n_ranges;
     if (blockIdx.x == 0)  // for the merge kernel: first record and number of records of every sequence
@@ -366,9 +377,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
         const int g = gi % Hkv, rowblock = gi / Hkv;
         int t_lo, t_hi, b;  // its tiles, and the sequence that holds the first of them
         if (INLINE_PLAN && by_sequence) {
-            b = __popcll(__ballot(lane < B && my_first <= range)) - 1;
-            const SeqCut c = {0, lane_get(my_cut.q, b), lane_get(my_cut.rem, b)};
-            const int j = range - lane_get(my_first, b);
+            b = __popcll(__ballot(lane < B && s_cut[lane][0] <= range)) - 1;
+            const SeqCut c = {0, uni(s_cut[b][1]), uni(s_cut[b][2])};
+            const int j = range - uni(s_cut[b][0]);
             t_lo = sps[b] + seq_cut_begin(c, j);
             t_hi = sps[b] + seq_cut_begin(c, j + 1);
         } else {
