@@ -139,14 +139,14 @@ __global__ __launch_bounds__(256) void scores_stream_kernel(ScoreArgs a) {
     // eight heads 290 -> 227.)
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-        const float m = vmax(vmax(vmax(sc[0][h], sc[1][h]), vmax(sc[2][h], sc[3][h])), kNegBig);
-        float M = vmax(m, dpp_mov<0xB1>(m));
-        M = xrow_max4(vmax(M, dpp_mov<0x4E>(M)));
-        const float Mc = M * a.c;
+        const float m = vmax(vmax(vmax(sc[0][h], sc[1][h]), vmax(sc[2][h], sc[3][h])), kNegBig), mc = m * a.c;
         float lv = 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (ntok[j] > 0) lv += fast_exp2(__builtin_fmaf(sc[j][h], a.c, -Mc));
+            if (ntok[j] > 0) lv += fast_exp2(__builtin_fmaf(sc[j][h], a.c, -mc));
+        float M = vmax(m, dpp_mov<0xB1>(m));
+        M = xrow_max4(vmax(M, dpp_mov<0x4E>(M)));
+        lv *= fast_exp2((m - M) * a.c);
         lv += dpp_mov<0xB1>(lv);
         lv += dpp_mov<0x4E>(lv);
         lv = xrow_sum4(lv);
