@@ -146,6 +146,24 @@ def lib() -> C.CDLL:
 _native = None
 
 
+class _WrongType(C.ArgumentError, TypeError):
+    """What ctypes raises for an argument that it does not convert; a TypeError by nature."""
+
+
+class _NotATensor(TypeError, AttributeError):
+    pass
+
+
+def _by_ctypes(function):
+    """`function`, a ctypes function of one argument, for objects that the extension module does not know itself."""
+    def convert(o):
+        try:
+            return function(o)
+        except C.ArgumentError as e:
+            raise _WrongType(str(e)) from None
+    return convert
+
+
 def _load_native():
     global _native
     L = lib()
@@ -153,7 +171,9 @@ def _load_native():
         from . import _binding
     except ImportError as e:
         raise ImportError(f"{_HERE}/_binding.so cannot be loaded ({e}): build it with `python -m paper_2502_15294_amd.build`") from e
-    _binding.setup(_check, *[C.cast(getattr(L, name), C.c_void_p).value for name in (
+    handle, scale = _binding.conversions()
+    _binding.setup(_check, C.c_void_p, ra_kv_view, ra_select_params, _by_ctypes(C.CFUNCTYPE(C.c_void_p, C.c_void_p)(handle)),
+                   _by_ctypes(C.CFUNCTYPE(C.c_float, C.c_float)(scale)), _WrongType, _NotATensor, *[C.cast(getattr(L, name), C.c_void_p).value for name in (
         "ra_round_scores", "ra_round_scores_select", "ra_round_scores_accumulate", "ra_selection_coverage",
         "ra_round_sparse_attn_decode", "ra_watershed_attn_decode", "ra_round_sparse_attn_prefill", "ra_watershed_attn_prefill")])
     _native = _binding

@@ -31,41 +31,42 @@ struct Functions {
 } fn;
 PyObject* on_error = nullptr;  // called with a status that is not RA_OK; raises
 PyObject* name_c = nullptr;    // "c"
+// What an argument may be is ctypes' rule, as for every other call of the package: structures by their type (only a
+// c_void_p is read as a handle, only a ra_kv_view as a view, ...), and whatever is not of the usual type goes to ctypes itself,
+// which converts or refuses it.
+PyObject *handle_type = nullptr, *view_type = nullptr, *params_type = nullptr;  // c_void_p, ra_kv_view, ra_select_params
+PyObject *to_handle = nullptr, *to_float = nullptr;                             // object -> int, object -> float by ctypes
+PyObject *wrong_type = nullptr, *not_a_tensor = nullptr;                        // exceptions
 
 // A Python error is set: leave the entry point.
 struct PythonError {};
 
+// A ctypes object's memory, if it is of `type`.
 template <typename T>
-T* address_of(PyObject* o, const char* what) {  // a ctypes object's memory; None is a null pointer
-    if (o == Py_None) return nullptr;
+T* address_of(PyObject* o, PyObject* type, const char* what) {
+    if (!PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(type))) {
+        PyErr_Format(wrong_type, "%s: %s expected, not %s", what, reinterpret_cast<PyTypeObject*>(type)->tp_name, Py_TYPE(o)->tp_name);
+        throw PythonError();
+    }
     Py_buffer buf;
     if (PyObject_GetBuffer(o, &buf, PyBUF_SIMPLE) != 0) throw PythonError();
     T* p = static_cast<T*>(buf.buf);
-    const bool fits = buf.len >= (Py_ssize_t)sizeof(T);
     PyBuffer_Release(&buf);  // the object itself is kept by the caller's reference
-    if (!fits) {
-        PyErr_Format(PyExc_TypeError, "%s: not the structure that the library takes", what);
-        throw PythonError();
-    }
     return p;
 }
 
-ra_ctx* context(PyObject* o) {
-    if (PyLong_Check(o)) {
-        void* p = PyLong_AsVoidPtr(o);
-        if (PyErr_Occurred()) throw PythonError();
-        return static_cast<ra_ctx*>(p);
-    }
-    void** p = address_of<void*>(o, "ctx");
-    return p ? static_cast<ra_ctx*>(*p) : nullptr;
-}
-
-void* stream_handle(PyObject* o) {
+void* handle(PyObject* o) {
     if (o == Py_None) return nullptr;
-    void* p = PyLong_AsVoidPtr(o);
+    if (PyLong_Check(o)) return reinterpret_cast<void*>(PyLong_AsUnsignedLongMask(o));
+    if (PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(handle_type))) return *address_of<void*>(o, handle_type, "handle");
+    PyObject* r = PyObject_CallOneArg(to_handle, o);
+    if (!r) throw PythonError();
+    void* p = r == Py_None ? nullptr : PyLong_AsVoidPtr(r);
+    Py_DECREF(r);
     if (PyErr_Occurred()) throw PythonError();
     return p;
 }
+ra_ctx* context(PyObject* o) { return static_cast<ra_ctx*>(handle(o)); }
 
 // The C view of a KVView; holds a reference to the structure while the call lasts.
 struct View {
@@ -74,11 +75,7 @@ struct View {
     explicit View(PyObject* view) : c(PyObject_GetAttr(view, name_c)), p(nullptr) {
         if (!c) throw PythonError();
         try {
-            p = address_of<ra_kv_view>(c, "view");
-            if (!p) {
-                PyErr_SetString(PyExc_TypeError, "view: not a KVView");
-                throw PythonError();
-            }
+            p = address_of<ra_kv_view>(c, view_type, "view");
         } catch (...) {
             Py_DECREF(c);
             throw;
@@ -93,7 +90,7 @@ struct View {
 const at::Tensor* tensor_or_null(PyObject* o) {
     if (o == Py_None) return nullptr;
     if (!THPVariable_Check(o)) {
-        PyErr_Format(PyExc_TypeError, "expected a torch.Tensor, not %s", Py_TYPE(o)->tp_name);
+        PyErr_Format(not_a_tensor, "expected a torch.Tensor, not %s", Py_TYPE(o)->tp_name);
         throw PythonError();
     }
     return &THPVariable_Unpack(o);
@@ -128,8 +125,18 @@ int second_size(PyObject* o) {  // tokens of the current round; 0 without one
     return t ? (int)t->size(1) : 0;
 }
 float scale_of(PyObject* o, int64_t d) {
-    if (o == Py_None) return (float)std::pow((double)d, -0.5);
-    const double v = PyFloat_AsDouble(o);
+    if (o == Py_None) {
+        if (d == 0) {
+            PyErr_SetString(PyExc_ZeroDivisionError, "no default scale without channels");
+            throw PythonError();
+        }
+        return (float)std::pow((double)d, -0.5);
+    }
+    if (PyFloat_Check(o)) return (float)PyFloat_AS_DOUBLE(o);
+    PyObject* r = PyObject_CallOneArg(to_float, o);
+    if (!r) throw PythonError();
+    const double v = PyFloat_AsDouble(r);
+    Py_DECREF(r);
     if (v == -1.0 && PyErr_Occurred()) throw PythonError();
     return (float)v;
 }
@@ -180,7 +187,7 @@ PyObject* scores(PyObject* const* a) {
     const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), R = view->R_max;
     const Output ph(a[6], {B, Hq, R}, kF32, q), p(a[7], {B, R}, kF32, q);
     ra_ctx* ctx = context(a[0]);
-    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[4]);
+    void *st = handle(a[1]), *qp = data(q), *ck = data(a[4]);
     float *php = ph.ptr<float>(), *pp = p.ptr<float>();
     const int cur = second_size(a[4]);
     const float scale = scale_of(a[5], q.size(3));
@@ -196,8 +203,8 @@ PyObject* scores_select(PyObject* const* a) {
     const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), R = view->R_max;
     const Output ph(a[7], {B, Hq, R}, kF32, q), p(a[8], {B, R}, kF32, q), sel(a[9], {B, R}, kI32, q), n(a[10], {B}, kI32, q);
     ra_ctx* ctx = context(a[0]);
-    const ra_select_params* params = address_of<ra_select_params>(a[4], "params");
-    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[5]);
+    const ra_select_params* params = address_of<ra_select_params>(a[4], params_type, "params");
+    void *st = handle(a[1]), *qp = data(q), *ck = data(a[5]);
     float *php = ph.ptr<float>(), *pp = p.ptr<float>();
     int32_t *sp = sel.ptr<int32_t>(), *np = n.ptr<int32_t>();
     const int cur = second_size(a[5]);
@@ -212,6 +219,10 @@ PyObject* scores_accumulate(PyObject* const* a) {
     want_dims(q, 4);
     const View view(a[3]);
     const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), R = view->R_max;
+    if (a[4] != Py_None && !THPVariable_Check(a[4])) {
+        PyErr_SetString(PyExc_AssertionError, "acc must be a tensor");
+        throw PythonError();
+    }
     const at::Tensor& acc = tensor(a[4]);
     if (acc.scalar_type() != kF32 || acc.sizes() != at::IntArrayRef({B, Hq, R})) {
         PyErr_SetString(PyExc_AssertionError, "acc must be float32 [B, Hq, R_max]");
@@ -219,7 +230,7 @@ PyObject* scores_accumulate(PyObject* const* a) {
     }
     const Output ph(a[7], {B, Hq, R}, kF32, q), p(a[8], {B, R}, kF32, q);
     ra_ctx* ctx = context(a[0]);
-    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[5]);
+    void *st = handle(a[1]), *qp = data(q), *ck = data(a[5]);
     float *ap = static_cast<float*>(data(acc)), *php = ph.ptr<float>(), *pp = p.ptr<float>();
     const int cur = second_size(a[5]);
     const float scale = scale_of(a[6], q.size(3));
@@ -234,7 +245,7 @@ PyObject* coverage(PyObject* const* a) {
     const int64_t B = s.size(0), R = s.size(1);
     Output cov(Py_None, {B}, kF32, s);
     ra_ctx* ctx = context(a[0]);
-    void* st = stream_handle(a[1]);
+    void* st = handle(a[1]);
     const float* sp = static_cast<float*>(data(s));
     const int32_t *sel = data<int32_t>(a[3]), *n = data<int32_t>(a[4]);
     float* cp = cov.ptr<float>();
@@ -252,7 +263,7 @@ PyObject* decode(PyObject* const* a) {
     const int64_t B = q.size(0), Hq = q.size(1), d = q.size(2);
     const Output out(a[10], {B, Hq, d}, kF32, q), lse(a[11], {B, Hq}, kF32, q);
     ra_ctx* ctx = context(a[0]);
-    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[6]), *cv = data(a[7]);
+    void *st = handle(a[1]), *qp = data(q), *ck = data(a[6]), *cv = data(a[7]);
     const int32_t *sel = data<int32_t>(a[4]), *n = data<int32_t>(a[5]), *cl = data<int32_t>(a[8]);
     float *op = out.ptr<float>(), *lp = lse.ptr<float>();
     const int cap = second_size(a[6]);
@@ -270,7 +281,7 @@ PyObject* watershed_decode(PyObject* const* a) {
     const Output out(a[8], {B, Hq, d}, kF32, q), lse(a[9], {B, Hq}, kF32, q);
     const Output ph(a[10], {B, Hq, R}, kF32, q), p(a[11], {B, R}, kF32, q);
     ra_ctx* ctx = context(a[0]);
-    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[4]), *cv = data(a[5]);
+    void *st = handle(a[1]), *qp = data(q), *ck = data(a[4]), *cv = data(a[5]);
     const int32_t* cl = data<int32_t>(a[6]);
     float *op = out.ptr<float>(), *lp = lse.ptr<float>(), *php = ph.ptr<float>(), *pp = p.ptr<float>();
     const int cap = second_size(a[4]);
@@ -287,7 +298,7 @@ PyObject* prefill(PyObject* const* a) {
     const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), d = q.size(3);
     const Output out(a[9], {B, q_len, Hq, d}, kF32, q), lse(a[10], {B, q_len, Hq}, kF32, q);
     ra_ctx* ctx = context(a[0]);
-    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[6]), *cv = data(a[7]);
+    void *st = handle(a[1]), *qp = data(q), *ck = data(a[6]), *cv = data(a[7]);
     const int32_t *sel = data<int32_t>(a[4]), *n = data<int32_t>(a[5]);
     float *op = out.ptr<float>(), *lp = lse.ptr<float>();
     const int cur = second_size(a[6]);
@@ -305,7 +316,7 @@ PyObject* watershed_prefill(PyObject* const* a) {
     const Output out(a[7], {B, q_len, Hq, d}, kF32, q), lse(a[8], {B, q_len, Hq}, kF32, q);
     const Output ph(a[9], {B, Hq, R}, kF32, q), p(a[10], {B, R}, kF32, q);
     ra_ctx* ctx = context(a[0]);
-    void *st = stream_handle(a[1]), *qp = data(q), *ck = data(a[4]), *cv = data(a[5]);
+    void *st = handle(a[1]), *qp = data(q), *ck = data(a[4]), *cv = data(a[5]);
     float *op = out.ptr<float>(), *lp = lse.ptr<float>(), *php = ph.ptr<float>(), *pp = p.ptr<float>();
     const int cur = second_size(a[4]);
     const float scale = scale_of(a[6], d);
@@ -329,23 +340,41 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     END_HANDLE_TH_ERRORS
 }
 
-// setup(status handler, addresses in the order of Functions)
+// setup(status handler, c_void_p, ra_kv_view, ra_select_params, to_handle, to_float, wrong_type, not_a_tensor, addresses in the
+// order of Functions)
+PyObject** const kObjects[] = {&on_error, &handle_type, &view_type, &params_type, &to_handle, &to_float, &wrong_type, &not_a_tensor};
+constexpr Py_ssize_t kNumObjects = sizeof(kObjects) / sizeof(kObjects[0]), kNumFunctions = sizeof(Functions) / sizeof(void*);
 PyObject* setup(PyObject* const* a) {
-    void* p[sizeof(Functions) / sizeof(void*)];
-    for (size_t i = 0; i < sizeof(p) / sizeof(p[0]); ++i) {
-        p[i] = PyLong_AsVoidPtr(a[1 + i]);
+    void* p[kNumFunctions];
+    for (Py_ssize_t i = 0; i < kNumFunctions; ++i) {
+        p[i] = PyLong_AsVoidPtr(a[kNumObjects + i]);
         if (PyErr_Occurred()) throw PythonError();
     }
+    for (Py_ssize_t i = 1; i <= 3; ++i)
+        if (!PyType_Check(a[i])) {
+            PyErr_SetString(PyExc_TypeError, "setup: a type is expected");
+            throw PythonError();
+        }
     std::memcpy(&fn, p, sizeof(fn));
-    Py_INCREF(a[0]);
-    Py_XDECREF(on_error);
-    on_error = a[0];
+    for (Py_ssize_t i = 0; i < kNumObjects; ++i) {
+        Py_INCREF(a[i]);
+        Py_XSETREF(*kObjects[i], a[i]);
+    }
     Py_RETURN_NONE;
+}
+
+// What ctypes calls to convert an argument for us: the value comes back as it arrives.
+void* same_handle(void* p) { return p; }
+float same_float(float v) { return v; }
+PyObject* conversions(PyObject* const*) {
+    return Py_BuildValue("(NN)", PyLong_FromVoidPtr(reinterpret_cast<void*>(same_handle)),
+                         PyLong_FromVoidPtr(reinterpret_cast<void*>(same_float)));
 }
 
 #define RA_METHOD(NAME, N) {#NAME, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(entry<NAME, N>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    RA_METHOD(setup, 9),
+    RA_METHOD(setup, kNumObjects + kNumFunctions),
+    RA_METHOD(conversions, 0),
     RA_METHOD(scores, 8),
     RA_METHOD(scores_select, 11),
     RA_METHOD(scores_accumulate, 9),

@@ -1,6 +1,7 @@
 """The extension module that the compute calls go through: what it refuses, and how, without a GPU."""
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
@@ -64,6 +65,69 @@ def test_structures_are_checked():
 
     with pytest.raises(TypeError):
         ra.ra_round_scores(None, q, Other(), stream=0)
+
+
+class Adapter:
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+class Handle(ctypes.c_void_p):
+    pass
+
+
+class View(ra.ra_kv_view):
+    pass
+
+
+class Stream:
+    def __init__(self, handle):
+        self.cuda_stream = handle
+
+
+# what ctypes takes as a handle or a number, and what it refuses although it has memory of the right size; all handles are null,
+# so that the library itself ends every call that gets through
+@pytest.mark.parametrize("ctx", [0, 1 << 64, Handle(), ctypes.POINTER(ctypes.c_int)(), Adapter(None), Adapter(ctypes.c_void_p())])
+def test_handles_that_are_taken(ctx):
+    with pytest.raises(ra.RaError, match="ctx is NULL"):
+        ra.ra_round_scores(ctx, torch.zeros(1, 1, 4, 64), view(), stream=0)
+
+
+@pytest.mark.parametrize("ctx", [np.zeros(1, np.int64), view().c, ra.ra_problem(), bytearray(8), 1.5, [0]])
+def test_handles_that_are_refused(ctx):
+    with pytest.raises(ctypes.ArgumentError):
+        ra.ra_round_scores(ctx, torch.zeros(1, 1, 4, 64), view(), stream=0)
+    with pytest.raises(ctypes.ArgumentError):
+        ra.ra_round_scores(None, torch.zeros(1, 1, 4, 64), view(), stream=Stream(ctx))
+
+
+@pytest.mark.parametrize("given", [dict(stream=Stream(ctypes.c_void_p())), dict(stream=(1 << 64) + 8), dict(stream=0, scale=ctypes.c_float(1)),
+                                   dict(stream=0, scale=Adapter(1.0)), dict(stream=0, scale=np.float32(1)), dict(stream=0, scale=1)])
+def test_streams_and_scales_that_are_taken(given):
+    with pytest.raises(ra.RaError, match="ctx is NULL"):
+        ra.ra_round_scores(None, torch.zeros(1, 1, 4, 64), view(), **given)
+
+
+@pytest.mark.parametrize("scale", ["1", 1j, ctypes.c_double(1), pytest.param(10**400, id="huge")])
+def test_scales_that_are_refused(scale):
+    with pytest.raises(ctypes.ArgumentError):
+        ra.ra_round_scores(None, torch.zeros(1, 1, 4, 64), view(), scale=scale, stream=0)
+
+
+def test_structures_are_known_by_their_type():
+    q = torch.zeros(1, 1, 4, 64)
+    size = max(ctypes.sizeof(ra.ra_kv_view), ctypes.sizeof(ra.ra_select_params))
+    for params in (view().c, bytes(size), bytearray(size), ctypes.pointer(ra.make_select_params()), (ra.ra_select_params * 2)()):
+        with pytest.raises(TypeError):
+            ra.ra_round_scores_select(None, q, view(), params=params, stream=0)
+    v = view()
+    for c in (bytes(size), bytearray(size), None, ctypes.pointer(v.c), (ra.ra_kv_view * 1)(), np.zeros(size, np.uint8)):
+        v.c = c
+        with pytest.raises(TypeError):
+            ra.ra_round_scores(None, q, v, stream=0)
+    v.c = View.from_buffer_copy(view().c)
+    with pytest.raises(ra.RaError, match="ctx is NULL"):
+        ra.ra_round_scores(None, q, v, stream=0)
 
 
 @pytest.mark.gpu
