@@ -141,34 +141,65 @@ float scale_of(PyObject* o, int64_t d) {
     return (float)v;
 }
 
-// An output: the caller's tensor, or a new one.
+// An output: the caller's tensor, or a new one, which allocate() gets.
+template <typename T>
 struct Output {
-    PyObject* o;
-    Output(PyObject* given, at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) : o(given) {
-        if (given != Py_None) Py_INCREF(given);
-        else o = THPVariable_Wrap(at::empty(shape, at::TensorOptions().dtype(type).device(like.device())));
-        if (!o) throw PythonError();
+    PyObject* given;  // None: a new one
+    T* p;
+    at::DimVector shape;
+    at::TensorOptions options;
+    at::Tensor made;
+    Output(PyObject* o, at::IntArrayRef dims, const at::Tensor& like)
+        : given(o), p(data<T>(o)), shape(dims.begin(), dims.end()),
+          options(at::TensorOptions().dtype(c10::CppTypeToScalarType<T>::value).device(like.device())) {}
+    void allocate() {
+        if (given != Py_None) return;
+        made = at::empty(shape, options);
+        p = static_cast<T*>(made.data_ptr());
     }
-    Output(const Output&) = delete;
-    Output& operator=(const Output&) = delete;
-    ~Output() { Py_XDECREF(o); }
-    template <typename T>
-    T* ptr() const { return data<T>(o); }
+    PyObject* object() {  // a new reference
+        if (given == Py_None) return THPVariable_Wrap(made);
+        Py_INCREF(given);
+        return given;
+    }
 };
 
+template <typename T>
+PyObject* results(Output<T>& out) { return out.object(); }
 template <typename... Outputs>
-PyObject* results(const Outputs&... outs) {
-    return PyTuple_Pack((Py_ssize_t)sizeof...(Outputs), outs.o...);
+PyObject* results(Outputs&... outs) {
+    PyObject* tuple = PyTuple_New((Py_ssize_t)sizeof...(Outputs));
+    if (!tuple) return nullptr;
+    Py_ssize_t i = 0;
+    const auto add = [&](PyObject* o) {
+        if (o) PyTuple_SET_ITEM(tuple, i++, o);
+        return o != nullptr;
+    };
+    if ((add(outs.object()) && ...)) return tuple;
+    Py_DECREF(tuple);
+    return nullptr;
 }
 
-// The library call with the interpreter released, as ctypes does it; a status that is not RA_OK is raised.
-template <typename Call>
-void checked(Call call) {
+// The interpreter, given to the other threads until the end of the block, also by an exception.
+struct Released {
+    PyThreadState* state = PyEval_SaveThread();
+    Released() = default;
+    Released(const Released&) = delete;
+    Released& operator=(const Released&) = delete;
+    ~Released() { PyEval_RestoreThread(state); }
+};
+
+// New outputs and the library call, with the interpreter released: an allocation may have to get memory from the device, or
+// wait for it.  A status that is not RA_OK is raised.
+template <typename Call, typename... Outputs>
+PyObject* checked(Call call, Outputs&... outs) {
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = call();
-    Py_END_ALLOW_THREADS
-    if (rc == RA_OK) return;
+    {
+        const Released released;
+        (outs.allocate(), ...);
+        rc = call();
+    }
+    if (rc == RA_OK) return results(outs...);
     PyObject* r = PyObject_CallFunction(on_error, "i", rc);
     if (r) {
         Py_DECREF(r);
@@ -177,22 +208,18 @@ void checked(Call call) {
     throw PythonError();
 }
 
-constexpr at::ScalarType kF32 = at::kFloat, kI32 = at::kInt;
-
 // (ctx, stream, q, view, cur_k, scale, scores_head, scores)
 PyObject* scores(PyObject* const* a) {
     const at::Tensor& q = tensor(a[2]);
     want_dims(q, 4);
     const View view(a[3]);
     const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), R = view->R_max;
-    const Output ph(a[6], {B, Hq, R}, kF32, q), p(a[7], {B, R}, kF32, q);
+    Output<float> ph(a[6], {B, Hq, R}, q), p(a[7], {B, R}, q);
     ra_ctx* ctx = context(a[0]);
     void *st = handle(a[1]), *qp = data(q), *ck = data(a[4]);
-    float *php = ph.ptr<float>(), *pp = p.ptr<float>();
     const int cur = second_size(a[4]);
     const float scale = scale_of(a[5], q.size(3));
-    checked([&] { return fn.scores(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, php, pp); });
-    return results(ph, p);
+    return checked([&] { return fn.scores(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, ph.p, p.p); }, ph, p);
 }
 
 // (ctx, stream, q, view, params, cur_k, scale, scores_head, scores, sel_idx, n_sel)
@@ -201,16 +228,17 @@ PyObject* scores_select(PyObject* const* a) {
     want_dims(q, 4);
     const View view(a[3]);
     const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), R = view->R_max;
-    const Output ph(a[7], {B, Hq, R}, kF32, q), p(a[8], {B, R}, kF32, q), sel(a[9], {B, R}, kI32, q), n(a[10], {B}, kI32, q);
+    Output<float> ph(a[7], {B, Hq, R}, q), p(a[8], {B, R}, q);
+    Output<int32_t> sel(a[9], {B, R}, q), n(a[10], {B}, q);
     ra_ctx* ctx = context(a[0]);
     const ra_select_params* params = address_of<ra_select_params>(a[4], params_type, "params");
     void *st = handle(a[1]), *qp = data(q), *ck = data(a[5]);
-    float *php = ph.ptr<float>(), *pp = p.ptr<float>();
-    int32_t *sp = sel.ptr<int32_t>(), *np = n.ptr<int32_t>();
     const int cur = second_size(a[5]);
     const float scale = scale_of(a[6], q.size(3));
-    checked([&] { return fn.scores_select(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, params, php, pp, sp, np); });
-    return results(ph, p, sel, n);
+    return checked(
+        [&] { return fn.scores_select(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, params, ph.p, p.p, sel.p,
+                                      n.p); },
+        ph, p, sel, n);
 }
 
 // (ctx, stream, q, view, acc, cur_k, scale, scores_head, scores)
@@ -224,18 +252,19 @@ PyObject* scores_accumulate(PyObject* const* a) {
         throw PythonError();
     }
     const at::Tensor& acc = tensor(a[4]);
-    if (acc.scalar_type() != kF32 || acc.sizes() != at::IntArrayRef({B, Hq, R})) {
+    if (acc.scalar_type() != at::kFloat || acc.sizes() != at::IntArrayRef({B, Hq, R})) {
         PyErr_SetString(PyExc_AssertionError, "acc must be float32 [B, Hq, R_max]");
         throw PythonError();
     }
-    const Output ph(a[7], {B, Hq, R}, kF32, q), p(a[8], {B, R}, kF32, q);
+    Output<float> ph(a[7], {B, Hq, R}, q), p(a[8], {B, R}, q);
     ra_ctx* ctx = context(a[0]);
     void *st = handle(a[1]), *qp = data(q), *ck = data(a[5]);
-    float *ap = static_cast<float*>(data(acc)), *php = ph.ptr<float>(), *pp = p.ptr<float>();
+    float* ap = static_cast<float*>(data(acc));
     const int cur = second_size(a[5]);
     const float scale = scale_of(a[6], q.size(3));
-    checked([&] { return fn.scores_accumulate(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, ap, php, pp); });
-    return results(ph, p);
+    return checked(
+        [&] { return fn.scores_accumulate(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cur, scale, ap, ph.p, p.p); },
+        ph, p);
 }
 
 // (ctx, stream, scores, sel_idx, n_sel)
@@ -243,16 +272,12 @@ PyObject* coverage(PyObject* const* a) {
     const at::Tensor& s = tensor(a[2]);
     want_dims(s, 2);
     const int64_t B = s.size(0), R = s.size(1);
-    Output cov(Py_None, {B}, kF32, s);
+    Output<float> cov(Py_None, {B}, s);
     ra_ctx* ctx = context(a[0]);
     void* st = handle(a[1]);
     const float* sp = static_cast<float*>(data(s));
     const int32_t *sel = data<int32_t>(a[3]), *n = data<int32_t>(a[4]);
-    float* cp = cov.ptr<float>();
-    checked([&] { return fn.coverage(ctx, st, sp, sel, n, (int)B, (int)R, cp); });
-    PyObject* r = cov.o;
-    cov.o = nullptr;
-    return r;
+    return checked([&] { return fn.coverage(ctx, st, sp, sel, n, (int)B, (int)R, cov.p); }, cov);
 }
 
 // (ctx, stream, q, view, sel_idx, n_sel, cur_k, cur_v, cur_len, scale, out, lse)
@@ -261,15 +286,15 @@ PyObject* decode(PyObject* const* a) {
     want_dims(q, 3);
     const View view(a[3]);
     const int64_t B = q.size(0), Hq = q.size(1), d = q.size(2);
-    const Output out(a[10], {B, Hq, d}, kF32, q), lse(a[11], {B, Hq}, kF32, q);
+    Output<float> out(a[10], {B, Hq, d}, q), lse(a[11], {B, Hq}, q);
     ra_ctx* ctx = context(a[0]);
     void *st = handle(a[1]), *qp = data(q), *ck = data(a[6]), *cv = data(a[7]);
     const int32_t *sel = data<int32_t>(a[4]), *n = data<int32_t>(a[5]), *cl = data<int32_t>(a[8]);
-    float *op = out.ptr<float>(), *lp = lse.ptr<float>();
     const int cap = second_size(a[6]);
     const float scale = scale_of(a[9], d);
-    checked([&] { return fn.decode(ctx, st, qp, (int)Hq, view.p, sel, n, ck, cv, cl, cap, scale, op, lp); });
-    return results(out, lse);
+    return checked(
+        [&] { return fn.decode(ctx, st, qp, (int)Hq, view.p, sel, n, ck, cv, cl, cap, scale, out.p, lse.p); },
+        out, lse);
 }
 
 // (ctx, stream, q, view, cur_k, cur_v, cur_len, scale, out, lse, scores_head, scores)
@@ -278,16 +303,17 @@ PyObject* watershed_decode(PyObject* const* a) {
     want_dims(q, 3);
     const View view(a[3]);
     const int64_t B = q.size(0), Hq = q.size(1), d = q.size(2), R = view->R_max;
-    const Output out(a[8], {B, Hq, d}, kF32, q), lse(a[9], {B, Hq}, kF32, q);
-    const Output ph(a[10], {B, Hq, R}, kF32, q), p(a[11], {B, R}, kF32, q);
+    Output<float> out(a[8], {B, Hq, d}, q), lse(a[9], {B, Hq}, q);
+    Output<float> ph(a[10], {B, Hq, R}, q), p(a[11], {B, R}, q);
     ra_ctx* ctx = context(a[0]);
     void *st = handle(a[1]), *qp = data(q), *ck = data(a[4]), *cv = data(a[5]);
     const int32_t* cl = data<int32_t>(a[6]);
-    float *op = out.ptr<float>(), *lp = lse.ptr<float>(), *php = ph.ptr<float>(), *pp = p.ptr<float>();
     const int cap = second_size(a[4]);
     const float scale = scale_of(a[7], d);
-    checked([&] { return fn.watershed_decode(ctx, st, qp, (int)Hq, view.p, ck, cv, cl, cap, scale, op, lp, php, pp); });
-    return results(out, lse, ph, p);
+    return checked(
+        [&] { return fn.watershed_decode(ctx, st, qp, (int)Hq, view.p, ck, cv, cl, cap, scale, out.p, lse.p, ph.p,
+                                         p.p); },
+        out, lse, ph, p);
 }
 
 // (ctx, stream, q, view, sel_idx, n_sel, cur_k, cur_v, scale, out, lse)
@@ -296,15 +322,15 @@ PyObject* prefill(PyObject* const* a) {
     want_dims(q, 4);
     const View view(a[3]);
     const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), d = q.size(3);
-    const Output out(a[9], {B, q_len, Hq, d}, kF32, q), lse(a[10], {B, q_len, Hq}, kF32, q);
+    Output<float> out(a[9], {B, q_len, Hq, d}, q), lse(a[10], {B, q_len, Hq}, q);
     ra_ctx* ctx = context(a[0]);
     void *st = handle(a[1]), *qp = data(q), *ck = data(a[6]), *cv = data(a[7]);
     const int32_t *sel = data<int32_t>(a[4]), *n = data<int32_t>(a[5]);
-    float *op = out.ptr<float>(), *lp = lse.ptr<float>();
     const int cur = second_size(a[6]);
     const float scale = scale_of(a[8], d);
-    checked([&] { return fn.prefill(ctx, st, qp, (int)q_len, (int)Hq, view.p, sel, n, ck, cv, cur, scale, op, lp); });
-    return results(out, lse);
+    return checked(
+        [&] { return fn.prefill(ctx, st, qp, (int)q_len, (int)Hq, view.p, sel, n, ck, cv, cur, scale, out.p, lse.p); },
+        out, lse);
 }
 
 // (ctx, stream, q, view, cur_k, cur_v, scale, out, lse, scores_head, scores)
@@ -313,15 +339,16 @@ PyObject* watershed_prefill(PyObject* const* a) {
     want_dims(q, 4);
     const View view(a[3]);
     const int64_t B = q.size(0), q_len = q.size(1), Hq = q.size(2), d = q.size(3), R = view->R_max;
-    const Output out(a[7], {B, q_len, Hq, d}, kF32, q), lse(a[8], {B, q_len, Hq}, kF32, q);
-    const Output ph(a[9], {B, Hq, R}, kF32, q), p(a[10], {B, R}, kF32, q);
+    Output<float> out(a[7], {B, q_len, Hq, d}, q), lse(a[8], {B, q_len, Hq}, q);
+    Output<float> ph(a[9], {B, Hq, R}, q), p(a[10], {B, R}, q);
     ra_ctx* ctx = context(a[0]);
     void *st = handle(a[1]), *qp = data(q), *ck = data(a[4]), *cv = data(a[5]);
-    float *op = out.ptr<float>(), *lp = lse.ptr<float>(), *php = ph.ptr<float>(), *pp = p.ptr<float>();
     const int cur = second_size(a[4]);
     const float scale = scale_of(a[6], d);
-    checked([&] { return fn.watershed_prefill(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cv, cur, scale, op, lp, php, pp); });
-    return results(out, lse, ph, p);
+    return checked(
+        [&] { return fn.watershed_prefill(ctx, st, qp, (int)q_len, (int)Hq, view.p, ck, cv, cur, scale, out.p, lse.p,
+                                          ph.p, p.p); },
+        out, lse, ph, p);
 }
 
 // The Python function: argument count, C++ exceptions (an allocation that fails among them) turned into Python's.

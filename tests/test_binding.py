@@ -1,5 +1,7 @@
 """The extension module that the compute calls go through: what it refuses, and how, without a GPU."""
 import ctypes
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -128,6 +130,38 @@ def test_structures_are_known_by_their_type():
     v.c = View.from_buffer_copy(view().c)
     with pytest.raises(ra.RaError, match="ctx is NULL"):
         ra.ra_round_scores(None, q, v, stream=0)
+
+
+def test_other_threads_run_while_outputs_are_allocated():
+    """An allocation that takes long (here: one that is filled) does not hold the interpreter."""
+    heads, rounds = 2048, 131072  # 1 GB of round scores
+    v = view()
+    v.c.R_max = v.R_max = rounds
+    q = torch.zeros(1, 1, heads, 64)
+    stop, ticks = threading.Event(), []
+
+    def watch():
+        while not stop.is_set():
+            time.sleep(0.001)
+            ticks.append(time.perf_counter())
+
+    before = torch.are_deterministic_algorithms_enabled()
+    torch.use_deterministic_algorithms(True)  # torch.empty then fills what it returns
+    watcher = threading.Thread(target=watch)
+    watcher.start()
+    try:
+        while not ticks:
+            time.sleep(0.001)
+        t0 = time.perf_counter()
+        with pytest.raises(ra.RaError, match="ctx is NULL"):
+            ra.ra_round_scores(None, q, v, scale=1.0, stream=0)
+        t1 = time.perf_counter()
+    finally:
+        torch.use_deterministic_algorithms(before)
+        stop.set()
+        watcher.join()
+    during = [t0] + [t for t in ticks if t0 < t < t1] + [t1]
+    assert max(b - a for a, b in zip(during, during[1:])) < (t1 - t0) / 2, (len(during), t1 - t0)
 
 
 @pytest.mark.gpu
