@@ -54,6 +54,7 @@ struct AttnArgs {
     int max_ranges;   // most ranges the batch's key tiles are cut into
     int shape_units;  // shortest range the launch shape and the records have room for (mfma_decode_shape)
     int range_skew;   // in 1/1000: how much more than half of the tiles the first half of the ranges gets (see RangeCut)
+    int spread_longest;  // most tiles of a sequence in a launch of ranges that short
     int num_cu;       // compute units of the device (many-row kernel)
     int plan_inline;  // many-row kernel: it plans itself, no planning kernel ran
     int slots;        // ... and cuts the batch into at most so many ranges
@@ -81,7 +82,7 @@ int attn_min_units();  // smallest piece of a sequence's key set, in 32-token ti
 
 // bf16, d = 128 (one query token: also 64), Hq/Hkv <= 16, up to 32 query rows per KV head: matrix-core streaming
 // kernel, one wavefront per (range of the batch's key tiles, KV head, block of 16 query rows).
-int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st);
+int launch_attn_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st);
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st);  // ... and its second step
 // Same operands, many query rows per KV head: the waves own different rows and share key tiles through LDS.
 int launch_attn_prefill_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st);
@@ -97,8 +98,7 @@ inline bool attn_mfma_plans_inline(int B, int R_max) {
 }
 // Launch shape and scratch of that kernel.  `max_tiles` bounds the 32-token key tiles of the whole batch.
 constexpr int kMfmaMinUnits = 4;     // shortest range in key tiles (two tiles are in flight per wave; ranges of 2 and of 8 measured no better)
-constexpr int kMfmaSpreadUnits = 2;  // ... and while the launch has waves to spare for all of them
-constexpr int kMfmaSpreadLongest = 384;  // ... and no sequence has more tiles than this
+constexpr int kMfmaSpreadUnits = 2;  // ... and while the launch has waves to spare for all of them and the merge is quick (spread_longest)
 struct MfmaDecodeShape {
     int n_rowblocks, inner, grid, max_ranges, records;
     size_t rec_bytes, ml_bytes;

@@ -304,18 +304,16 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     // While every range of two tiles still gets a wave of its own the ranges are that short: one round trip to memory
     // instead of two (one dialogue's step, 45 tiles: 14.2 -> 11.4 microseconds).  With more work than that the shorter ranges
     // only add records (8 dialogues, 480 tiles: 18.7 -> 19.6).  And the records of one sequence must not cost the merge more
-    // than that.  (Whole call, ranges of four and of two tiles: 65 tiles of 8 rows 15.6 and 13.1 microseconds, 193 16.5 and
-    // 15.5, 241 16.6 and 16.4; of 16 rows 65 tiles 15.5 and 12.8, 241 16.3 and 14.7, 481 17.5 and 17.0, twice 481 18.2 and
-    // 18.9, 801 19.6 and 20.9; 64 channels, 97 tiles of 4 rows 12.9 and 11.4.)
+    // than that (spread_longest).
     bool spread = (unsigned)total <= kMfmaSpreadUnits * (gridDim.x * 4u / (unsigned)inner);
-    if (spread && total > kMfmaSpreadLongest) {
+    if (spread && total > a.spread_longest) {
         float most = 0.f;  // tiles of the longest sequence (exact: fewer than 2^24)
         for (int b = lane; b < B; b += 64) most = vmax(most, (float)sU[b]);
         most = vmax(most, dpp_mov<0xB1>(most));
         most = vmax(most, dpp_mov<0x4E>(most));
         most = vmax(most, dpp_mov<0x141>(most));
         most = xrow_max4(vmax(most, dpp_mov<0x140>(most)));
-        spread = uni((int)most) <= kMfmaSpreadLongest;
+        spread = uni((int)most) <= a.spread_longest;
     }
     const int min_units = spread ? kMfmaSpreadUnits : a.min_units;
     const RangeCut cut = range_cut((unsigned)total, min_units, a.max_ranges, a.range_skew);
@@ -758,7 +756,12 @@ static void launch_attn_mfma_d(const AttnArgs& a, bool paged, const MfmaDecodeSh
 #undef RA_ATTN_CASE
 }
 
-int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) {
+static MergeShape merge_shape_of(const AttnArgs& a, const MfmaDecodeShape& s, int num_cu) {
+    const int rows = a.q_len * a.G;
+    return merge_shape(a.view.B * s.inner, rows < 16 ? rows : 16, num_cu);
+}
+
+int launch_attn_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st) {
     const int rows_total = a.q_len * a.G;
     const int B = a.view.B, Hkv = a.view.Hkv, D = a.view.d;
     if (a.G > 16) return fail(RA_ERR_UNSUPPORTED, "attention: Hq / Hkv = %d exceeds 16", a.G);
@@ -766,28 +769,22 @@ int launch_attn_mfma(const AttnArgs& a, bool paged, int num_cu, hipStream_t st) 
     const MfmaDecodeShape s =
         mfma_decode_shape(num_cu, B, Hkv, D, rows_total, mfma_max_tiles(B, a.max_tokens, a.view.R_max, a.cur_cap), a.shape_units);
     if (a.max_ranges != s.max_ranges) return fail(RA_ERR_INVALID_ARG, "attention: launch shape mismatch");
+    a.spread_longest = spread_longest(merge_shape_of(a, s, num_cu));
     if (D == 128) launch_attn_mfma_d<128>(a, paged, s, st);
     else launch_attn_mfma_d<64>(a, paged, s, st);
     return RA_OK;
 }
 
-// A workgroup for every row while they are at most four to a compute unit: few sequences are cut into many records each, and
-// one workgroup walking them for eight rows took most of the call (whole decode call, in microseconds: one dialogue of 100
-// rounds of 600 tokens, 30 % kept, 2 KV heads of 16 rows 87.5 -> 19.1, of 200 rounds, 8 KV heads of 4 rows 49.3 -> 35.0;
-// four of 20 rounds 25.9 -> 20.6).  More rows than that have few records each, and a workgroup per row is mostly
-// its own start: 64 dialogues, 512 blocks of 8 rows, 30.5 with a workgroup for 8 rows, 34.3 with one per row; 80 blocks of 16
-// rows 37.3 and 38.0; 128 blocks of 8 rows 79.1 and 78.8.
-constexpr unsigned kMergeByRow = 1024;
 // Second step of the matrix-core kernel above: merges the records of the sequences that were cut.
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st) {
     const MfmaDecodeShape s = mfma_decode_shape(num_cu, a.view.B, a.view.Hkv, a.view.d, a.q_len * a.G,
                                                 mfma_max_tiles(a.view.B, a.max_tokens, a.view.R_max, a.cur_cap), a.shape_units);
     if (s.max_ranges <= 1) return;  // a single range never cuts a sequence
     const int rows = a.q_len * a.G < 16 ? a.q_len * a.G : 16;
-    const unsigned units = (unsigned)(a.view.B * s.inner);
+    const MergeShape m = merge_shape_of(a, s, num_cu);
     auto launch = [&](auto rows_per_workgroup, auto flight) {
         constexpr int ROWS = decltype(rows_per_workgroup)::value, FLIGHT = decltype(flight)::value;
-        const dim3 g(units, (rows + ROWS - 1) / ROWS), blk(256);
+        const dim3 g((unsigned)(a.view.B * s.inner), (rows + ROWS - 1) / ROWS), blk(256);
         if (a.view.d == 128) hipLaunchKernelGGL((merge_records_kernel<128, ROWS, FLIGHT>), g, blk, 0, st, a, s.n_rowblocks);
         else hipLaunchKernelGGL((merge_records_kernel<64, ROWS, FLIGHT>), g, blk, 0, st, a, s.n_rowblocks);
     };
@@ -795,10 +792,10 @@ void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st) {
     typedef std::integral_constant<int, 2> two;
     typedef std::integral_constant<int, 4> four;
     typedef std::integral_constant<int, 8> eight;
-    if (units * rows <= kMergeByRow) launch(one(), eight());
-    else if (rows <= 1) launch(one(), four());
-    else if (rows <= 2) launch(two(), four());
-    else if (rows <= 4) launch(four(), four());
+    if (m.flight == 8) launch(one(), eight());
+    else if (m.rows == 1) launch(one(), four());
+    else if (m.rows == 2) launch(two(), four());
+    else if (m.rows == 4) launch(four(), four());
     else launch(eight(), four());
 }
 

@@ -125,6 +125,32 @@ RA_HD inline int record_index(int r, int b) { return r + b; }
 // Upper bound of record_index + 1 for a launch.
 RA_HD inline int record_capacity(int max_ranges, int B) { return max_ranges + B; }
 
+// The second step: 256 threads merge `rows` rows of a (sequence, KV head, block of up to 16 query rows), d / 4 threads a row; the
+// groups of threads that this leaves take the records in turn, with `flight` of them in flight in every group.
+// A workgroup for every row while they are at most four to a compute unit: few sequences are cut into many records each, and
+// one workgroup walking them for eight rows took most of the call (whole decode call, in microseconds: one dialogue of 100
+// rounds of 600 tokens, 30 % kept, 2 KV heads of 16 rows 87.5 -> 19.1, of 200 rounds, 8 KV heads of 4 rows 49.3 -> 35.0;
+// four of 20 rounds 25.9 -> 20.6).  More rows than that have few records each, and a workgroup per row is mostly
+// its own start: 64 dialogues, 512 blocks of 8 rows, 30.5 with a workgroup for 8 rows, 34.3 with one per row; 80 blocks of 16
+// rows 37.3 and 38.0; 128 blocks of 8 rows 79.1 and 78.8.
+struct MergeShape {
+    int rows, flight;
+};
+RA_HD inline MergeShape merge_shape(int blocks, int rows, int num_cu) {
+    if ((long long)blocks * rows <= 4ll * num_cu) return {1, 8};
+    return {rows <= 1 ? 1 : rows <= 2 ? 2 : rows <= 4 ? 4 : 8, 4};
+}
+// Ranges are as short as two tiles (kMfmaSpreadUnits) while no sequence has more tiles than this: twice as many records as with
+// four must not cost the merge more than the shorter ranges save, and it walks them the more slowly the more rows a workgroup has.
+// (Whole call, ranges of four and of two tiles.  A workgroup for every row, one dialogue: 65 tiles of 8 rows 15.6 and 13.1
+// microseconds, 193 16.5 and 15.5, 241 16.6 and 16.4; of 16 rows 65 tiles 15.5 and 12.8, 241 16.3 and 14.7, 481 17.5 and 17.0,
+// twice 481 18.2 and 18.9, 801 19.6 and 20.9; 64 channels, 97 tiles of 4 rows 12.9 and 11.4.  Eight rows to one, a long dialogue
+// among short ones: 17 dialogues of 8 rows, 64 tiles 20.4 and 17.9, 96 21.8 and 20.5, 128 23.0 and 23.0, 240 28.8 and 32.9; 34 of
+// 16 rows, 64 tiles 17.8 and 17.5, 96 19.5 and 20.3, 384 30.8 and 43.3; 64 channels, 17 of 8 rows, 96 tiles 14.6 and 14.7, 384
+// 21.3 and 28.5, 64 of 8 rows, 128 18.5 and 17.1, 240 21.0 and 21.7.  Four: 64 dialogues, 192 tiles 24.1 and 23.3; 64 channels,
+// 192 18.2 and 16.6, 240 18.9 and 19.4, 384 21.2 and 22.6.)
+RA_HD inline int spread_longest(const MergeShape& m) { return m.rows <= 2 ? 384 : 768 / m.rows; }
+
 // Largest b in [0, n) with begin[b] <= t, for begin[0] <= t < begin[n] (begin non-decreasing).
 template <typename T>
 RA_HD inline int upper_slot(const T* begin, int n, long long t) {

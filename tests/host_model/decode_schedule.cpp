@@ -216,6 +216,19 @@ int main(int argc, char** argv) {
             if (!(r < cut.n_ranges && range_begin(cut, r) <= t && t < range_begin(cut, r + 1))) ++bad;
         }
     }
+    // the merge: its workgroups' threads are the rows' times a whole number of groups; where ranges may be of two tiles only, the
+    // longest sequence's records are at most twelve round trips of it (with 384 tiles, a workgroup of eight rows takes 48)
+    for (int c = 0; c < 4000; ++c) {
+        const int d = rng() % 2 ? 128 : 64, rows = 1 + (int)(rng() % 16), num_cu = 1 << (rng() % 9);
+        const int blocks = 1 + (int)(rng() % 1024) * (1 + (int)(rng() % 16));
+        const MergeShape m = merge_shape(blocks, rows, num_cu);
+        const int groups = 256 / (d / 4 * m.rows), in_flight = groups * m.flight;
+        if (groups < 1 || groups * (d / 4) * m.rows != 256) ++bad;
+        if (m.rows > 1 && m.rows / 2 >= rows) ++bad;  // more rows to a workgroup than there are
+        if ((blocks * rows <= 4 * num_cu) != (m.flight == 8)) ++bad;
+        const int longest = spread_longest(m), records = (longest + 1) / 2;
+        if (longest > 384 || longest < 64 || (records + in_flight - 1) / in_flight > 12) ++bad;
+    }
     if (cases >= 40 && by_sequence == 0) ++bad;  // the other cut was never met
     std::printf("%s: %d cases x 2 launches, seed %u, %d failed checks\n", bad ? "FAILED" : "ok", cases, seed, bad);
     return bad ? 1 : 0;

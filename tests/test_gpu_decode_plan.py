@@ -69,6 +69,15 @@ def test_many_rows_in_few_records(B, Hq, Hkv):
     check(w, [[0, 1]] * B, [0, B // 2, B - 1])
 
 
+# more rows than are merged by a workgroup each, one dialogue of as many tiles as still allow ranges of two, or of one more
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("B,Hq,Hkv,d,longest", [(17, 64, 8, 128, 96), (34, 32, 2, 128, 96), (64, 32, 8, 128, 191), (17, 64, 8, 64, 96), (64, 32, 8, 64, 192)])
+def test_a_long_dialogue_among_short_ones(B, Hq, Hkv, d, longest, more):
+    lens = [[32 * (longest + more) - 3]] + [[17]] * (B - 1)
+    w = make_workload("cfg2", B=B, Hq=Hq, Hkv=Hkv, d=d, lens=lens, n_relevant=0, cur_len=0)
+    check(w, [[0]] * B, [0, 1, B - 1])
+
+
 # dialogues cut each by itself (up to a twelfth as many as there may be ranges) and one more than that, some of them empty
 @pytest.mark.parametrize("B,Hq,Hkv,d", [(2, 16, 2, 128), (10, 32, 8, 128), (11, 32, 8, 128), (21, 32, 8, 64), (22, 32, 8, 64), (42, 16, 2, 128), (43, 16, 2, 128)])
 def test_dialogues_cut_each_by_itself(B, Hq, Hkv, d):
