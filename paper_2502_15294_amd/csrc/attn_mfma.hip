@@ -318,19 +318,17 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     const int min_units = spread ? kMfmaSpreadUnits : a.min_units;
     const RangeCut cut = range_cut((unsigned)total, min_units, a.max_ranges, a.range_skew);
     int n_ranges = (int)cut.n_ranges;
-    // Few sequences are cut each by itself (lane b: sequence b, its first range and its pieces) if that takes no more ranges
-    // than there may be, of no more than a tile more.  (Whole decode call: 8 dialogues of 20 rounds, 30 % kept, 30.6 -> 29.8
-    // microseconds, 3 of 33 rounds 22.4 -> 22.0; 5 of 20 rounds, paged, 23.7 -> 22.4; 16 of 24 rounds, 64 channels, 34.7 ->
-    // 33.5, 2 KV heads 26.0 -> 24.2.)  With more sequences the pieces come out uneven, and the launch waits for the longest:
-    // 16 dialogues, 128 ranges, 121.6 -> 122.7; 24, 256 ranges, 56.8 -> 58.0; 40 of a few tiles 16.0 -> 17.5.
+    // Few sequences with short ranges are cut each by itself (lane b: sequence b, its first range and its pieces) if that takes no
+    // more ranges than there may be (seq_cut_lengths).
     bool by_sequence = false;
     int my_first = 0;
     SeqCut my_cut = {0, 0, 0};
-    if (INLINE_PLAN && B * kSeqCutRanges <= a.max_ranges) {
-        const int U = lane < B ? sU[lane] : 0, len = seq_cut_len((unsigned)total, min_units, a.max_ranges);
+    int len = 0;
+    if (const int tries = INLINE_PLAN ? seq_cut_lengths(B, D, (unsigned)total, min_units, a.max_ranges, &len) : 0) {
+        const int U = lane < B ? sU[lane] : 0;
 #pragma unroll
         for (int i = 0; i < kSeqCutTries; ++i) {
-            if (by_sequence) break;
+            if (by_sequence || i >= tries) break;
             my_cut = seq_cut(U, len + i);
             const int incl = wave_inclusive_sum(my_cut.n), n = __builtin_amdgcn_readlane(incl, 63);
             if (n <= a.max_ranges) {

@@ -87,8 +87,8 @@ RA_HD inline unsigned range_of_tile(const RangeCut& c, unsigned t) {
     return c.n_a + (u < big ? u / (c.q_b + 1) : c.rem_b + (u - big) / c.q_b);
 }
 
-// The other cut, for launches of short ranges: every sequence by itself, into pieces of at most `len` tiles that are equal to
-// within one.  A range that goes on with the next sequence starts twice, queries, segment table and first tile one memory
+// The other cut, for few sequences and short ranges: every sequence by itself, into pieces of at most `len` tiles that are equal
+// to within one.  A range that goes on with the next sequence starts twice, queries, segment table and first tile one memory
 // round trip behind the other, and with a few tiles a range that is the longest wave of the launch.  Piece j of sequence b is
 // range first(b) + j, first(b) being the number of pieces of the sequences before b; records as above.
 struct SeqCut {
@@ -102,14 +102,26 @@ RA_HD inline SeqCut seq_cut(int tiles, int len) {
     return c;
 }
 RA_HD inline int seq_cut_begin(const SeqCut& c, int j) { return j * c.q + (j < c.rem ? j : c.rem); }
-// Piece length to try first: as many pieces as there may be ranges, if every sequence were a whole number of them.  A tile
-// more is tried after it; a range that starts twice costs more than that.
-RA_HD inline int seq_cut_len(unsigned total, int min_units, int max_ranges) {
-    const int len = (int)((total + (unsigned)max_ranges - 1) / (unsigned)max_ranges);
-    return len < min_units ? min_units : len;
-}
+// The lengths to try, *len and up to two of them, until there are no more pieces than ranges; 0: the batch is cut as one list.
+// The first is that of the one list's longest range: as many pieces as there may be ranges, if every sequence were a whole
+// number of them.  A tile more is worth it while it costs less than a second start.  (Whole decode call, batch cut as one list
+// and by sequence, tiles per range in brackets, 128 channels.  At the first length: 8 dialogues [4.2] 23.4 and 22.5 microseconds,
+// [6.2] 27.4 and 26.4, [8.3] 32.2 and 32.1; 10 of 64 heads [8.3] 34.4 and 33.2, [12.5] 42.7 and 42.3; 42 of 2 KV heads [4.2] 26.4
+// and 24.3, [13] 45.5 and 45.1; longer ones alike or slower, 8 dialogues [18] 55.6 and 56.0.  At the second: 8 dialogues [5] 25.1
+// and 24.2, [8.9] 33.5 and 34.0, [15] 47.8 and 48.5.  And a length that does not fit costs 0.3 in the prologue.  64 channels:
+// 42 dialogues [4.2] 25.4 and 23.9; 16 [5.3] 24.6 and 24.6, [7.5] 29.1 and 29.6, [11.3] 39.5 and 40.3.  With less than twelve
+// possible ranges for a sequence the pieces come out uneven, and the launch waits for the longest: 16 dialogues, 128 ranges,
+// 121.6 -> 122.7; 24, 256 ranges, 56.8 -> 58.0; 40 of a few tiles 16.0 -> 17.5.)
 constexpr int kSeqCutTries = 2;
-constexpr int kSeqCutRanges = 12;  // ranges there may be for every sequence of a batch that is cut this way, at least
+constexpr int kSeqCutRanges = 12;      // ranges there may be for every sequence, at least
+constexpr int kSeqCutTwice = 5;        // longest first length with a second
+RA_HD constexpr int seq_cut_longest(int d) { return d == 64 ? 5 : 12; }  // longest first length
+RA_HD inline int seq_cut_lengths(int B, int d, unsigned total, int min_units, int max_ranges, int* len) {
+    if (B * kSeqCutRanges > max_ranges || total > (unsigned)(seq_cut_longest(d) * max_ranges)) return 0;
+    *len = (int)((total + (unsigned)max_ranges - 1) / (unsigned)max_ranges);
+    if (*len < min_units) *len = min_units;
+    return *len > kSeqCutTwice ? 1 : 2;
+}
 
 // Records of a sequence with tiles [t_lo, t_hi), t_hi > t_lo.
 struct SeqParts {

@@ -12,8 +12,9 @@
 //   * for a sequence cut into n parts the merge step (a second kernel, after all waves have exited) finds exactly
 //     the n records first .. first + n - 1 that the streaming kernel announced, and they add up to the sequence.
 //
-// Built with -DPLANT_RECORD_BY_RANGE or -DPLANT_SKIP_LAST_ITEM the model carries a planted mistake and must fail:
-// that is how the test shows that the checks can fail at all.
+// Built with -DPLANT_RECORD_BY_RANGE, -DPLANT_SKIP_LAST_ITEM, -DPLANT_PIECES_WITHOUT_REMAINDER or -DPLANT_ONE_PIECE_TOO_FEW
+// (the last two: sequences cut each by itself) the model carries a planted mistake and must fail: that is how the test shows
+// that the checks can fail at all.
 //
 // usage: decode_schedule [seed] [cases]     exit status 0 = every check passed
 #include <atomic>
@@ -45,14 +46,29 @@ static void fail(Launch& L, const char* what, int a, int b) {
     if (L.errors.fetch_add(1) < 5) std::fprintf(stderr, "  model check failed: %s (%d, %d)\n", what, a, b);
 }
 
-static void choose_cut(Launch& L, bool allowed) {
-    const int len = seq_cut_len((unsigned)L.begin[L.B], L.min_units, L.max_ranges);
-    for (int i = 0; i < kSeqCutTries && allowed && !L.by_sequence; ++i) {
+// Piece j of a sequence that is cut by itself begins at this tile of it.
+static int piece_begin(const SeqCut& c, int j) {
+#ifdef PLANT_PIECES_WITHOUT_REMAINDER
+    return j * c.q;  // planted mistake: the tiles that are left over after equal pieces are streamed by nobody
+#else
+    return seq_cut_begin(c, j);
+#endif
+}
+
+static void choose_cut(Launch& L, int d) {
+    int len = 0;
+    const int tries = L.B <= 64 ? seq_cut_lengths(L.B, d, (unsigned)L.begin[L.B], L.min_units, L.max_ranges, &len) : 0;
+    if (tries > kSeqCutTries || (tries > 0 && len < L.min_units)) fail(L, "lengths to try", tries, len);
+    for (int i = 0; i < tries && !L.by_sequence; ++i) {
         L.cuts.clear();
         L.first.assign(1, 0);
         for (int b = 0; b < L.B; ++b) {
             L.cuts.push_back(seq_cut(L.U[b], len + i));
+#ifdef PLANT_ONE_PIECE_TOO_FEW
+            L.first.push_back(L.first.back() + (L.cuts.back().n > 1 ? L.cuts.back().n - 1 : L.cuts.back().n));  // planted mistake
+#else
             L.first.push_back(L.first.back() + L.cuts.back().n);
+#endif
         }
         L.by_sequence = L.first.back() <= L.max_ranges;
         for (int b = 0; b < L.B && L.by_sequence; ++b)
@@ -60,6 +76,11 @@ static void choose_cut(Launch& L, bool allowed) {
                 const int n = seq_cut_begin(L.cuts[b], j + 1) - seq_cut_begin(L.cuts[b], j);
                 if (n < 1 || n > len + i) fail(L, "a piece is empty or too long", b, n);
             }
+        // no longer than the longest range of the one list, or by a tile where that is still short
+        const RangeCut list = range_cut((unsigned)L.begin[L.B], L.min_units, L.max_ranges);
+        const int longest = (int)range_begin(list, 1);
+        if (L.by_sequence && len + i > longest && len + i > kSeqCutTwice + 1 && len > L.min_units) fail(L, "pieces longer than the list's ranges", len + i, longest);
+        if (L.by_sequence && len + i > seq_cut_longest(d) + 1) fail(L, "a long range cut by sequence", len, i);
     }
 }
 
@@ -84,8 +105,8 @@ static void wave(Launch& L, int w, unsigned jitter) {
         if (L.by_sequence) {
             b = -1;
             for (int k = 0; k < L.B; ++k) b += L.first[k] <= range ? 1 : 0;
-            t_lo = L.begin[b] + seq_cut_begin(L.cuts[b], range - L.first[b]);
-            t_hi = L.begin[b] + seq_cut_begin(L.cuts[b], range - L.first[b] + 1);
+            t_lo = L.begin[b] + piece_begin(L.cuts[b], range - L.first[b]);
+            t_hi = L.begin[b] + piece_begin(L.cuts[b], range - L.first[b] + 1);
         } else {
             t_lo = (int)range_begin(cut, range);
             t_hi = (int)range_begin(cut, range + 1);
@@ -148,8 +169,10 @@ int main(int argc, char** argv) {
     int bad = 0, by_sequence = 0;
     for (int c = 0; c < cases; ++c) {
         // mostly small batches; every tenth case a batch beyond one wavefront's lanes, up to the library's limit
-        const int B = c % 10 == 9 ? 65 + (int)(rng() % 960) : 1 + (int)(rng() % 24);
-        const int inner = 1 + (int)(rng() % 4), n_waves = 1 + (int)(rng() % 48);
+        // and every third of few sequences with the ranges to be cut each by itself
+        const bool few = c % 3 == 1;
+        const int B = few ? 1 + (int)(rng() % 5) : c % 10 == 9 ? 65 + (int)(rng() % 960) : 1 + (int)(rng() % 24);
+        const int inner = 1 + (int)(rng() % 4), n_waves = few ? 4 * 12 * B : 1 + (int)(rng() % 48);
         const int min_units = 1 + (int)(rng() % 4);
         int max_ranges = n_waves * (1 + (int)(rng() % 3)) / inner;  // also more ranges than waves: several items per wave
         if (max_ranges < 1) max_ranges = 1;
@@ -169,7 +192,7 @@ int main(int argc, char** argv) {
             }
             L.begin.assign(B + 1, 0);
             for (int b = 0; b < B; ++b) L.begin[b + 1] = L.begin[b] + L.U[b];
-            if (L.begin[B] > 0) choose_cut(L, B <= 64 && c % 4 < 2);
+            if (L.begin[B] > 0) choose_cut(L, c % 2 ? 64 : 128);
             by_sequence += L.by_sequence;
             std::vector<std::thread> th;
             for (int w = 0; w < n_waves; ++w) th.emplace_back(wave, std::ref(L), w, (unsigned)rng());

@@ -87,3 +87,14 @@ def test_dialogues_cut_each_by_itself(B, Hq, Hkv, d):
     lens[B // 2] = [0, 0, 0, 0]
     w = make_workload("cfg2", B=B, Hq=Hq, Hkv=Hkv, d=d, lens=lens, n_relevant=0, cur_len=0)
     check(w, [[0, 1, 3]] * B, [b for b in (0, 1, B - 1) if b != B // 2])
+
+
+# ... and as far as their ranges are short: tiles of the batch for each range that there may be, and one more tile, which is cut
+# as one list; 5 tiles and two dialogues of unequal length take the second of the lengths that are tried
+@pytest.mark.parametrize("d,per_range,more", [(128, 5, 0), (128, 12, 0), (128, 12, 1), (64, 5, 0), (64, 5, 1)])
+def test_dialogues_cut_each_by_itself_while_ranges_are_short(d, per_range, more):
+    ranges = torch.cuda.get_device_properties(0).multi_processor_count * (4 if d == 128 else 8) // 8
+    tiles = per_range * ranges + more
+    first = 32 * (tiles // 3) - 7
+    w = make_workload("cfg2", B=2, Hq=32, Hkv=8, d=d, lens=[[first], [32 * (tiles - tiles // 3) - 30]], n_relevant=0, cur_len=0)
+    check(w, [[0], [0]], [0, 1])

@@ -30,7 +30,7 @@ def test_every_wave_exits_every_tile_streamed_once_every_cut_sequence_has_its_re
     assert r.returncode == 0, r.stdout + r.stderr
 
 
-@pytest.mark.parametrize("plant", ["-DPLANT_SKIP_LAST_ITEM", "-DPLANT_RECORD_BY_RANGE"])
+@pytest.mark.parametrize("plant", ["-DPLANT_SKIP_LAST_ITEM", "-DPLANT_RECORD_BY_RANGE", "-DPLANT_PIECES_WITHOUT_REMAINDER", "-DPLANT_ONE_PIECE_TOO_FEW"])
 def test_the_model_fails_when_a_mistake_is_planted(tmp_path, plant):
     exe = _build(tmp_path, "planted", plant)
     r = subprocess.run([exe, "1", "150"], capture_output=True, text=True, timeout=300)
