@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "tile_ranges.hpp"
 
 namespace ra {
 
@@ -94,7 +95,7 @@ inline size_t attn_mfma_inline_bytes(int B, int R_max) {
     return (size_t)B * R_max * 24 + (size_t)B * (R_max + 2) * 4 + (size_t)B * 16 + 16;
 }
 inline bool attn_mfma_plans_inline(int B, int R_max) {
-    return B <= 64 && (long long)B * R_max <= 1024;  // at most 29 KB of LDS beside the 17 KB of score staging
+    return B <= kInlineBatch && (long long)B * R_max <= kInlineRounds;  // at most 29 KB of LDS beside the 17 KB of score staging
 }
 // Launch shape and scratch of that kernel.  `max_tiles` bounds the 32-token key tiles of the whole batch.
 constexpr int kMfmaMinUnits = 4;     // shortest range in key tiles (two tiles are in flight per wave; ranges of 2 and of 8 measured no better)

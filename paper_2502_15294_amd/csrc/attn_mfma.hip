@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
 
     // ---- prologue (the only part with barriers): tiles of every sequence, their prefix over the batch ----------
     if constexpr (INLINE_PLAN) {
-        // The batch's lists (at most 64 sequences, 1024 rounds) in one memory round trip: everything a thread reads is asked
+        // The batch's lists (kInlineBatch sequences, kInlineRounds rounds at most) in one memory round trip: everything a thread reads is asked
         // for before any of it is used.  With a loop over the entries, and the counts behind it, this was a round trip per
         // 256 rounds and one more; and with the prefixes below taken by one thread per sequence and one for the batch, a
         // dependent LDS operation per round and per sequence.  (Whole decode call: 64 dialogues of 10 rounds 31.9 -> 29.4
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                 }
             }
         };
-        if (BR > 256) read_lists(std::integral_constant<int, 4>());
+        if (BR > 256) read_lists(std::integral_constant<int, kInlineRounds / 256>());
         else if (BR > 0) read_lists(std::integral_constant<int, 1>());
         if (tid < B) {
             const int n_rounds = min(max(c_rounds, 0), vw.R_max);

@@ -370,7 +370,6 @@ __device__ __forceinline__ int find_slot(const T* cum, int n, T u) {
 // ---- planning inside a launch, for small batches ------------------------------------------------------
 // The segment lists of the whole batch in LDS, read in one memory round trip: a kernel that has them needs no planning
 // kernel before it and no second trip for the tables that one would have written.
-constexpr int kInlineRounds = 1024;  // most sequences times R_max
 // A launch that plans itself must still hold as many workgroups on a compute unit as it has for one: the lists, 24 bytes per
 // (sequence, round), come on top of the table's.  (128-token question, one dialogue of 619 rounds: the score kernel, three
 // to a unit, 78.9 microseconds behind the planning kernel and 109.4 with its own plan while only two of that fitted; 618

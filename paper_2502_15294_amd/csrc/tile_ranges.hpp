@@ -31,7 +31,10 @@
 
 namespace ra {
 
-constexpr int kInlineBatch = 64;  // most sequences
+// Launches that plan themselves, questions and decode alike: a lane for every sequence, the lists in one pass of 256 threads.
+constexpr int kInlineBatch = 64;     // most sequences
+constexpr int kInlineRounds = 1024;  // most sequences times R_max
+static_assert(kInlineBatch <= 64 && kInlineRounds % 256 == 0, "what the planning code reads in one pass");
 constexpr int kMaxRanges = 1024;  // most ranges, whatever the launch
 
 template <int C>
