@@ -48,15 +48,15 @@ WORKLOADS = {
 # count).  RECORDED figures for the workload's own inputs at lambda = 1, copied from the files named below; they are
 # not measurements of the current run, and other lambda / alpha report null.
 RECORDED_TRAFFIC = {
-    ("cfg5", "ra_round_sparse_attn_decode"): 1195475329 + 6290229,
-    ("cfg2", "ra_round_sparse_attn_decode"): 49746404 + 1630784,
+    ("cfg5", "ra_round_sparse_attn_decode"): 1195397845 + 6290233,
+    ("cfg2", "ra_round_sparse_attn_decode"): 49768714 + 1831488,
 }
 TRAFFIC_SOURCES = {
     "cfg5": "profiles/kernel_traces_step_and_question.md",
     "cfg2": "profiles/kernel_traces_step_and_question.md",
 }
 MFMA_BUSY_SOURCE = "profiles/kernel_traces_step_and_question.md (rocprofv3 --pmc; recorded, not measured in this run)"
-RECORDED_MFMA_BUSY = {"scores_prefill_mfma_kernel": 0.416, "attn_prefill_mfma_kernel": 0.499}
+RECORDED_MFMA_BUSY = {"scores_prefill_mfma_kernel": 0.443, "attn_prefill_mfma_kernel": 0.497}
 
 
 def parse():
