@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "score_places.hpp"
 #include "tile_ranges.hpp"
 
 namespace ra {
@@ -44,9 +45,10 @@ struct AttnArgs {
     float* lse;       // [rows] or null
     // at the watershed layer only: natural-log sum-exp of the scaled logits of every score unit of a sequence's
     // table (history rounds in order, then the current round), [rows][n_tiles_max]; the unit is a 32-token key
-    // tile in the 16-row kernel and a 256-token chunk of a round in the many-row kernel; null otherwise
+    // tile in the 16-row kernel and what a piece has of a round in the many-row kernel; null otherwise
     float* tile_lse;
-    int n_tiles_max;
+    int n_tiles_max;     // row length of tile_lse
+    ScorePlaces places;  // many-row kernel: where its values lie
     // matrix-core kernel for up to 32 query rows per KV head (range schedule, see range_schedule.hpp): partial
     // results of the sequences that lie in several ranges
     float* rec_acc;   // [records][inner][16][D]   inner = Hkv * row blocks
@@ -88,7 +90,7 @@ void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st);  // ..
 // Same operands, many query rows per KV head: the waves own different rows and share key tiles through LDS.
 int launch_attn_prefill_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st);
 // ... which needs no planning kernel before it then (AttnArgs::plan_inline); the shape, min_units and S must be set
-bool attn_prefill_plans_inline(const AttnArgs& a, bool tile_lse, int num_cu);
+bool attn_prefill_plans_inline(const AttnArgs& a, int num_cu);
 // Small batches: the first kernel resolves the selection itself (every workgroup reads the whole batch's segment
 // lists in one memory round trip and keeps them in LDS), so that no planning kernel runs before it.
 inline size_t attn_mfma_inline_bytes(int B, int R_max) {

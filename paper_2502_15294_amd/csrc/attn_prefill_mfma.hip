@@ -16,10 +16,10 @@
 // merge kernel.
 //
 // At the watershed layer the same pass also yields the round scores' raw material (TILE_LSE): one log-sum-exp
-// per (query row, 256-token chunk of a round), the unit of the stand-alone score pass.  A row's running sum is
-// never restarted for that: the chunk's share is the difference of the running sum between the chunk's ends (a
+// per query row and part of a round that a piece holds, as in the stand-alone score pass (score_places.hpp).  A row's
+// running sum is never restarted for that: the part's share is the difference of the running sum between the part's ends (a
 // mark that is rescaled together with the sum), exact to a few ulp of the sum, i.e. far below the 1e-5 the
-// normalised scores are held to.  Pieces then begin and end on chunk boundaries, so that one piece owns a chunk.
+// normalised scores are held to.
 //
 // P_HALF (ra_set_prefill_precision, not the default): P goes to the matrix cores once, as fp16, instead of twice
 // as hi + lo bf16.  The values are converted to fp16 on their way into LDS (a bf16 number is an fp16 number as
@@ -31,6 +31,7 @@
 // from about 2e-5 to about 4e-4 of the row's largest magnitude (contract: 2e-3).
 #include "attn_common.hpp"
 #include "mfma_util.hpp"
+#include "score_places.hpp"
 #include "stream_kv.hpp"
 
 #include <type_traits>
@@ -88,20 +89,19 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
     const int lane = tid & 63, n = lane & 15, q4 = lane >> 4;
     const int G = a.G, q_len = a.q_len;
     const int rows_total = q_len * G;
+    const RowsPerToken per_token(G);
 
     const int cap = vw.R_max + 1;
     SlotTable tab;
     tab.carve(smem, cap);
     char* tiles = smem + ((SlotTable::bytes(cap) + 15) & ~(size_t)15);  // two tile buffers
     const unsigned tiles_lds = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)tiles);
-    int* ccum = reinterpret_cast<int*>(tiles + 2 * kTileBytes);        // [cap + 1] chunk prefix (score output only)
 
     const int inner = Hkv * n_rowblocks;
     int P;
     BatchLists lists;
     if constexpr (INLINE_PLAN) {
-        lists.load(reinterpret_cast<char*>(ccum) + (TILE_LSE ? align16((cap + 1) * (int)sizeof(int)) : 0), vw, a.sel_idx, a.n_sel,
-                   [&](int) { return a.cur_k ? a.cur_len_host : 0; });
+        lists.load(tiles + 2 * kTileBytes, vw, a.sel_idx, a.n_sel, [&](int) { return a.cur_k ? a.cur_len_host : 0; });
         lists.count_tiles(vw.B, sU);
         P = cut_tiles<kWorkgroupsPerCuP>(ranges, sU, vw.B, a.slots, a.min_units, a.S,
                                          !PAGED && !P_HALF && gridDim.x >= kWorkgroupsPerCuP * (unsigned)a.num_cu &&
@@ -171,29 +171,29 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
             b = uniform(find_slot(sps, vw.B, piece));
             s = piece - sps[b];
             S_eff = sps[b + 1] - sps[b];
-            u_lo = (int)(((long long)sU[b] * s) / S_eff);
-            u_hi = (int)(((long long)sU[b] * (s + 1)) / S_eff);
+            u_lo = piece_begin(sU[b], s, S_eff);
+            u_hi = piece_begin(sU[b], s + 1, S_eff);
         }
         if (reached == 0) item += gridDim.x;
-        const int U = sU[b];
 
-        // ---- this wave's query rows: the block's 16-row tiles are dealt out to the waves in turn; asked for before the table is built
+        // ---- this wave's query rows: the block's 16-row tiles are dealt out to the waves in turn
         const int wv = (wave + rowblock + piece) & 3;  // not always the same SIMD gets the odd tile
         const int my_tiles = !RAGGED ? 2 : (wv < block_tiles(rowblock) ? 1 : 0) + (wv + 4 < block_tiles(rowblock) ? 1 : 0);
         int qtok[kNTP];
         bool row_ok[kNTP];
         size_t rowid[kNTP];
-        uint4 qf[kNTP][4];
+        uint4 qf[kNTP][4];  // asked for before the table is built
 #pragma unroll
         for (int nt = 0; nt < kNTP; ++nt) {
             const int row = (rowblock * tiles_per_block + nt * 4 + wv) * 16 + n;
             row_ok[nt] = nt < my_tiles && row < rows_total;
             const int rr = row_ok[nt] ? row : 0;
-            qtok[nt] = rr / G;
+            qtok[nt] = per_token.token(rr);
             rowid[nt] = ((size_t)b * q_len + qtok[nt]) * a.Hq + (size_t)g * G + (rr - qtok[nt] * G);
+            if (RAGGED && nt >= my_tiles) continue;
             const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + rowid[nt] * 256);
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = qp[kk * 4 + q4];  // rows past the last repeat row 0, unused: no wait here
+            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = qp[kk * 4 + q4];  // rows past the last repeat row 0, unused
         }
         int n_slots, n_hist;
         if (!INLINE_PLAN || !first) __syncthreads();  // the previous pass's readers of the table and the tile buffers are done
@@ -201,32 +201,17 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
         if constexpr (INLINE_PLAN) {
             n_hist = __builtin_amdgcn_readfirstlane(lists.meta[3 * b + 1]);
             n_slots = n_hist + (__builtin_amdgcn_readfirstlane(lists.meta[3 * b + 2]) > 0 ? 1 : 0);
-            lists.table<TILE_LSE>(b, tab, ccum);
+            lists.table(b, tab);
         } else {
             const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
             n_slots = __builtin_amdgcn_readfirstlane(hdr.n_slots);
             n_hist = __builtin_amdgcn_readfirstlane(hdr.n_hist);
             __syncthreads();
         }
-        if constexpr (TILE_LSE) {
-            // chunk prefix of the sequence's segments (a chunk = 256 tokens = 8 tiles, never crossing a segment)
-            if constexpr (!INLINE_PLAN) {
-                for (int i = tid; i < cap; i += 256) ccum[i] = i < n_slots ? (tab.len[i] + 255) >> 8 : 0;
-                exclusive_scan_units(ccum, cap);
-            }
-            // a piece owns whole chunks: its ends move down to the chunk start at or before them
-            auto snap = [&](int u) {
-                if (u <= 0 || u >= U) return u <= 0 ? 0 : U;
-                const int sl = find_slot_wave(tab.cum, n_slots, u);
-                return tab.cum[sl] + ((u - tab.cum[sl]) & ~7);
-            };
-            u_lo = __builtin_amdgcn_readfirstlane(snap(u_lo));
-            u_hi = __builtin_amdgcn_readfirstlane(snap(u_hi));
-        }
 
         floatx4_t acc[kNTP][8];
         float m[kNTP], l[kNTP];
-        float l_mark[kNTP];  // the running sum as it stood at the start of the current chunk (score output only)
+        float l_mark[kNTP];  // the running sum as it stood at the start of the current segment (score output only)
         const float slack = (P_HALF ? 8.f : 16.f) / a.c;
 #pragma unroll
         for (int nt = 0; nt < kNTP; ++nt) {
@@ -487,6 +472,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
         // ---- walk the key tiles: the whole workgroup in lockstep -----------------------------------------
         if (u_lo < u_hi) {
             int slot = find_slot_wave(tab.cum, n_slots, u_lo);
+            const int slot_lo = slot;
             open_seg(slot, u_lo);
             int c_tok0 = seg_len - rows_left;
             Share sh = load_tile(tiles_lds);
@@ -497,7 +483,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
                 wait_for_direct_loads();  // this wave's quarter of the tile has landed in LDS
                 const int len = seg_len, tok0 = c_tok0;  // of the tile just stored
                 const bool is_cur = seg_cur;
-                const int t_slot = slot, t_first = seg_first, t_end = seg_end;
+                const int t_slot = slot, t_end = seg_end;
                 __syncthreads();
                 if (u + 1 < u_hi) {
                     if (u + 1 >= seg_end) {
@@ -510,18 +496,16 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
                 if (!RAGGED || my_tiles == 2) consume(std::integral_constant<int, 2>(), buf, tok0, len, is_cur);
                 else if (my_tiles == 1) consume(std::integral_constant<int, 1>(), buf, tok0, len, is_cur);
                 if constexpr (TILE_LSE) {
-                    const int uin = u - t_first;
-                    if ((uin & 7) == 7 || u + 1 == t_end || u + 1 == u_hi) {  // the chunk ends with this tile
-                        const int chunk = ccum[t_slot] + (uin >> 3);
+                    if (u + 1 == t_end || u + 1 == u_hi) {  // what this piece has of the segment ends with this tile
 #pragma unroll
                         for (int nt = 0; nt < kNTP; ++nt) {
                             const float share = xrow_sum4(l[nt] - l_mark[nt]);
                             l_mark[nt] = l[nt];
-                            if (q4 == 0 && row_ok[nt] && chunk < a.n_tiles_max) {
+                            if (q4 == 0 && row_ok[nt]) {
                                 // row order of the score pass: [B][Hq][q_len]
                                 const size_t head = rowid[nt] - ((size_t)b * q_len + qtok[nt]) * a.Hq;
                                 const size_t srow = ((size_t)b * a.Hq + head) * q_len + qtok[nt];
-                                a.tile_lse[srow * a.n_tiles_max + chunk] =
+                                a.tile_lse[srow * a.n_tiles_max + t_slot + s] =
                                     share > 0.f ? kLn2 * (__builtin_fmaf(m[nt], a.c, fast_log2(share)) -
                                                           (P_HALF ? (float)kHalfScaleLog2 : 0.f))
                                                 : -__builtin_inff();
@@ -531,6 +515,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
                 }
                 bufsel ^= 1;
             }
+            if constexpr (TILE_LSE)
+                if (rest == 0 && wave == 0) note_places(a.places, b, vw.R_max, n_hist, tab.cum, slot_lo, slot, s, u_lo, u_hi);
         }
 
         // ---- the four lane groups hold partial sums of the same rows; each wave owns its rows ------------------
@@ -568,9 +554,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
 
 
 // Dynamic LDS of a launch.
-static size_t attn_prefill_lds(int B, int R_max, bool tile_lse, bool plan_inline) {
-    return align_up(SlotTable::bytes(R_max + 1), 16) + 2 * kTileBytes + (tile_lse ? align_up((size_t)(R_max + 2) * sizeof(int), 16) : 0) +
-           (plan_inline ? BatchLists::bytes(B, R_max) : 0);
+static size_t attn_prefill_lds(int B, int R_max, bool plan_inline) {
+    return align_up(SlotTable::bytes(R_max + 1), 16) + 2 * kTileBytes + (plan_inline ? BatchLists::bytes(B, R_max) : 0);
 }
 // Workgroups of a launch: as many as the chip holds, if there are as many pieces.
 static long long attn_prefill_grid(const AttnArgs& a, int num_cu, int inner) {
@@ -583,9 +568,9 @@ static long long attn_prefill_grid(const AttnArgs& a, int num_cu, int inner) {
     return grid < 1 ? 1 : grid;
 }
 static int attn_prefill_rowblocks(const AttnArgs& a) { return (a.q_len * a.G + kRowsPerItem - 1) / kRowsPerItem; }
-bool attn_prefill_plans_inline(const AttnArgs& a, bool tile_lse, int num_cu) {
+bool attn_prefill_plans_inline(const AttnArgs& a, int num_cu) {
     const int B = a.view.B, R_max = a.view.R_max;
-    return prefill_plans_inline(B, R_max, attn_prefill_lds(B, R_max, tile_lse, true),
+    return prefill_plans_inline(B, R_max, attn_prefill_lds(B, R_max, true),
                                 attn_prefill_grid(a, num_cu, a.view.Hkv * attn_prefill_rowblocks(a)), num_cu);
 }
 
@@ -596,7 +581,7 @@ int launch_attn_prefill_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st)
     if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "prefill: batch %d exceeds %d", B, kMaxBatch);
     const int n_rowblocks = attn_prefill_rowblocks(a);
     const bool plan_inline = a.plan_inline != 0;
-    const size_t smem = attn_prefill_lds(B, a.view.R_max, a.tile_lse != nullptr, plan_inline);
+    const size_t smem = attn_prefill_lds(B, a.view.R_max, plan_inline);
     const long long grid = attn_prefill_grid(a, num_cu, Hkv * n_rowblocks);
     a.slots = question_slots(Hkv * n_rowblocks, grid, num_cu, true);
     const bool lse = a.tile_lse != nullptr, half = a.p_half != 0;

@@ -9,7 +9,7 @@ using namespace ra;
 
 // Shared by the two prefill entry points.  With `scores` given (watershed layer) the attention runs over every
 // history round and the kernel also leaves one log-sum-exp per (query row, score unit: a 32-token key tile in the
-// 16-row kernel, a 256-token chunk of a round in the many-row kernel), which the finishing kernels of the score
+// 16-row kernel, what a piece has of a round in the many-row kernel), which the finishing kernels of the score
 // pass turn into Eq. 1.
 static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int Hq, const ra_kv_view* layer,
                         const int32_t* sel_idx, const int32_t* n_sel, const void* cur_k, const void* cur_v, int cur_len,
@@ -41,15 +41,17 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     const size_t rows = (size_t)B * q_len * Hq;
     const bool with_scores = scores != nullptr;
     RA_REQUIRE(!with_scores || layer->R_max > 0, RA_ERR_INVALID_ARG, "watershed prefill: R_max is 0, there is nothing to score");
-    // score output: one entry per 32-token tile (decode kernel) or per 256-token chunk (many-row kernel) of a
-    // sequence's table: history rounds (each rounded up), then the current round
+    // score output: one entry per 32-token tile (decode kernel) of a sequence's table: history rounds (each rounded up),
+    // then the current round; the many-row kernel's rows are as long as they have places, but the scratch is asked for and
+    // an understated max_tokens is told by 256-token chunks
     const int score_unit = few_rows ? 32 : 256;
     const int64_t n_tiles64 = layer->max_tokens / score_unit + layer->R_max + cur_len / score_unit + 1;
     RA_REQUIRE(!with_scores || n_tiles64 <= (int64_t)1 << 24, RA_ERR_UNSUPPORTED, "watershed prefill: max_tokens too large");
-    const int n_tiles_max = (int)n_tiles64;
-    const size_t tile_bytes = with_scores ? align_up(rows * n_tiles_max * sizeof(float), 256) : 0;
+    int n_tiles_max = (int)n_tiles64;
+    const int chunk_limit = n_tiles_max;
+    size_t tile_bytes = with_scores ? align_up(rows * n_tiles_max * sizeof(float), 256) : 0;
     const size_t p_bytes = with_scores ? scores_finish_part_bytes(q_len, B, Hq, layer->R_max, n_tiles_max) : 0;
-    const size_t score_bytes = tile_bytes + p_bytes;
+    size_t score_bytes = tile_bytes + p_bytes;
     AttnArgs a = {};
     a.view = to_dev(layer);
     a.cur_len_host = cur_len;
@@ -76,13 +78,23 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     } else {
         // Small batches: the kernel plans itself and cuts the batch into ranges, whose ends a sequence shares with its
         // neighbours (two parts more).  A workspace that only fits the other schedule gets that one.
-        a.S = mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2;
-        w = attn_workspace(rows, a.S, D, B, layer->R_max);
-        plan_inline = attn_prefill_plans_inline(a, with_scores, ctx->num_cu) && ctx->ws.bytes >= w.total + score_bytes;
-        if (!plan_inline) {
-            a.S = mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 8);
-            w = attn_workspace(rows, a.S, D, B, layer->R_max);
-        }
+        auto fits = [&](int S) {  // S parts of a sequence, and as many more values in a row of the score output
+            a.S = S;
+            w = attn_workspace(rows, S, D, B, layer->R_max);
+            if (with_scores) {
+                n_tiles_max = layer->R_max + (cur_len > 0) + S - 1;
+                tile_bytes = align_up(rows * n_tiles_max * sizeof(float), 256);
+                score_bytes = tile_bytes + p_bytes;
+            }
+            return ctx->ws.bytes >= w.total + score_bytes;
+        };
+        int S = mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2;
+        const size_t least = attn_workspace(rows, S - 2 < 8 ? S - 2 : 8, D, B, layer->R_max).total + score_bytes;
+        RA_REQUIRE(ctx->ws.base != nullptr && ctx->ws.bytes >= least, RA_ERR_WORKSPACE,
+                   "prefill: workspace has %zu bytes, this call needs %zu", ctx->ws.bytes, least);
+        plan_inline = fits(S) && attn_prefill_plans_inline(a, ctx->num_cu);
+        if (!plan_inline)  // (a part less is 520 bytes a row, so it fits in two at the most)
+            for (S = S - 2 < 8 ? S - 2 : 8; !fits(S) && S > 1;) --S;
         plan_off = w.plan_off;
         scratch_total = w.total;
     }
@@ -106,6 +118,8 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     a.lse = lse;
     a.tile_lse = with_scores ? reinterpret_cast<float*>(ctx->ws.base + scratch_total) : nullptr;
     a.n_tiles_max = with_scores ? n_tiles_max : 0;
+    if (with_scores && !few_rows)
+        a.places = {reinterpret_cast<PlaceNote*>(scores), reinterpret_cast<PlaceNote*>(ctx->ws.base + kWsPlacesOff), chunk_limit};
     a.rec_acc = few_rows ? reinterpret_cast<float*>(ctx->ws.base + mw.rec_off) : nullptr;
     a.rec_ml = few_rows ? reinterpret_cast<float*>(ctx->ws.base + mw.ml_off) : nullptr;
     a.seq_rec = reinterpret_cast<int*>(ctx->ws.base + kWsSeqRecOff);
@@ -136,7 +150,8 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
         f.has_cur = cur_len > 0 && q_len > 1;
         f.cur_len = f.has_cur ? cur_len : 0;
         f.n_chunks_max = n_tiles_max;
-        f.chunk_shift = few_rows ? 5 : 8;
+        f.chunk_shift = 5;
+        f.places = a.places;
         f.p_out = scores_head;
         f.s_out = scores;
         launch_scores_finish(f, B, reinterpret_cast<float*>(ctx->ws.base + scratch_total + tile_bytes), st);

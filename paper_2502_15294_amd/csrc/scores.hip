@@ -199,12 +199,9 @@ __device__ __forceinline__ float sum_segments(float v) {
     }
     return v;
 }
-// log-sum-exp of x[lo .. hi).  A round of up to four values (1024 tokens) is read in one go; with ONE_FIRST, for dialogues of
-// so many rounds that most are a single value, that one is read first.
-template <bool ONE_FIRST>
+// log-sum-exp of x[lo .. hi).  A round of up to four values (1024 tokens) is read in one go.
 __device__ __forceinline__ float lse_range(const float* x, int lo, int hi) {
     if (hi <= lo) return -__builtin_inff();
-    if (ONE_FIRST && hi - lo == 1) return x[lo];
     float v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = x[min(lo + j, hi - 1)];
@@ -275,6 +272,49 @@ __device__ __forceinline__ int round_places(const FinishArgs& a, int b, int& R, 
     }
 }
 
+// The same by the streaming kernel's notes: the rounds' values and the current round's.  Returns whether the caller's
+// max_tokens was too small for the sequence.
+template <int SEG, int KPL>
+__device__ __forceinline__ bool noted_places(const FinishArgs& a, int b, int& R, int (&lo)[KPL], int (&hi)[KPL], int& cur_lo, int& cur_hi) {
+    const int j = threadIdx.x & (SEG - 1);
+    auto ask = [&](int k, int& len, PlaceNote& note) {
+        const int r = j + SEG * k;
+        len = r < a.R_max ? a.seg_len[(size_t)b * a.R_max + r] : 0;
+        note = r < a.R_max ? a.places.round[(size_t)b * a.R_max + r] : PlaceNote{0, 0};
+    };
+    int chunks = 0;
+    auto place = [&](int k, int len, PlaceNote note) {
+        const int r = j + SEG * k;
+        const bool some = r < R && len > 0;
+        lo[k] = some ? r + note.first : 0;
+        hi[k] = some ? r + note.last + 1 : 0;
+        chunks += some ? (len + 255) >> 8 : 0;
+    };
+    PlaceNote cur = {0, 0};
+    if (a.has_cur) cur = a.places.cur[b];
+    if constexpr (KPL == 1) {
+        int len;
+        PlaceNote note;
+        ask(0, len, note);  // before R has arrived
+        R = min(max(a.n_rounds[b], 0), a.R_max);
+        place(0, len, note);
+    } else {
+        R = min(max(a.n_rounds[b], 0), a.R_max);
+#pragma unroll
+        for (int k = 0; k < KPL; ++k) lo[k] = hi[k] = 0;
+        for_rounds<KPL>(a.R_max, [&](int k) {
+            int len;
+            PlaceNote note;
+            ask(k, len, note);
+            place(k, len, note);
+        });
+    }
+    cur_lo = R + cur.first;
+    cur_hi = R + cur.last + 1;
+    chunks = __builtin_amdgcn_readlane(wave_inclusive_sum<SEG>(chunks), SEG - 1);
+    return chunks + (a.has_cur ? (a.cur_len + 255) >> 8 : 0) > a.places.chunk_limit;
+}
+
 // n consecutive floats of memory into the wave's LDS strip, 512 of them in flight at a time.
 __device__ __forceinline__ void stage_floats(const float* src, int n, float* strip) {
     const int lane = threadIdx.x & 63;
@@ -300,11 +340,40 @@ template <int SEG, int KPL>
 __device__ __forceinline__ void round_masses(int R_max, const float* row, const int (&lo)[KPL], const int (&hi)[KPL],
                                              bool has_cur, int cur_lo, int cur_hi, float (&e)[KPL]) {
     float mx = -__builtin_inff();
-    for_rounds<KPL>(R_max, [&](int k) {
-        e[k] = lse_range<(KPL > 4)>(row, lo[k], hi[k]);
-        mx = fmaxf(mx, e[k]);
-    });
-    const float lc = has_cur ? lse_range<(KPL > 4)>(row, cur_lo, cur_hi) : -__builtin_inff();
+    if constexpr (KPL > 4) {
+        // Dialogues of so many rounds have one value for most of them, two where a range of tiles ends inside: all of those
+        // are fetched before any is used (behind a branch per round every one is a round trip of its own).
+        // Four rounds' at a time: all sixteen, and registers spill.
+        bool more = false;
+#pragma unroll
+        for (int k0 = 0; k0 < KPL; k0 += 4) {
+            if (k0 > 0 && 64 * k0 >= R_max) continue;
+            float a[4], b[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                a[j] = row[lo[k0 + j]];
+                b[j] = row[max(hi[k0 + j] - 1, 0)];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int n = hi[k0 + j] - lo[k0 + j];
+                const float top = fmaxf(a[j], b[j]), two = top + __logf(1.f + __expf(fminf(a[j], b[j]) - top));
+                e[k0 + j] = n <= 0 ? -__builtin_inff() : (n == 1 || top == -__builtin_inff() ? a[j] : two);
+                more |= n > 2;
+            }
+        }
+        if (__any(more))
+            for_rounds<KPL>(R_max, [&](int k) {
+                if (hi[k] - lo[k] > 2) e[k] = lse_range(row, lo[k], hi[k]);
+            });
+        for_rounds<KPL>(R_max, [&](int k) { mx = fmaxf(mx, e[k]); });
+    } else {
+        for_rounds<KPL>(R_max, [&](int k) {
+            e[k] = lse_range(row, lo[k], hi[k]);
+            mx = fmaxf(mx, e[k]);
+        });
+    }
+    const float lc = has_cur ? lse_range(row, cur_lo, cur_hi) : -__builtin_inff();
     mx = fmaxf(wave_max<SEG>(mx), lc);
     const bool none = mx == -__builtin_inff();
     float sum = 0.f;
@@ -423,7 +492,7 @@ __global__ __launch_bounds__(most_head_waves(KPL) * 64) void scores_finish_kerne
 // the groups of P = 64 / SEG consecutive query tokens 8 z + w, + 8 Z, ..., the rows of TB groups asked for together.  The
 // per-wave round masses are summed over the waves in LDS in a fixed order and written, not yet normalised, to p_part
 // [B][Hq][Z][R_max]; scores_heads_kernel finishes.
-template <int SEG, int KPL, int TB, bool STAGED>
+template <int SEG, int KPL, int TB, bool STAGED, bool NOTED>
 __global__ __launch_bounds__(kFinishWaves * 64) void scores_finish_rows_kernel(FinishArgs a, float* p_part) {
     constexpr int P = 64 / SEG;
     extern __shared__ __align__(16) char smem[];
@@ -448,10 +517,15 @@ __global__ __launch_bounds__(kFinishWaves * 64) void scores_finish_rows_kernel(F
     };
     const int i_first = (blockIdx.z * kFinishWaves + wave) * P;
     fetch(i_first);
-    int R, lo[KPL], hi[KPL];
-    const int hist_chunks = round_places<SEG, KPL>(a, b, R, cum, lo, hi);
-    const int all_chunks = hist_chunks + (a.has_cur ? (a.cur_len + (1 << a.chunk_shift) - 1) >> a.chunk_shift : 0);
-    const bool overflow = all_chunks > n;
+    int R, lo[KPL], hi[KPL], cur_lo, cur_hi;
+    bool overflow;
+    if constexpr (NOTED) {
+        overflow = noted_places<SEG, KPL>(a, b, R, lo, hi, cur_lo, cur_hi);
+    } else {
+        cur_lo = round_places<SEG, KPL>(a, b, R, cum, lo, hi);
+        cur_hi = cur_lo + (a.has_cur ? (a.cur_len + (1 << a.chunk_shift) - 1) >> a.chunk_shift : 0);
+        overflow = cur_hi > n;
+    }
 
     float qatt[KPL];
 #pragma unroll
@@ -465,7 +539,7 @@ __global__ __launch_bounds__(kFinishWaves * 64) void scores_finish_rows_kernel(F
             const int in = mine ? seg : 0;
             float e[KPL];
             round_masses<SEG>(a.R_max, STAGED ? strip + (j * P + in) * n : part_h + (size_t)(ij + in) * n, lo, hi, a.has_cur,
-                              hist_chunks, all_chunks, e);
+                              cur_lo, cur_hi, e);
             for_rounds<KPL>(a.R_max, [&](int k) { qatt[k] += mine ? e[k] : 0.f; });
         }
     }
@@ -704,17 +778,17 @@ static int head_waves(int groups, int most, int R_max) {
     return W;
 }
 
-template <int SEG, int KPL, int TB>
+template <int SEG, int KPL, int TB, bool NOTED>
 static void launch_rows(const FinishArgs& f, int B, float* p_part, int Z, hipStream_t st) {
     const size_t base = (size_t)(f.R_max + 2) * sizeof(int) + (size_t)kFinishWaves * f.R_max * sizeof(float);
     const size_t staged = base + (size_t)kFinishWaves * TB * (64 / SEG) * f.n_chunks_max * sizeof(float);
     const dim3 grid(B, f.Hq, Z), block(kFinishWaves * 64);
     if (staged <= kFinishLdsMax / 2)  // two workgroups per compute unit
-        hipLaunchKernelGGL((scores_finish_rows_kernel<SEG, KPL, TB, true>), grid, block, staged, st, f, p_part);
+        hipLaunchKernelGGL((scores_finish_rows_kernel<SEG, KPL, TB, true, NOTED>), grid, block, staged, st, f, p_part);
     else if (TB > 1)
-        launch_rows<SEG, KPL, 1>(f, B, p_part, Z, st);
+        launch_rows<SEG, KPL, 1, NOTED>(f, B, p_part, Z, st);
     else
-        hipLaunchKernelGGL((scores_finish_rows_kernel<SEG, KPL, 1, false>), grid, block, base, st, f, p_part);
+        hipLaunchKernelGGL((scores_finish_rows_kernel<SEG, KPL, 1, false, NOTED>), grid, block, base, st, f, p_part);
 }
 
 template <int SEG, int KPL, int HB>
@@ -741,8 +815,11 @@ void launch_scores_finish_rows(const FinishArgs& f, int B, float* p_part, int Z,
         const bool several = f.q_len > kFinishWaves * Z;  // a wave may have more than one group of tokens
 #define RA_ROWS(SEG, KPL)                                                              \
     do {                                                                               \
-        if (several) launch_rows<SEG, KPL, (KPL) == 1 ? 4 : 1>(f, B, p_part, Z, st);   \
-        else launch_rows<SEG, KPL, 1>(f, B, p_part, Z, st);                            \
+        constexpr int several_tb = (KPL) == 1 ? 4 : 1;                                 \
+        if (f.places.round && several) launch_rows<SEG, KPL, several_tb, true>(f, B, p_part, Z, st); \
+        else if (f.places.round) launch_rows<SEG, KPL, 1, true>(f, B, p_part, Z, st);  \
+        else if (several) launch_rows<SEG, KPL, several_tb, false>(f, B, p_part, Z, st); \
+        else launch_rows<SEG, KPL, 1, false>(f, B, p_part, Z, st);                     \
     } while (0)
         RA_FINISH_SHAPE(f.R_max, RA_ROWS);
 #undef RA_ROWS
@@ -812,7 +889,7 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
     RA_REQUIRE(nc64 <= (int64_t)1 << 24, RA_ERR_UNSUPPORTED, "round_scores: max_tokens too large");
     const int n_chunks_max = (int)(nc64 < 1 ? 1 : nc64);
     const size_t rows = (size_t)B * Hq * q_len;
-    const size_t part_bytes = align_up(rows * n_chunks_max * sizeof(float), 256);
+    size_t part_bytes = align_up(rows * n_chunks_max * sizeof(float), 256);
     // several query tokens (or many chunks): Z workgroups per head leave partial round masses in a buffer
     const size_t p_bytes = scores_finish_part_bytes(q_len, B, Hq, R_max, n_chunks_max);
     // more than 16 query rows per KV head on the matrix cores: persistent kernel driven by segment tables
@@ -835,21 +912,31 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
                kWsReserved + part_bytes + p_bytes + plan_bytes + desc_bytes);
 
     ScoreArgs a;
+    int row_len = n_chunks_max;
     a.view = to_dev(watershed);
+    a.q_len = q_len;
+    a.Hq = Hq;
+    a.num_cu = ctx->num_cu;
+    if (many_rows) {
+        // A value for every round (and the current one) and for every further part that a sequence is cut into, no more
+        // than the workspace has room for: the least that passed the check above has room for one part.
+        a.max_tiles = watershed->max_tokens / 32 + R_max + (use_cur ? (cur_len + 31) / 32 : 0);
+        const int slots = R_max + (use_cur ? 1 : 0);
+        const size_t room = (ctx->ws.bytes - kWsReserved - p_bytes - plan_bytes) / 256 * 256 / (rows * sizeof(float));
+        scores_prefill_shape(a, (long long)room - slots + 1);
+        row_len = slots + a.S - 1;
+        part_bytes = align_up(rows * row_len * sizeof(float), 256);
+        a.places = {reinterpret_cast<PlaceNote*>(scores), reinterpret_cast<PlaceNote*>(ctx->ws.base + kWsPlacesOff), n_chunks_max};
+    }
     a.q = q;
     a.cur_k = use_cur ? cur_k : nullptr;
     a.cur_len = use_cur ? cur_len : 0;
-    a.q_len = q_len;
-    a.Hq = Hq;
-    a.n_chunks_max = n_chunks_max;
+    a.n_chunks_max = row_len;
     a.chunk_tokens = chunk_tokens;
     a.c = scale * kLog2e;
     a.part = reinterpret_cast<float*>(ctx->ws.base + kWsReserved);
     a.plan = ctx->ws.base + kWsReserved + part_bytes + p_bytes;
     a.chunks = desc_bytes ? ctx->ws.base + kWsReserved + part_bytes + p_bytes + plan_bytes : nullptr;
-    a.num_cu = ctx->num_cu;
-    a.S = 1 << 20;
-    a.min_units = 8;  // a chunk: ranges end at chunks (16: short question over three short dialogues 41.7 -> 37.8 microseconds)
 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const dim3 grid(n_chunks_max, watershed->Hkv, B * q_len);
@@ -859,7 +946,7 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
     {
         KernelTimer timer(ctx, st);
         if (many_rows)
-            rc = launch_scores_prefill_mfma(a, paged, ctx->num_cu, st);
+            rc = launch_scores_prefill_mfma(a, paged, st);
         else if (mfma)
             rc = launch_scores_mfma(a, paged, ctx->num_cu, st);
         else if (watershed->dtype == RA_BF16)
@@ -878,8 +965,9 @@ static int scores_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int 
     f.Hq = Hq;
     f.q_len = q_len;
     f.cur_len = a.cur_len;
-    f.n_chunks_max = n_chunks_max;
+    f.n_chunks_max = row_len;
     f.chunk_shift = 8;
+    f.places = a.places;
     f.has_cur = use_cur;
     f.p_out = scores_head;
     f.s_out = scores;

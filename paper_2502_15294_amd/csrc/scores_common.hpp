@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "score_places.hpp"
 
 namespace ra {
 
@@ -13,7 +14,7 @@ struct ScoreArgs {
     const void* q;      // [B][q_len][Hq][D]
     const void* cur_k;  // [B][cur_len][Hkv][D] or null
     int cur_len, q_len, Hq;
-    int n_chunks_max;   // row length of `part`
+    int n_chunks_max;   // row length of `part` (many-row kernel: places, see score_places.hpp)
     int chunk_tokens;   // tokens per chunk (a chunk never crosses a round)
     float c;            // scale * log2(e)
     float* part;        // [B][Hq][q_len][n_chunks_max] natural-log sum-exp of the scaled logits of one chunk
@@ -22,8 +23,13 @@ struct ScoreArgs {
     // many-row kernel only: room for its segment tables and the bounds of its schedule
     const char* plan;   // [B][plan_stride(R_max + 1)]
     int num_cu = 0;     // compute units of the device
-    int slots = 0;      // most ranges a launch that plans itself cuts the batch into
-    int S, min_units;   // a sequence is cut into at most S pieces of at least min_units key tiles
+    int grid = 0, n_rowblocks = 0;  // workgroups; blocks of query rows
+    int plan_inline = 0;  // the launch plans itself
+    int slots = 0;        // most ranges it cuts the batch into
+    int max_parts = 0;    // ... that meet one sequence
+    int S = 0, min_units = 0;   // a sequence is cut into at most S pieces of at least min_units key tiles
+    long long max_tiles = 0;  // bound of a sequence's key tiles
+    ScorePlaces places = {};
 };
 
 // Input of the finishing kernels: per-chunk log-sum-exps -> Eq. 1.
@@ -33,6 +39,7 @@ struct FinishArgs {
     const int32_t* seg_len;
     int R_max, Hq, q_len, cur_len, n_chunks_max;
     int chunk_shift;           // tokens per value: 1 << chunk_shift (8: the score pass's chunks, 5: key tiles)
+    ScorePlaces places = {};   // several query tokens: if set, the values lie where the streaming kernel noted
     bool has_cur;
     float* p_out;  // may be null
     float* s_out;
@@ -69,7 +76,10 @@ __device__ __forceinline__ int cur_visible(int cur_len, int q_len, int i) {
 }
 
 // bf16, d = 128, Hq/Hkv <= 16: matrix-core streaming kernels, for up to 16 query rows per KV head and for more.
-int launch_scores_prefill_mfma(ScoreArgs a, bool paged, int num_cu, hipStream_t st);
+// The many-row kernel's launch (view, q_len, Hq, num_cu and max_tiles given): grid, slots, min_units, plan_inline and S, the most
+// parts that the tiles of a sequence are cut into.  `room`: no more than so many.
+void scores_prefill_shape(ScoreArgs& a, long long room);
+int launch_scores_prefill_mfma(const ScoreArgs& a, bool paged, hipStream_t st);
 int launch_scores_mfma(const ScoreArgs& a, bool paged, int num_cu, hipStream_t st);
 
 }  // namespace ra

@@ -3,20 +3,25 @@
 //
 // Same roles as in the attention kernels: S^T[16 tokens x 16 rows] = K . Q^T, lane%16 is the query row, so a
 // row's running (reference logit, sum of exponentials) stays in its lane.  What is produced is one
-// log-sum-exp per (query row, 256-token chunk of a round); the finishing kernels turn those into round masses.
+// log-sum-exp per query row and part of a round: the key tiles of the batch are cut into ranges, a range may end
+// anywhere inside a round, and every (round, range) that meet leave one value a row (score_places.hpp says
+// where).  The finishing kernels turn those into round masses.
 //
-//   * a work item is (piece of the sequence's chunks, KV head, block of 256 query rows): four waves with
-//     four 16-row tiles each walk the key tiles of the piece's chunks in lockstep;
+//   * a work item is (range of the batch's key tiles, KV head, block of 256 query rows): four waves with
+//     four 16-row tiles each walk the range's tiles in lockstep;
 //   * every 32-token key tile (8 KB) is fetched from global memory once per workgroup, one tile ahead, with
 //     whole-row coalesced loads that go straight into one of two LDS buffers (no registers, no LDS stores): the
 //     tile's image there is row-major with the 16-byte chunks of row r rotated by r, so that the operand reads
 //     (16 lanes = 16 rows, one chunk) touch every bank once; all four waves read it; one barrier per tile;
 //   * the reference logit of a lane is only raised when the exponentials of a tile relative to it add up to more than
 //     2^16, so the common tile costs one multiply-add, one exponential and one add per logit;
-//   * persistent launch with the batch-wide balanced schedule used by the attention kernels.  The schedule
-//     is made in units of key tiles (chunks at the end of a round are short, so chunk counts would balance
-//     badly) and each piece boundary is then moved to the start of the chunk it falls in.
+//   * persistent launch with the batch-wide balanced schedule used by the attention kernels, in units of key tiles.  (With
+//     one value per 256-token chunk of a round a range had to begin and end with a chunk: ranges of eight tiles, as a short
+//     question has them, then came out between none and seventeen tiles long, and their ends spread from 12 to 32
+//     microseconds.  19 tokens over three dialogues of 23 rounds, whole call 76.1 -> 71.3 microseconds; 128 tokens over four
+//     of 32 000 tokens 324.5 -> 313; 24 tokens over three of 17 rounds at the watershed layer 49.8 -> 43.7.)
 #include "scores_common.hpp"
+#include "score_places.hpp"
 #include "mfma_util.hpp"
 #include "stream_kv.hpp"
 
@@ -27,25 +32,22 @@ namespace ra {
 constexpr int kTileSP = 32;                      // tokens per key tile
 constexpr int kNTS = 4;                          // 16-row tiles per wave
 constexpr int kRowsPerItemS = 4 * kNTS * 16;     // 256
-constexpr int kTilesPerChunk = kChunkTokens / kTileSP;
 constexpr int kKTileBytes = 8192;
 constexpr int kPiecesPerWorkgroupS = 1;  // measured on the 4 x 32 K-token question-prefill workload: 1: 167-172 us, 2: 174-180, 3: 176
 constexpr int kWorkgroupsPerCuS = 3;
 
 // Planning kernel, grid (B): the table of segments of sequence b (all history rounds, then the current round)
-// in the layout the attention kernels use, with cum = prefix sum of the segments' chunk counts, the unused
-// value-offset column holding the prefix sum of their key-tile counts, and U = total key tiles.
+// in the layout the attention kernels use, with cum = prefix sum of the segments' key-tile counts and U = total key tiles.
 __global__ __launch_bounds__(256) void scores_plan_kernel(ScoreArgs a, char* plan) {
     extern __shared__ __align__(16) char smem[];
     const DevView& vw = a.view;
     const int b = blockIdx.x, tid = threadIdx.x;
     const int cap = vw.R_max + 1;
-    int* cum = reinterpret_cast<int*>(smem);  // [cap + 1] chunks
-    int* tcum = cum + cap + 1;                // [cap + 1] tiles
+    int* cum = reinterpret_cast<int*>(smem);  // [cap + 1] tiles
     char* plan_b = plan + (size_t)b * plan_stride(cap);
     long long* g_off_k = reinterpret_cast<long long*>(plan_b + sizeof(PlanHeader));
-    long long* g_tcum = g_off_k + cap;
-    int* g_len = reinterpret_cast<int*>(g_tcum + cap);
+    long long* g_off_v = g_off_k + cap;
+    int* g_len = reinterpret_cast<int*>(g_off_v + cap);
     int* g_cum = g_len + cap;
     const int n_hist = min(max(vw.n_rounds[b], 0), vw.R_max);
     const int n_slots = n_hist + (a.cur_k && a.cur_len > 0 ? 1 : 0);
@@ -60,18 +62,16 @@ __global__ __launch_bounds__(256) void scores_plan_kernel(ScoreArgs a, char* pla
         }
         g_len[i] = len;
         g_off_k[i] = ok;
-        cum[i] = chunks_of(len);
-        tcum[i] = (len + kTileSP - 1) / kTileSP;
+        g_off_v[i] = 0;
+        cum[i] = (len + kTileSP - 1) / kTileSP;
     }
     exclusive_scan_units(cum, cap);
-    exclusive_scan_units(tcum, cap);
     for (int i = tid; i <= cap; i += 256) g_cum[i] = cum[i];
-    for (int i = tid; i < cap; i += 256) g_tcum[i] = tcum[i];
     if (tid == 0) {
         PlanHeader h;
         h.n_slots = n_slots;
         h.n_hist = n_hist;
-        h.U = tcum[n_slots];
+        h.U = cum[n_slots];
         h.S_eff = 1;
         *reinterpret_cast<PlanHeader*>(plan_b) = h;
     }
@@ -92,6 +92,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
     const int lane = tid & 63, n = lane & 15, q4 = lane >> 4;
     const int G = a.Hq / Hkv, q_len = a.q_len;
     const int rows_total = q_len * G;
+    const RowsPerToken per_token(G);
 
     const int cap = vw.R_max + 1;
     SlotTable tab;
@@ -102,12 +103,10 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
     const int inner = Hkv * n_rowblocks;
     int P;
     BatchLists lists;
-    int* tcum = reinterpret_cast<int*>(tiles + 2 * kKTileBytes);  // [cap + 1] prefix of the segments' key tiles
     if constexpr (INLINE_PLAN) {
-        lists.load(reinterpret_cast<char*>(tcum) + align16((cap + 1) * (int)sizeof(int)), vw, nullptr, nullptr,
-                   [&](int) { return a.cur_k ? a.cur_len : 0; });
+        lists.load(tiles + 2 * kKTileBytes, vw, nullptr, nullptr, [&](int) { return a.cur_k ? a.cur_len : 0; });
         lists.count_tiles(vw.B, sU);
-        P = cut_tiles<kWorkgroupsPerCuS>(ranges, sU, vw.B, a.slots, a.min_units, kMaxRanges + 2,
+        P = cut_tiles<kWorkgroupsPerCuS>(ranges, sU, vw.B, a.slots, a.min_units, a.max_parts,
                                          !PAGED && gridDim.x >= kWorkgroupsPerCuS * (unsigned)a.num_cu &&
                                              a.slots * inner <= (int)gridDim.x,
                                          score_range_weights());
@@ -136,7 +135,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
     for (int item = blockIdx.x; item < n_items;) {
         const int piece = uni(item / inner), rest = item - piece * inner;
         const int rowblock = uni(rest / Hkv), g = rest - rowblock * Hkv;
-        int b, t_lo, t_hi;  // the pass: tiles [t_lo, t_hi) of sequence b, moved to chunk starts
+        int b, part, t_lo, t_hi;  // the pass: tiles [t_lo, t_hi) of sequence b, its part-th piece
         if constexpr (INLINE_PLAN) {
             const int r = range_at<kWorkgroupsPerCuS>(piece, P);
             const LaneSequence sq = lane_sequence(sU, vw.B);
@@ -146,35 +145,35 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                 continue;
             }
             b = sequence_of_tile(sq, vw.B, g_lo);
+            part = r - first_part_of(ranges, P, sq, b);
             const int seq_lo = __builtin_amdgcn_readlane(sq.tile0, b), end = min(g_hi, seq_lo + __builtin_amdgcn_readlane(sq.U, b));
             t_lo = g_lo - seq_lo;
             t_hi = end - seq_lo;
             reached = end < g_hi ? end : 0;
         } else {
             b = uni(find_slot(sps, vw.B, piece));
-            const int s = piece - sps[b], S_eff = sps[b + 1] - sps[b];
-            t_lo = (int)(((long long)sU[b] * s) / S_eff);
-            t_hi = (int)(((long long)sU[b] * (s + 1)) / S_eff);
+            part = piece - sps[b];
+            t_lo = piece_begin(sU[b], part, sps[b + 1] - sps[b]);
+            t_hi = piece_begin(sU[b], part + 1, sps[b + 1] - sps[b]);
         }
         if (reached == 0) item += gridDim.x;
-        const int T = sU[b];
 
-        // ---- this wave's query rows, asked for before the table is built -------------------------------
         // The block's 16-row tiles are dealt out to the waves in turn: row nt of this lane is row0 + 64 nt (whatever else is
         // needed of it is recomputed where it is used).
         const int wv = (wave + rowblock + piece) & 3;  // not always the same SIMD gets the odd tile
         const int row0 = (rowblock * tiles_per_block + wv) * 16 + n;
         const int my_tiles = !RAGGED ? 4 : (min(tiles_per_block, row_tiles - rowblock * tiles_per_block) - wv + 3) >> 2;
-        uint4 qf[kNTS][4];
+        uint4 qf[kNTS][4];  // asked for before the table is built
 #pragma unroll
         for (int nt = 0; nt < kNTS; ++nt) {
+            if (nt >= my_tiles) continue;
             const int row = row0 + nt * 64;
             const int rr = row < rows_total ? row : 0;
-            const int qtok = rr / G;
+            const int qtok = per_token.token(rr);
             const size_t qrow = ((size_t)b * q_len + qtok) * a.Hq + (size_t)g * G + (rr - qtok * G);
             const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q) + qrow * 256);
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = qp[kk * 4 + q4];  // rows past the last repeat row 0, unused: no wait here
+            for (int kk = 0; kk < 4; ++kk) qf[nt][kk] = qp[kk * 4 + q4];  // rows past the last repeat row 0, unused
         }
         float m[kNTS], l[kNTS];  // reference logit times a.c, sum of the exponentials relative to it
 #pragma unroll
@@ -189,30 +188,18 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
         if constexpr (INLINE_PLAN) {
             n_hist = uni(lists.meta[3 * b + 1]);
             n_slots = n_hist + (uni(lists.meta[3 * b + 2]) > 0 ? 1 : 0);
-            SlotTable by_tile = tab;  // `cum` of the table is the chunk prefix here
-            by_tile.cum = tcum;
-            lists.table<true>(b, by_tile, tab.cum);
+            lists.table(b, tab);
         } else {
             const PlanHeader hdr = load_plan(a.plan + (size_t)b * plan_stride(cap), cap, tab);
             n_slots = uni(hdr.n_slots);
             n_hist = uni(hdr.n_hist);
             __syncthreads();
-            for (int i = tid; i < cap; i += 256) tcum[i] = (int)tab.off_v[i];  // where the planning kernel put it
-            if (tid == 0) tcum[cap] = T;
-            __syncthreads();
         }
-        int slot = 0;
-        auto chunk_of_tile = [&](int t) {  // index of the chunk that holds tile t, of segment `slot` (the chunk count for t == T)
-            if (t >= T) return uni(tab.cum[n_slots]);
-            slot = find_slot_wave(tcum, n_slots, t);
-            return uni(tab.cum[slot] + (t - tcum[slot]) / kTilesPerChunk);
-        };
-        const int u_hi = chunk_of_tile(t_hi), u_lo = chunk_of_tile(t_lo);  // chunks [u_lo, u_hi) of sequence b
-        if (u_lo >= u_hi) continue;
+        if (t_lo >= t_hi) continue;  // (a sequence without keys)
 
         // Uniform state of the loader: the segment it stands in (the table in LDS is read on entry only), and
         // inside it the next tile: the address of its first token's keys (head g) and the tokens left from there.
-        int seg_len = 0, seg_first = 0, seg_end = 0, rows_left = 0;
+        int seg_len = 0, seg_end = 0, rows_left = 0;
         bool seg_cur = false;
         const char *seg_k = nullptr, *tile_k = nullptr;  // contiguous history / current round
         long long seg_tab = 0;                           // paged history: first block-table slot
@@ -225,9 +212,9 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
         const int row_a = 8 * wave + q4;                 // this lane helps to load tile rows row_a and row_a + 4
         const unsigned chunk_a = (unsigned)((n - row_a) & 15) * 16u, chunk_b = (unsigned)((n - row_a - 4) & 15) * 16u;
         unsigned off_a = 0, off_b = 0;                   // byte offsets from tile_k for a full tile
-        auto open_seg = [&](int slot) {
+        auto open_seg = [&](int slot, int t) {  // ... and stand at its tile of the sequence's tile t
             seg_len = uni(tab.len[slot]);
-            seg_first = uni(tab.cum[slot]);
+            const int tok0 = (t - uni(tab.cum[slot])) * kTileSP;
             seg_end = uni(tab.cum[slot + 1]);
             seg_cur = slot >= n_hist;
             kstride = seg_cur ? (unsigned)Hkv * 256u : 256u;
@@ -239,9 +226,6 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                 seg_k = kbase + ((size_t)uni64(tab.off_k[slot]) * Hkv + (size_t)g * seg_len) * 256;
             off_a = (unsigned)row_a * kstride + chunk_a;
             off_b = (unsigned)(row_a + 4) * kstride + chunk_b;
-        };
-        auto open_chunk = [&](int u) {  // of the open segment
-            const int tok0 = (u - seg_first) * kChunkTokens;
             rows_left = seg_len - tok0;
             tile_k = reinterpret_cast<const char*>(uni64(reinterpret_cast<long long>(seg_k + (size_t)tok0 * kstride)));
         };
@@ -292,7 +276,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
 #pragma unroll
                 for (int nt = 0; nt < N; ++nt) {
                     // tokens of this segment the row may see (causal inside the current round)
-                    const int lim = is_cur ? cur_visible(len, q_len, min(row0 + nt * 64, rows_total - 1) / G) : len;
+                    const int lim = is_cur ? cur_visible(len, q_len, per_token.token(min(row0 + nt * 64, rows_total - 1))) : len;
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -327,13 +311,13 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
 #pragma unroll
             for (int nt = 0; nt < N; ++nt) l[nt] += sum[nt];
         };
-        // End of chunk u: merge the four lane groups of every row into the chunk's log-sum-exp.  It is stored behind the
-        // request for the tile after next (store_chunk): at once, the wait for that tile's loads, which counts stores
-        // too, would sit out the whole trip of the stores, once per chunk.  The reference logit stays: a later chunk's
-        // sum underflows only where its share of the row's softmax is below 2^-126.
+        // End of a segment or of the range: merge the four lane groups of every row into the log-sum-exp of what the range
+        // has of the segment.  It is stored behind the request for the tile after next (store_place): at once, the wait for
+        // that tile's loads, which counts stores too, would sit out the whole trip of the stores.  The reference logit
+        // stays: a later part's sum underflows only where its share of the row's softmax is below 2^-126.
         float done[kNTS];
-        int done_u = -1;
-        auto finish_chunk = [&](int u) {
+        int done_slot = -1;
+        auto finish_place = [&](int slot) {
 #pragma unroll
             for (int nt = 0; nt < kNTS; ++nt) {
                 const float M = xrow_max4(m[nt]);
@@ -341,89 +325,102 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuS) void scores_prefill_mfma_ke
                 done[nt] = lv > 0.f ? kLn2 * (M + fast_log2(lv)) : -__builtin_inff();
                 l[nt] = 0.f;
             }
-            done_u = u;
+            done_slot = slot;
         };
-        auto store_chunk = [&]() {
-            if (done_u < 0) return;
+        auto store_place = [&]() {
+            if (done_slot < 0) return;
+            int first_row = row0;
+            asm volatile("" : "+v"(first_row));  // the four rows' addresses are made here, not kept in eight registers all through
 #pragma unroll
             for (int nt = 0; nt < kNTS; ++nt) {
-                const int row = row0 + nt * 64;
-                if (nt < my_tiles && row < rows_total && q4 == 0 && done_u < a.n_chunks_max) {  // (a caller that understated max_tokens loses chunks)
-                    const int qtok = row / G;
+                const int row = first_row + nt * 64;
+                if (nt < my_tiles && row < rows_total && q4 == 0) {
+                    const int qtok = per_token.token(row);
                     const size_t rowid = ((size_t)b * a.Hq + (size_t)g * G + (row - qtok * G)) * q_len + qtok;  // [B][Hq][q_len]
-                    a.part[rowid * a.n_chunks_max + done_u] = done[nt];
+                    a.part[rowid * a.n_chunks_max + done_slot + part] = done[nt];
                 }
             }
-            done_u = -1;
+            done_slot = -1;
         };
-        // ---- walk the key tiles of chunks [u_lo, u_hi): the whole workgroup in lockstep ------------------------
-        open_seg(slot);
-        open_chunk(u_lo);
-        int lu = u_lo, lj = 0;  // the tile the loader fetches next: tile lj of chunk lu
+        // ---- walk the key tiles [t_lo, t_hi): the whole workgroup in lockstep ----------------------------------
+        int slot = find_slot_wave(tab.cum, n_slots, t_lo);
+        const int slot_lo = slot;
+        open_seg(slot, t_lo);
         int c_tok0 = seg_len - rows_left;
         load_tile(tiles_lds);
         int bufsel = 0;
-        while (true) {
+        for (int t = t_lo; t < t_hi; ++t) {
             char* buf = tiles + bufsel * kKTileBytes;
             wait_for_direct_loads();  // this wave's quarter of the tile has landed in LDS
-            // the tile just stored, as the consumer needs it; it ends its chunk if the chunk or the segment ends
-            const int c_len = seg_len, c_u = lu, c_t = c_tok0;
-            const bool c_cur = seg_cur, c_last = lj + 1 == kTilesPerChunk || rows_left <= 0;
+            // the tile just stored, as the consumer needs it
+            const int c_len = seg_len, c_t = c_tok0, c_slot = slot;
+            const bool c_cur = seg_cur, c_last = t + 1 == seg_end || t + 1 == t_hi;
             __syncthreads();
-            bool more = true;
-            if (!c_last) {
-                ++lj;
-            } else {
-                ++lu;
-                lj = 0;
-                more = lu < u_hi;
-                if (more && lu >= seg_end) {
-                    do ++slot; while (lu >= uni(tab.cum[slot + 1]));
-                    open_seg(slot);
-                    open_chunk(lu);
+            if (t + 1 < t_hi) {
+                if (t + 1 >= seg_end) {
+                    do ++slot; while (t + 1 >= uni(tab.cum[slot + 1]));
+                    open_seg(slot, t + 1);
                 }
-            }
-            if (more) {
                 c_tok0 = seg_len - rows_left;
                 load_tile(tiles_lds + (bufsel ^ 1) * kKTileBytes);
             }
-            store_chunk();
+            store_place();
             if (!RAGGED || my_tiles == 4) consume(std::integral_constant<int, 4>(), buf, c_t, c_len, c_cur);
             else if (my_tiles == 3) consume(std::integral_constant<int, 3>(), buf, c_t, c_len, c_cur);
             else if (my_tiles == 2) consume(std::integral_constant<int, 2>(), buf, c_t, c_len, c_cur);
             else if (my_tiles == 1) consume(std::integral_constant<int, 1>(), buf, c_t, c_len, c_cur);
-            if (c_last) finish_chunk(c_u);
-            if (!more) break;
+            if (c_last) finish_place(c_slot);
             bufsel ^= 1;
         }
-        store_chunk();
+        store_place();
+        if (rest == 0 && wave == 0) note_places(a.places, b, vw.R_max, n_hist, tab.cum, slot_lo, slot, part, t_lo, t_hi);
     }
 }
 
 
 static void launch_scores_plan(const ScoreArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(scores_plan_kernel, dim3(a.view.B), dim3(256), (size_t)(a.view.R_max + 2) * 2 * sizeof(int), st, a,
+    hipLaunchKernelGGL(scores_plan_kernel, dim3(a.view.B), dim3(256), (size_t)(a.view.R_max + 2) * sizeof(int), st, a,
                        const_cast<char*>(a.plan));
 }
 
-int launch_scores_prefill_mfma(ScoreArgs a, bool paged, int num_cu, hipStream_t st) {
-    const int G = a.Hq / a.view.Hkv;
-    if (G > 16) return fail(RA_ERR_UNSUPPORTED, "round_scores: Hq / Hkv = %d exceeds 16", G);
-    const int B = a.view.B, Hkv = a.view.Hkv;
-    if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "round_scores: batch %d exceeds %d", B, kMaxBatch);
-    const int rows_total = a.q_len * G;
-    const int n_rowblocks = (rows_total + kRowsPerItemS - 1) / kRowsPerItemS;
-    const size_t table_lds = align_up(SlotTable::bytes(a.view.R_max + 1), 16) + 2 * kKTileBytes +
-                             align_up((size_t)(a.view.R_max + 2) * sizeof(int), 16);
-    const size_t inline_lds = table_lds + BatchLists::bytes(B, a.view.R_max);
-    long long max_pieces = (long long)B + (long long)B * a.n_chunks_max * kTilesPerChunk / a.min_units;
-    if (max_pieces > (long long)B * a.S) max_pieces = (long long)B * a.S;
-    long long grid = (long long)kWorkgroupsPerCuS * num_cu;
-    if (grid > max_pieces * Hkv * n_rowblocks) grid = max_pieces * Hkv * n_rowblocks;
-    if (grid < 1) grid = 1;
-    a.slots = question_slots(Hkv * n_rowblocks, grid, num_cu, false);
-    const bool plan_inline = prefill_plans_inline(B, a.view.R_max, inline_lds, grid, num_cu);
-    const size_t smem = plan_inline ? inline_lds : table_lds;
+// A launch that plans itself cuts down to two tiles a range, so that small questions spread over the chip (25 rounds of 50
+// tokens, 32 tokens of 64 heads, whole call 49.5 -> 43.0 microseconds against ranges of at least eight, 45.1 with four; 5 short
+// rounds, 102 tokens of 8 heads 47.7 -> 41.0).  Planned apart the batch is large and shorter ranges only add starts (100
+// dialogues, 16 tokens: 8 tiles 263.6, 2 tiles 268.0).
+constexpr int kMinTilesInline = 2, kMinTilesPlanned = 8;
+
+static size_t scores_prefill_lds(int B, int R_max, bool plan_inline) {
+    return align_up(SlotTable::bytes(R_max + 1), 16) + 2 * kKTileBytes + (plan_inline ? BatchLists::bytes(B, R_max) : 0);
+}
+
+void scores_prefill_shape(ScoreArgs& a, long long room) {
+    const int B = a.view.B, rows_total = a.q_len * (a.Hq / a.view.Hkv);
+    a.n_rowblocks = (rows_total + kRowsPerItemS - 1) / kRowsPerItemS;
+    const int inner = a.view.Hkv * a.n_rowblocks;
+    for (int plan_inline = 1; plan_inline >= 0; --plan_inline) {
+        a.plan_inline = plan_inline;
+        a.min_units = plan_inline ? kMinTilesInline : kMinTilesPlanned;
+        const long long most = B + B * a.max_tiles / a.min_units;  // ranges
+        long long grid = (long long)kWorkgroupsPerCuS * a.num_cu;
+        if (grid > most * inner) grid = most * inner;
+        if (grid < 1) grid = 1;
+        a.grid = (int)grid;
+        a.slots = plan_inline ? question_slots(inner, grid, a.num_cu, false)
+                              : (int)(grid * kPiecesPerWorkgroupS / inner < 1 ? 1 : grid * kPiecesPerWorkgroupS / inner);
+        if (a.slots > kMaxRanges) a.slots = kMaxRanges;
+        long long parts = a.max_tiles / a.min_units + 2;
+        if (parts > a.slots) parts = a.slots;
+        a.S = (int)(parts > room ? room : parts);
+        a.max_parts = a.S >= a.slots ? kMaxRanges + 2 : a.S;
+        if (plan_inline && a.max_parts > 2 && prefill_plans_inline(B, a.view.R_max, scores_prefill_lds(B, a.view.R_max, true), grid, a.num_cu))
+            return;
+    }
+}
+
+int launch_scores_prefill_mfma(const ScoreArgs& a, bool paged, hipStream_t st) {
+    const int rows_total = a.q_len * (a.Hq / a.view.Hkv), n_rowblocks = a.n_rowblocks, grid = a.grid;
+    const bool plan_inline = a.plan_inline != 0;
+    const size_t smem = scores_prefill_lds(a.view.B, a.view.R_max, plan_inline);
     if (!plan_inline) launch_scores_plan(a, st);
     const int row_tiles = (rows_total + 15) / 16;
     const bool ragged = row_tiles != n_rowblocks * 4 * kNTS;

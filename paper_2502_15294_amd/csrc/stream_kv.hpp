@@ -314,6 +314,15 @@ struct BlockWindow {
     }
 };
 
+// Row / G for the query rows of the many-row kernels, G <= 16, by one multiplication: exact below 2^27 rows, of whose partial
+// results a workspace would hold terabytes.  (A division is twenty instructions, and a question kernel had a dozen of them
+// in front of its first tile and in every store of scores.)
+struct RowsPerToken {
+    unsigned magic;  // ceil(2^31 / G)
+    __device__ explicit RowsPerToken(int G) : magic((0x80000000u + (unsigned)G - 1) / (unsigned)G) {}
+    __device__ __forceinline__ int token(int row) const { return (int)__umulhi(2u * (unsigned)row, magic); }
+};
+
 // ---- balanced schedule of a whole batch ------------------------------------------------------------
 // Every workgroup of a persistent attention launch derives the same schedule from the per-sequence
 // unit counts U_b the planning kernel left in the plan headers: sequence b is cut into
@@ -460,13 +469,11 @@ struct BatchLists {
         }
         lds_barrier();
     }
-    // Sequence b's table by the first wave, cum the prefix of the segments' key tiles; with CHUNKS the prefix of their
-    // 256-token chunks goes to ccum.  Ends with a barrier.
-    template <bool CHUNKS>
-    __device__ __forceinline__ void table(int b, const SlotTable& tab, int* ccum) const {
+    // Sequence b's table by the first wave, cum the prefix of the segments' key tiles.  Ends with a barrier.
+    __device__ __forceinline__ void table(int b, const SlotTable& tab) const {
         if (threadIdx.x < 64) {
             const int lane = threadIdx.x, cap = R_max + 1;
-            int t0 = 0, c0 = 0;
+            int t0 = 0;
             for (int i0 = 0; i0 < cap; i0 += 64) {
                 const int i = i0 + lane;
                 long long k = 0, v = 0;
@@ -479,16 +486,8 @@ struct BatchLists {
                     tab.cum[i] = t0 + t - tiles;
                 }
                 t0 += __builtin_amdgcn_readlane(t, 63);
-                if constexpr (CHUNKS) {
-                    const int chunks = (n + 255) >> 8, c = wave_inclusive_sum(chunks);
-                    if (i < cap) ccum[i] = c0 + c - chunks;
-                    c0 += __builtin_amdgcn_readlane(c, 63);
-                }
             }
-            if (lane == 0) {
-                tab.cum[cap] = t0;
-                if constexpr (CHUNKS) ccum[cap] = c0;
-            }
+            if (lane == 0) tab.cum[cap] = t0;
         }
         lds_barrier();
     }
@@ -566,6 +565,10 @@ __device__ __forceinline__ int parts_of(const TileRanges& tr, int P, const LaneS
     if (U <= 0) return 0;
     first = find_slot_wave(tr.bound, P, t0);
     return find_slot_wave(tr.bound, P, t0 + U - 1) - first + 1;
+}
+// The first of them, for a sequence with tiles.
+__device__ __forceinline__ int first_part_of(const TileRanges& tr, int P, const LaneSequence& sq, int b) {
+    return find_slot_wave(tr.bound, P, __builtin_amdgcn_readlane(sq.tile0, b));
 }
 // The range that the position-th group of workgroups takes: class 0's ranges first, then class 1's, ...
 template <int C>

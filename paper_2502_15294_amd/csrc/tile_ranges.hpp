@@ -44,6 +44,8 @@ struct RangeWeights {
 RA_HD constexpr RangeWeights<3> score_range_weights() { return {{1370, 1080, 550}}; }
 RA_HD constexpr RangeWeights<2> attn_range_weights() { return {{1180, 820}}; }
 
+constexpr int kWeightedTiles = 8;  // shortest ranges that are cut by weight (and none of which a light class leaves without a tile)
+
 // Most ranges of a launch of `grid` workgroups, `inner` of which stream each range (its KV heads and blocks of query rows).
 // A range's workgroups lie on consecutive units, and the launch lasts as long as the unit with the most of them.  As many
 // ranges as run at the same time, if that leaves no more than an eighth of the units' time unused; otherwise the fewest
@@ -86,7 +88,7 @@ struct TileCut {
         for (int k = 0; k < C; ++k) sum += w[k] = weights.w[k];
         const bool fits = n_ranges <= max_parts ||
                           (long long)lightest_run(max_parts - 1) * total >= (long long)most * weight_before(n_ranges % C, n_ranges / C);
-        if (!(full && n_ranges == slots && n_ranges % C == 0 && fits)) {
+        if (!(full && len >= kWeightedTiles && n_ranges == slots && n_ranges % C == 0 && fits)) {
             for (int k = 0; k < C; ++k) w[k] = 1000;
             sum = 1000 * C;
         }
