@@ -367,6 +367,8 @@ size_t ra_kv_store_round_bytes(const ra_kv_store* store, int len);
 /*
  * Enqueue on `side_stream` the host-to-device copies of every selected round and of the index
  * tables of the compact per-layer views, and record one "ready" event per layer.
+ * (The copies of a group of layers are one kernel launch that reads the pinned host memory; asynchronous copies
+ * where it cannot: memory made non-coherent, tensors not 16-byte aligned.)
  *   sel_idx_host int32 [B][R_max], n_sel_host int32 [B]  (host memory; read before returning)
  * Returns RA_ERR_STATE if a selected round was never registered, RA_ERR_OOM if the pool is too
  * small (nothing is enqueued in either case).

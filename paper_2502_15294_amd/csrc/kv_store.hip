@@ -3,33 +3,61 @@
 // moved to the GPU, each in one transfer, once the selection is known).
 //
 // Mostly host side: a registry of pinned per-round tensors, a bump-allocated device pool, the index
-// tables of the compact per-layer views, and the hipMemcpyAsync / event choreography on a side
+// tables of the compact per-layer views, and the choreography of copies and events on a side
 // stream.  The copied bytes keep the host layout: per layer the keys [Hkv][len][d] followed by the
 // values in transposed 16-token tiles [Hkv][ceil(len/16)][d][16].  Every slice is therefore already a
 // round block in the device layout and staging needs no repacking kernel.
 //
-// The one kernel here runs at the end of a turn (Sec. 3.2, last step; Alg. 1, last line): it gathers
+// The copies into the pool are made by a kernel that reads the pinned host memory itself (stage_kernel).  The kernel at the
+// end of a turn (Sec. 3.2, last step; Alg. 1, last line) gathers
 // the new round's token-major keys and values of every post-watershed layer into that round layout
 // behind the staged rounds in the pool, from where each sequence's new round leaves for host memory
 // in one copy.  The registry also counts how often each round was staged, which is what KV-cache
 // dropping (Sec. 3.4) decides on.
 #include "common.hpp"
 
+#include <memory>
 #include <new>
 #include <vector>
 
+namespace ra {
+constexpr int kStageGroups = 5;  // most groups of layers of different size (grouped order)
+// A selected round on its way into the pool.
+struct StageJob {
+    const char* src;
+    int64_t dst;          // byte offset of its first layer in the pool
+    int64_t layer_bytes;  // of one layer, a multiple of 16
+};
+// Byte offsets of the tables in their block.
+struct StoreTables {
+    size_t off = 0, len = 0, n = 0, jobs = 0, units = 0, bytes = 0;
+    void layout(const ra_store_cfg& c) {
+        const size_t plane = (size_t)c.B * c.R_max;
+        len = align_up(off + (size_t)c.n_layers * 2 * plane * sizeof(int64_t), 16);
+        n = align_up(len + plane * sizeof(int32_t), 16);
+        jobs = align_up(n + (size_t)c.B * sizeof(int32_t), 16);
+        units = align_up(jobs + plane * sizeof(StageJob), 16);  // [kStageGroups][B * R_max + 1] prefix of the jobs' units
+        bytes = align_up(units + kStageGroups * (plane + 1) * sizeof(int32_t), 16);
+    }
+};
+}  // namespace ra
+
 struct ra_kv_store {
+    using StoreTables = ra::StoreTables;
     ra_store_cfg cfg;
     size_t token_bytes = 0;  // bytes of one token of one layer of K (or V): Hkv * d * elem
     struct Round {
         const char* host = nullptr;
+        bool direct = false;  // kernels may read the host tensor
         int len = -1;  // -1 = never registered
         uint32_t turns = 0, hits = 0;  // stage calls since registration / of those, the ones that selected it
         bool dropped = false;
     };
     std::vector<Round> rounds;  // [B][R_max]
     char* pool = nullptr;
-    // index tables: host pinned mirror and device copy
+    // index tables of the views and the staging kernel's: one block, host pinned mirror and device copy
+    char *h_tab = nullptr, *d_tab = nullptr;
+    StoreTables tab;
     int64_t* h_off = nullptr;  // [n_layers][2][B][R_max]
     int32_t* h_len = nullptr;  // [B][R_max]
     int32_t* h_n = nullptr;    // [B]
@@ -68,17 +96,65 @@ static int grouped_stage_size(int L, int gi) {
     return 1;
 }
 
-static bool is_pinned_host(const void* p) {
+// `direct`: whether kernels may read and write it (pinned memory made coherent, at the same address).
+static bool is_pinned_host(const void* p, bool* direct = nullptr) {
     hipPointerAttribute_t attr;
     hipError_t e = hipPointerGetAttributes(&attr, p);
     if (e != hipSuccess) {
         (void)hipGetLastError();  // ordinary pageable memory: not an error of ours, clear the sticky code
         return false;
     }
+    if (direct) *direct = attr.devicePointer == p && !(attr.allocationFlags & hipHostMallocNonCoherent);
     return attr.type == hipMemoryTypeHost;
 }
 
 namespace {
+// ---- host memory into the pool ------------------------------------------------------------------------
+// The kernel reads pinned host memory over the link, in units of 16 KB (a workgroup's four 16-byte loads a thread) that a
+// small grid takes in turn.  The link is the bound, and it is full with half a megabyte asked for: 57 GB/s with 32 to 1024
+// workgroups, as one large asynchronous copy has.  But every asynchronous copy costs 10 microseconds of its own on the
+// stream, whatever its size (45 GB/s in copies of 2 MB, 38 of 1 MB, 18 of 256 KB), and a turn has one per (group of layers,
+// round): a turn of 16 selected rounds and 6 layers 4 173 -> 3 501 microseconds (with 16 workgroups 3 705, 64 3 520, 128 3 475),
+// of 30 short rounds and 5 layers 3 789 -> 2 403 (64: 2 390), of one dialogue and 3 layers 387 -> 304 (64: 319).  The grid is
+// small also so that the decode launches that run beside it find every compute unit.
+constexpr int kStageThreads = 256, kStageLoads = 4, kStageGrid = 32;
+constexpr int kUnitBytes = kStageThreads * kStageLoads * 16;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) u32x4 global_u32x4;  // (a pointer out of a table would be a flat one)
+
+// unit0[j]: first unit of job j, unit0[n_jobs] = n_units.  Layers [l0, l0 + n_l) of every job.
+__global__ __launch_bounds__(kStageThreads) void stage_kernel(const StageJob* jobs, const int32_t* unit0, int n_jobs, int n_units, int l0,
+                                                             int n_l, char* pool) {
+    const int lane = threadIdx.x & 63;
+    int j = 0;  // unit0[j] <= u
+    for (int u = blockIdx.x; u < n_units; u += gridDim.x) {
+        while (true) {
+            const int at_or_before = __popcll(__ballot(j + lane < n_jobs && unit0[min(j + lane, n_jobs)] <= u));
+            j += at_or_before - 1;
+            if (at_or_before < 64) break;
+        }
+        const StageJob jb = jobs[j];
+        const int64_t first = (int64_t)l0 * jb.layer_bytes, end = first + (int64_t)n_l * jb.layer_bytes;
+        const int64_t at = first + (int64_t)(u - unit0[j]) * kUnitBytes + threadIdx.x * 16;
+        u32x4 v[kStageLoads];
+#pragma unroll
+        for (int i = 0; i < kStageLoads; ++i) {
+            const int64_t o = at + i * (kStageThreads * 16);
+            if (o < end) v[i] = __builtin_nontemporal_load((const global_u32x4*)(jb.src + o));
+        }
+#pragma unroll
+        for (int i = 0; i < kStageLoads; ++i) {
+            const int64_t o = at + i * (kStageThreads * 16);
+            if (o < end) *reinterpret_cast<u32x4*>(pool + jb.dst + o) = v[i];
+        }
+    }
+}
+
+// The tables, 16-byte pieces.
+__global__ __launch_bounds__(kStageThreads) void copy_tables_kernel(const u32x4* src, u32x4* dst, int n) {
+    for (int i = blockIdx.x * kStageThreads + threadIdx.x; i < n; i += gridDim.x * kStageThreads) dst[i] = src[i];
+}
+
 constexpr int kRepackThreads = 256;
 
 template <typename T>
@@ -154,15 +230,16 @@ int ra_kv_store_create(ra_kv_store** out, const ra_store_cfg* cfg) {
     s->cfg = *cfg;
     s->token_bytes = (size_t)cfg->Hkv * cfg->d * (cfg->dtype == RA_BF16 ? 2 : 4);
     s->rounds.resize((size_t)cfg->B * cfg->R_max);
-    const size_t n_off = (size_t)cfg->n_layers * 2 * cfg->B * cfg->R_max;
-    const size_t n_len = (size_t)cfg->B * cfg->R_max;
+    s->tab.layout(*cfg);
     hipError_t e = hipMalloc((void**)&s->pool, cfg->device_pool_bytes);
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_off, n_off * sizeof(int64_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_len, n_len * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_n, (size_t)cfg->B * sizeof(int32_t));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_off, n_off * sizeof(int64_t), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_len, n_len * sizeof(int32_t), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_n, (size_t)cfg->B * sizeof(int32_t), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipMalloc((void**)&s->d_tab, s->tab.bytes);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_tab, s->tab.bytes, hipHostMallocDefault);
+    s->h_off = reinterpret_cast<int64_t*>(s->h_tab + s->tab.off);
+    s->h_len = reinterpret_cast<int32_t*>(s->h_tab + s->tab.len);
+    s->h_n = reinterpret_cast<int32_t*>(s->h_tab + s->tab.n);
+    s->d_off = reinterpret_cast<int64_t*>(s->d_tab + s->tab.off);
+    s->d_len = reinterpret_cast<int32_t*>(s->d_tab + s->tab.len);
+    s->d_n = reinterpret_cast<int32_t*>(s->d_tab + s->tab.n);
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_wb_off, (size_t)cfg->B * sizeof(int64_t));
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_wb_len, (size_t)cfg->B * sizeof(int32_t));
     if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_wb_off, (size_t)cfg->B * sizeof(int64_t), hipHostMallocDefault);
@@ -190,12 +267,8 @@ int ra_kv_store_destroy(ra_kv_store* s) {
     for (hipEvent_t ev : s->ready)
         if (ev) (void)hipEventDestroy(ev);
     if (s->pool) (void)hipFree(s->pool);
-    if (s->d_off) (void)hipFree(s->d_off);
-    if (s->d_len) (void)hipFree(s->d_len);
-    if (s->d_n) (void)hipFree(s->d_n);
-    if (s->h_off) (void)hipHostFree(s->h_off);
-    if (s->h_len) (void)hipHostFree(s->h_len);
-    if (s->h_n) (void)hipHostFree(s->h_n);
+    if (s->d_tab) (void)hipFree(s->d_tab);
+    if (s->h_tab) (void)hipHostFree(s->h_tab);
     if (s->wb_pending) (void)hipEventSynchronize(s->wb_done);  // host tensors may be freed right after this call
     if (s->d_wb_off) (void)hipFree(s->d_wb_off);
     if (s->d_wb_len) (void)hipFree(s->d_wb_len);
@@ -220,11 +293,13 @@ int ra_kv_store_register_round(ra_kv_store* s, int seq, int round, const void* h
     RA_REQUIRE(len >= 0, RA_ERR_INVALID_ARG, "kv_store_register_round: negative length");
     RA_REQUIRE(len == 0 || host_kv != nullptr, RA_ERR_INVALID_ARG, "kv_store_register_round: host_kv is NULL");
     RA_REQUIRE(!s->staged, RA_ERR_STATE, "kv_store_register_round: rounds are staged; call ra_kv_store_release first");
+    bool direct = false;
     if (len > 0)
-        RA_REQUIRE(is_pinned_host(host_kv), RA_ERR_INVALID_ARG,
+        RA_REQUIRE(is_pinned_host(host_kv, &direct), RA_ERR_INVALID_ARG,
                    "kv_store_register_round: host_kv is not pinned host memory (use hipHostMalloc / pin_memory)");
     ra_kv_store::Round& r = s->rounds[(size_t)seq * s->cfg.R_max + round];
     r.host = static_cast<const char*>(host_kv);
+    r.direct = direct;
     r.len = len;
     r.turns = r.hits = 0;
     r.dropped = false;
@@ -242,6 +317,7 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
     // ---- validate the selection and place every selected round in the pool ----------------------
     struct Job { const char* src; size_t dst_tok; int len; };
     std::vector<Job> jobs;
+    bool direct = s->token_bytes % 16 == 0;  // every copy can be the kernel's
     size_t tok = 0;  // pool cursor in units of token_bytes
     int64_t max_tokens = 0;
     for (int b = 0; b < B; ++b) {
@@ -257,6 +333,7 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
             const ra_kv_store::Round& rd = s->rounds[(size_t)b * R + r];
             RA_REQUIRE(rd.len >= 0, RA_ERR_STATE, "kv_store_stage: round %d of sequence %d was never registered", r, b);
             jobs.push_back({rd.host, tok, rd.len});
+            direct &= rd.len == 0 || (rd.direct && (uintptr_t)rd.host % 16 == 0);
             tok += (size_t)L * layer_tokens(rd.len);
             seq_tokens += rd.len;
         }
@@ -298,52 +375,59 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
     // a round saved at the end of the last turn may be selected now, and its packed copy may still
     // sit where this selection is about to land: both wait for the write-back
     if (s->wb_pending) RA_HIP_CHECK(hipStreamWaitEvent(st, s->wb_done, 0));
-    RA_HIP_CHECK(hipMemcpyAsync(s->d_off, s->h_off, (size_t)L * 2 * plane * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    RA_HIP_CHECK(hipMemcpyAsync(s->d_len, s->h_len, plane * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    RA_HIP_CHECK(hipMemcpyAsync(s->d_n, s->h_n, (size_t)B * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    s->staged_bytes = 0;
-    s->n_copies = 0;
-    if (order == RA_STAGE_ROUND_MAJOR) {
+    // Groups of consecutive layers [l0, l1) in the order they are copied, every round's layers of a group as one slice: a
+    // round's layers are contiguous in its host tensor.  Grouped: a small first group lets the first post-watershed layer
+    // start early, a last group of one layer leaves a single layer's attention to run after the last byte has arrived.
+    std::vector<int> bounds{0};
+    for (int gi = 0; bounds.back() < L; ++gi)
+        bounds.push_back(order == RA_STAGE_ROUND_MAJOR ? L
+                                                       : bounds.back() + (order == RA_STAGE_LAYER_MAJOR ? 1 : grouped_stage_size(L, gi)));
+    const int n_groups = (int)bounds.size() - 1;
+    int n_jobs = 0;  // rounds with tokens
+    for (const Job& jb : jobs) n_jobs += jb.len > 0;
+    s->staged_bytes = (uint64_t)tok * s->token_bytes;
+    s->n_copies = (uint64_t)n_groups * n_jobs;
+    // units of 16 KB of every group; the layer-major order's groups are all of one size
+    std::vector<int64_t> n_units(n_groups, 0);
+    if (direct) {
+        StageJob* h_jobs = reinterpret_cast<StageJob*>(s->h_tab + s->tab.jobs);
+        int32_t* h_units = reinterpret_cast<int32_t*>(s->h_tab + s->tab.units);
+        int k = 0;
+        for (const Job& jb : jobs)
+            if (jb.len > 0) h_jobs[k++] = {jb.src, (int64_t)(jb.dst_tok * s->token_bytes), (int64_t)(layer_tokens(jb.len) * s->token_bytes)};
+        for (int g = 0; g < n_groups; ++g) {
+            int32_t* row = h_units + (size_t)(order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1);
+            for (k = 0; k < n_jobs && n_units[g] <= INT32_MAX / 2; ++k) {
+                row[k] = (int32_t)n_units[g];
+                n_units[g] += ((bounds[g + 1] - bounds[g]) * h_jobs[k].layer_bytes + kUnitBytes - 1) / kUnitBytes;
+            }
+            row[n_jobs] = (int32_t)n_units[g];
+            direct &= n_units[g] <= INT32_MAX / 2;
+        }
+    }
+    int prev_device = 0;
+    RA_HIP_CHECK(hipGetDevice(&prev_device));
+    RA_HIP_CHECK(hipSetDevice(s->cfg.device));
+    struct Back { int device; ~Back() { (void)hipSetDevice(device); } } back{prev_device};
+    const int n_pieces = (int)(s->tab.bytes / 16);
+    hipLaunchKernelGGL(copy_tables_kernel, dim3(n_pieces < kStageGrid * kStageThreads ? (n_pieces + kStageThreads - 1) / kStageThreads : kStageGrid),
+                       dim3(kStageThreads), 0, st, reinterpret_cast<const u32x4*>(s->h_tab), reinterpret_cast<u32x4*>(s->d_tab), n_pieces);
+    for (int g = 0; g < n_groups; ++g) {
+        const int l0 = bounds[g], n_l = bounds[g + 1] - l0;
+        if (direct && n_jobs > 0) {
+            const int32_t* row = reinterpret_cast<const int32_t*>(s->d_tab + s->tab.units) + (size_t)(order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1);
+            const int grid = n_units[g] < kStageGrid ? (int)n_units[g] : kStageGrid;
+            hipLaunchKernelGGL(stage_kernel, dim3(grid), dim3(kStageThreads), 0, st, reinterpret_cast<const StageJob*>(s->d_tab + s->tab.jobs),
+                               row, n_jobs, (int)n_units[g], l0, n_l, s->pool);
+        }
         for (const Job& jb : jobs) {
-            if (jb.len == 0) continue;
-            const size_t bytes = (size_t)L * layer_tokens(jb.len) * s->token_bytes;
-            RA_HIP_CHECK(hipMemcpyAsync(s->pool + jb.dst_tok * s->token_bytes, jb.src, bytes, hipMemcpyHostToDevice, st));
-            s->staged_bytes += bytes;
-            ++s->n_copies;
+            if (direct || jb.len == 0) continue;
+            const size_t slice = layer_tokens(jb.len) * s->token_bytes;
+            RA_HIP_CHECK(hipMemcpyAsync(s->pool + jb.dst_tok * s->token_bytes + l0 * slice, jb.src + l0 * slice, n_l * slice,
+                                        hipMemcpyHostToDevice, st));
         }
-        for (int l = 0; l < L; ++l) RA_HIP_CHECK(hipEventRecord(s->ready[l], st));
-    } else if (order == RA_STAGE_GROUPED) {
-        // Groups of consecutive layers, one copy per (group, round): a round's layers are contiguous in its host
-        // tensor, so a group is one slice.  A small first group lets the first post-watershed layer start early, a
-        // last group of one layer leaves a single layer's attention to run after the last byte has arrived, and
-        // up to three larger groups in between keep the number of copies (and their fixed cost on the link) down.
-        for (int l0 = 0, gi = 0; l0 < L; ++gi) {
-            const int l1 = l0 + grouped_stage_size(L, gi);
-            for (const Job& jb : jobs) {
-                if (jb.len == 0) continue;
-                const size_t bytes = (size_t)(l1 - l0) * layer_tokens(jb.len) * s->token_bytes;
-                const size_t o = (size_t)l0 * layer_tokens(jb.len) * s->token_bytes;
-                RA_HIP_CHECK(hipMemcpyAsync(s->pool + jb.dst_tok * s->token_bytes + o, jb.src + o, bytes,
-                                            hipMemcpyHostToDevice, st));
-                s->staged_bytes += bytes;
-                ++s->n_copies;
-            }
-            for (int l = l0; l < l1; ++l) RA_HIP_CHECK(hipEventRecord(s->ready[l], st));
-            l0 = l1;
-        }
-    } else {
-        for (int l = 0; l < L; ++l) {
-            for (const Job& jb : jobs) {
-                if (jb.len == 0) continue;
-                const size_t bytes = layer_tokens(jb.len) * s->token_bytes;
-                const size_t o = (size_t)l * layer_tokens(jb.len) * s->token_bytes;
-                RA_HIP_CHECK(hipMemcpyAsync(s->pool + jb.dst_tok * s->token_bytes + o, jb.src + o, bytes,
-                                            hipMemcpyHostToDevice, st));
-                s->staged_bytes += bytes;
-                ++s->n_copies;
-            }
-            RA_HIP_CHECK(hipEventRecord(s->ready[l], st));
-        }
+        RA_HIP_CHECK(hipGetLastError());
+        for (int l = l0; l < l0 + n_l; ++l) RA_HIP_CHECK(hipEventRecord(s->ready[l], st));
     }
     s->max_tokens = max_tokens;
     s->staged_tok = tok;
@@ -410,6 +494,7 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
     size_t tok = s->staged ? s->staged_tok : 0;
     int max_len = 0;
     std::vector<int64_t> off(B, -1);
+    std::unique_ptr<bool[]> direct(new bool[B]());
     for (int b = 0; b < B; ++b) {
         const int r = round_host[b];
         if (r == -1) continue;
@@ -418,7 +503,7 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
         RA_REQUIRE(n >= 0 && n <= cur_cap, RA_ERR_INVALID_ARG, "kv_store_save_round: len[%d] = %d outside [0, %d]", b,
                    n, cur_cap);
         if (n > 0)
-            RA_REQUIRE(host_kv[b] != nullptr && is_pinned_host(host_kv[b]), RA_ERR_INVALID_ARG,
+            RA_REQUIRE(host_kv[b] != nullptr && is_pinned_host(host_kv[b], &direct[b]), RA_ERR_INVALID_ARG,
                        "kv_store_save_round: host_kv[%d] is not pinned host memory", b);
         off[b] = (int64_t)tok;
         tok += (size_t)L * layer_tokens(n);
@@ -483,6 +568,7 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
         if (off[b] < 0) continue;
         ra_kv_store::Round& r = s->rounds[(size_t)b * R + round_host[b]];
         r.host = len_host[b] > 0 ? static_cast<const char*>(host_kv[b]) : nullptr;
+        r.direct = direct[b];
         r.len = len_host[b];
         r.turns = r.hits = 0;
         r.dropped = false;

@@ -1,0 +1,60 @@
+"""Staging: the kernel that reads pinned host memory against asynchronous copies of the same bytes (host tensors at addresses that
+the kernel cannot read in 16-byte pieces), for every order, rounds of a token and of none, and more rounds than a wave looks up at
+once."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2502_15294_amd as ra
+
+pytestmark = pytest.mark.gpu
+
+LENS = {
+    "few": [[700, 0, 1, 33], [16, 17, 250, 0]],
+    "130_short": [[1 + i % 3 for i in range(130)], [5] * 130],
+    "unit_ends": [[32, 64, 31, 480], [1, 96, 2000, 4]],  # a unit of 16 KB is 32 tokens' keys and values of one layer at 2 KV heads
+}
+
+
+def _stage(lens, layers, order, offset):
+    """(outputs of a decode over every staged layer, bytes staged): the host tensors begin `offset` bytes into their buffers."""
+    B, R, Hkv, d = len(lens), len(lens[0]), 2, 64
+    rng = np.random.default_rng(1)
+    store = ra.ra_kv_store_create(0, layers, B, R, Hkv, d, ra.RA_BF16, 64 << 20)
+    keep = []
+    for b in range(B):
+        for r in range(R):
+            n = ra.ra_kv_store_round_bytes(store, lens[b][r])
+            buf = torch.zeros(n + 64, dtype=torch.uint8, pin_memory=True)
+            if n:
+                buf[offset:offset + n] = torch.from_numpy(rng.normal(size=n // 2).astype(np.float32)).to(torch.bfloat16).view(torch.uint8)
+            keep.append(buf)
+            ra.ra_kv_store_register_round(store, b, r, buf[offset:], lens[b][r])
+    sel = torch.arange(R, dtype=torch.int32).repeat(B, 1)
+    sel[:, -1] = -1  # all rounds but the last
+    side = torch.cuda.Stream()
+    ra.ra_kv_store_stage(store, sel, torch.full((B,), R - 1, dtype=torch.int32), order, side)
+    ctx = ra.ra_create(0)
+    ws = torch.empty(ra.ra_workspace_bytes(B, R, 8, Hkv, d, 1, ra.RA_BF16, max(sum(x) for x in lens)), dtype=torch.uint8, device="cuda")
+    ra.ra_set_workspace(ctx, ws)
+    q = torch.randn((B, 8, d), generator=torch.Generator("cuda").manual_seed(2), device="cuda", dtype=torch.bfloat16)
+    outs = []
+    for layer in range(layers):
+        ra.ra_kv_store_wait_layer(store, layer)
+        outs.append(ra.ra_round_sparse_attn_decode(ctx, q, ra.ra_kv_store_layer_view(store, layer))[0])
+    torch.cuda.synchronize()
+    staged = ra.ra_kv_store_stats(store)[0]
+    ra.ra_kv_store_release(store)
+    ra.ra_kv_store_destroy(store)
+    ra.ra_destroy(ctx)
+    return torch.stack(outs).cpu(), staged
+
+
+@pytest.mark.parametrize("name", list(LENS))
+@pytest.mark.parametrize("order,layers", [(ra.RA_STAGE_ROUND_MAJOR, 3), (ra.RA_STAGE_LAYER_MAJOR, 7), (ra.RA_STAGE_GROUPED, 9), (ra.RA_STAGE_GROUPED, 1)])
+def test_kernel_and_copies_stage_the_same_bytes(name, order, layers):
+    lens = LENS[name]
+    by_kernel, n = _stage(lens, layers, order, 16)
+    by_copies, m = _stage(lens, layers, order, 8)
+    assert n == m == sum((x + (x + 15) // 16 * 16) * 2 * 64 * 2 * layers for row in lens for x in row[:-1])
+    assert torch.isfinite(by_kernel).all() and torch.equal(by_kernel, by_copies)
