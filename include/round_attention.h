@@ -399,9 +399,9 @@ int ra_kv_store_release(ra_kv_store* store);
  *                calls), 16-byte aligned
  *   host_kv      host array of B pointers to PINNED host memory of ra_kv_store_round_bytes(len[b])
  *                bytes each; written asynchronously, owned by the caller, kept alive while registered
- * On `compute_stream` (after the work that wrote cur_k / cur_v) a gather kernel per layer packs the
- * rounds into the device pool behind the staged rounds; `side_stream` waits for it and carries one
- * device-to-host copy per sequence.  The call returns without waiting; a later ra_kv_store_stage
+ * On `compute_stream` (after the work that wrote cur_k / cur_v) a gather kernel packs the
+ * rounds into the device pool behind the staged rounds; `side_stream` waits for it and carries the
+ * copies to host memory (one kernel launch; an asynchronous copy per sequence where the kernel cannot write it).  The call returns without waiting; a later ra_kv_store_stage
  * that selects the new round is ordered behind the copy.  Needs d * element size to be a multiple
  * of 16 bytes (RA_ERR_UNSUPPORTED otherwise).  RA_ERR_OOM if staged rounds plus the new rounds
  * exceed the pool; nothing is enqueued or registered on any error found before the first launch.

@@ -22,10 +22,10 @@
 
 namespace ra {
 constexpr int kStageGroups = 5;  // most groups of layers of different size (grouped order)
-// A selected round on its way into the pool.
+// A round on its way between host memory and the pool.
 struct StageJob {
-    const char* src;
-    int64_t dst;          // byte offset of its first layer in the pool
+    const char* src;      // its first layer
+    char* dst;
     int64_t layer_bytes;  // of one layer, a multiple of 16
 };
 // Byte offsets of the tables in their block.
@@ -40,10 +40,22 @@ struct StoreTables {
         bytes = align_up(units + kStageGroups * (plane + 1) * sizeof(int32_t), 16);
     }
 };
+// ... of the turn-end write-back.
+struct SaveTables {
+    size_t off = 0, len = 0, cur = 0, jobs = 0, units = 0, bytes = 0;
+    void layout(const ra_store_cfg& c) {
+        len = align_up(off + (size_t)c.B * sizeof(int64_t), 16);        // off [B]: start of the round's tensor in the pool, in tokens; -1 = skip
+        cur = align_up(len + (size_t)c.B * sizeof(int32_t), 16);        // len [B]
+        jobs = align_up(cur + (size_t)c.n_layers * 2 * sizeof(void*), 16);  // cur [2][n_layers]: keys and values of the current round
+        units = align_up(jobs + (size_t)c.B * sizeof(StageJob), 16);
+        bytes = align_up(units + ((size_t)c.B + 1) * sizeof(int32_t), 16);
+    }
+};
 }  // namespace ra
 
 struct ra_kv_store {
     using StoreTables = ra::StoreTables;
+    using SaveTables = ra::SaveTables;
     ra_store_cfg cfg;
     size_t token_bytes = 0;  // bytes of one token of one layer of K (or V): Hkv * d * elem
     struct Round {
@@ -68,11 +80,9 @@ struct ra_kv_store {
     bool staged = false;
     int64_t max_tokens = 0;
     size_t staged_tok = 0;  // pool cursor behind the staged rounds, in units of token_bytes
-    // turn-end write-back of the new round: placement table (pinned mirror + device copy) and events
-    int64_t* h_wb_off = nullptr;  // [B] start of the round's tensor in the pool, in tokens; -1 = skip
-    int32_t* h_wb_len = nullptr;  // [B]
-    int64_t* d_wb_off = nullptr;
-    int32_t* d_wb_len = nullptr;
+    // turn-end write-back of the new round: its tables (pinned mirror + device copy) and events
+    char *h_wb = nullptr, *d_wb = nullptr;
+    SaveTables wb;
     hipEvent_t wb_packed = nullptr, wb_done = nullptr;
     bool wb_pending = false;
     uint64_t saved_bytes = 0;
@@ -109,8 +119,8 @@ static bool is_pinned_host(const void* p, bool* direct = nullptr) {
 }
 
 namespace {
-// ---- host memory into the pool ------------------------------------------------------------------------
-// The kernel reads pinned host memory over the link, in units of 16 KB (a workgroup's four 16-byte loads a thread) that a
+// ---- between host memory and the pool -----------------------------------------------------------------
+// The kernel reads (at a turn's end: writes) pinned host memory over the link, in units of 16 KB (a workgroup's four 16-byte loads a thread) that a
 // small grid takes in turn.  The link is the bound, and it is full with half a megabyte asked for: 57 GB/s with 32 to 1024
 // workgroups, as one large asynchronous copy has.  But every asynchronous copy costs 10 microseconds of its own on the
 // stream, whatever its size (45 GB/s in copies of 2 MB, 38 of 1 MB, 18 of 256 KB), and a turn has one per (group of layers,
@@ -124,7 +134,7 @@ typedef __attribute__((address_space(1))) u32x4 global_u32x4;  // (a pointer out
 
 // unit0[j]: first unit of job j, unit0[n_jobs] = n_units.  Layers [l0, l0 + n_l) of every job.
 __global__ __launch_bounds__(kStageThreads) void stage_kernel(const StageJob* jobs, const int32_t* unit0, int n_jobs, int n_units, int l0,
-                                                             int n_l, char* pool) {
+                                                             int n_l) {
     const int lane = threadIdx.x & 63;
     int j = 0;  // unit0[j] <= u
     for (int u = blockIdx.x; u < n_units; u += gridDim.x) {
@@ -145,7 +155,7 @@ __global__ __launch_bounds__(kStageThreads) void stage_kernel(const StageJob* jo
 #pragma unroll
         for (int i = 0; i < kStageLoads; ++i) {
             const int64_t o = at + i * (kStageThreads * 16);
-            if (o < end) *reinterpret_cast<u32x4*>(pool + jb.dst + o) = v[i];
+            if (o < end) *(global_u32x4*)(jb.dst + o) = v[i];
         }
     }
 }
@@ -155,6 +165,24 @@ __global__ __launch_bounds__(kStageThreads) void copy_tables_kernel(const u32x4*
     for (int i = blockIdx.x * kStageThreads + threadIdx.x; i < n; i += gridDim.x * kStageThreads) dst[i] = src[i];
 }
 
+static int copy_tables(const char* host, char* device, size_t bytes, hipStream_t st) {
+    const int n = (int)(bytes / 16), grid = (n + kStageThreads - 1) / kStageThreads;
+    hipLaunchKernelGGL(copy_tables_kernel, dim3(grid < kStageGrid ? grid : kStageGrid), dim3(kStageThreads), 0, st,
+                       reinterpret_cast<const u32x4*>(host), reinterpret_cast<u32x4*>(device), n);
+    RA_HIP_CHECK(hipGetLastError());
+    return RA_OK;
+}
+// The store's device while it launches.
+struct OnDevice {
+    int prev = -1;
+    explicit OnDevice(int device) {
+        if (hipGetDevice(&prev) != hipSuccess || prev == device || hipSetDevice(device) != hipSuccess) prev = -1;
+    }
+    ~OnDevice() {
+        if (prev >= 0) (void)hipSetDevice(prev);
+    }
+};
+
 constexpr int kRepackThreads = 256;
 
 template <typename T>
@@ -163,28 +191,29 @@ union Vec16 {
     T e[16 / sizeof(T)];
 };
 
-// Turn-end gather of one layer of the new round (Sec. 3.2, last step).  A workgroup moves one
-// 16-token tile of one kv head of one sequence: the key rows go out unchanged to row t of head g,
+// Turn-end gather of the new round (Sec. 3.2, last step), every layer in one launch.  A workgroup moves one
+// 16-token tile of one layer and kv head of one sequence: the key rows go out unchanged to row t of head g,
 // the value rows are turned through LDS into the [d][16] tile of the round layout, rows past the
 // round's length as zeros.  Pure data movement in 16-byte pieces; T only fixes the element width.
 template <typename T>
-__global__ __launch_bounds__(kRepackThreads) void repack_round_kernel(const T* __restrict__ cur_k,
-                                                                      const T* __restrict__ cur_v, int cur_cap,
-                                                                      int Hkv, int d, int layer,
+__global__ __launch_bounds__(kRepackThreads) void repack_round_kernel(const T* const* __restrict__ cur, int n_layers, int n_tiles,
+                                                                      int cur_cap, int Hkv, int d,
                                                                       const int64_t* __restrict__ wb_off,
                                                                       const int32_t* __restrict__ wb_len,
                                                                       T* __restrict__ pool) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int V = 16 / sizeof(T);  // elements per 16-byte piece; also the row padding in LDS
     T* tile = reinterpret_cast<T*>(smem);  // [16][d + V]
-    const int b = blockIdx.z, g = blockIdx.y, t0 = blockIdx.x * 16;
+    const int layer = blockIdx.x / n_tiles, tile16 = blockIdx.x - layer * n_tiles;
+    const int b = blockIdx.z, g = blockIdx.y, t0 = tile16 * 16;
     const int64_t off = wb_off[b];
     const int n = wb_len[b];
     if (off < 0 || t0 >= n) return;
+    const T *cur_k = cur[layer], *cur_v = cur[n_layers + layer];
     const int tiles = (n + 15) / 16;
     const size_t layer_tok = (size_t)off + (size_t)layer * ((size_t)n + (size_t)tiles * 16);
     T* kdst = pool + (layer_tok * Hkv + (size_t)g * n) * d;
-    T* vdst = pool + (layer_tok + n) * Hkv * d + ((size_t)g * tiles + blockIdx.x) * d * 16;
+    T* vdst = pool + (layer_tok + n) * Hkv * d + ((size_t)g * tiles + tile16) * d * 16;
     const int pieces = d / V, pitch = d + V;
     for (int i = threadIdx.x; i < 16 * pieces; i += kRepackThreads) {
         const int j = i / pieces, c = (i % pieces) * V, t = t0 + j;
@@ -240,10 +269,9 @@ int ra_kv_store_create(ra_kv_store** out, const ra_store_cfg* cfg) {
     s->d_off = reinterpret_cast<int64_t*>(s->d_tab + s->tab.off);
     s->d_len = reinterpret_cast<int32_t*>(s->d_tab + s->tab.len);
     s->d_n = reinterpret_cast<int32_t*>(s->d_tab + s->tab.n);
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_wb_off, (size_t)cfg->B * sizeof(int64_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_wb_len, (size_t)cfg->B * sizeof(int32_t));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_wb_off, (size_t)cfg->B * sizeof(int64_t), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_wb_len, (size_t)cfg->B * sizeof(int32_t), hipHostMallocDefault);
+    s->wb.layout(*cfg);
+    if (e == hipSuccess) e = hipMalloc((void**)&s->d_wb, s->wb.bytes);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_wb, s->wb.bytes, hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&s->wb_packed, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&s->wb_done, hipEventDisableTiming);
     if (e == hipSuccess) {
@@ -270,10 +298,8 @@ int ra_kv_store_destroy(ra_kv_store* s) {
     if (s->d_tab) (void)hipFree(s->d_tab);
     if (s->h_tab) (void)hipHostFree(s->h_tab);
     if (s->wb_pending) (void)hipEventSynchronize(s->wb_done);  // host tensors may be freed right after this call
-    if (s->d_wb_off) (void)hipFree(s->d_wb_off);
-    if (s->d_wb_len) (void)hipFree(s->d_wb_len);
-    if (s->h_wb_off) (void)hipHostFree(s->h_wb_off);
-    if (s->h_wb_len) (void)hipHostFree(s->h_wb_len);
+    if (s->d_wb) (void)hipFree(s->d_wb);
+    if (s->h_wb) (void)hipHostFree(s->h_wb);
     if (s->wb_packed) (void)hipEventDestroy(s->wb_packed);
     if (s->wb_done) (void)hipEventDestroy(s->wb_done);
     delete s;
@@ -394,7 +420,7 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
         int32_t* h_units = reinterpret_cast<int32_t*>(s->h_tab + s->tab.units);
         int k = 0;
         for (const Job& jb : jobs)
-            if (jb.len > 0) h_jobs[k++] = {jb.src, (int64_t)(jb.dst_tok * s->token_bytes), (int64_t)(layer_tokens(jb.len) * s->token_bytes)};
+            if (jb.len > 0) h_jobs[k++] = {jb.src, s->pool + jb.dst_tok * s->token_bytes, (int64_t)(layer_tokens(jb.len) * s->token_bytes)};
         for (int g = 0; g < n_groups; ++g) {
             int32_t* row = h_units + (size_t)(order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1);
             for (k = 0; k < n_jobs && n_units[g] <= INT32_MAX / 2; ++k) {
@@ -405,20 +431,15 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
             direct &= n_units[g] <= INT32_MAX / 2;
         }
     }
-    int prev_device = 0;
-    RA_HIP_CHECK(hipGetDevice(&prev_device));
-    RA_HIP_CHECK(hipSetDevice(s->cfg.device));
-    struct Back { int device; ~Back() { (void)hipSetDevice(device); } } back{prev_device};
-    const int n_pieces = (int)(s->tab.bytes / 16);
-    hipLaunchKernelGGL(copy_tables_kernel, dim3(n_pieces < kStageGrid * kStageThreads ? (n_pieces + kStageThreads - 1) / kStageThreads : kStageGrid),
-                       dim3(kStageThreads), 0, st, reinterpret_cast<const u32x4*>(s->h_tab), reinterpret_cast<u32x4*>(s->d_tab), n_pieces);
+    OnDevice on(s->cfg.device);
+    if (int rc = copy_tables(s->h_tab, s->d_tab, s->tab.bytes, st)) return rc;
     for (int g = 0; g < n_groups; ++g) {
         const int l0 = bounds[g], n_l = bounds[g + 1] - l0;
         if (direct && n_jobs > 0) {
             const int32_t* row = reinterpret_cast<const int32_t*>(s->d_tab + s->tab.units) + (size_t)(order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1);
             const int grid = n_units[g] < kStageGrid ? (int)n_units[g] : kStageGrid;
             hipLaunchKernelGGL(stage_kernel, dim3(grid), dim3(kStageThreads), 0, st, reinterpret_cast<const StageJob*>(s->d_tab + s->tab.jobs),
-                               row, n_jobs, (int)n_units[g], l0, n_l, s->pool);
+                               row, n_jobs, (int)n_units[g], l0, n_l);
         }
         for (const Job& jb : jobs) {
             if (direct || jb.len == 0) continue;
@@ -529,38 +550,56 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
     hipStream_t ss = reinterpret_cast<hipStream_t>(side_stream);
     s->saved_bytes = 0;
     if (max_len > 0) {
+        int64_t* h_off = reinterpret_cast<int64_t*>(s->h_wb + s->wb.off);
+        int32_t* h_len = reinterpret_cast<int32_t*>(s->h_wb + s->wb.len);
+        const void** h_cur = reinterpret_cast<const void**>(s->h_wb + s->wb.cur);
+        StageJob* h_jobs = reinterpret_cast<StageJob*>(s->h_wb + s->wb.jobs);
+        int32_t* h_units = reinterpret_cast<int32_t*>(s->h_wb + s->wb.units);
+        int n_jobs = 0;
+        int64_t n_units = 0;
+        bool by_kernel = true;  // every tensor can be written by the kernel (a row is whole 16-byte pieces)
         for (int b = 0; b < B; ++b) {
-            s->h_wb_off[b] = off[b];
-            s->h_wb_len[b] = off[b] < 0 ? 0 : len_host[b];
+            h_off[b] = off[b];
+            h_len[b] = off[b] < 0 ? 0 : len_host[b];
+            if (h_len[b] == 0) continue;
+            const int64_t bytes = (int64_t)((size_t)L * layer_tokens(h_len[b]) * s->token_bytes);
+            by_kernel &= direct[b] && (uintptr_t)host_kv[b] % 16 == 0 && n_units <= INT32_MAX / 2;
+            h_jobs[n_jobs] = {s->pool + (size_t)off[b] * s->token_bytes, static_cast<char*>(host_kv[b]), bytes};
+            h_units[n_jobs++] = (int32_t)n_units;
+            n_units += (bytes + kUnitBytes - 1) / kUnitBytes;
+            s->saved_bytes += (uint64_t)bytes;
         }
-        RA_HIP_CHECK(hipMemcpyAsync(s->d_wb_off, s->h_wb_off, (size_t)B * sizeof(int64_t), hipMemcpyHostToDevice, cs));
-        RA_HIP_CHECK(hipMemcpyAsync(s->d_wb_len, s->h_wb_len, (size_t)B * sizeof(int32_t), hipMemcpyHostToDevice, cs));
-        const dim3 grid((max_len + 15) / 16, s->cfg.Hkv, B), block(kRepackThreads);
+        by_kernel &= n_units <= INT32_MAX / 2;
+        h_units[n_jobs] = (int32_t)n_units;
         for (int l = 0; l < L; ++l) {
-            if (elem == 2) {
-                const size_t smem = 16 * (size_t)(s->cfg.d + 8) * 2;
-                hipLaunchKernelGGL(repack_round_kernel<uint16_t>, grid, block, smem, cs,
-                                   static_cast<const uint16_t*>(cur_k_layers[l]),
-                                   static_cast<const uint16_t*>(cur_v_layers[l]), cur_cap, s->cfg.Hkv, s->cfg.d, l,
-                                   s->d_wb_off, s->d_wb_len, reinterpret_cast<uint16_t*>(s->pool));
-            } else {
-                const size_t smem = 16 * (size_t)(s->cfg.d + 4) * 4;
-                hipLaunchKernelGGL(repack_round_kernel<uint32_t>, grid, block, smem, cs,
-                                   static_cast<const uint32_t*>(cur_k_layers[l]),
-                                   static_cast<const uint32_t*>(cur_v_layers[l]), cur_cap, s->cfg.Hkv, s->cfg.d, l,
-                                   s->d_wb_off, s->d_wb_len, reinterpret_cast<uint32_t*>(s->pool));
-            }
-            RA_HIP_CHECK(hipGetLastError());
+            h_cur[l] = cur_k_layers[l];
+            h_cur[L + l] = cur_v_layers[l];
         }
+        OnDevice on(s->cfg.device);
+        if (int rc = copy_tables(s->h_wb, s->d_wb, s->wb.bytes, cs)) return rc;
+        const int n_tiles = (max_len + 15) / 16;
+        const dim3 grid((unsigned)n_tiles * L, s->cfg.Hkv, B), block(kRepackThreads);
+        const int64_t* d_off = reinterpret_cast<const int64_t*>(s->d_wb + s->wb.off);
+        const int32_t* d_len = reinterpret_cast<const int32_t*>(s->d_wb + s->wb.len);
+        if (elem == 2)
+            hipLaunchKernelGGL(repack_round_kernel<uint16_t>, grid, block, 16 * (size_t)(s->cfg.d + 8) * 2, cs,
+                               reinterpret_cast<const uint16_t* const*>(s->d_wb + s->wb.cur), L, n_tiles, cur_cap, s->cfg.Hkv, s->cfg.d,
+                               d_off, d_len, reinterpret_cast<uint16_t*>(s->pool));
+        else
+            hipLaunchKernelGGL(repack_round_kernel<uint32_t>, grid, block, 16 * (size_t)(s->cfg.d + 4) * 4, cs,
+                               reinterpret_cast<const uint32_t* const*>(s->d_wb + s->wb.cur), L, n_tiles, cur_cap, s->cfg.Hkv, s->cfg.d,
+                               d_off, d_len, reinterpret_cast<uint32_t*>(s->pool));
+        RA_HIP_CHECK(hipGetLastError());
         RA_HIP_CHECK(hipEventRecord(s->wb_packed, cs));
         RA_HIP_CHECK(hipStreamWaitEvent(ss, s->wb_packed, 0));
-        for (int b = 0; b < B; ++b) {
-            if (off[b] < 0 || len_host[b] == 0) continue;
-            const size_t bytes = (size_t)L * layer_tokens(len_host[b]) * s->token_bytes;
-            RA_HIP_CHECK(hipMemcpyAsync(host_kv[b], s->pool + (size_t)off[b] * s->token_bytes, bytes,
-                                        hipMemcpyDeviceToHost, ss));
-            s->saved_bytes += bytes;
+        if (by_kernel) {
+            hipLaunchKernelGGL(stage_kernel, dim3(n_units < kStageGrid ? (int)n_units : kStageGrid), dim3(kStageThreads), 0, ss,
+                               reinterpret_cast<const StageJob*>(s->d_wb + s->wb.jobs),
+                               reinterpret_cast<const int32_t*>(s->d_wb + s->wb.units), n_jobs, (int)n_units, 0, 1);
+            RA_HIP_CHECK(hipGetLastError());
         }
+        for (int j = 0; j < n_jobs && !by_kernel; ++j)
+            RA_HIP_CHECK(hipMemcpyAsync(h_jobs[j].dst, h_jobs[j].src, (size_t)h_jobs[j].layer_bytes, hipMemcpyDeviceToHost, ss));
         RA_HIP_CHECK(hipEventRecord(s->wb_done, ss));
         s->wb_pending = true;
     }

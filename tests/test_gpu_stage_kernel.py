@@ -58,3 +58,35 @@ def test_kernel_and_copies_stage_the_same_bytes(name, order, layers):
     by_copies, m = _stage(lens, layers, order, 8)
     assert n == m == sum((x + (x + 15) // 16 * 16) * 2 * 64 * 2 * layers for row in lens for x in row[:-1])
     assert torch.isfinite(by_kernel).all() and torch.equal(by_kernel, by_copies)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_saved_rounds_are_the_same_bytes_by_kernel_and_by_copies(dtype):
+    """Sequences of 1 to 300 tokens, one without any and one skipped; several layers in one gather."""
+    L, Hkv, d, cap = 5, 2, 64, 300
+    new = [300, 1, 0, 47, 16, 33]
+    B, skip = len(new), 4
+    gen = torch.Generator("cuda").manual_seed(3)
+    ks, vs = ([torch.randn((B, cap, Hkv, d), generator=gen, device="cuda").to(dtype) for _ in range(L)] for _ in range(2))
+    results = []
+    for offset in (16, 8):
+        store = ra.ra_kv_store_create(0, L, B, 1, Hkv, d, ra.RA_BF16 if dtype == torch.bfloat16 else ra.RA_F32, 64 << 20)
+        sizes = [ra.ra_kv_store_round_bytes(store, n) for n in new]
+        bufs = [torch.full((n + 64,), 77, dtype=torch.uint8, pin_memory=True) for n in sizes]
+        rounds = torch.tensor([-1 if b == skip else 0 for b in range(B)], dtype=torch.int32)
+        ra.ra_kv_store_save_round(store, rounds, torch.tensor(new, dtype=torch.int32), ks, vs, [x[offset:] for x in bufs], None,
+                                  torch.cuda.Stream())
+        assert ra.ra_kv_store_save_wait(store) == sum(n for b, n in enumerate(sizes) if b != skip)
+        results.append([x[offset:offset + n].clone() for x, n in zip(bufs, sizes)])
+        assert all((x[:offset] == 77).all() and (x[offset + n:] == 77).all() for x, n in zip(bufs, sizes))
+        assert (bufs[skip] == 77).all()
+        ra.ra_kv_store_destroy(store)
+    assert all(torch.equal(x, y) for x, y in zip(*results))
+    for b, n in enumerate(new):  # the layout by its definition
+        if b == skip or n == 0:
+            continue
+        tiles, parts = (n + 15) // 16, []
+        for k, v in zip(ks, vs):
+            padded = torch.nn.functional.pad(v[b, :n].transpose(0, 1), (0, 0, 0, tiles * 16 - n))
+            parts += [k[b, :n].transpose(0, 1).reshape(-1), padded.reshape(Hkv, tiles, 16, d).transpose(2, 3).reshape(-1)]
+        assert torch.equal(results[0][b], torch.cat(parts).view(torch.uint8).cpu())
