@@ -127,12 +127,16 @@ namespace {
 // round): a turn of 16 selected rounds and 6 layers 4 173 -> 3 501 microseconds (with 16 workgroups 3 705, 64 3 520, 128 3 475),
 // of 30 short rounds and 5 layers 3 789 -> 2 403 (64: 2 390), of one dialogue and 3 layers 387 -> 304 (64: 319).  The grid is
 // small also so that the decode launches that run beside it find every compute unit.
-constexpr int kStageThreads = 256, kStageLoads = 4, kStageGrid = 32;
+// At the end of a turn nothing runs beside it and host memory is written past the caches: 64 workgroups, a turn 3 516 -> 3 466
+// (32 with such stores 3 470, 256 3 469; 128 with ordinary ones 3 470; of one dialogue and 3 layers 292 -> 289, two and 4 373 -> 356).
+constexpr int kStageThreads = 256, kStageLoads = 4, kStageGrid = 32, kSaveGrid = 64;
 constexpr int kUnitBytes = kStageThreads * kStageLoads * 16;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) u32x4 global_u32x4;  // (a pointer out of a table would be a flat one)
 
 // unit0[j]: first unit of job j, unit0[n_jobs] = n_units.  Layers [l0, l0 + n_l) of every job.
+// TO_HOST: the destination is host memory.
+template <bool TO_HOST>
 __global__ __launch_bounds__(kStageThreads) void stage_kernel(const StageJob* jobs, const int32_t* unit0, int n_jobs, int n_units, int l0,
                                                              int n_l) {
     const int lane = threadIdx.x & 63;
@@ -155,7 +159,9 @@ __global__ __launch_bounds__(kStageThreads) void stage_kernel(const StageJob* jo
 #pragma unroll
         for (int i = 0; i < kStageLoads; ++i) {
             const int64_t o = at + i * (kStageThreads * 16);
-            if (o < end) *(global_u32x4*)(jb.dst + o) = v[i];
+            if (o >= end) continue;
+            if (TO_HOST) __builtin_nontemporal_store(v[i], (global_u32x4*)(jb.dst + o));
+            else *(global_u32x4*)(jb.dst + o) = v[i];
         }
     }
 }
@@ -438,7 +444,7 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
         if (direct && n_jobs > 0) {
             const int32_t* row = reinterpret_cast<const int32_t*>(s->d_tab + s->tab.units) + (size_t)(order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1);
             const int grid = n_units[g] < kStageGrid ? (int)n_units[g] : kStageGrid;
-            hipLaunchKernelGGL(stage_kernel, dim3(grid), dim3(kStageThreads), 0, st, reinterpret_cast<const StageJob*>(s->d_tab + s->tab.jobs),
+            hipLaunchKernelGGL(stage_kernel<false>, dim3(grid), dim3(kStageThreads), 0, st, reinterpret_cast<const StageJob*>(s->d_tab + s->tab.jobs),
                                row, n_jobs, (int)n_units[g], l0, n_l);
         }
         for (const Job& jb : jobs) {
@@ -593,7 +599,7 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
         RA_HIP_CHECK(hipEventRecord(s->wb_packed, cs));
         RA_HIP_CHECK(hipStreamWaitEvent(ss, s->wb_packed, 0));
         if (by_kernel) {
-            hipLaunchKernelGGL(stage_kernel, dim3(n_units < kStageGrid ? (int)n_units : kStageGrid), dim3(kStageThreads), 0, ss,
+            hipLaunchKernelGGL(stage_kernel<true>, dim3(n_units < kSaveGrid ? (int)n_units : kSaveGrid), dim3(kStageThreads), 0, ss,
                                reinterpret_cast<const StageJob*>(s->d_wb + s->wb.jobs),
                                reinterpret_cast<const int32_t*>(s->d_wb + s->wb.units), n_jobs, (int)n_units, 0, 1);
             RA_HIP_CHECK(hipGetLastError());
