@@ -82,6 +82,10 @@ inline AttnWorkspace attn_workspace(size_t rows, int S, int D, int B, int R_max)
 // Builds the per-sequence segment tables for work units of `unit_tokens` tokens (grid B).
 void launch_plan(const AttnArgs& a, int unit_tokens, hipStream_t st);
 int attn_min_units();  // smallest piece of a sequence's key set, in 32-token tiles
+// ... of the many-row kernel that plans itself.  Small questions spread over the chip: 95 tokens of 8 heads over 22 short rounds,
+// whole call 40.9 -> 34.7 microseconds against pieces of at least eight, 20 tokens over three paged dialogues at the watershed
+// layer 36.8 -> 27.3 (28.9 with four), 9 tokens of 32 heads over 8 rounds 32.3 -> 28.0 (30.5 with four).
+constexpr int kPrefillMinUnits = 2;
 
 // bf16, d = 128 (one query token: also 64), Hq/Hkv <= 16, up to 32 query rows per KV head: matrix-core streaming
 // kernel, one wavefront per (range of the batch's key tiles, KV head, block of 16 query rows).

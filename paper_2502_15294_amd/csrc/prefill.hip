@@ -88,13 +88,16 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
             }
             return ctx->ws.bytes >= w.total + score_bytes;
         };
-        int S = mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2;
-        const size_t least = attn_workspace(rows, S - 2 < 8 ? S - 2 : 8, D, B, layer->R_max).total + score_bytes;
+        int S = mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 8);
+        const size_t least = attn_workspace(rows, S, D, B, layer->R_max).total + score_bytes;
         RA_REQUIRE(ctx->ws.base != nullptr && ctx->ws.bytes >= least, RA_ERR_WORKSPACE,
                    "prefill: workspace has %zu bytes, this call needs %zu", ctx->ws.bytes, least);
-        plan_inline = fits(S) && attn_prefill_plans_inline(a, ctx->num_cu);
-        if (!plan_inline)  // (a part less is 520 bytes a row, so it fits in two at the most)
-            for (S = S - 2 < 8 ? S - 2 : 8; !fits(S) && S > 1;) --S;
+        a.min_units = kPrefillMinUnits;
+        plan_inline = fits(mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2) && attn_prefill_plans_inline(a, ctx->num_cu);
+        if (!plan_inline) {
+            a.min_units = attn_min_units();
+            while (!fits(S) && S > 1) --S;  // (a part less is 520 bytes a row, so one less fits)
+        }
         plan_off = w.plan_off;
         scratch_total = w.total;
     }

@@ -102,6 +102,7 @@ struct TileCut {
         }
         return n / C * sum + (n % C ? least : 0);
     }
+    RA_HD bool by_weight() const { return w[0] != 1000; }
     RA_HD int weight_before(int k, int turns) const {  // of the first k classes, and of so many whole turns of the classes
         int x = turns * sum;
         for (int j = 0; j < C; ++j) x += j < k ? w[j] : 0;
@@ -116,8 +117,7 @@ struct TileCut {
     }
     // pieces of a sequence of U tiles that is cut by itself
     RA_HD int cuts(int U) const { return U > 0 ? (U + len - 1) / len : 0; }
-    // A launch that does not fill the chip anyway, its ranges as short as they get (n_apart: the sum of cuts()): every
-    // sequence by itself, so that no workgroup starts twice.
+    // Ranges of min_tiles (n_apart: the sum of cuts()): every sequence by itself, so that no workgroup starts twice.
     RA_HD bool apart(int n_apart, int slots, int min_tiles) const { return len == min_tiles && n_apart <= slots && n_apart > 0; }
 };
 
