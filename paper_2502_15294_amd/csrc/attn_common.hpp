@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "range_schedule.hpp"
 #include "score_places.hpp"
 #include "tile_ranges.hpp"
 
@@ -56,7 +57,8 @@ struct AttnArgs {
     int* seq_rec;     // [B][2] first record and number of records of every sequence (written by the kernel)
     int max_ranges;   // most ranges the batch's key tiles are cut into
     int shape_units;  // shortest range the launch shape and the records have room for (mfma_decode_shape)
-    int range_skew;   // in 1/1000: how much more than half of the tiles the first half of the ranges gets (see RangeCut)
+    int range_waves;  // ranges of which every one has a wave of its own for each of its items
+    Divisor by_inner, by_hkv, by_g;  // inner, Hkv, G
     int spread_longest;  // most tiles of a sequence in a launch of ranges that short
     int num_cu;       // compute units of the device (many-row kernel)
     int plan_inline;  // many-row kernel: it plans itself, no planning kernel ran

@@ -152,7 +152,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     constexpr int KK = D / 32, DT = D / 16, kParts = D == 64 ? 3 : 2;  // contraction steps of Q.K^T, 16-channel tiles of the output,
                                                                         // bf16 numbers a probability is carried as
     extern __shared__ __align__(16) char smem[];
-    __shared__ int sU[kMaxBatch], sps[kMaxBatch + 1];
+    // Tiles of every sequence and their prefix; planned inline every wave keeps the prefix (and the cut below) for itself, so that
+    // no barrier stands between its parts and the items.
+    __shared__ int sU[INLINE_PLAN ? kInlineBatch : kMaxBatch], sps_of[INLINE_PLAN ? 4 * (kInlineBatch + 1) : kMaxBatch + 1];
     const DevView& vw = a.view;
     const int Hkv = vw.Hkv, B = vw.B;
     const int tid = threadIdx.x;
@@ -162,6 +164,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     const int rows_total = q_len * G;
     const int cap = vw.R_max + 1;
     const int inner = Hkv * n_rowblocks;
+    int* const sps = sps_of + (INLINE_PLAN ? wave * (kInlineBatch + 1) : 0);
+    int total;
 
     // ---- LDS: this wave's strip of staged tile log-sum-exps; the batch's raw segment lists ---------------------
     float* lse_buf = reinterpret_cast<float*>(smem) + (TILE_LSE ? wave * 16 * kLsePitch : 0);  // [16][kLsePitch]
@@ -270,20 +274,19 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
         else if (cap <= 32) count_tiles(std::integral_constant<int, 32>());
         else count_tiles(std::integral_constant<int, 64>());
         lds_barrier();
-        if (wave == 0) {
-            const int U = lane < B ? sU[lane] : 0, incl = wave_inclusive_sum(U);
-            if (lane < B) sps[lane] = incl - U;
-            if (lane == 63) sps[B] = incl;
-        }
-        lds_barrier();
+        const int U = lane < B ? sU[lane] : 0, incl = wave_inclusive_sum(U);
+        if (lane < B) sps[lane] = incl - U;
+        if (lane == 63) sps[B] = incl;
+        total = lane_get(incl, 63);
+        __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
     } else {
         for (int b = tid; b < B; b += 256) sU[b] = reinterpret_cast<const PlanHeader*>(a.plan + (size_t)b * pstride)->U;
         __syncthreads();
         for (int b = tid; b < B; b += 256) sps[b] = sU[b];
         exclusive_scan_units(sps, B);
+        total = sps[B];
     }
     // sps[b] = first tile of sequence b in the batch's list, sps[B] = all tiles
-    const int total = sps[B];
 
     // A sequence with an empty key set has no tile and therefore no wave: its rows are written here.
     if (blockIdx.x == 0) {
@@ -305,7 +308,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     // instead of two (one dialogue's step, 45 tiles: 14.2 -> 11.4 microseconds).  With more work than that the shorter ranges
     // only add records (8 dialogues, 480 tiles: 18.7 -> 19.6).  And the records of one sequence must not cost the merge more
     // than that (spread_longest).
-    bool spread = (unsigned)total <= kMfmaSpreadUnits * (gridDim.x * 4u / (unsigned)inner);
+    bool spread = total <= kMfmaSpreadUnits * a.range_waves;
     if (spread && total > a.spread_longest) {
         float most = 0.f;  // tiles of the longest sequence (exact: fewer than 2^24)
         for (int b = lane; b < B; b += 64) most = vmax(most, (float)sU[b]);
@@ -315,15 +318,13 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
         most = xrow_max4(vmax(most, dpp_mov<0x140>(most)));
         spread = uni((int)most) <= a.spread_longest;
     }
-    const int min_units = spread ? kMfmaSpreadUnits : a.min_units;
-    const RangeCut cut = range_cut((unsigned)total, min_units, a.max_ranges, a.range_skew);
-    int n_ranges = (int)cut.n_ranges;
+    const int min_units = spread ? kMfmaSpreadUnits : kMfmaMinUnits;
     // Few sequences with short ranges are cut each by itself (lane b: sequence b, its first range and its pieces) if that takes no
     // more ranges than there may be (seq_cut_lengths).
     bool by_sequence = false;
     int my_first = 0;
     SeqCut my_cut = {0, 0, 0};
-    int len = 0;
+    int len = 0, n_ranges = 0;
     if (const int tries = INLINE_PLAN ? seq_cut_lengths(B, D, (unsigned)total, min_units, a.max_ranges, &len) : 0) {
         const int U = lane < B ? sU[lane] : 0;
 #pragma unroll
@@ -340,14 +341,18 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     }
     // (in LDS for the items: kept in registers over the streaming loop they cost some, and the compiler's iterative-ilp schedule,
     // which the tests compare with, crashes on 64 channels)
-    __shared__ int s_cut[INLINE_PLAN ? 64 : 1][3];  // [sequence]: first range, q, rem
+    __shared__ int s_cut_of[INLINE_PLAN ? 256 : 1][3];  // [wave, sequence]: first range, q, rem
+    int(*const s_cut)[3] = s_cut_of + (INLINE_PLAN ? wave * 64 : 0);
+    RangeCut cut = {};
     if (INLINE_PLAN && by_sequence) {
-        if (wave == 0) {
-            s_cut[lane][0] = my_first;
-            s_cut[lane][1] = my_cut.q;
-            s_cut[lane][2] = my_cut.rem;
-        }
-        lds_barrier();
+        s_cut[lane][0] = my_first;
+        s_cut[lane][1] = my_cut.q;
+        s_cut[lane][2] = my_cut.rem;
+        __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
+    } else {
+        cut = spread ? range_cut((unsigned)total, kMfmaSpreadUnits, a.max_ranges, kRangeSkew)
+                     : range_cut((unsigned)total, kMfmaMinUnits, a.max_ranges, kRangeSkew);
+        n_ranges = (int)cut.n_ranges;
     }
     const int n_items = n_ranges * inner;
     const bool long_ranges = total > (kMfmaMinUnits + 1) * n_ranges;
@@ -369,8 +374,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     // dynamically in smaller ranges was measured and lost: under load every dependent memory round trip at the
     // start of an item waits for the compute unit's whole queue of tile loads, 5 to 10 microseconds.
     for (int item = blockIdx.x * 4 + wave; item < n_items; item += n_waves) {
-        const int range = item / inner, gi = item - range * inner;  // the (KV head, row block) items of a range are neighbours
-        const int g = gi % Hkv, rowblock = gi / Hkv;
+        const int range = a.by_inner.divide(item), gi = item - range * inner;  // the (KV head, row block) items of a range are neighbours
+        const int rowblock = a.by_hkv.divide(gi), g = gi - rowblock * Hkv;
         int t_lo, t_hi, b;  // its tiles, and the sequence that holds the first of them
         if (INLINE_PLAN && by_sequence) {
             b = __popcll(__ballot(lane < B && s_cut[lane][0] <= range)) - 1;
@@ -400,7 +405,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             const int row = rowblock * 16 + n;
             const bool row_ok = row < rows_total;
             const int rr = row_ok ? row : 0;
-            const int qtok = rr / G;
+            const int qtok = a.by_g.divide(rr);
             const size_t rowid = ((size_t)b * q_len + qtok) * a.Hq + (size_t)g * G + (rr - qtok * G);
             uint4 qf[KK];
             {
@@ -768,6 +773,10 @@ int launch_attn_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st) {
         mfma_decode_shape(num_cu, B, Hkv, D, rows_total, mfma_max_tiles(B, a.max_tokens, a.view.R_max, a.cur_cap), a.shape_units);
     if (a.max_ranges != s.max_ranges) return fail(RA_ERR_INVALID_ARG, "attention: launch shape mismatch");
     a.spread_longest = spread_longest(merge_shape_of(a, s, num_cu));
+    a.range_waves = s.grid * 4 / s.inner;
+    a.by_inner = divisor(s.inner, (long long)s.max_ranges * s.inner);
+    a.by_hkv = divisor(Hkv, s.inner);
+    a.by_g = divisor(a.G, rows_total);
     if (D == 128) launch_attn_mfma_d<128>(a, paged, s, st);
     else launch_attn_mfma_d<64>(a, paged, s, st);
     return RA_OK;

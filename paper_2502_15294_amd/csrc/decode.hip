@@ -607,7 +607,6 @@ static int decode_impl(ra_ctx* ctx, const Workspace* scratch, void* stream, cons
     a.seq_rec = reinterpret_cast<int*>(ws.base + kWsSeqRecOff);
     a.max_ranges = shape.max_ranges;
     a.shape_units = shape_units;
-    a.range_skew = kRangeSkew;
 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const bool paged = layer->block_size != 0;

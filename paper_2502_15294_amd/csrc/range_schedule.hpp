@@ -30,6 +30,29 @@
 
 namespace ra {
 
+// a / b for a < 2^21, b >= 1.  On the device by a reciprocal: (a + 1/2) / b is at least 1 / (2 b) away from a whole number, and
+// the product is off by less than that.
+RA_HD inline unsigned small_div(unsigned a, unsigned b) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return (unsigned)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+#else
+    return a / b;
+#endif
+}
+
+// n / d, 0 <= n <= n_max, by one multiplication with a number made on the host, which is exact while n_max d < 2^31.  A division
+// is about 35 dependent instructions, 0.1 microseconds for a wave that is alone on its SIMD, and the decode kernel had a dozen
+// between its lists and its first tile.  (In the question kernels, which have scalar registers to spare for neither the numbers
+// nor the way out, the same change costs 1 %.)
+struct Divisor {
+    unsigned magic;  // ceil(2^31 / d), 0: divide
+    int d;
+    RA_HD int divide(int n) const { return magic ? (int)((unsigned long long)(2u * (unsigned)n) * magic >> 32) : n / d; }
+};
+inline Divisor divisor(int d, long long n_max) {
+    return {n_max * d < 0x80000000ll ? (unsigned)((0x80000000ull + (unsigned)d - 1) / (unsigned)d) : 0u, d};
+}
+
 // Number of ranges for a batch of `total` tiles: never more than `max_ranges` (the wavefronts of the launch
 // divided by the work items per range) and no range shorter than `min_units` tiles.
 RA_HD inline unsigned range_count(unsigned total, int min_units, int max_ranges) {
@@ -96,8 +119,8 @@ struct SeqCut {
 };
 RA_HD inline SeqCut seq_cut(int tiles, int len) {
     SeqCut c;
-    c.n = (int)(((unsigned)tiles + (unsigned)len - 1) / (unsigned)len);
-    c.q = c.n > 0 ? (int)((unsigned)tiles / (unsigned)c.n) : 0;
+    c.n = (int)small_div((unsigned)tiles + (unsigned)len - 1, (unsigned)len);
+    c.q = c.n > 0 ? (int)small_div((unsigned)tiles, (unsigned)c.n) : 0;
     c.rem = tiles - c.q * c.n;
     return c;
 }
@@ -118,7 +141,7 @@ constexpr int kSeqCutTwice = 5;        // longest first length with a second
 RA_HD constexpr int seq_cut_longest(int d) { return d == 64 ? 5 : 12; }  // longest first length
 RA_HD inline int seq_cut_lengths(int B, int d, unsigned total, int min_units, int max_ranges, int* len) {
     if (B * kSeqCutRanges > max_ranges || total > (unsigned)(seq_cut_longest(d) * max_ranges)) return 0;
-    *len = (int)((total + (unsigned)max_ranges - 1) / (unsigned)max_ranges);
+    *len = (int)small_div(total + (unsigned)max_ranges - 1, (unsigned)max_ranges);  // (total is at most twelve times max_ranges)
     if (*len < min_units) *len = min_units;
     return *len > kSeqCutTwice ? 1 : 2;
 }
