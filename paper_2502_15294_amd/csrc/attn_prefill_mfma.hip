@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
                                          !PAGED && !P_HALF && gridDim.x >= kWorkgroupsPerCuP * (unsigned)a.num_cu &&
                                              a.slots * inner <= (int)gridDim.x,
                                          attn_range_weights());
-        if (blockIdx.x == 0) {
+        if (blockIdx.x == gridDim.x - 1) {  // the last workgroup: it often has no range, and the lightest ones are dealt out last
             const LaneSequence sq = lane_sequence(sU, vw.B);
             for (int b = wave; b < vw.B; b += 4) {
                 int part0;
@@ -115,7 +115,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
                 if (lane == 0) a.n_parts[b] = parts;
             }
             // a sequence with an empty key set lies in no range: its rows are written here
-            for (int b = 0; b < vw.B; ++b) {
+            const bool some_empty = __any(lane < vw.B && sq.U == 0);
+            for (int b = 0; b < vw.B && some_empty; ++b) {
                 if (sU[b] != 0) continue;
                 const size_t rows = (size_t)q_len * a.Hq;
                 for (size_t i = tid; i < rows * 128; i += 256) a.out[(size_t)b * rows * 128 + i] = 0.f;
@@ -149,7 +150,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
     for (int item = blockIdx.x; item < n_items;) {
         const int piece = uniform(item / inner), rest = item - piece * inner;
         const int rowblock = uniform(rest / Hkv), g = rest - rowblock * Hkv;
-        int b, s, S_eff, u_lo, u_hi;
+        int b, s, u_lo, u_hi;
+        bool whole;  // the pass has all tiles of its sequence
         if constexpr (INLINE_PLAN) {
             const int r = range_at<kWorkgroupsPerCuP>(piece, P);
             const LaneSequence sq = lane_sequence(sU, vw.B);
@@ -161,16 +163,16 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
             b = sequence_of_tile(sq, vw.B, t_lo);
             const int seq_lo = __builtin_amdgcn_readlane(sq.tile0, b);
             const int end = min(t_hi, seq_lo + __builtin_amdgcn_readlane(sq.U, b));
-            int part0;
-            S_eff = parts_of(ranges, P, sq, b, part0);
-            s = r - part0;
+            s = r - first_part_of(ranges, P, sq, b);
             u_lo = t_lo - seq_lo;
             u_hi = end - seq_lo;
+            whole = u_lo == 0 && u_hi == __builtin_amdgcn_readlane(sq.U, b);
             reached = end < t_hi ? end : 0;
         } else {
             b = uniform(find_slot(sps, vw.B, piece));
             s = piece - sps[b];
-            S_eff = sps[b + 1] - sps[b];
+            const int S_eff = sps[b + 1] - sps[b];
+            whole = S_eff == 1;
             u_lo = piece_begin(sU[b], s, S_eff);
             u_hi = piece_begin(sU[b], s + 1, S_eff);
         }
@@ -530,7 +532,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
                 for (int dt = 0; dt < 8; ++dt) acc[nt][dt] *= unscale;
             }
             if (!row_ok[nt]) continue;
-            if (S_eff > 1) {
+            if (!whole) {
                 const size_t pr = rowid[nt] * a.S + s;
 #pragma unroll
                 for (int dt = 0; dt < 8; ++dt)
