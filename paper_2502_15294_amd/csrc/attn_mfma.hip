@@ -374,8 +374,10 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     // dynamically in smaller ranges was measured and lost: under load every dependent memory round trip at the
     // start of an item waits for the compute unit's whole queue of tile loads, 5 to 10 microseconds.
     for (int item = blockIdx.x * 4 + wave; item < n_items; item += n_waves) {
-        const int range = a.by_inner.divide(item), gi = item - range * inner;  // the (KV head, row block) items of a range are neighbours
-        const int rowblock = a.by_hkv.divide(gi), g = gi - rowblock * Hkv;
+        // the (KV head, row block) items of a range are neighbours
+        // (the compiler's iterative-ilp schedule, which the tests compare with, crashes on 64 channels with the other form)
+        const int range = D == 64 ? item / inner : a.by_inner.divide(item), gi = item - range * inner;
+        const int rowblock = D == 64 ? gi / Hkv : a.by_hkv.divide(gi), g = gi - rowblock * Hkv;
         int t_lo, t_hi, b;  // its tiles, and the sequence that holds the first of them
         if (INLINE_PLAN && by_sequence) {
             b = __popcll(__ballot(lane < B && s_cut[lane][0] <= range)) - 1;
