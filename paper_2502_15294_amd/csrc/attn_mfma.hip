@@ -153,8 +153,10 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
                                                                         // bf16 numbers a probability is carried as
     extern __shared__ __align__(16) char smem[];
     // Tiles of every sequence and their prefix; planned inline every wave keeps the prefix (and the cut below) for itself, so that
-    // no barrier stands between its parts and the items.
-    __shared__ int sU[INLINE_PLAN ? kInlineBatch : kMaxBatch], sps_of[INLINE_PLAN ? 4 * (kInlineBatch + 1) : kMaxBatch + 1];
+    // no barrier stands between its parts and the items.  (Not at the watershed layer, whose variants have no register left: 214.3
+    // -> 215.4 microseconds for 1.3 GB.)
+    constexpr bool kOwn = INLINE_PLAN && !TILE_LSE;
+    __shared__ int sU[INLINE_PLAN ? kInlineBatch : kMaxBatch], sps_of[kOwn ? 4 * (kInlineBatch + 1) : kMaxBatch + 1];
     const DevView& vw = a.view;
     const int Hkv = vw.Hkv, B = vw.B;
     const int tid = threadIdx.x;
@@ -164,7 +166,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     const int rows_total = q_len * G;
     const int cap = vw.R_max + 1;
     const int inner = Hkv * n_rowblocks;
-    int* const sps = sps_of + (INLINE_PLAN ? wave * (kInlineBatch + 1) : 0);
+    int* const sps = sps_of + (kOwn ? wave * (kInlineBatch + 1) : 0);
     int total;
 
     // ---- LDS: this wave's strip of staged tile log-sum-exps; the batch's raw segment lists ---------------------
@@ -275,10 +277,11 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
         else count_tiles(std::integral_constant<int, 64>());
         lds_barrier();
         const int U = lane < B ? sU[lane] : 0, incl = wave_inclusive_sum(U);
-        if (lane < B) sps[lane] = incl - U;
-        if (lane == 63) sps[B] = incl;
+        if ((kOwn || wave == 0) && lane < B) sps[lane] = incl - U;
+        if ((kOwn || wave == 0) && lane == 63) sps[B] = incl;
         total = lane_get(incl, 63);
-        __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
+        if constexpr (kOwn) __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
+        else lds_barrier();
     } else {
         for (int b = tid; b < B; b += 256) sU[b] = reinterpret_cast<const PlanHeader*>(a.plan + (size_t)b * pstride)->U;
         __syncthreads();
@@ -341,14 +344,17 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     }
     // (in LDS for the items: kept in registers over the streaming loop they cost some, and the compiler's iterative-ilp schedule,
     // which the tests compare with, crashes on 64 channels)
-    __shared__ int s_cut_of[INLINE_PLAN ? 256 : 1][3];  // [wave, sequence]: first range, q, rem
-    int(*const s_cut)[3] = s_cut_of + (INLINE_PLAN ? wave * 64 : 0);
+    __shared__ int s_cut_of[kOwn ? 256 : INLINE_PLAN ? 64 : 1][3];  // [wave, sequence]: first range, q, rem
+    int(*const s_cut)[3] = s_cut_of + (kOwn ? wave * 64 : 0);
     RangeCut cut = {};
     if (INLINE_PLAN && by_sequence) {
-        s_cut[lane][0] = my_first;
-        s_cut[lane][1] = my_cut.q;
-        s_cut[lane][2] = my_cut.rem;
-        __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
+        if (kOwn || wave == 0) {
+            s_cut[lane][0] = my_first;
+            s_cut[lane][1] = my_cut.q;
+            s_cut[lane][2] = my_cut.rem;
+        }
+        if constexpr (kOwn) __builtin_amdgcn_wave_barrier();  // same wave: LDS operations complete in program order
+        else lds_barrier();
     } else {
         cut = spread ? range_cut((unsigned)total, kMfmaSpreadUnits, a.max_ranges, kRangeSkew)
                      : range_cut((unsigned)total, kMfmaMinUnits, a.max_ranges, kRangeSkew);
@@ -375,9 +381,11 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
     // start of an item waits for the compute unit's whole queue of tile loads, 5 to 10 microseconds.
     for (int item = blockIdx.x * 4 + wave; item < n_items; item += n_waves) {
         // the (KV head, row block) items of a range are neighbours
-        // (the compiler's iterative-ilp schedule, which the tests compare with, crashes on 64 channels with the other form)
-        const int range = D == 64 ? item / inner : a.by_inner.divide(item), gi = item - range * inner;
-        const int rowblock = D == 64 ? gi / Hkv : a.by_hkv.divide(gi), g = gi - rowblock * Hkv;
+        // (Plain divisions with 64 channels, where the compiler's iterative-ilp schedule, which the tests compare with, crashes on the
+        // other form, and at the watershed layer, see above.)
+        constexpr bool kPlain = D == 64 || TILE_LSE;
+        const int range = kPlain ? item / inner : a.by_inner.divide(item), gi = item - range * inner;
+        const int rowblock = kPlain ? gi / Hkv : a.by_hkv.divide(gi), g = gi - rowblock * Hkv;
         int t_lo, t_hi, b;  // its tiles, and the sequence that holds the first of them
         if (INLINE_PLAN && by_sequence) {
             b = __popcll(__ballot(lane < B && s_cut[lane][0] <= range)) - 1;
@@ -407,7 +415,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a, int n_row
             const int row = rowblock * 16 + n;
             const bool row_ok = row < rows_total;
             const int rr = row_ok ? row : 0;
-            const int qtok = a.by_g.divide(rr);
+            const int qtok = TILE_LSE ? rr / G : a.by_g.divide(rr);
             const size_t rowid = ((size_t)b * q_len + qtok) * a.Hq + (size_t)g * G + (rr - qtok * G);
             uint4 qf[KK];
             {
