@@ -106,7 +106,6 @@ static int grouped_stage_size(int L, int gi) {
     return 1;
 }
 
-// `direct`: whether kernels may read and write it (pinned memory made coherent, at the same address).
 static bool is_pinned_host(const void* p, bool* direct = nullptr) {
     hipPointerAttribute_t attr;
     hipError_t e = hipPointerGetAttributes(&attr, p);
@@ -116,6 +115,14 @@ static bool is_pinned_host(const void* p, bool* direct = nullptr) {
     }
     if (direct) *direct = attr.devicePointer == p && !(attr.allocationFlags & hipHostMallocNonCoherent);
     return attr.type == hipMemoryTypeHost;
+}
+// Pinned memory of `bytes` bytes; `direct`: whether kernels may read and write it: coherent, at the same address, and pinned to its
+// last byte (of a tensor that is shorter than its round a copy reports an error, a kernel faults).
+static bool is_pinned_host(const void* p, size_t bytes, bool* direct) {
+    bool last = false;
+    if (!is_pinned_host(p, direct)) return false;
+    *direct = *direct && is_pinned_host(static_cast<const char*>(p) + bytes - 1, &last) && last;
+    return true;
 }
 
 namespace {
@@ -327,7 +334,7 @@ int ra_kv_store_register_round(ra_kv_store* s, int seq, int round, const void* h
     RA_REQUIRE(!s->staged, RA_ERR_STATE, "kv_store_register_round: rounds are staged; call ra_kv_store_release first");
     bool direct = false;
     if (len > 0)
-        RA_REQUIRE(is_pinned_host(host_kv, &direct), RA_ERR_INVALID_ARG,
+        RA_REQUIRE(is_pinned_host(host_kv, ra_kv_store_round_bytes(s, len), &direct), RA_ERR_INVALID_ARG,
                    "kv_store_register_round: host_kv is not pinned host memory (use hipHostMalloc / pin_memory)");
     ra_kv_store::Round& r = s->rounds[(size_t)seq * s->cfg.R_max + round];
     r.host = static_cast<const char*>(host_kv);
@@ -530,7 +537,7 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
         RA_REQUIRE(n >= 0 && n <= cur_cap, RA_ERR_INVALID_ARG, "kv_store_save_round: len[%d] = %d outside [0, %d]", b,
                    n, cur_cap);
         if (n > 0)
-            RA_REQUIRE(host_kv[b] != nullptr && is_pinned_host(host_kv[b], &direct[b]), RA_ERR_INVALID_ARG,
+            RA_REQUIRE(host_kv[b] != nullptr && is_pinned_host(host_kv[b], ra_kv_store_round_bytes(s, n), &direct[b]), RA_ERR_INVALID_ARG,
                        "kv_store_save_round: host_kv[%d] is not pinned host memory", b);
         off[b] = (int64_t)tok;
         tok += (size_t)L * layer_tokens(n);
