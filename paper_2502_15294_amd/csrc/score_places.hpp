@@ -42,7 +42,4 @@ __device__ __forceinline__ void note_places(const ScorePlaces& pl, int b, int R_
     }
 }
 
-// Piece s of S pieces of U tiles begins at tile floor(U s / S).
-__device__ __forceinline__ int piece_begin(int U, int s, int S) { return (int)(((long long)U * s) / S); }
-
 }  // namespace ra

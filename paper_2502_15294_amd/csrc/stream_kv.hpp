@@ -521,7 +521,6 @@ __device__ __forceinline__ LaneSequence lane_sequence(const int* sU, int B) {
     const int lane = threadIdx.x & 63, U = lane < B ? sU[lane] : 0;
     return {U, wave_inclusive_sum(U) - U};
 }
-constexpr int kShortRange = 8;
 // Fills `tr` from the sequences' tiles sU; returns the number of ranges.  All threads call it; no barrier behind the counts
 // needed before it, one at its end.
 template <int C>
@@ -539,25 +538,18 @@ __device__ __forceinline__ int cut_tiles(TileRanges& tr, const int* sU, int B, i
     if (slots > kMaxRanges) slots = kMaxRanges;
     const TileCut<C> cut(total, most, slots, min_tiles, max_parts, full, weights);
     int P = cut.n_ranges;
-    // Every sequence by itself if that takes no more ranges, or, while they are short, with pieces up to two tiles longer: a range that
-    // crosses from one sequence into the next starts twice, which takes as long as one to three tiles.  (Whole calls: 38 tokens
-    // over 9 dialogues 73.3 -> 70.9 microseconds, 19 over three paged ones, no tile longer, 71.2 -> 68.0; with three tiles longer
-    // at any length 10 dialogues of 48 tiles a range 146.0 -> 148.0, three of 10 at the watershed layer 43.6 -> 45.2.)
-    if (B > 1 && !cut.by_weight()) {
-        TileCut<C> own = cut;
-        for (; own.len <= cut.len + (cut.len <= kShortRange ? 2 : 0); ++own.len) {
-            const int cuts = own.cuts(sq.U), cuts_incl = wave_inclusive_sum(cuts);
-            const int P_apart = __builtin_amdgcn_readlane(cuts_incl, 63);
-            if (!own.apart(P_apart, slots, own.len)) continue;
-            for (int b = tid >> 6; b < B; b += 4) {  // a wave per sequence (a thread's loop over 96 ranges took 6 microseconds)
-                const int n = __builtin_amdgcn_readlane(cuts, b), first = __builtin_amdgcn_readlane(cuts_incl, b) - n;
-                const int U = __builtin_amdgcn_readlane(sq.U, b), t0 = __builtin_amdgcn_readlane(sq.tile0, b);
-                for (int j = tid & 63; j < n; j += 64) tr.bound[first + j] = t0 + U * j / n;
-            }
-            if (tid == 0) tr.bound[P_apart] = total;
-            lds_barrier();
-            return P_apart;
+    for (int len = cut.len; len <= cut.longest_apart(B); ++len) {
+        const int cuts = cut.cuts(sq.U, len), cuts_incl = wave_inclusive_sum(cuts);
+        const int P_apart = __builtin_amdgcn_readlane(cuts_incl, 63);
+        if (!cut.apart(P_apart, slots)) continue;
+        for (int b = tid >> 6; b < B; b += 4) {  // a wave per sequence (a thread's loop over 96 ranges took 6 microseconds)
+            const int n = __builtin_amdgcn_readlane(cuts, b), first = __builtin_amdgcn_readlane(cuts_incl, b) - n;
+            const int U = __builtin_amdgcn_readlane(sq.U, b), t0 = __builtin_amdgcn_readlane(sq.tile0, b);
+            for (int j = tid & 63; j < n; j += 64) tr.bound[first + j] = t0 + piece_begin(U, j, n);
         }
+        if (tid == 0) tr.bound[P_apart] = total;
+        lds_barrier();
+        return P_apart;
     }
     const double per_weight = cut.tiles_per_weight();
     for (int r = tid; r <= P; r += blockDim.x) tr.bound[r] = cut.begin(r, per_weight);

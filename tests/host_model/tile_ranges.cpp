@@ -2,7 +2,7 @@
 // part limits and weights, among them one long dialogue between two short ones.  Checked for every batch:
 //   * the ranges tile [0, total), none is empty, there are at most `slots` of them;
 //   * at most max_parts ranges meet one sequence: the partial results of a row have room for that many and no more;
-//   * sequences cut by themselves have at most max_parts pieces.
+//   * sequences cut by themselves have at most max_parts pieces, at most `slots` together, which tile every sequence.
 // And the number of ranges that launches of many query rows are given.
 //
 // usage: tile_ranges [seed] [cases]     exit status 0 = every check passed
@@ -15,12 +15,12 @@
 
 using namespace ra;
 
-static int bad = 0, weighted = 0;
+static int bad = 0, weighted = 0, apart = 0;
 static long long n_checked = 0;
 
 template <int C>
 static void check(const std::vector<int>& U, int slots, int min_tiles, int max_parts, bool full, const RangeWeights<C>& weights) {
-    int total = 0, most = 0, n_apart = 0;
+    int total = 0, most = 0;
     for (int u : U) {
         total += u;
         most = u > most ? u : most;
@@ -33,10 +33,19 @@ static void check(const std::vector<int>& U, int slots, int min_tiles, int max_p
             std::fprintf(stderr, "  %s: sequence %d (%d tiles) %d, of %d tiles, %d slots, max_parts %d, %d classes, full %d\n", what, b,
                          b < 0 ? 0 : U[b], n, total, slots, max_parts, C, (int)full);
     };
-    for (int u : U) n_apart += cut.cuts(u);
-    if (cut.apart(n_apart, slots, min_tiles)) {
-        for (size_t b = 0; b < U.size(); ++b)
-            if (cut.cuts(U[b]) > max_parts) report("pieces of a sequence cut by itself", (int)b, cut.cuts(U[b]));
+    for (int len = cut.len; len <= cut.longest_apart((int)U.size()); ++len) {
+        int n_apart = 0;
+        for (int u : U) n_apart += cut.cuts(u, len);
+        if (!cut.apart(n_apart, slots)) continue;
+        ++apart;
+        for (size_t b = 0; b < U.size(); ++b) {
+            const int n = cut.cuts(U[b], len);
+            if (n > max_parts) report("pieces of a sequence cut by itself", (int)b, n);
+            for (int j = 0; j < n; ++j) {
+                const int lo = piece_begin(U[b], j, n), hi = j + 1 < n ? piece_begin(U[b], j + 1, n) : U[b];
+                if ((j == 0 && lo != 0) || lo >= hi || hi > U[b] || hi - lo > len) report("a piece of a sequence cut by itself", (int)b, j);
+            }
+        }
         return;
     }
     const double per_weight = cut.tiles_per_weight();
@@ -60,9 +69,12 @@ static void check(const std::vector<int>& U, int slots, int min_tiles, int max_p
     }
 }
 
+// Both kernels, and the shortest ranges of their launches.  The score kernel's limit is lifted where there are no more ranges.
 static void check_both(const std::vector<int>& U, int slots, int max_parts, bool full) {
-    check(U, slots, 8, max_parts, full, attn_range_weights());      // the attention kernel's buffers have max_parts
-    check(U, slots, 8, kMaxRanges + 2, full, score_range_weights());  // the score kernel keeps no partial results
+    for (int min_tiles : {2, 8}) {
+        check(U, slots, min_tiles, max_parts, full, attn_range_weights());
+        check(U, slots, min_tiles, max_parts >= slots ? kMaxRanges + 2 : max_parts, full, score_range_weights());
+    }
 }
 
 int main(int argc, char** argv) {
@@ -74,6 +86,12 @@ int main(int argc, char** argv) {
     check_both({21, 320, 21}, 19, 18, true);
     check_both({90, 44, 2239, 3, 146}, 19, 18, true);
     check_both({30, 392, 30}, 17, 16, true);
+    // the largest sequences and the most ranges there are
+    for (int slots : {384, 768, kMaxRanges}) {
+        check_both({5700000, 5700000}, slots, kMaxRanges + 2, false);
+        check_both({(1 << 24) - 1, (1 << 24) - 1}, slots, kMaxRanges + 2, false);
+        check_both({(1 << 24) - 1, 1, 16000000, 12345678}, slots, kMaxRanges + 2, false);
+    }
     // one long dialogue between two short ones, every slot count and part limit near each other
     for (int slots = 3; slots <= 40; ++slots)
         for (int max_parts = 3; max_parts <= 18; ++max_parts)
@@ -93,6 +111,7 @@ int main(int argc, char** argv) {
         }
         if (style == 0) U[uni(0, B - 1)] = uni(1, 5000);
         check_both(U, slots, uni(3, 18), uni(0, 3) > 0);
+        check_both(U, style == 4 ? uni(65, kMaxRanges) : slots, uni(3, 1200), uni(0, 3) > 0);
     }
     // ranges handed to a launch that fills the chip: one at least, all at the same time, or a whole number of rounds to within
     // an eighth
@@ -102,6 +121,6 @@ int main(int argc, char** argv) {
             const long long busiest = ((long long)s * inner + cu - 1) / cu;
             if (s < at_once || (s > at_once && busiest * cu * 8 > 9ll * s * inner)) ++bad;
         }
-    std::printf("%s: %lld cuts (%d with unequal ranges), seed %u, %d failed checks\n", bad ? "FAILED" : "ok", n_checked, weighted, seed, bad);
+    std::printf("%s: %lld cuts (%d with unequal ranges, %d by sequence), seed %u, %d failed checks\n", bad ? "FAILED" : "ok", n_checked, weighted, apart, seed, bad);
     return bad ? 1 : 0;
 }
