@@ -185,7 +185,16 @@ static int copy_tables(const char* host, char* device, size_t bytes, hipStream_t
     RA_HIP_CHECK(hipGetLastError());
     return RA_OK;
 }
-// The store's device while it launches.
+// Everything goes to the store's device, where its events are: a stream of another one is refused before anything is enqueued.
+// (The handles that name a default stream mean the current device's; hipStreamGetDevice takes only the first of them.)
+static int check_stream(const ra_kv_store* s, hipStream_t st, const char* who) {
+    int device = -1;
+    if (st == nullptr || st == hipStreamLegacy || st == hipStreamPerThread) RA_HIP_CHECK(hipGetDevice(&device));
+    else RA_HIP_CHECK(hipStreamGetDevice(st, &device));
+    RA_REQUIRE(device == s->cfg.device, RA_ERR_HIP, "%s: a stream of device %d, the store is on device %d", who, device, s->cfg.device);
+    return RA_OK;
+}
+// The store's device while it enqueues.
 struct OnDevice {
     int prev = -1;
     explicit OnDevice(int device) {
@@ -381,6 +390,8 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
     RA_REQUIRE(tok * s->token_bytes <= s->cfg.device_pool_bytes, RA_ERR_OOM,
                "kv_store_stage: selected rounds need %zu bytes, the device pool has %zu", tok * s->token_bytes,
                s->cfg.device_pool_bytes);
+    hipStream_t st = reinterpret_cast<hipStream_t>(side_stream);
+    if (int rc = check_stream(s, st, "kv_store_stage")) return rc;
     // ---- index tables of the compact views (round i of the view = i-th selected round) ----------
     const size_t plane = (size_t)B * R;
     for (size_t i = 0; i < (size_t)L * 2 * plane; ++i) s->h_off[i] = 0;
@@ -410,7 +421,7 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
         }
     }
     // ---- enqueue the copies ------------------------------------------------------------------------
-    hipStream_t st = reinterpret_cast<hipStream_t>(side_stream);
+    OnDevice on(s->cfg.device);
     // a round saved at the end of the last turn may be selected now, and its packed copy may still
     // sit where this selection is about to land: both wait for the write-back
     if (s->wb_pending) RA_HIP_CHECK(hipStreamWaitEvent(st, s->wb_done, 0));
@@ -444,7 +455,6 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
             direct &= n_units[g] <= INT32_MAX / 2;
         }
     }
-    OnDevice on(s->cfg.device);
     if (int rc = copy_tables(s->h_tab, s->d_tab, s->tab.bytes, st)) return rc;
     for (int g = 0; g < n_groups; ++g) {
         const int l0 = bounds[g], n_l = bounds[g + 1] - l0;
@@ -553,14 +563,18 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
             RA_REQUIRE(((uintptr_t)cur_k_layers[l] | (uintptr_t)cur_v_layers[l]) % 16 == 0, RA_ERR_INVALID_ARG,
                        "kv_store_save_round: layer %d pointers are not 16-byte aligned", l);
         }
+    hipStream_t cs = reinterpret_cast<hipStream_t>(compute_stream);
+    hipStream_t ss = reinterpret_cast<hipStream_t>(side_stream);
+    if (max_len > 0) {
+        if (int rc = check_stream(s, cs, "kv_store_save_round")) return rc;
+        if (int rc = check_stream(s, ss, "kv_store_save_round")) return rc;
+    }
     // the placement table's pinned mirror and the pool area behind the staged rounds are reused from
     // call to call: the previous write-back must have left them
     if (s->wb_pending) {
         RA_HIP_CHECK(hipEventSynchronize(s->wb_done));
         s->wb_pending = false;
     }
-    hipStream_t cs = reinterpret_cast<hipStream_t>(compute_stream);
-    hipStream_t ss = reinterpret_cast<hipStream_t>(side_stream);
     s->saved_bytes = 0;
     if (max_len > 0) {
         int64_t* h_off = reinterpret_cast<int64_t*>(s->h_wb + s->wb.off);
