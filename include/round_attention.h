@@ -367,8 +367,9 @@ size_t ra_kv_store_round_bytes(const ra_kv_store* store, int len);
 /*
  * Enqueue on `side_stream` the host-to-device copies of every selected round and of the index
  * tables of the compact per-layer views, and record one "ready" event per layer.
- * (The copies of a group of layers are one kernel launch that reads the pinned host memory; asynchronous copies
- * where it cannot: memory made non-coherent, tensors not 16-byte aligned.)
+ * (Slices of a megabyte and more are asynchronous copies, on side_stream and on a stream of the store's own that
+ * side_stream waits for in the end.  Smaller ones are one kernel launch per group of layers that reads the pinned host
+ * memory, or copies where it cannot: memory made non-coherent, tensors not 16-byte aligned.)
  *   sel_idx_host int32 [B][R_max], n_sel_host int32 [B]  (host memory; read before returning)
  * Returns RA_ERR_STATE if a selected round was never registered, RA_ERR_OOM if the pool is too
  * small (nothing is enqueued in either case).
@@ -401,8 +402,8 @@ int ra_kv_store_release(ra_kv_store* store);
  *                bytes each; written asynchronously, owned by the caller, kept alive while registered
  * On `compute_stream` (after the work that wrote cur_k / cur_v) a gather kernel packs the
  * rounds into the device pool behind the staged rounds; `side_stream` waits for it and carries the
- * copies to host memory (one kernel launch; an asynchronous copy per sequence where the kernel cannot write it).  The call returns without waiting; a later ra_kv_store_stage
- * that selects the new round is ordered behind the copy.  Needs d * element size to be a multiple
+ * copies to host memory (split between copies and a kernel as those of ra_kv_store_stage).  The call returns without
+ * waiting; a later ra_kv_store_stage that selects the new round is ordered behind the copy.  Needs d * element size to be a multiple
  * of 16 bytes (RA_ERR_UNSUPPORTED otherwise).  RA_ERR_OOM if staged rounds plus the new rounds
  * exceed the pool; nothing is enqueued or registered on any error found before the first launch.
  * A second call first waits (on the host) for the previous call's copies.

@@ -16,6 +16,7 @@
 // dropping (Sec. 3.4) decides on.
 #include "common.hpp"
 
+#include <algorithm>
 #include <memory>
 #include <new>
 #include <vector>
@@ -77,6 +78,11 @@ struct ra_kv_store {
     int32_t* d_len = nullptr;
     int32_t* d_n = nullptr;
     std::vector<hipEvent_t> ready;
+    // second stream for large copies, with the events that order it: behind the side stream, and per layer (the first of a group)
+    hipStream_t lane = nullptr;
+    hipEvent_t fork = nullptr, lane_done = nullptr;
+    std::vector<hipEvent_t> lane_ready;
+    std::vector<int> lane_layer;  // [n_layers] whose lane_ready a layer waits for, -1 = none
     bool staged = false;
     int64_t max_tokens = 0;
     size_t staged_tok = 0;  // pool cursor behind the staged rounds, in units of token_bytes
@@ -127,21 +133,26 @@ static bool is_pinned_host(const void* p, size_t bytes, bool* direct) {
 
 namespace {
 // ---- between host memory and the pool -----------------------------------------------------------------
-// The kernel reads (at a turn's end: writes) pinned host memory over the link, in units of 16 KB (a workgroup's four 16-byte loads a thread) that a
-// small grid takes in turn.  The link is the bound, and it is full with half a megabyte asked for: 57 GB/s with 32 to 1024
-// workgroups, as one large asynchronous copy has.  But every asynchronous copy costs 10 microseconds of its own on the
-// stream, whatever its size (45 GB/s in copies of 2 MB, 38 of 1 MB, 18 of 256 KB), and a turn has one per (group of layers,
-// round): a turn of 16 selected rounds and 6 layers 4 173 -> 3 501 microseconds (with 16 workgroups 3 705, 64 3 520, 128 3 475),
-// of 30 short rounds and 5 layers 3 789 -> 2 403 (64: 2 390), of one dialogue and 3 layers 387 -> 304 (64: 319).  The grid is
-// small also so that the decode launches that run beside it find every compute unit.
-// At the end of a turn nothing runs beside it and host memory is written past the caches: 64 workgroups, a turn 3 516 -> 3 466
-// (32 with such stores 3 470, 256 3 469; 128 with ordinary ones 3 470; of one dialogue and 3 layers 292 -> 289, two and 4 373 -> 356).
+// Slices of kCopyBytes and more are asynchronous copies: the copy engines leave the compute units to the work beside them.  Each
+// copy costs 10 microseconds of its own on its stream, whatever its size, so they are dealt out to the side stream and to one of
+// the store's own: 50 GB/s in copies of 1 MB and 55 of 2 MB, against 37 and 44 on one stream (the link: 57).
+// Smaller slices, of which a turn of short rounds has hundreds, are one launch of a kernel that reads (at a turn's end: writes)
+// the pinned host memory itself, in units of 16 KB (a workgroup's four 16-byte loads a thread) that a small grid takes in turn:
+// 57 GB/s with half a megabyte asked for.  While it runs the work beside it is slow: memory-bound products at 40 % of their rate,
+// and beside the write-back at next to nothing.  Microseconds with everything by the kernel, by copies on one stream, and so:
+//   turn of 16 rounds of 425 tokens, 6 layers                   3 305   4 043   3 315
+//   ... with 5.8 ms of memory-bound products behind the layers  7 900   6 650   6 590
+//   ... with 5.0 ms of products of 4096^3                       6 810   6 170   6 000
+//   save of 4 x 500 tokens, 2.6 ms of such products behind it   3 526   2 721   2 668
+//   turn of 5 x 7 rounds of 50 tokens, 5 layers                   946   2 707     985  (1 320 with copies from 256 KB on)
+//   turn of one dialogue, 4 rounds of 350 tokens, 3 layers        510     628     545
+constexpr size_t kCopyBytes = 1 << 20;
 constexpr int kStageThreads = 256, kStageLoads = 4, kStageGrid = 32, kSaveGrid = 64;
 constexpr int kUnitBytes = kStageThreads * kStageLoads * 16;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) u32x4 global_u32x4;  // (a pointer out of a table would be a flat one)
 
-// unit0[j]: first unit of job j, unit0[n_jobs] = n_units.  Layers [l0, l0 + n_l) of every job.
+// unit0[j]: first unit of job j, unit0[n_jobs] = n_units; a job without units is left out.  Layers [l0, l0 + n_l) of every job.
 // TO_HOST: the destination is host memory.
 template <bool TO_HOST>
 __global__ __launch_bounds__(kStageThreads) void stage_kernel(const StageJob* jobs, const int32_t* unit0, int n_jobs, int n_units, int l0,
@@ -204,6 +215,65 @@ struct OnDevice {
         if (prev >= 0) (void)hipSetDevice(prev);
     }
 };
+
+// Tensors on their way, all in one direction: the kernel's jobs (in the pinned mirror of a table) and which of them it can reach.
+struct Moves {
+    StageJob* jobs;
+    std::vector<bool> direct;
+    hipMemcpyKind kind;
+    int64_t ahead = 0;  // bytes given to the side stream more than to the lane
+    bool forked = false;
+    void add(const char* src, char* dst, size_t layer_bytes, bool reachable) {
+        jobs[direct.size()] = {src, dst, (int64_t)layer_bytes};
+        direct.push_back(reachable && ((uintptr_t)src | (uintptr_t)dst | layer_bytes) % 16 == 0);
+    }
+    int size() const { return (int)direct.size(); }
+    bool any_large(int n_l) const {
+        for (int k = 0; k < size(); ++k)
+            if ((size_t)(n_l * jobs[k].layer_bytes) >= kCopyBytes) return true;
+        return false;
+    }
+    // Prefix of the units of n_l layers of every job, none for the jobs that are copied.
+    int units(int n_l, int32_t* row) const {
+        int64_t n = 0;
+        for (int k = 0; k < size(); ++k) {
+            const int64_t bytes = n_l * jobs[k].layer_bytes, more = (bytes + kUnitBytes - 1) / kUnitBytes;
+            row[k] = (int32_t)n;
+            if (direct[k] && (size_t)bytes < kCopyBytes && n + more <= INT32_MAX / 2) n += more;
+        }
+        return row[size()] = (int32_t)n;
+    }
+};
+
+// Enqueues layers [l0, l0 + n_l) of every tensor on `st` and the lane, which is made to follow `fork` when it is first used.  row
+// (and its device copy): the units.  lane_used: whether copies went to the lane.
+static int enqueue_moves(const ra_kv_store* s, Moves& m, const char* d_jobs, const int32_t* row, const char* d_row, int l0, int n_l, hipStream_t st,
+                         bool* lane_used) {
+    const int n = m.size(), n_units = row[n];
+    *lane_used = false;
+    if (n_units > 0) {
+        const bool to_host = m.kind == hipMemcpyDeviceToHost;
+        const int most = to_host ? kSaveGrid : kStageGrid;
+        const auto kernel = to_host ? stage_kernel<true> : stage_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3(n_units < most ? n_units : most), dim3(kStageThreads), 0, st, reinterpret_cast<const StageJob*>(d_jobs),
+                           reinterpret_cast<const int32_t*>(d_row), n, n_units, l0, n_l);
+        RA_HIP_CHECK(hipGetLastError());
+        m.ahead += (int64_t)n_units * kUnitBytes;
+    }
+    for (int k = 0; k < n; ++k) {
+        if (row[k + 1] > row[k]) continue;
+        const size_t o = (size_t)l0 * m.jobs[k].layer_bytes, bytes = (size_t)n_l * m.jobs[k].layer_bytes;
+        const bool to_lane = m.ahead > 0 && bytes >= kCopyBytes;
+        if (to_lane && !m.forked) {
+            RA_HIP_CHECK(hipStreamWaitEvent(s->lane, s->fork, 0));
+            m.forked = true;
+        }
+        RA_HIP_CHECK(hipMemcpyAsync(m.jobs[k].dst + o, m.jobs[k].src + o, bytes, m.kind, to_lane ? s->lane : st));
+        m.ahead += to_lane ? -(int64_t)bytes : (int64_t)bytes;
+        *lane_used |= to_lane;
+    }
+    return RA_OK;
+}
 
 constexpr int kRepackThreads = 256;
 
@@ -301,6 +371,18 @@ int ra_kv_store_create(ra_kv_store** out, const ra_store_cfg* cfg) {
         for (int l = 0; l < cfg->n_layers && e == hipSuccess; ++l)
             e = hipEventCreateWithFlags(&s->ready[l], hipEventDisableTiming);
     }
+    if (e == hipSuccess) {
+        s->lane_ready.resize(cfg->n_layers, nullptr);
+        s->lane_layer.resize(cfg->n_layers, -1);
+        for (int l = 0; l < cfg->n_layers && e == hipSuccess; ++l)
+            e = hipEventCreateWithFlags(&s->lane_ready[l], hipEventDisableTiming);
+    }
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->lane_done, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->lane, hipStreamNonBlocking);
+    // (its first copy sets up its queue, 250 microseconds)
+    if (e == hipSuccess) e = hipMemcpyAsync(s->d_tab, s->h_tab, 16, hipMemcpyHostToDevice, s->lane);
+    if (e == hipSuccess) e = hipStreamSynchronize(s->lane);
     (void)hipSetDevice(prev);
     if (e != hipSuccess) {
         const bool oom = e == hipErrorOutOfMemory;
@@ -314,8 +396,11 @@ int ra_kv_store_create(ra_kv_store** out, const ra_store_cfg* cfg) {
 
 int ra_kv_store_destroy(ra_kv_store* s) {
     if (!s) return RA_OK;
-    for (hipEvent_t ev : s->ready)
-        if (ev) (void)hipEventDestroy(ev);
+    for (const auto* events : {&s->ready, &s->lane_ready})
+        for (hipEvent_t ev : *events)
+            if (ev) (void)hipEventDestroy(ev);
+    if (s->fork) (void)hipEventDestroy(s->fork);
+    if (s->lane_done) (void)hipEventDestroy(s->lane_done);
     if (s->pool) (void)hipFree(s->pool);
     if (s->d_tab) (void)hipFree(s->d_tab);
     if (s->h_tab) (void)hipHostFree(s->h_tab);
@@ -324,6 +409,7 @@ int ra_kv_store_destroy(ra_kv_store* s) {
     if (s->h_wb) (void)hipHostFree(s->h_wb);
     if (s->wb_packed) (void)hipEventDestroy(s->wb_packed);
     if (s->wb_done) (void)hipEventDestroy(s->wb_done);
+    if (s->lane) (void)hipStreamDestroy(s->lane);
     delete s;
     return RA_OK;
 }
@@ -363,9 +449,8 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
     RA_REQUIRE(!s->staged, RA_ERR_STATE, "kv_store_stage: already staged; call ra_kv_store_release first");
     const int B = s->cfg.B, R = s->cfg.R_max, L = s->cfg.n_layers;
     // ---- validate the selection and place every selected round in the pool ----------------------
-    struct Job { const char* src; size_t dst_tok; int len; };
+    struct Job { const char* src; size_t dst_tok; int len; bool direct; };
     std::vector<Job> jobs;
-    bool direct = s->token_bytes % 16 == 0;  // every copy can be the kernel's
     size_t tok = 0;  // pool cursor in units of token_bytes
     int64_t max_tokens = 0;
     for (int b = 0; b < B; ++b) {
@@ -380,8 +465,7 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
             prev = r;
             const ra_kv_store::Round& rd = s->rounds[(size_t)b * R + r];
             RA_REQUIRE(rd.len >= 0, RA_ERR_STATE, "kv_store_stage: round %d of sequence %d was never registered", r, b);
-            jobs.push_back({rd.host, tok, rd.len});
-            direct &= rd.len == 0 || (rd.direct && (uintptr_t)rd.host % 16 == 0);
+            jobs.push_back({rd.host, tok, rd.len, rd.direct});
             tok += (size_t)L * layer_tokens(rd.len);
             seq_tokens += rd.len;
         }
@@ -433,45 +517,32 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
         bounds.push_back(order == RA_STAGE_ROUND_MAJOR ? L
                                                        : bounds.back() + (order == RA_STAGE_LAYER_MAJOR ? 1 : grouped_stage_size(L, gi)));
     const int n_groups = (int)bounds.size() - 1;
-    int n_jobs = 0;  // rounds with tokens
-    for (const Job& jb : jobs) n_jobs += jb.len > 0;
+    Moves moves{reinterpret_cast<StageJob*>(s->h_tab + s->tab.jobs), {}, hipMemcpyHostToDevice};
+    for (const Job& jb : jobs)
+        if (jb.len > 0) moves.add(jb.src, s->pool + jb.dst_tok * s->token_bytes, layer_tokens(jb.len) * s->token_bytes, jb.direct);
     s->staged_bytes = (uint64_t)tok * s->token_bytes;
-    s->n_copies = (uint64_t)n_groups * n_jobs;
-    // units of 16 KB of every group; the layer-major order's groups are all of one size
-    std::vector<int64_t> n_units(n_groups, 0);
-    if (direct) {
-        StageJob* h_jobs = reinterpret_cast<StageJob*>(s->h_tab + s->tab.jobs);
-        int32_t* h_units = reinterpret_cast<int32_t*>(s->h_tab + s->tab.units);
-        int k = 0;
-        for (const Job& jb : jobs)
-            if (jb.len > 0) h_jobs[k++] = {jb.src, s->pool + jb.dst_tok * s->token_bytes, (int64_t)(layer_tokens(jb.len) * s->token_bytes)};
-        for (int g = 0; g < n_groups; ++g) {
-            int32_t* row = h_units + (size_t)(order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1);
-            for (k = 0; k < n_jobs && n_units[g] <= INT32_MAX / 2; ++k) {
-                row[k] = (int32_t)n_units[g];
-                n_units[g] += ((bounds[g + 1] - bounds[g]) * h_jobs[k].layer_bytes + kUnitBytes - 1) / kUnitBytes;
-            }
-            row[n_jobs] = (int32_t)n_units[g];
-            direct &= n_units[g] <= INT32_MAX / 2;
-        }
+    s->n_copies = (uint64_t)n_groups * moves.size();
+    // (the layer-major order's groups are all of one size)
+    auto row_off = [&](int g) { return s->tab.units + (order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1) * sizeof(int32_t); };
+    auto row = [&](int g) { return reinterpret_cast<int32_t*>(s->h_tab + row_off(g)); };
+    int most_layers = 0;
+    for (int g = 0; g < n_groups; ++g) {
+        (void)moves.units(bounds[g + 1] - bounds[g], row(g));
+        most_layers = std::max(most_layers, bounds[g + 1] - bounds[g]);
     }
+    if (moves.any_large(most_layers)) RA_HIP_CHECK(hipEventRecord(s->fork, st));
     if (int rc = copy_tables(s->h_tab, s->d_tab, s->tab.bytes, st)) return rc;
     for (int g = 0; g < n_groups; ++g) {
         const int l0 = bounds[g], n_l = bounds[g + 1] - l0;
-        if (direct && n_jobs > 0) {
-            const int32_t* row = reinterpret_cast<const int32_t*>(s->d_tab + s->tab.units) + (size_t)(order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1);
-            const int grid = n_units[g] < kStageGrid ? (int)n_units[g] : kStageGrid;
-            hipLaunchKernelGGL(stage_kernel<false>, dim3(grid), dim3(kStageThreads), 0, st, reinterpret_cast<const StageJob*>(s->d_tab + s->tab.jobs),
-                               row, n_jobs, (int)n_units[g], l0, n_l);
+        bool lane_used = false;
+        if (int rc = enqueue_moves(s, moves, s->d_tab + s->tab.jobs, row(g), s->d_tab + row_off(g), l0, n_l, st, &lane_used)) return rc;
+        const bool join = g + 1 == n_groups && moves.forked;  // the side stream ends behind the lane
+        if (lane_used || join) RA_HIP_CHECK(hipEventRecord(s->lane_ready[l0], s->lane));
+        if (join) RA_HIP_CHECK(hipStreamWaitEvent(st, s->lane_ready[l0], 0));
+        for (int l = l0; l < l0 + n_l; ++l) {
+            s->lane_layer[l] = lane_used && !join ? l0 : -1;
+            RA_HIP_CHECK(hipEventRecord(s->ready[l], st));
         }
-        for (const Job& jb : jobs) {
-            if (direct || jb.len == 0) continue;
-            const size_t slice = layer_tokens(jb.len) * s->token_bytes;
-            RA_HIP_CHECK(hipMemcpyAsync(s->pool + jb.dst_tok * s->token_bytes + l0 * slice, jb.src + l0 * slice, n_l * slice,
-                                        hipMemcpyHostToDevice, st));
-        }
-        RA_HIP_CHECK(hipGetLastError());
-        for (int l = l0; l < l0 + n_l; ++l) RA_HIP_CHECK(hipEventRecord(s->ready[l], st));
     }
     s->max_tokens = max_tokens;
     s->staged_tok = tok;
@@ -483,7 +554,9 @@ int ra_kv_store_wait_layer(ra_kv_store* s, int layer, void* compute_stream) {
     RA_REQUIRE(s != nullptr, RA_ERR_INVALID_ARG, "kv_store_wait_layer: store is NULL");
     RA_REQUIRE(layer >= 0 && layer < s->cfg.n_layers, RA_ERR_INVALID_ARG, "kv_store_wait_layer: layer out of range");
     RA_REQUIRE(s->staged, RA_ERR_STATE, "kv_store_wait_layer: nothing is staged");
-    RA_HIP_CHECK(hipStreamWaitEvent(reinterpret_cast<hipStream_t>(compute_stream), s->ready[layer], 0));
+    hipStream_t cs = reinterpret_cast<hipStream_t>(compute_stream);
+    RA_HIP_CHECK(hipStreamWaitEvent(cs, s->ready[layer], 0));
+    if (s->lane_layer[layer] >= 0) RA_HIP_CHECK(hipStreamWaitEvent(cs, s->lane_ready[s->lane_layer[layer]], 0));
     return RA_OK;
 }
 
@@ -580,24 +653,17 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
         int64_t* h_off = reinterpret_cast<int64_t*>(s->h_wb + s->wb.off);
         int32_t* h_len = reinterpret_cast<int32_t*>(s->h_wb + s->wb.len);
         const void** h_cur = reinterpret_cast<const void**>(s->h_wb + s->wb.cur);
-        StageJob* h_jobs = reinterpret_cast<StageJob*>(s->h_wb + s->wb.jobs);
         int32_t* h_units = reinterpret_cast<int32_t*>(s->h_wb + s->wb.units);
-        int n_jobs = 0;
-        int64_t n_units = 0;
-        bool by_kernel = true;  // every tensor can be written by the kernel (a row is whole 16-byte pieces)
+        Moves moves{reinterpret_cast<StageJob*>(s->h_wb + s->wb.jobs), {}, hipMemcpyDeviceToHost};
         for (int b = 0; b < B; ++b) {
             h_off[b] = off[b];
             h_len[b] = off[b] < 0 ? 0 : len_host[b];
             if (h_len[b] == 0) continue;
-            const int64_t bytes = (int64_t)((size_t)L * layer_tokens(h_len[b]) * s->token_bytes);
-            by_kernel &= direct[b] && (uintptr_t)host_kv[b] % 16 == 0 && n_units <= INT32_MAX / 2;
-            h_jobs[n_jobs] = {s->pool + (size_t)off[b] * s->token_bytes, static_cast<char*>(host_kv[b]), bytes};
-            h_units[n_jobs++] = (int32_t)n_units;
-            n_units += (bytes + kUnitBytes - 1) / kUnitBytes;
+            const size_t bytes = (size_t)L * layer_tokens(h_len[b]) * s->token_bytes;
+            moves.add(s->pool + (size_t)off[b] * s->token_bytes, static_cast<char*>(host_kv[b]), bytes, direct[b]);
             s->saved_bytes += (uint64_t)bytes;
         }
-        by_kernel &= n_units <= INT32_MAX / 2;
-        h_units[n_jobs] = (int32_t)n_units;
+        (void)moves.units(1, h_units);
         for (int l = 0; l < L; ++l) {
             h_cur[l] = cur_k_layers[l];
             h_cur[L + l] = cur_v_layers[l];
@@ -619,14 +685,13 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
         RA_HIP_CHECK(hipGetLastError());
         RA_HIP_CHECK(hipEventRecord(s->wb_packed, cs));
         RA_HIP_CHECK(hipStreamWaitEvent(ss, s->wb_packed, 0));
-        if (by_kernel) {
-            hipLaunchKernelGGL(stage_kernel<true>, dim3(n_units < kSaveGrid ? (int)n_units : kSaveGrid), dim3(kStageThreads), 0, ss,
-                               reinterpret_cast<const StageJob*>(s->d_wb + s->wb.jobs),
-                               reinterpret_cast<const int32_t*>(s->d_wb + s->wb.units), n_jobs, (int)n_units, 0, 1);
-            RA_HIP_CHECK(hipGetLastError());
+        if (moves.any_large(1)) RA_HIP_CHECK(hipEventRecord(s->fork, ss));
+        bool lane_used = false;
+        if (int rc = enqueue_moves(s, moves, s->d_wb + s->wb.jobs, h_units, s->d_wb + s->wb.units, 0, 1, ss, &lane_used)) return rc;
+        if (lane_used) {
+            RA_HIP_CHECK(hipEventRecord(s->lane_done, s->lane));
+            RA_HIP_CHECK(hipStreamWaitEvent(ss, s->lane_done, 0));
         }
-        for (int j = 0; j < n_jobs && !by_kernel; ++j)
-            RA_HIP_CHECK(hipMemcpyAsync(h_jobs[j].dst, h_jobs[j].src, (size_t)h_jobs[j].layer_bytes, hipMemcpyDeviceToHost, ss));
         RA_HIP_CHECK(hipEventRecord(s->wb_done, ss));
         s->wb_pending = true;
     }

@@ -28,6 +28,8 @@ struct Op {
     dim3 grid, block;
     const char *dst, *src;
     size_t bytes;
+    hipStream_t stream;
+    hipEvent_t event;
 };
 struct Allocation {
     size_t bytes;
@@ -65,6 +67,38 @@ inline const std::pair<const uintptr_t, Allocation>* find(const void* p) {
     if (it == state().memory.begin()) return nullptr;
     --it;
     return x < it->first + it->second.bytes ? &*it : nullptr;
+}
+// Whether op j is ordered behind op i: the same stream, or over events recorded behind it and waited for.
+inline bool before(const std::vector<Op>& ops, size_t i, size_t j) {
+    std::vector<hipStream_t> streams{ops[i].stream};
+    std::vector<hipEvent_t> events;
+    auto has = [](const auto& v, auto x) {
+        for (auto y : v)
+            if (y == x) return true;
+        return false;
+    };
+    for (size_t k = i + 1; k <= j; ++k) {
+        if (ops[k].what == "wait" && has(events, ops[k].event) && !has(streams, ops[k].stream)) streams.push_back(ops[k].stream);
+        if (ops[k].what == "record") {
+            for (size_t e = 0; e < events.size();) {  // recorded anew
+                if (events[e] == ops[k].event) events.erase(events.begin() + e);
+                else ++e;
+            }
+            if (has(streams, ops[k].stream)) events.push_back(ops[k].event);
+        }
+    }
+    return has(streams, ops[j].stream);
+}
+// Whether a wait for `event` behind all of the ops covers op i.
+inline bool reaches(std::vector<Op> ops, hipEvent_t event, size_t i) {
+    static Stream probe{0};
+    ops.push_back({"wait", "", 0, {}, {}, nullptr, nullptr, 0, handle(probe), event});
+    return before(ops, i, ops.size() - 1);
+}
+// Whether what is enqueued next on `st` comes behind op i.
+inline bool reaches_end(std::vector<Op> ops, hipStream_t st, size_t i) {
+    ops.push_back({"next", "", 0, {}, {}, nullptr, nullptr, 0, st, nullptr});
+    return before(ops, i, ops.size() - 1);
 }
 inline int count(const char* what) {
     int n = 0;
@@ -115,6 +149,9 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* bytes, hipDevicep
 hipError_t hipStreamGetDevice(hipStream_t st, hipDevice_t* d) {  // (the runtime's reads what the handle points to)
     return *d = st == nullptr ? fake::state().current : reinterpret_cast<fake::Stream*>(st)->device, hipSuccess;
 }
+hipError_t hipStreamCreateWithFlags(hipStream_t* st, unsigned) { return *st = fake::handle(*new fake::Stream{fake::state().current}), hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t st) { return delete reinterpret_cast<fake::Stream*>(st), hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
     *e = reinterpret_cast<hipEvent_t>(new fake::Event{fake::state().current});
     return hipSuccess;
@@ -125,19 +162,19 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.f, hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t st) {
     if (reinterpret_cast<fake::Event*>(e)->device != fake::device_of(st)) return hipErrorInvalidHandle;
-    fake::note({"record", "", fake::device_of(st), {}, {}, nullptr, nullptr, 0});
+    fake::note({"record", "", fake::device_of(st), {}, {}, nullptr, nullptr, 0, st, e});
     return hipSuccess;
 }
-hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t, unsigned) {
-    fake::note({"wait", "", fake::device_of(st), {}, {}, nullptr, nullptr, 0});
+hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t e, unsigned) {
+    fake::note({"wait", "", fake::device_of(st), {}, {}, nullptr, nullptr, 0, st, e});
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t st) {
-    fake::note({"copy", "", fake::device_of(st), {}, {}, static_cast<const char*>(dst), static_cast<const char*>(src), n});
+    fake::note({"copy", "", fake::device_of(st), {}, {}, static_cast<const char*>(dst), static_cast<const char*>(src), n, st, nullptr});
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t, hipStream_t st) {
-    fake::note({"kernel", fake::state().kernels[f], fake::device_of(st), grid, block, nullptr, nullptr, 0});
+    fake::note({"kernel", fake::state().kernels[f], fake::device_of(st), grid, block, nullptr, nullptr, 0, st, nullptr});
     return hipSuccess;
 }
 hipError_t hipExtLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t shared, hipStream_t st, hipEvent_t, hipEvent_t, int) {

@@ -1,6 +1,6 @@
 """Staging: the kernel that reads pinned host memory against asynchronous copies of the same bytes (host tensors at addresses that
 the kernel cannot read in 16-byte pieces), for every order, rounds of a token and of none, and more rounds than a wave looks up at
-once."""
+once; and rounds on both sides of the megabyte from which a slice is copied, against the rounds themselves."""
 import numpy as np
 import pytest
 import torch
@@ -47,24 +47,43 @@ def _stage(lens, layers, order, offset):
     ra.ra_kv_store_release(store)
     ra.ra_kv_store_destroy(store)
     ra.ra_destroy(ctx)
-    return torch.stack(outs).cpu(), staged
+    return torch.stack(outs).cpu(), staged, q, keep
 
 
 @pytest.mark.parametrize("name", list(LENS))
 @pytest.mark.parametrize("order,layers", [(ra.RA_STAGE_ROUND_MAJOR, 3), (ra.RA_STAGE_LAYER_MAJOR, 7), (ra.RA_STAGE_GROUPED, 9), (ra.RA_STAGE_GROUPED, 1)])
 def test_kernel_and_copies_stage_the_same_bytes(name, order, layers):
     lens = LENS[name]
-    by_kernel, n = _stage(lens, layers, order, 16)
-    by_copies, m = _stage(lens, layers, order, 8)
+    by_kernel, n = _stage(lens, layers, order, 16)[:2]
+    by_copies, m = _stage(lens, layers, order, 8)[:2]
     assert n == m == sum((x + (x + 15) // 16 * 16) * 2 * 64 * 2 * layers for row in lens for x in row[:-1])
     assert torch.isfinite(by_kernel).all() and torch.equal(by_kernel, by_copies)
 
 
+@pytest.mark.parametrize("order", [ra.RA_STAGE_ROUND_MAJOR, ra.RA_STAGE_LAYER_MAJOR, ra.RA_STAGE_GROUPED])
+def test_large_and_small_rounds_arrive_before_their_layer_is_read(order):
+    """Slices of 2 048 tokens and more are copied on two streams (a token of a layer: 512 bytes), the others come by the kernel."""
+    lens, layers, Hkv, d, offset = [[2100, 3, 4097, 2047, 1], [2500, 2048, 40, 2080, 9]], 6, 2, 64, 16
+    for _ in range(3):
+        out, _, q, bufs = _stage(lens, layers, order, offset)
+        for b, row in enumerate(lens):
+            ks, vs = [], []
+            for r, n in enumerate(row[:-1]):
+                tiles = (n + 15) // 16
+                x = bufs[b * len(row) + r][offset:offset + (n + tiles * 16) * Hkv * d * 2 * layers].view(torch.bfloat16).view(layers, -1).cuda().double()
+                ks.append(x[:, :n * Hkv * d].view(layers, Hkv, n, d))
+                vs.append(x[:, n * Hkv * d:].view(layers, Hkv, tiles, d, 16).transpose(3, 4).reshape(layers, Hkv, tiles * 16, d)[:, :, :n])
+            p = torch.softmax(q[b].double().view(Hkv, -1, d) @ torch.cat(ks, 2).transpose(2, 3).contiguous() * d ** -0.5, -1)
+            exact = (p @ torch.cat(vs, 2)).view(layers, -1, d)
+            assert (out[:, b].cuda().double() - exact).norm() < 1e-5 * exact.norm(), b  # fp32 sums: 2e-7
+
+
+@pytest.mark.parametrize("new", [[300, 1, 0, 47, 16, 33], [2000, 400, 0, 410, 5, 420]], ids=["small", "large"])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-def test_saved_rounds_are_the_same_bytes_by_kernel_and_by_copies(dtype):
-    """Sequences of 1 to 300 tokens, one without any and one skipped; several layers in one gather."""
-    L, Hkv, d, cap = 5, 2, 64, 300
-    new = [300, 1, 0, 47, 16, 33]
+def test_saved_rounds_are_the_same_bytes_by_kernel_and_by_copies(dtype, new):
+    """Sequences of 1 to 300 tokens, one without any and one skipped; several layers in one gather.  2 000 tokens and, of those of
+    400 to 420, the longer: tensors of a megabyte and more, which are copied on two streams."""
+    L, Hkv, d, cap = 5, 2, 64, max(new)
     B, skip = len(new), 4
     gen = torch.Generator("cuda").manual_seed(3)
     ks, vs = ([torch.randn((B, cap, Hkv, d), generator=gen, device="cuda").to(dtype) for _ in range(L)] for _ in range(2))
