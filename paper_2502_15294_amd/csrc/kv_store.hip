@@ -112,22 +112,24 @@ static int grouped_stage_size(int L, int gi) {
     return 1;
 }
 
-static bool is_pinned_host(const void* p, bool* direct = nullptr) {
+// Pinned memory.  `direct`: whether kernels may read and write `bytes` bytes of it: coherent, at the same address, and all in one
+// allocation (of a tensor that is shorter than its round a copy reports an error, a kernel faults).
+static bool is_pinned_host(const void* p, size_t bytes, bool* direct) {
     hipPointerAttribute_t attr;
-    hipError_t e = hipPointerGetAttributes(&attr, p);
-    if (e != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    *direct = false;
+    if (hipPointerGetAttributes(&attr, p) != hipSuccess) {
         (void)hipGetLastError();  // ordinary pageable memory: not an error of ours, clear the sticky code
         return false;
     }
-    if (direct) *direct = attr.devicePointer == p && !(attr.allocationFlags & hipHostMallocNonCoherent);
-    return attr.type == hipMemoryTypeHost;
-}
-// Pinned memory of `bytes` bytes; `direct`: whether kernels may read and write it: coherent, at the same address, and pinned to its
-// last byte (of a tensor that is shorter than its round a copy reports an error, a kernel faults).
-static bool is_pinned_host(const void* p, size_t bytes, bool* direct) {
-    bool last = false;
-    if (!is_pinned_host(p, direct)) return false;
-    *direct = *direct && is_pinned_host(static_cast<const char*>(p) + bytes - 1, &last) && last;
+    if (attr.type != hipMemoryTypeHost) return false;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess) {
+        const size_t at = (size_t)(static_cast<const char*>(p) - static_cast<const char*>(base));
+        *direct = attr.devicePointer == p && !(attr.allocationFlags & hipHostMallocNonCoherent) && at <= size && bytes <= size - at;
+    } else {
+        (void)hipGetLastError();
+    }
     return true;
 }
 
