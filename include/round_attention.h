@@ -369,7 +369,8 @@ size_t ra_kv_store_round_bytes(const ra_kv_store* store, int len);
  * tables of the compact per-layer views, and record one "ready" event per layer.
  * (Slices of a megabyte and more are asynchronous copies, on side_stream and on a stream of the store's own that
  * side_stream waits for in the end.  Smaller ones are one kernel launch per group of layers that reads the pinned host
- * memory, or copies where it cannot: memory made non-coherent, tensors not 16-byte aligned.)
+ * memory, or copies where it cannot: memory not coherent by its flags, tensors not 16-byte aligned or not in one
+ * allocation.)
  *   sel_idx_host int32 [B][R_max], n_sel_host int32 [B]  (host memory; read before returning)
  * Returns RA_ERR_STATE if a selected round was never registered, RA_ERR_OOM if the pool is too
  * small (nothing is enqueued in either case).

@@ -112,6 +112,12 @@ static int grouped_stage_size(int L, int gi) {
     return 1;
 }
 
+// Whether an allocation of these flags is coherent for the kernels whatever HIP_HOST_COHERENT says, which decides for the ones
+// that have other flags alone (hipHostMallocPortable).
+static bool is_coherent(unsigned flags) {
+    if (flags & (hipHostMallocNonCoherent | hipHostMallocUncached | hipHostMallocWriteCombined)) return false;
+    return flags == hipHostMallocDefault || flags & (hipHostMallocCoherent | hipHostMallocMapped);
+}
 // Pinned memory.  `direct`: whether kernels may read and write `bytes` bytes of it: coherent, at the same address, and all in one
 // allocation (of a tensor that is shorter than its round a copy reports an error, a kernel faults).
 static bool is_pinned_host(const void* p, size_t bytes, bool* direct) {
@@ -126,7 +132,7 @@ static bool is_pinned_host(const void* p, size_t bytes, bool* direct) {
     if (attr.type != hipMemoryTypeHost) return false;
     if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess) {
         const size_t at = (size_t)(static_cast<const char*>(p) - static_cast<const char*>(base));
-        *direct = attr.devicePointer == p && !(attr.allocationFlags & hipHostMallocNonCoherent) && at <= size && bytes <= size - at;
+        *direct = attr.devicePointer == p && is_coherent(attr.allocationFlags) && at <= size && bytes <= size - at;
     } else {
         (void)hipGetLastError();
     }

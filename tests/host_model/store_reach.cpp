@@ -1,5 +1,5 @@
 // Which host tensors the store's kernels read and write themselves (fake_hip.hpp): those that lie in one allocation from their
-// first byte to their last.  Everything else is left to copies, which report an error where a kernel would fault.
+// first byte to their last, allocated in a way that is coherent whatever the environment says.  Everything else is left to copies, which report an error where a kernel would fault.
 //
 // exit status 0 = every check passed
 #include "fake_hip.hpp"
@@ -85,6 +85,20 @@ int main() {
     check_tensor(memory + 2 * bytes + 32, 33, false);
     fake::place(memory + 3 * bytes, 16, 0);
     check_tensor(memory + 2 * bytes + 32, 33, false);
+    // Coherent whatever HIP_HOST_COHERENT says: allocations without flags, mapped ones and those that ask for it.  By the
+    // environment: other flags alone.  Not, or not for kernels to read at speed: non-coherent, uncached and write-combined ones.
+    char* other = memory + 5 * bytes;
+    for (unsigned flags : {(unsigned)hipHostMallocDefault, (unsigned)hipHostMallocMapped, (unsigned)hipHostMallocCoherent,
+                           (unsigned)(hipHostMallocPortable | hipHostMallocMapped), (unsigned)(hipHostMallocPortable | hipHostMallocCoherent)}) {
+        fake::place(other, bytes, flags);
+        check_tensor(other, 33, true);
+    }
+    for (unsigned flags : {(unsigned)hipHostMallocPortable, (unsigned)hipHostMallocNumaUser, (unsigned)hipHostMallocWriteCombined,
+                           (unsigned)(hipHostMallocWriteCombined | hipHostMallocMapped), (unsigned)hipHostMallocNonCoherent,
+                           (unsigned)(hipHostMallocNonCoherent | hipHostMallocMapped), (unsigned)(hipHostMallocUncached | hipHostMallocMapped)}) {
+        fake::place(other, bytes, flags);
+        check_tensor(other, 33, false);
+    }
     std::printf("%s: %d failed checks\n", bad ? "FAILED" : "ok", bad);
     return bad ? 1 : 0;
 }
