@@ -291,12 +291,12 @@ union Vec16 {
     T e[16 / sizeof(T)];
 };
 
-// Turn-end gather of the new round (Sec. 3.2, last step), every layer in one launch.  A workgroup moves one
+// Turn-end gather of the new round (Sec. 3.2, last step), the layers from layer0 on in one launch.  A workgroup moves one
 // 16-token tile of one layer and kv head of one sequence: the key rows go out unchanged to row t of head g,
 // the value rows are turned through LDS into the [d][16] tile of the round layout, rows past the
 // round's length as zeros.  Pure data movement in 16-byte pieces; T only fixes the element width.
 template <typename T>
-__global__ __launch_bounds__(kRepackThreads) void repack_round_kernel(const T* const* __restrict__ cur, int n_layers, int n_tiles,
+__global__ __launch_bounds__(kRepackThreads) void repack_round_kernel(const T* const* __restrict__ cur, int n_layers, int layer0, int n_tiles,
                                                                       int cur_cap, int Hkv, int d,
                                                                       const int64_t* __restrict__ wb_off,
                                                                       const int32_t* __restrict__ wb_len,
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kRepackThreads) void repack_round_kernel(const T* c
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int V = 16 / sizeof(T);  // elements per 16-byte piece; also the row padding in LDS
     T* tile = reinterpret_cast<T*>(smem);  // [16][d + V]
-    const int layer = blockIdx.x / n_tiles, tile16 = blockIdx.x - layer * n_tiles;
+    const int local = blockIdx.x / n_tiles, tile16 = blockIdx.x - local * n_tiles, layer = layer0 + local;
     const int b = blockIdx.z, g = blockIdx.y, t0 = tile16 * 16;
     const int64_t off = wb_off[b];
     const int n = wb_len[b];
@@ -679,18 +679,22 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
         OnDevice on(s->cfg.device);
         if (int rc = copy_tables(s->h_wb, s->d_wb, s->wb.bytes, cs)) return rc;
         const int n_tiles = (max_len + 15) / 16;
-        const dim3 grid((unsigned)n_tiles * L, s->cfg.Hkv, B), block(kRepackThreads);
         const int64_t* d_off = reinterpret_cast<const int64_t*>(s->d_wb + s->wb.off);
         const int32_t* d_len = reinterpret_cast<const int32_t*>(s->d_wb + s->wb.len);
-        if (elem == 2)
-            hipLaunchKernelGGL(repack_round_kernel<uint16_t>, grid, block, 16 * (size_t)(s->cfg.d + 8) * 2, cs,
-                               reinterpret_cast<const uint16_t* const*>(s->d_wb + s->wb.cur), L, n_tiles, cur_cap, s->cfg.Hkv, s->cfg.d,
-                               d_off, d_len, reinterpret_cast<uint16_t*>(s->pool));
-        else
-            hipLaunchKernelGGL(repack_round_kernel<uint32_t>, grid, block, 16 * (size_t)(s->cfg.d + 4) * 4, cs,
-                               reinterpret_cast<const uint32_t* const*>(s->d_wb + s->wb.cur), L, n_tiles, cur_cap, s->cfg.Hkv, s->cfg.d,
-                               d_off, d_len, reinterpret_cast<uint32_t*>(s->pool));
-        RA_HIP_CHECK(hipGetLastError());
+        const char* d_cur = s->d_wb + s->wb.cur;
+        const int at_once = std::max(1, (int)(UINT32_MAX / kRepackThreads) / n_tiles);  // layers: a launch has fewer than 2^32 threads
+        for (int l = 0; l < L; l += at_once) {
+            const dim3 grid((unsigned)n_tiles * std::min(at_once, L - l), s->cfg.Hkv, B), block(kRepackThreads);
+            if (elem == 2)
+                hipLaunchKernelGGL(repack_round_kernel<uint16_t>, grid, block, 16 * (size_t)(s->cfg.d + 8) * 2, cs,
+                                   reinterpret_cast<const uint16_t* const*>(d_cur), L, l, n_tiles, cur_cap, s->cfg.Hkv, s->cfg.d, d_off, d_len,
+                                   reinterpret_cast<uint16_t*>(s->pool));
+            else
+                hipLaunchKernelGGL(repack_round_kernel<uint32_t>, grid, block, 16 * (size_t)(s->cfg.d + 4) * 4, cs,
+                                   reinterpret_cast<const uint32_t* const*>(d_cur), L, l, n_tiles, cur_cap, s->cfg.Hkv, s->cfg.d, d_off, d_len,
+                                   reinterpret_cast<uint32_t*>(s->pool));
+            RA_HIP_CHECK(hipGetLastError());
+        }
         RA_HIP_CHECK(hipEventRecord(s->wb_packed, cs));
         RA_HIP_CHECK(hipStreamWaitEvent(ss, s->wb_packed, 0));
         if (moves.any_large(1)) RA_HIP_CHECK(hipEventRecord(s->fork, ss));
