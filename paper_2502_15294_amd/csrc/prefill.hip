@@ -5,6 +5,8 @@
 #include "scores_common.hpp"
 #include "stream_kv.hpp"
 
+#include <algorithm>
+
 using namespace ra;
 
 // Shared by the two prefill entry points.  With `scores` given (watershed layer) the attention runs over every
@@ -77,7 +79,9 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
         scratch_total = mw.total;
     } else {
         // Small batches: the kernel plans itself and cuts the batch into ranges, whose ends a sequence shares with its
-        // neighbours (two parts more).  A workspace that only fits the other schedule gets that one.
+        // neighbours (two parts more).  As many parts as the workspace has room for, down to those of ranges of eight tiles
+        // (with scores one less: a row's values need the room of the last one); with less room, or if the lists in LDS leave
+        // none for as many workgroups as there are ranges even then, it gets the other schedule.
         auto fits = [&](int S) {  // S parts of a sequence, and as many more values in a row of the score output
             a.S = S;
             w = attn_workspace(rows, S, D, B, layer->R_max);
@@ -92,8 +96,14 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
         const size_t least = attn_workspace(rows, S, D, B, layer->R_max).total + score_bytes;
         RA_REQUIRE(ctx->ws.base != nullptr && ctx->ws.bytes >= least, RA_ERR_WORKSPACE,
                    "prefill: workspace has %zu bytes, this call needs %zu", ctx->ws.bytes, least);
-        a.min_units = kPrefillMinUnits;
-        plan_inline = fits(mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2) && attn_prefill_plans_inline(a, ctx->num_cu);
+        const int fewest = std::max(3, mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2 - with_scores);
+        for (int units : {kPrefillMinUnits, a.min_units}) {
+            if (plan_inline) break;
+            a.min_units = units;
+            int parts = mfma_max_pieces(layer->max_tokens + cur_len, units, 16) + 2;
+            while (!fits(parts) && parts >= fewest) --parts;
+            plan_inline = parts >= fewest && attn_prefill_plans_inline(a, ctx->num_cu);
+        }
         if (!plan_inline) {
             a.min_units = attn_min_units();
             while (!fits(S) && S > 1) --S;  // (a part less is 520 bytes a row, so one less fits)

@@ -1,4 +1,5 @@
-"""Calls whose workspace has room for ranges of four key tiles and not for ones of two: they take the longer ranges."""
+"""Calls whose workspace has room for ranges of four key tiles and not for ones of two, or for few partial results of a question's
+rows: they take longer ranges."""
 import pytest
 import torch
 
@@ -61,4 +62,30 @@ def test_a_workspace_for_four_tile_ranges_is_enough(what):
     ra.ra_set_workspace(eng.ctx, small[:n - 4096])
     with pytest.raises(ra.RaError):
         call(eng.ctx)
+    eng.close()
+
+
+@pytest.mark.parametrize("lens,parts", [([700, 33, 1250], 9), ([700, 33, 1250], 13), ([300, 20], 3), ([2] * 1000, 9)],
+                         ids=["2000_9", "2000_13", "320_3", "1000_rounds"])
+def test_a_question_with_room_for_a_few_parts(lens, parts):
+    """160 query rows per KV head, the workspace with room for so many partial results of a row: ranges as short as those take."""
+    w = make_workload("cfg3", B=1, q_len=40, cur_len=40, Hq=8, Hkv=2, lens=[lens], n_relevant=1)
+    R, rows = len(lens), 40 * w.Hq
+    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    n = 32768 + up(((R + 1) * 24 + 4 + 16 + 15) // 16 * 16) + up(rows * parts * w.d * 4) + 2 * up(rows * parts * 4)
+    n += up(rows * max(R + parts, sum(lens) // 256 + R + 1) * 4) + up(w.Hq * R * 4)
+    eng = Engine(w)
+    workspace = torch.empty(n, dtype=torch.uint8, device="cuda")
+    ra.ra_set_workspace(eng.ctx, workspace)
+    for layer in (0, 1):
+        v, ck, cv = device_view(w, layer), to_device(w.cur_k(layer), "bf16"), to_device(w.cur_v(layer), "bf16")
+        q = to_device(w.q(layer), "bf16")
+        got = ra.ra_watershed_attn_prefill(eng.ctx, q, v, ck, cv, scale=w.scale) if layer == 0 else \
+            ra.ra_round_sparse_attn_prefill(eng.ctx, q, v, None, None, ck, cv, scale=w.scale)
+        torch.cuda.synchronize()
+        ro, _ = pipeline.attention_for_sequence(w, 0, layer, list(range(R)))
+        assert ora.row_error(got[0][0].cpu().numpy().reshape(ro.shape), ro) < STREAM_TOL
+        if layer == 0:
+            rP, rS = (torch.from_numpy(x) for x in pipeline.scores_for_sequence(w, 0))
+            assert (got[2][0].cpu() - rP).abs().max() < SCORE_TOL and (got[3][0].cpu() - rS).abs().max() < SCORE_TOL
     eng.close()

@@ -28,6 +28,6 @@ def _run(tmp_path, name):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
-@pytest.mark.parametrize("name", ["store_streams", "store_routes", "store_reach", "store_grid"])
+@pytest.mark.parametrize("name", ["store_streams", "store_routes", "store_reach", "store_grid", "prefill_workspace"])
 def test_host_code(tmp_path, name):
     _run(tmp_path, name)
