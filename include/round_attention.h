@@ -367,10 +367,9 @@ size_t ra_kv_store_round_bytes(const ra_kv_store* store, int len);
 /*
  * Enqueue on `side_stream` the host-to-device copies of every selected round and of the index
  * tables of the compact per-layer views, and record one "ready" event per layer.
- * (Slices of a megabyte and more are asynchronous copies, on side_stream and on a stream of the store's own that
- * side_stream waits for in the end.  Smaller ones are one kernel launch per group of layers that reads the pinned host
- * memory, or copies where it cannot: memory not coherent by its flags, tensors not 16-byte aligned or not in one
- * allocation.)
+ * (Slices of four megabytes and more are asynchronous copies.  Smaller ones are one kernel launch per group of layers that
+ * reads the pinned host memory, or copies where it cannot: memory not coherent by its flags, tensors not 16-byte aligned or
+ * not in one allocation.)
  *   sel_idx_host int32 [B][R_max], n_sel_host int32 [B]  (host memory; read before returning)
  * Returns RA_ERR_STATE if a selected round was never registered, RA_ERR_OOM if the pool is too
  * small (nothing is enqueued in either case).
@@ -403,7 +402,7 @@ int ra_kv_store_release(ra_kv_store* store);
  *                bytes each; written asynchronously, owned by the caller, kept alive while registered
  * On `compute_stream` (after the work that wrote cur_k / cur_v) a gather kernel packs the
  * rounds into the device pool behind the staged rounds; `side_stream` waits for it and carries the
- * copies to host memory (split between copies and a kernel as those of ra_kv_store_stage).  The call returns without
+ * copies to host memory (from a megabyte on; smaller tensors by a kernel as in ra_kv_store_stage).  The call returns without
  * waiting; a later ra_kv_store_stage that selects the new round is ordered behind the copy.  Needs d * element size to be a multiple
  * of 16 bytes (RA_ERR_UNSUPPORTED otherwise).  RA_ERR_OOM if staged rounds plus the new rounds
  * exceed the pool; nothing is enqueued or registered on any error found before the first launch.

@@ -78,11 +78,6 @@ struct ra_kv_store {
     int32_t* d_len = nullptr;
     int32_t* d_n = nullptr;
     std::vector<hipEvent_t> ready;
-    // second stream for large copies, with the events that order it: behind the side stream, and per layer (the first of a group)
-    hipStream_t lane = nullptr;
-    hipEvent_t fork = nullptr, lane_done = nullptr;
-    std::vector<hipEvent_t> lane_ready;
-    std::vector<int> lane_layer;  // [n_layers] whose lane_ready a layer waits for, -1 = none
     bool staged = false;
     int64_t max_tokens = 0;
     size_t staged_tok = 0;  // pool cursor behind the staged rounds, in units of token_bytes
@@ -141,20 +136,25 @@ static bool is_pinned_host(const void* p, size_t bytes, bool* direct) {
 
 namespace {
 // ---- between host memory and the pool -----------------------------------------------------------------
-// Slices of kCopyBytes and more are asynchronous copies: the copy engines leave the compute units to the work beside them.  Each
-// copy costs 10 microseconds of its own on its stream, whatever its size, so they are dealt out to the side stream and to one of
-// the store's own: 50 GB/s in copies of 1 MB and 55 of 2 MB, against 37 and 44 on one stream (the link: 57).
+// Slices of kStageCopyBytes (kSaveCopyBytes) and more are asynchronous copies: the copy engines leave the compute units to the
+// work beside them.  Each costs 10 microseconds of its own on the stream, whatever its size (49 GB/s in copies of 4 MB, 44 of 2,
+// 37 of 1, 18 of 256 KB; the link: 57).
 // Smaller slices, of which a turn of short rounds has hundreds, are one launch of a kernel that reads (at a turn's end: writes)
 // the pinned host memory itself, in units of 16 KB (a workgroup's four 16-byte loads a thread) that a small grid takes in turn:
 // 57 GB/s with half a megabyte asked for.  While it runs the work beside it is slow: memory-bound products at 40 % of their rate,
-// and beside the write-back at next to nothing.  Microseconds with everything by the kernel, by copies on one stream, and so:
-//   turn of 16 rounds of 425 tokens, 6 layers                   3 305   4 043   3 315
-//   ... with 5.8 ms of memory-bound products behind the layers  7 900   6 650   6 590
-//   ... with 5.0 ms of products of 4096^3                       6 810   6 170   6 000
-//   save of 4 x 500 tokens, 2.6 ms of such products behind it   3 526   2 721   2 668
-//   turn of 5 x 7 rounds of 50 tokens, 5 layers                   946   2 707     985  (1 320 with copies from 256 KB on)
-//   turn of one dialogue, 4 rounds of 350 tokens, 3 layers        510     628     545
-constexpr size_t kCopyBytes = 1 << 20;
+// and beside the write-back at next to nothing, where a copy saves as much as it costs from 0.6 MB on.  While rounds are staged
+// there is often nothing to compute yet, so the line lies higher there.  Microseconds with everything by copies, everything by
+// the kernel, and staged so with copies from 2, 4 and 8 MB on (a copy of a layer of 425 tokens and 8 KV heads: 1.8 MB):
+//   turn of 8 rounds of 425 tokens, 24 layers                   7 209   6 880   7 088   7 022   6 988
+//   ... with 3.6 ms of memory-bound products behind the layers  8 068  10 280   8 057   8 171   8 452
+//   turn of 16 such rounds, 6 layers                            4 590   3 800   4 231   3 891   3 822
+//   ... with 5.8 ms of memory-bound products behind the layers  6 912   8 300   7 338   7 886   8 326
+//   turn of one dialogue, 4 rounds of 350 tokens, 3 layers        639     514     520     521     525
+//   turn of 5 x 7 rounds of 50 tokens, 5 layers                 2 750     943   1 000     987   1 003
+//   save of 4 x 500 tokens, 6 layers, 2.6 ms of products of 4096^3 behind it: 2 721 and 3 526
+// (Copies dealt out to two streams reach 55 GB/s in 2 MB, but 25 from a release of device memory on until the runtime next
+// changes its mind, single ones 56 all the while.)
+constexpr size_t kStageCopyBytes = 4 << 20, kSaveCopyBytes = 1 << 20;
 constexpr int kStageThreads = 256, kStageLoads = 4, kStageGrid = 32, kSaveGrid = 64;
 constexpr int kUnitBytes = kStageThreads * kStageLoads * 16;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -229,59 +229,39 @@ struct Moves {
     StageJob* jobs;
     std::vector<bool> direct;
     hipMemcpyKind kind;
-    int64_t ahead = 0;  // bytes given to the side stream more than to the lane
-    bool forked = false;
     void add(const char* src, char* dst, size_t layer_bytes, bool reachable) {
         jobs[direct.size()] = {src, dst, (int64_t)layer_bytes};
         direct.push_back(reachable && ((uintptr_t)src | (uintptr_t)dst | layer_bytes) % 16 == 0);
     }
     int size() const { return (int)direct.size(); }
-    bool any_large(int n_l) const {
-        for (int k = 0; k < size(); ++k)
-            if ((size_t)(n_l * jobs[k].layer_bytes) >= kCopyBytes) return true;
-        return false;
-    }
     // Prefix of the units of n_l layers of every job, none for the jobs that are copied.
-    int units(int n_l, int32_t* row) const {
+    void units(int n_l, int32_t* row) const {
+        const size_t copied = kind == hipMemcpyDeviceToHost ? kSaveCopyBytes : kStageCopyBytes;
         int64_t n = 0;
         for (int k = 0; k < size(); ++k) {
             const int64_t bytes = n_l * jobs[k].layer_bytes, more = (bytes + kUnitBytes - 1) / kUnitBytes;
             row[k] = (int32_t)n;
-            if (direct[k] && (size_t)bytes < kCopyBytes && n + more <= INT32_MAX / 2) n += more;
+            if (direct[k] && (size_t)bytes < copied && n + more <= INT32_MAX / 2) n += more;
         }
-        return row[size()] = (int32_t)n;
+        row[size()] = (int32_t)n;
+    }
+    // Enqueues layers [l0, l0 + n_l) of every tensor on `st`.  row, and its device copy: the units.
+    int enqueue(const char* d_jobs, const int32_t* row, const char* d_row, int l0, int n_l, hipStream_t st) const {
+        if (const int n_units = row[size()]; n_units > 0) {
+            const bool to_host = kind == hipMemcpyDeviceToHost;
+            const int most = to_host ? kSaveGrid : kStageGrid;
+            const auto kernel = to_host ? stage_kernel<true> : stage_kernel<false>;
+            hipLaunchKernelGGL(kernel, dim3(n_units < most ? n_units : most), dim3(kStageThreads), 0, st, reinterpret_cast<const StageJob*>(d_jobs),
+                               reinterpret_cast<const int32_t*>(d_row), size(), n_units, l0, n_l);
+            RA_HIP_CHECK(hipGetLastError());
+        }
+        for (int k = 0; k < size(); ++k) {
+            const size_t o = (size_t)l0 * jobs[k].layer_bytes, bytes = (size_t)n_l * jobs[k].layer_bytes;
+            if (row[k + 1] == row[k]) RA_HIP_CHECK(hipMemcpyAsync(jobs[k].dst + o, jobs[k].src + o, bytes, kind, st));
+        }
+        return RA_OK;
     }
 };
-
-// Enqueues layers [l0, l0 + n_l) of every tensor on `st` and the lane, which is made to follow `fork` when it is first used.  row
-// (and its device copy): the units.  lane_used: whether copies went to the lane.
-static int enqueue_moves(const ra_kv_store* s, Moves& m, const char* d_jobs, const int32_t* row, const char* d_row, int l0, int n_l, hipStream_t st,
-                         bool* lane_used) {
-    const int n = m.size(), n_units = row[n];
-    *lane_used = false;
-    if (n_units > 0) {
-        const bool to_host = m.kind == hipMemcpyDeviceToHost;
-        const int most = to_host ? kSaveGrid : kStageGrid;
-        const auto kernel = to_host ? stage_kernel<true> : stage_kernel<false>;
-        hipLaunchKernelGGL(kernel, dim3(n_units < most ? n_units : most), dim3(kStageThreads), 0, st, reinterpret_cast<const StageJob*>(d_jobs),
-                           reinterpret_cast<const int32_t*>(d_row), n, n_units, l0, n_l);
-        RA_HIP_CHECK(hipGetLastError());
-        m.ahead += (int64_t)n_units * kUnitBytes;
-    }
-    for (int k = 0; k < n; ++k) {
-        if (row[k + 1] > row[k]) continue;
-        const size_t o = (size_t)l0 * m.jobs[k].layer_bytes, bytes = (size_t)n_l * m.jobs[k].layer_bytes;
-        const bool to_lane = m.ahead > 0 && bytes >= kCopyBytes;
-        if (to_lane && !m.forked) {
-            RA_HIP_CHECK(hipStreamWaitEvent(s->lane, s->fork, 0));
-            m.forked = true;
-        }
-        RA_HIP_CHECK(hipMemcpyAsync(m.jobs[k].dst + o, m.jobs[k].src + o, bytes, m.kind, to_lane ? s->lane : st));
-        m.ahead += to_lane ? -(int64_t)bytes : (int64_t)bytes;
-        *lane_used |= to_lane;
-    }
-    return RA_OK;
-}
 
 constexpr int kRepackThreads = 256;
 
@@ -379,18 +359,6 @@ int ra_kv_store_create(ra_kv_store** out, const ra_store_cfg* cfg) {
         for (int l = 0; l < cfg->n_layers && e == hipSuccess; ++l)
             e = hipEventCreateWithFlags(&s->ready[l], hipEventDisableTiming);
     }
-    if (e == hipSuccess) {
-        s->lane_ready.resize(cfg->n_layers, nullptr);
-        s->lane_layer.resize(cfg->n_layers, -1);
-        for (int l = 0; l < cfg->n_layers && e == hipSuccess; ++l)
-            e = hipEventCreateWithFlags(&s->lane_ready[l], hipEventDisableTiming);
-    }
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->lane_done, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->lane, hipStreamNonBlocking);
-    // (its first copy sets up its queue, 250 microseconds)
-    if (e == hipSuccess) e = hipMemcpyAsync(s->d_tab, s->h_tab, 16, hipMemcpyHostToDevice, s->lane);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->lane);
     (void)hipSetDevice(prev);
     if (e != hipSuccess) {
         const bool oom = e == hipErrorOutOfMemory;
@@ -404,11 +372,8 @@ int ra_kv_store_create(ra_kv_store** out, const ra_store_cfg* cfg) {
 
 int ra_kv_store_destroy(ra_kv_store* s) {
     if (!s) return RA_OK;
-    for (const auto* events : {&s->ready, &s->lane_ready})
-        for (hipEvent_t ev : *events)
-            if (ev) (void)hipEventDestroy(ev);
-    if (s->fork) (void)hipEventDestroy(s->fork);
-    if (s->lane_done) (void)hipEventDestroy(s->lane_done);
+    for (hipEvent_t ev : s->ready)
+        if (ev) (void)hipEventDestroy(ev);
     if (s->pool) (void)hipFree(s->pool);
     if (s->d_tab) (void)hipFree(s->d_tab);
     if (s->h_tab) (void)hipHostFree(s->h_tab);
@@ -417,7 +382,6 @@ int ra_kv_store_destroy(ra_kv_store* s) {
     if (s->h_wb) (void)hipHostFree(s->h_wb);
     if (s->wb_packed) (void)hipEventDestroy(s->wb_packed);
     if (s->wb_done) (void)hipEventDestroy(s->wb_done);
-    if (s->lane) (void)hipStreamDestroy(s->lane);
     delete s;
     return RA_OK;
 }
@@ -533,24 +497,12 @@ int ra_kv_store_stage(ra_kv_store* s, const int32_t* sel_idx_host, const int32_t
     // (the layer-major order's groups are all of one size)
     auto row_off = [&](int g) { return s->tab.units + (order == RA_STAGE_LAYER_MAJOR ? 0 : g) * (plane + 1) * sizeof(int32_t); };
     auto row = [&](int g) { return reinterpret_cast<int32_t*>(s->h_tab + row_off(g)); };
-    int most_layers = 0;
-    for (int g = 0; g < n_groups; ++g) {
-        (void)moves.units(bounds[g + 1] - bounds[g], row(g));
-        most_layers = std::max(most_layers, bounds[g + 1] - bounds[g]);
-    }
-    if (moves.any_large(most_layers)) RA_HIP_CHECK(hipEventRecord(s->fork, st));
+    for (int g = 0; g < n_groups; ++g) moves.units(bounds[g + 1] - bounds[g], row(g));
     if (int rc = copy_tables(s->h_tab, s->d_tab, s->tab.bytes, st)) return rc;
     for (int g = 0; g < n_groups; ++g) {
         const int l0 = bounds[g], n_l = bounds[g + 1] - l0;
-        bool lane_used = false;
-        if (int rc = enqueue_moves(s, moves, s->d_tab + s->tab.jobs, row(g), s->d_tab + row_off(g), l0, n_l, st, &lane_used)) return rc;
-        const bool join = g + 1 == n_groups && moves.forked;  // the side stream ends behind the lane
-        if (lane_used || join) RA_HIP_CHECK(hipEventRecord(s->lane_ready[l0], s->lane));
-        if (join) RA_HIP_CHECK(hipStreamWaitEvent(st, s->lane_ready[l0], 0));
-        for (int l = l0; l < l0 + n_l; ++l) {
-            s->lane_layer[l] = lane_used && !join ? l0 : -1;
-            RA_HIP_CHECK(hipEventRecord(s->ready[l], st));
-        }
+        if (int rc = moves.enqueue(s->d_tab + s->tab.jobs, row(g), s->d_tab + row_off(g), l0, n_l, st)) return rc;
+        for (int l = l0; l < l0 + n_l; ++l) RA_HIP_CHECK(hipEventRecord(s->ready[l], st));
     }
     s->max_tokens = max_tokens;
     s->staged_tok = tok;
@@ -562,9 +514,7 @@ int ra_kv_store_wait_layer(ra_kv_store* s, int layer, void* compute_stream) {
     RA_REQUIRE(s != nullptr, RA_ERR_INVALID_ARG, "kv_store_wait_layer: store is NULL");
     RA_REQUIRE(layer >= 0 && layer < s->cfg.n_layers, RA_ERR_INVALID_ARG, "kv_store_wait_layer: layer out of range");
     RA_REQUIRE(s->staged, RA_ERR_STATE, "kv_store_wait_layer: nothing is staged");
-    hipStream_t cs = reinterpret_cast<hipStream_t>(compute_stream);
-    RA_HIP_CHECK(hipStreamWaitEvent(cs, s->ready[layer], 0));
-    if (s->lane_layer[layer] >= 0) RA_HIP_CHECK(hipStreamWaitEvent(cs, s->lane_ready[s->lane_layer[layer]], 0));
+    RA_HIP_CHECK(hipStreamWaitEvent(reinterpret_cast<hipStream_t>(compute_stream), s->ready[layer], 0));
     return RA_OK;
 }
 
@@ -671,7 +621,7 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
             moves.add(s->pool + (size_t)off[b] * s->token_bytes, static_cast<char*>(host_kv[b]), bytes, direct[b]);
             s->saved_bytes += (uint64_t)bytes;
         }
-        (void)moves.units(1, h_units);
+        moves.units(1, h_units);
         for (int l = 0; l < L; ++l) {
             h_cur[l] = cur_k_layers[l];
             h_cur[L + l] = cur_v_layers[l];
@@ -697,13 +647,7 @@ int ra_kv_store_save_round(ra_kv_store* s, const int32_t* round_host, const int3
         }
         RA_HIP_CHECK(hipEventRecord(s->wb_packed, cs));
         RA_HIP_CHECK(hipStreamWaitEvent(ss, s->wb_packed, 0));
-        if (moves.any_large(1)) RA_HIP_CHECK(hipEventRecord(s->fork, ss));
-        bool lane_used = false;
-        if (int rc = enqueue_moves(s, moves, s->d_wb + s->wb.jobs, h_units, s->d_wb + s->wb.units, 0, 1, ss, &lane_used)) return rc;
-        if (lane_used) {
-            RA_HIP_CHECK(hipEventRecord(s->lane_done, s->lane));
-            RA_HIP_CHECK(hipStreamWaitEvent(ss, s->lane_done, 0));
-        }
+        if (int rc = moves.enqueue(s->d_wb + s->wb.jobs, h_units, s->d_wb + s->wb.units, 0, 1, ss)) return rc;
         RA_HIP_CHECK(hipEventRecord(s->wb_done, ss));
         s->wb_pending = true;
     }

@@ -149,9 +149,6 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* bytes, hipDevicep
 hipError_t hipStreamGetDevice(hipStream_t st, hipDevice_t* d) {  // (the runtime's reads what the handle points to)
     return *d = st == nullptr ? fake::state().current : reinterpret_cast<fake::Stream*>(st)->device, hipSuccess;
 }
-hipError_t hipStreamCreateWithFlags(hipStream_t* st, unsigned) { return *st = fake::handle(*new fake::Stream{fake::state().current}), hipSuccess; }
-hipError_t hipStreamDestroy(hipStream_t st) { return delete reinterpret_cast<fake::Stream*>(st), hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
     *e = reinterpret_cast<hipEvent_t>(new fake::Event{fake::state().current});
     return hipSuccess;

@@ -1,6 +1,6 @@
-// How the host store's bytes travel (fake_hip.hpp): slices of a megabyte and more by asynchronous copies, which leave the compute
-// units to the work beside them, smaller ones by the kernel if it can reach the tensor.  Every byte of the selection goes exactly
-// once, a layer's waits cover the streams its copies are on, and the side stream ends behind all of them.
+// How the host store's bytes travel (fake_hip.hpp): slices of four megabytes and more (of the write-back: of one) by asynchronous
+// copies, which leave the compute units to the work beside them, smaller ones by the kernel if it can reach the tensor.  Every
+// byte of the selection goes exactly once, a layer's wait covers its copies, and the side stream ends behind all of them.
 //
 // exit status 0 = every check passed
 #include <algorithm>
@@ -47,14 +47,16 @@ int main() {
     };
     const std::vector<int> groups[3] = {{6}, {1, 1, 1, 1, 1, 1}, {1, 2, 1, 1, 1}};  // layers of a group, by order
     const std::vector<Case> cases = {
-        {RA_STAGE_GROUPED, {700, 425, 300, 2000}, {0, 0, 0, 0}, false},
-        {RA_STAGE_LAYER_MAJOR, {700, 425, 300, 2000}, {0, 0, 0, 0}, false},
-        {RA_STAGE_ROUND_MAJOR, {700, 60, 300, 2000}, {0, 0, 0, 0}, false},
-        {RA_STAGE_GROUPED, {700, 20, 300, 0}, {0, 0, 0, 0}, true},
+        {RA_STAGE_GROUPED, {2000, 1200, 1024, 3000}, {0, 0, 0, 0}, false},
+        {RA_STAGE_GROUPED, {2000, 900, 450, 3000}, {0, 0, 0, 0}, true},  // two of them copied in the group of two layers alone
+        {RA_STAGE_LAYER_MAJOR, {2000, 1025, 1024, 3000}, {0, 0, 0, 0}, false},
+        {RA_STAGE_LAYER_MAJOR, {2000, 1025, 1023, 3000}, {0, 0, 0, 0}, true},
+        {RA_STAGE_ROUND_MAJOR, {700, 300, 2000}, {0, 0, 0}, false},
+        {RA_STAGE_GROUPED, {700, 20, 3000, 0}, {0, 0, 0, 0}, true},
         {RA_STAGE_GROUPED, {1, 20, 33, 90}, {0, 0, 0, 0}, true},
         {RA_STAGE_GROUPED, {1, 20, 33, 90}, {0, 8, 0, 0}, true},  // one that the kernel cannot read in 16-byte pieces
         {RA_STAGE_GROUPED, {1, 20, 33, 90}, {8, 8, 8, 8}, false},
-        {RA_STAGE_GROUPED, {500}, {0}, false},
+        {RA_STAGE_GROUPED, {1200}, {0}, false},
     };
     for (const Case& c : cases) {
         const int n = (int)c.len.size();
@@ -78,7 +80,7 @@ int main() {
                 const size_t bytes = slice(c.len[r], n_l);
                 int copies = 0;
                 for (const fake::Op& op : s.ops) copies += bytes && op.what == "copy" && op.src == tensor[r] + at && op.bytes == bytes;
-                CHECK(copies == (bytes && (bytes >= (size_t)1 << 20 || c.at[r] % 16) ? 1 : 0));
+                CHECK(copies == (bytes && (bytes >= (size_t)4 << 20 || c.at[r] % 16) ? 1 : 0));
                 at += bytes;
             }
         }

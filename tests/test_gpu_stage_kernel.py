@@ -1,6 +1,6 @@
 """Staging: the kernel that reads pinned host memory against asynchronous copies of the same bytes (host tensors at addresses that
 the kernel cannot read in 16-byte pieces), for every order, rounds of a token and of none, and more rounds than a wave looks up at
-once; and rounds on both sides of the megabyte from which a slice is copied, against the rounds themselves."""
+once; and rounds on both sides of the sizes from which a slice is copied, against the rounds themselves."""
 import numpy as np
 import pytest
 import torch
@@ -20,7 +20,7 @@ def _stage(lens, layers, order, offset):
     """(outputs of a decode over every staged layer, bytes staged): the host tensors begin `offset` bytes into their buffers."""
     B, R, Hkv, d = len(lens), len(lens[0]), 2, 64
     rng = np.random.default_rng(1)
-    store = ra.ra_kv_store_create(0, layers, B, R, Hkv, d, ra.RA_BF16, 64 << 20)
+    store = ra.ra_kv_store_create(0, layers, B, R, Hkv, d, ra.RA_BF16, 128 << 20)
     keep = []
     for b in range(B):
         for r in range(R):
@@ -62,8 +62,9 @@ def test_kernel_and_copies_stage_the_same_bytes(name, order, layers):
 
 @pytest.mark.parametrize("order", [ra.RA_STAGE_ROUND_MAJOR, ra.RA_STAGE_LAYER_MAJOR, ra.RA_STAGE_GROUPED])
 def test_large_and_small_rounds_arrive_before_their_layer_is_read(order):
-    """Slices of 2 048 tokens and more are copied on two streams (a token of a layer: 512 bytes), the others come by the kernel."""
-    lens, layers, Hkv, d, offset = [[2100, 3, 4097, 2047, 1], [2500, 2048, 40, 2080, 9]], 6, 2, 64, 16
+    """Slices of 4 MB and more are copied (a token of a layer: 512 bytes; groups of one, two or six layers), the others come by the
+    kernel."""
+    lens, layers, Hkv, d, offset = [[8192, 3, 8191, 1361, 1], [1360, 4096, 40, 8208, 9]], 6, 2, 64, 16
     for _ in range(3):
         out, _, q, bufs = _stage(lens, layers, order, offset)
         for b, row in enumerate(lens):
@@ -82,7 +83,7 @@ def test_large_and_small_rounds_arrive_before_their_layer_is_read(order):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_saved_rounds_are_the_same_bytes_by_kernel_and_by_copies(dtype, new):
     """Sequences of 1 to 300 tokens, one without any and one skipped; several layers in one gather.  2 000 tokens and, of those of
-    400 to 420, the longer: tensors of a megabyte and more, which are copied on two streams."""
+    400 to 420, the longer: tensors of a megabyte and more, which are copied."""
     L, Hkv, d, cap = 5, 2, 64, max(new)
     B, skip = len(new), 4
     gen = torch.Generator("cuda").manual_seed(3)
