@@ -53,6 +53,15 @@ inline Divisor divisor(int d, long long n_max) {
     return {n_max * d < 0x80000000ll ? (unsigned)((0x80000000ull + (unsigned)d - 1) / (unsigned)d) : 0u, d};
 }
 
+// Row / G for the query rows of the many-row kernels, G <= 16, by one multiplication: exact below 2^27 rows, of whose partial
+// results a workspace would hold terabytes.  (A division is twenty instructions, and a question kernel had a dozen of them
+// in front of its first tile and in every store of scores.)
+struct RowsPerToken {
+    unsigned magic;  // ceil(2^31 / G)
+    RA_HD explicit RowsPerToken(int G) : magic((0x80000000u + (unsigned)G - 1) / (unsigned)G) {}
+    RA_HD int token(int row) const { return (int)((unsigned long long)(2u * (unsigned)row) * magic >> 32); }
+};
+
 // Number of ranges for a batch of `total` tiles: never more than `max_ranges` (the wavefronts of the launch
 // divided by the work items per range) and no range shorter than `min_units` tiles.
 RA_HD inline unsigned range_count(unsigned total, int min_units, int max_ranges) {

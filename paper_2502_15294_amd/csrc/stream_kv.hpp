@@ -314,15 +314,6 @@ struct BlockWindow {
     }
 };
 
-// Row / G for the query rows of the many-row kernels, G <= 16, by one multiplication: exact below 2^27 rows, of whose partial
-// results a workspace would hold terabytes.  (A division is twenty instructions, and a question kernel had a dozen of them
-// in front of its first tile and in every store of scores.)
-struct RowsPerToken {
-    unsigned magic;  // ceil(2^31 / G)
-    __device__ explicit RowsPerToken(int G) : magic((0x80000000u + (unsigned)G - 1) / (unsigned)G) {}
-    __device__ __forceinline__ int token(int row) const { return (int)__umulhi(2u * (unsigned)row, magic); }
-};
-
 // ---- balanced schedule of a whole batch ------------------------------------------------------------
 // Every workgroup of a persistent attention launch derives the same schedule from the per-sequence
 // unit counts U_b the planning kernel left in the plan headers: sequence b is cut into

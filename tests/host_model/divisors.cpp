@@ -1,5 +1,6 @@
-// The divisions of the decode kernel's schedule (range_schedule.hpp) against the compiler's: Divisor up to the largest numerator it
-// is made for, and the reciprocal that small_div takes on the device, off by a unit in its last place either way.
+// The divisions of the kernels' schedules and query rows (range_schedule.hpp) against the compiler's: Divisor up to the largest
+// numerator it is made for, RowsPerToken up to its last row, and the reciprocal that small_div takes on the device, off by a unit
+// in its last place either way.
 #include <cmath>
 #include <cstdio>
 #include <random>
@@ -16,7 +17,6 @@ int main() {
     auto by_reciprocal = [&](unsigned a, unsigned b) {
         const float r = 1.0f / (float)b;
         for (float x : {std::nextafterf(r, 0.f), r, std::nextafterf(r, 2.f)}) check((unsigned)(((float)a + 0.5f) * x), a, b, "reciprocal");
-        check(ra::small_div(a, b), a, b, "small_div");
     };
     for (unsigned b = 1; b < (1u << 21); b += 1 + b / 300) {
         for (int k = 0; k < 200; ++k) {
@@ -37,6 +37,12 @@ int main() {
                 if (a >= 0) check((unsigned)x.divide((int)a), (unsigned)a, (unsigned)d, "Divisor");
             }
         }
+    for (int G = 1; G <= 16; ++G) {
+        const ra::RowsPerToken per_token(G);
+        for (unsigned row = 0; row < (1u << 27); row += row < 100000 ? 1 : 1 + rng() % 4000)
+            for (unsigned r : {row, row / G * G, row / G * G + G - 1}) check((unsigned)per_token.token((int)r), r, (unsigned)G, "RowsPerToken");
+        for (unsigned r = (1u << 27) - 100; r < (1u << 27); ++r) check((unsigned)per_token.token((int)r), r, (unsigned)G, "RowsPerToken");
+    }
     std::printf("%s: %lld divisions, %lld wrong\n", bad ? "FAILED" : "ok", n, bad);
     return bad ? 1 : 0;
 }

@@ -1,4 +1,4 @@
-"""The decode schedule's divisions on the CPU (tests/host_model/divisors.cpp)."""
+"""The divisions of the kernels' schedules and query rows on the CPU (tests/host_model/divisors.cpp)."""
 import os
 import shutil
 import subprocess
