@@ -34,7 +34,8 @@ struct AttnArgs {
     long long max_tokens;        // host-known bound on a sequence's history tokens (sizes the launch only)
     int q_len, Hq, G;
     int S;          // upper bound of the pieces a sequence's key set is cut into
-    int min_units;  // a sequence is never cut into pieces of fewer work units than this
+    int min_units;  // generic and many-row kernels: a sequence is never cut into pieces of fewer work units than this (the 16-row
+                    // kernel goes by kMfmaMinUnits and kMfmaSpreadUnits)
     float c;        // scale * log2(e)
     float scale;
     float* part_acc;  // [rows][S][D]   rows = B * q_len * Hq, row = (b * q_len + i) * Hq + h

@@ -131,8 +131,8 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
             for (int b = tid; b < vw.B; b += 256) a.n_parts[b] = sps[b + 1] - sps[b];
     }
 
-    // Row blocks of equal size (to within one 16-row tile): a block is at most kRowTiles tiles, 8 KB of keys and 8 KB of
-    // values read for every one of them.
+    // Row blocks: as few as hold the rows at kRowsPerItem each, all of the same number of 16-row tiles but the last, which has
+    // what is left (25 tiles are 7, 7, 7 and 4).  Every block reads its own 8 KB of keys and 8 KB of values a key tile.
     const int row_tiles = (rows_total + 15) / 16, tiles_per_block = (row_tiles + n_rowblocks - 1) / n_rowblocks;
     auto block_tiles = [&](int rowblock) { return min(tiles_per_block, row_tiles - rowblock * tiles_per_block); };
     auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };

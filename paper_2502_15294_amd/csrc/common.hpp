@@ -94,7 +94,8 @@ constexpr int kUnitTokens = 16;   // tokens per work unit of the streaming kerne
 constexpr int kMaxRounds = 1024;  // largest R_max any entry point accepts
 constexpr int kMaxBatch = 1024;   // largest batch of the matrix-core attention kernels (their schedule lives in LDS)
 // Head of the workspace kept for small integer state (ra_set_workspace clears it once; nothing relies on that):
-//   [0, 16384)       pieces every sequence was cut into by the last generic / many-row attention call
+//   [0, 4096)        pieces every sequence was cut into by the last generic / many-row attention call
+//   [4096, 8192)     parts that the current round of every sequence meets, many-row scores (score_places.hpp)
 //   [16384, 24576)   first record and number of records of every sequence, matrix-core decode kernel
 //   last 64 bytes    a spare word for the bandwidth probe
 constexpr size_t kWsSmallState = 16384;

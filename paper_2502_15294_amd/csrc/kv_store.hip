@@ -1,6 +1,6 @@
 // Round-indexed KV store for the post-watershed layers (paper Sec. 3.2 and Fig. 1: the "upper half"
 // u_m of every round stays in host memory as one tensor; the tensors of the selected rounds are
-// moved to the GPU, each in one transfer, once the selection is known).
+// moved to the GPU once the selection is known, each in one transfer or in one per group of layers).
 //
 // Mostly host side: a registry of pinned per-round tensors, a bump-allocated device pool, the index
 // tables of the compact per-layer views, and the choreography of copies and events on a side
@@ -8,11 +8,11 @@
 // values in transposed 16-token tiles [Hkv][ceil(len/16)][d][16].  Every slice is therefore already a
 // round block in the device layout and staging needs no repacking kernel.
 //
-// The copies into the pool are made by a kernel that reads the pinned host memory itself (stage_kernel).  The kernel at the
-// end of a turn (Sec. 3.2, last step; Alg. 1, last line) gathers
+// Large slices are moved by asynchronous copies, small ones by a kernel that reads the pinned host memory itself
+// (stage_kernel).  The kernel at the end of a turn (Sec. 3.2, last step; Alg. 1, last line) gathers
 // the new round's token-major keys and values of every post-watershed layer into that round layout
 // behind the staged rounds in the pool, from where each sequence's new round leaves for host memory
-// in one copy.  The registry also counts how often each round was staged, which is what KV-cache
+// as a whole.  The registry also counts how often each round was staged, which is what KV-cache
 // dropping (Sec. 3.4) decides on.
 #include "common.hpp"
 

@@ -199,7 +199,8 @@ __device__ __forceinline__ float sum_segments(float v) {
     }
     return v;
 }
-// log-sum-exp of x[lo .. hi).  A round of up to four values (1024 tokens) is read in one go.
+// log-sum-exp of x[lo .. hi).  A round of up to four values (1024 tokens in the score pass's chunks; four parts of any length
+// where the many-row kernels noted them) is read in one go.
 __device__ __forceinline__ float lse_range(const float* x, int lo, int hi) {
     if (hi <= lo) return -__builtin_inff();
     float v[4];
