@@ -64,6 +64,8 @@ struct AttnArgs {
     int num_cu;       // compute units of the device (many-row kernel)
     int plan_inline;  // many-row kernel: it plans itself, no planning kernel ran
     int slots;        // ... and cuts the batch into at most so many ranges
+    int max_parts;    // ... of which at most so many meet one sequence
+    int grid;         // many-row kernel: workgroups
     int p_half;       // many-row kernel: probabilities as one fp16 operand instead of two bf16 (ra_set_prefill_precision)
 };
 
@@ -95,9 +97,11 @@ constexpr int kPrefillMinUnits = 2;
 int launch_attn_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st);
 void launch_merge_records(const AttnArgs& a, int num_cu, hipStream_t st);  // ... and its second step
 // Same operands, many query rows per KV head: the waves own different rows and share key tiles through LDS.
-int launch_attn_prefill_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st);
-// ... which needs no planning kernel before it then (AttnArgs::plan_inline); the shape, min_units and S must be set
-bool attn_prefill_plans_inline(const AttnArgs& a, int num_cu);
+int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, hipStream_t st);
+// ... its workgroups and ranges (grid, slots), for up to S pieces of a sequence, of at least min_units tiles
+void attn_prefill_shape(AttnArgs& a);
+// ... which needs no planning kernel before it then (AttnArgs::plan_inline)
+bool attn_prefill_plans_inline(const AttnArgs& a);
 // Small batches: the first kernel resolves the selection itself (every workgroup reads the whole batch's segment
 // lists in one memory round trip and keeps them in LDS), so that no planning kernel runs before it.
 inline size_t attn_mfma_inline_bytes(int B, int R_max) {

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
     if constexpr (INLINE_PLAN) {
         lists.load(tiles + 2 * kTileBytes, vw, a.sel_idx, a.n_sel, [&](int) { return a.cur_k ? a.cur_len_host : 0; });
         lists.count_tiles(vw.B, sU);
-        P = cut_tiles<kWorkgroupsPerCuP>(ranges, sU, vw.B, a.slots, a.min_units, a.S,
+        P = cut_tiles<kWorkgroupsPerCuP>(ranges, sU, vw.B, a.slots, a.min_units, a.max_parts,
                                          !PAGED && !P_HALF && gridDim.x >= kWorkgroupsPerCuP * (unsigned)a.num_cu &&
                                              a.slots * inner <= (int)gridDim.x,
                                          attn_range_weights());
@@ -559,33 +559,30 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCuP) void attn_prefill_mfma_kern
 static size_t attn_prefill_lds(int B, int R_max, bool plan_inline) {
     return align_up(SlotTable::bytes(R_max + 1), 16) + 2 * kTileBytes + (plan_inline ? BatchLists::bytes(B, R_max) : 0);
 }
+static int attn_prefill_rowblocks(const AttnArgs& a) { return (a.q_len * a.G + kRowsPerItem - 1) / kRowsPerItem; }
 // Workgroups of a launch: as many as the chip holds, if there are as many pieces.
-static long long attn_prefill_grid(const AttnArgs& a, int num_cu, int inner) {
-    const int B = a.view.B;
+void attn_prefill_shape(AttnArgs& a) {
+    const int B = a.view.B, inner = a.view.Hkv * attn_prefill_rowblocks(a);
     const long long max_tiles = (long long)B * (a.max_tokens / kTileP + a.view.R_max + 1 + a.cur_cap / kTileP + 1);
     long long max_pieces = (long long)B + max_tiles / a.min_units;
     if (max_pieces > (long long)B * a.S) max_pieces = (long long)B * a.S;
-    long long grid = (long long)kWorkgroupsPerCuP * num_cu;
+    long long grid = (long long)kWorkgroupsPerCuP * a.num_cu;
     if (grid > max_pieces * inner) grid = max_pieces * inner;
-    return grid < 1 ? 1 : grid;
+    a.grid = (int)(grid < 1 ? 1 : grid);
+    a.slots = question_slots(inner, a.grid, a.num_cu, true);
 }
-static int attn_prefill_rowblocks(const AttnArgs& a) { return (a.q_len * a.G + kRowsPerItem - 1) / kRowsPerItem; }
-bool attn_prefill_plans_inline(const AttnArgs& a, int num_cu) {
-    const int B = a.view.B, R_max = a.view.R_max;
-    return prefill_plans_inline(B, R_max, attn_prefill_lds(B, R_max, true),
-                                attn_prefill_grid(a, num_cu, a.view.Hkv * attn_prefill_rowblocks(a)), num_cu);
+bool attn_prefill_plans_inline(const AttnArgs& a) {
+    return prefill_plans_inline(a.view.B, a.view.R_max, attn_prefill_lds(a.view.B, a.view.R_max, true), a.grid, a.num_cu);
 }
 
-int launch_attn_prefill_mfma(AttnArgs a, bool paged, int num_cu, hipStream_t st) {
+int launch_attn_prefill_mfma(const AttnArgs& a, bool paged, hipStream_t st) {
     const int rows_total = a.q_len * a.G;
-    const int B = a.view.B, Hkv = a.view.Hkv;
+    const int B = a.view.B;
     if (a.G > 16) return fail(RA_ERR_UNSUPPORTED, "prefill: Hq / Hkv = %d exceeds 16", a.G);
     if (B > kMaxBatch) return fail(RA_ERR_UNSUPPORTED, "prefill: batch %d exceeds %d", B, kMaxBatch);
-    const int n_rowblocks = attn_prefill_rowblocks(a);
+    const int n_rowblocks = attn_prefill_rowblocks(a), grid = a.grid;
     const bool plan_inline = a.plan_inline != 0;
     const size_t smem = attn_prefill_lds(B, a.view.R_max, plan_inline);
-    const long long grid = attn_prefill_grid(a, num_cu, Hkv * n_rowblocks);
-    a.slots = question_slots(Hkv * n_rowblocks, grid, num_cu, true);
     const bool lse = a.tile_lse != nullptr, half = a.p_half != 0;
     const int row_tiles = (rows_total + 15) / 16;
     const bool ragged = row_tiles != n_rowblocks * 4 * kNTP;

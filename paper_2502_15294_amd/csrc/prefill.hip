@@ -79,9 +79,9 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
         scratch_total = mw.total;
     } else {
         // Small batches: the kernel plans itself and cuts the batch into ranges, whose ends a sequence shares with its
-        // neighbours (two parts more).  As many parts as the workspace has room for, down to those of ranges of eight tiles
-        // (with scores one less: a row's values need the room of the last one); with less room, or if the lists in LDS leave
-        // none for as many workgroups as there are ranges even then, it gets the other schedule.
+        // neighbours (two parts more).  As many parts as are worth it (question_parts) and the workspace has room for, down to
+        // those of ranges of eight tiles (with scores one less: a row's values need the room of the last one); with less room, or
+        // if the lists in LDS leave none for as many workgroups as there are ranges even then, it gets the other schedule.
         auto fits = [&](int S) {  // S parts of a sequence, and as many more values in a row of the score output
             a.S = S;
             w = attn_workspace(rows, S, D, B, layer->R_max);
@@ -96,17 +96,26 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
         const size_t least = attn_workspace(rows, S, D, B, layer->R_max).total + score_bytes;
         RA_REQUIRE(ctx->ws.base != nullptr && ctx->ws.bytes >= least, RA_ERR_WORKSPACE,
                    "prefill: workspace has %zu bytes, this call needs %zu", ctx->ws.bytes, least);
-        const int fewest = std::max(3, mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2 - with_scores);
+        const int of_eight = mfma_max_pieces(layer->max_tokens + cur_len, a.min_units, 16) + 2;
         for (int units : {kPrefillMinUnits, a.min_units}) {
             if (plan_inline) break;
             a.min_units = units;
-            int parts = mfma_max_pieces(layer->max_tokens + cur_len, units, 16) + 2;
+            a.S = mfma_max_pieces(layer->max_tokens + cur_len, units, 16) + 2;
+            attn_prefill_shape(a);
+            int most = question_parts(a.S, of_eight, a.slots, B);
+            if (most % 8 == 0 && most < a.S) ++most;  // (rows 8 KB apart are slower to merge: 128-token question, combine 9.9 -> 11.3 microseconds)
+            const int fewest = std::min(most, std::max(3, of_eight - with_scores));
+            int parts = most;
             while (!fits(parts) && parts >= fewest) --parts;
-            plan_inline = parts >= fewest && attn_prefill_plans_inline(a, ctx->num_cu);
+            if (parts < fewest) continue;
+            if (parts < most) attn_prefill_shape(a);
+            a.max_parts = parts >= a.slots ? kMaxRanges + 2 : parts;
+            plan_inline = attn_prefill_plans_inline(a);
         }
         if (!plan_inline) {
             a.min_units = attn_min_units();
             while (!fits(S) && S > 1) --S;  // (a part less is 520 bytes a row, so one less fits)
+            attn_prefill_shape(a);
         }
         plan_off = w.plan_off;
         scratch_total = w.total;
@@ -144,7 +153,7 @@ static int prefill_impl(ra_ctx* ctx, void* stream, const void* q, int q_len, int
     {
         KernelTimer timer(ctx, st);
         if (int rc = few_rows ? launch_attn_mfma(a, layer->block_size != 0, ctx->num_cu, st)
-                              : launch_attn_prefill_mfma(a, layer->block_size != 0, ctx->num_cu, st))
+                              : launch_attn_prefill_mfma(a, layer->block_size != 0, st))
             return rc;
     }
     if (few_rows) launch_merge_records(a, ctx->num_cu, st);

@@ -408,8 +408,8 @@ void scores_prefill_shape(ScoreArgs& a, long long room) {
         a.slots = plan_inline ? question_slots(inner, grid, a.num_cu, false)
                               : (int)(grid * kPiecesPerWorkgroupS / inner < 1 ? 1 : grid * kPiecesPerWorkgroupS / inner);
         if (a.slots > kMaxRanges) a.slots = kMaxRanges;
-        long long parts = a.max_tiles / a.min_units + 2;
-        if (parts > a.slots) parts = a.slots;
+        const long long of_eight = (a.max_tiles + kMinTilesPlanned - 1) / kMinTilesPlanned + 2;
+        const long long parts = question_parts(a.max_tiles / a.min_units + 2, of_eight, a.slots, plan_inline ? B : 1);
         a.S = (int)(parts > room ? room : parts);
         a.max_parts = a.S >= a.slots ? kMaxRanges + 2 : a.S;
         if (plan_inline && a.max_parts > 2 && prefill_plans_inline(B, a.view.R_max, scores_prefill_lds(B, a.view.R_max, true), grid, a.num_cu))

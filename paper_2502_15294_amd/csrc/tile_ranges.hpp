@@ -75,6 +75,17 @@ inline int question_slots(int inner, long long grid, int num_cu, bool partials) 
     return at_once;
 }
 
+// Parts of a sequence that the values and the partial results of a row have room for: those of the launch's shortest ranges
+// (`most`) as far as twice a sequence's share of the ranges goes, at least those of ranges of eight tiles (`of_eight`); no sequence
+// meets more than `slots`.  Rows with more room than that are longer to write and read (122 tokens of 64 heads over nine dialogues
+// of 27 short rounds, 24 ranges of scores and 8 of attention: 144.7 microseconds with the parts of eight tiles, 154.0 with room for
+// 24 and 18).
+inline int question_parts(long long most, long long of_eight, int slots, int n_sequences) {
+    const long long share = 2ll * ((slots + n_sequences - 1) / n_sequences) + 2;
+    const long long room = of_eight > share ? of_eight : share, parts = most < room ? most : room;
+    return (int)(parts < slots ? parts : slots);
+}
+
 // At most `slots` ranges of about `len` tiles, at least min_tiles, such that at most max_parts (> 2) of them meet one
 // sequence: the partial results of a row have room for that many.  A sequence that meets max_parts + 1 ranges holds the
 // max_parts - 1 between its first and its last one whole, and at least a tile of each of those two.

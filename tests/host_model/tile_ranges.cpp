@@ -6,6 +6,7 @@
 // And the number of ranges that launches of many query rows are given.
 //
 // usage: tile_ranges [seed] [cases]     exit status 0 = every check passed
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -77,6 +78,26 @@ static void check_both(const std::vector<int>& U, int slots, int max_parts, bool
     }
 }
 
+// The limit that a launch asks for: what it costs is at most that ranges shorter than eight tiles have eight, and nothing where two
+// dialogues or one share the ranges.
+static void check_parts(const std::vector<int>& U, int slots, int slack) {
+    int total = 0, most = 0;
+    for (int u : U) {
+        total += u;
+        most = u > most ? u : most;
+    }
+    if (slots > kMaxRanges) slots = kMaxRanges;
+    const int bound = most + slack, B = (int)U.size();
+    if (bound < 2) return;  // (room for two parts is left to launches that are planned apart)
+    const int S = question_parts(bound / 2 + 2, (bound + 7) / 8 + 2, slots, B);
+    const int max_parts = S >= slots ? kMaxRanges + 2 : S;
+    if (S < 1 || S > slots || (B <= 2 && S != std::min(bound / 2 + 2, slots)) || max_parts < 3) ++bad;
+    if (max_parts < 3) return;
+    check(U, slots, 2, max_parts, true, score_range_weights());
+    const TileCut<3> cut(total, most, slots, 2, max_parts, false, score_range_weights()), free(total, most, slots, 2, kMaxRanges + 2, false, score_range_weights());
+    if (cut.len > std::max(8, free.len) && ++bad <= 10) std::fprintf(stderr, "  ranges of %d tiles instead of %d by the limit %d\n", cut.len, free.len, S);
+}
+
 int main(int argc, char** argv) {
     const unsigned seed = argc > 1 ? (unsigned)std::atoi(argv[1]) : 1u;
     const int cases = argc > 2 ? std::atoi(argv[2]) : 20000;
@@ -112,6 +133,7 @@ int main(int argc, char** argv) {
         if (style == 0) U[uni(0, B - 1)] = uni(1, 5000);
         check_both(U, slots, uni(3, 18), uni(0, 3) > 0);
         check_both(U, style == 4 ? uni(65, kMaxRanges) : slots, uni(3, 1200), uni(0, 3) > 0);
+        check_parts(U, slots, uni(0, 40));
     }
     // ranges handed to a launch that fills the chip: one at least, all at the same time, or a whole number of rounds to within
     // an eighth
