@@ -372,7 +372,8 @@ size_t ra_kv_store_round_bytes(const ra_kv_store* store, int len);
  * not in one allocation.)
  *   sel_idx_host int32 [B][R_max], n_sel_host int32 [B]  (host memory; read before returning)
  * Returns RA_ERR_STATE if a selected round was never registered, RA_ERR_OOM if the pool is too
- * small (nothing is enqueued in either case).
+ * small, RA_ERR_HIP if side_stream (the null stream: the current device's) is not on the store's device (nothing is enqueued
+ * in any of these cases).
  */
 int ra_kv_store_stage(ra_kv_store* store, const int32_t* sel_idx_host, const int32_t* n_sel_host, int order,
                       void* side_stream);
